@@ -2,38 +2,413 @@
 // "Prefetching Scheme"): per head, A_h = V of the SVD Q_h = U S V^T of the calibration queries.
 //
 // As in the host version, V is obtained from the Gram matrix: Q_h^T Q_h = V S^2 V^T.
-//   gram_heads     G_h = Q_h^T Q_h in double, one thread per entry of the upper triangle
-//   jacobi_heads   one workgroup per head: cyclic two-sided Jacobi with a round-robin (tournament)
-//                  ordering, so that the d/2 rotations of a round act on disjoint index pairs and
-//                  run in parallel: rotations are computed from the current G, then applied to
-//                  the columns of G and V, then to the rows of G, with a barrier after each phase.
-//                  The number of sweeps is fixed (no data-dependent loop); what is left off the
-//                  diagonal afterwards is checked and flagged.  Eigenvalues are then ranked in
-//                  descending order (the earlier column first on ties), each eigenvector's sign is
-//                  chosen so that its largest-magnitude entry is positive, and A_h (float32) and
-//                  the singular values sqrt(lambda) are written.
-// G and V live in a double-precision workspace in device memory (128 KiB each per head at d = 128:
-// they stay in L2); all arithmetic is double.
+//   gram_heads       G_h = Q_h^T Q_h in double on the matrix cores, one 16 x 16 tile of the upper
+//                    triangle per workgroup
+//   onesided_heads   d <= 128: one workgroup per head, everything in LDS and registers.  A pivoted
+//                    Cholesky factor G = L L^T, then one-sided Jacobi rotations of L's columns until
+//                    they are orthogonal: L J = V S, so the columns' norms are the singular values
+//                    and the normalised columns are V; no second matrix is carried along.
+//   jacobi_heads     d > 128 (the factor does not fit the LDS): cyclic two-sided Jacobi on G with V
+//                    accumulated, both in device memory
+// The eigenvalues are then ranked in descending order (the earlier column first on ties), each
+// eigenvector's sign is chosen so that its largest-magnitude entry is positive, and A_h (float32)
+// and the singular values are written.  All sums and rotations are double.
 #include "ig_internal.h"
 
 namespace {
 
 constexpr int JACOBI_SWEEPS = 16;
 
+typedef double double4v __attribute__((ext_vector_type(4)));
+
+// One workgroup per 16 x 16 tile (ta <= tb) of G_h: the four waves take every fourth group of 4 rows
+// of Q_h, 8 groups (16 loads of 4 bytes a lane) in flight at a time, and their sums are added in wave
+// order.  Latency-bound: 512 rows are 32 matrix instructions a wave.  (One thread an entry, walking the
+// rows, took 159 us on 32 heads of 128 columns and 512 rows.)
 __global__ __launch_bounds__(256) void gram_heads(const float *__restrict__ Qcal, double *__restrict__ G,
-                                                  int n, int D, int d) {
+                                                  int n, int D, int d, int T) {
+  __shared__ double red[4][256];
   const int h = blockIdx.y;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= d * d) return;
-  const int a = e / d, b = e % d;
-  if (b < a) return;
-  const float *col = Qcal + (long)h * d;
-  double acc = 0.0;
-  for (int i = 0; i < n; ++i) acc += (double)col[(long)i * D + a] * (double)col[(long)i * D + b];
-  G[((long)h * d + a) * d + b] = acc;
-  G[((long)h * d + b) * d + a] = acc;
+  int ta = 0, rest = blockIdx.x;
+  while (rest >= T - ta) { rest -= T - ta; ++ta; }
+  const int tb = ta + rest;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i = lane & 15, k = lane >> 4;
+  // columns past the head and rows past the last are read clamped and multiplied as zeros
+  const int ca = ta * 16 + i, cb = tb * 16 + i;
+  const float *pa = Qcal + (long)h * d + min(ca, d - 1), *pb = Qcal + (long)h * d + min(cb, d - 1);
+  double4v acc = {0.0, 0.0, 0.0, 0.0};
+  constexpr int U = 8;
+  for (int r0 = w * 4; r0 < n; r0 += 16 * U) {
+    float a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long at = (long)min(r0 + 16 * u + k, n - 1) * D;
+      a[u] = pa[at];
+      b[u] = pb[at];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = r0 + 16 * u + k < n;
+      const double av = in && ca < d ? (double)a[u] : 0.0, bv = in && cb < d ? (double)b[u] : 0.0;
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+    }
+  }
+  // result register v of a lane: row v*4 + lane/16 of the tile, column lane%16
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[w][(v * 4 + k) * 16 + i] = acc[v];
+  __syncthreads();
+  const int t = threadIdx.x;
+  const double g = ((red[0][t] + red[1][t]) + red[2][t]) + red[3][t];
+  const int a = ta * 16 + t / 16, b = tb * 16 + t % 16;
+  if (a < d && b < d) {
+    G[((long)h * d + a) * d + b] = g;
+    if (ta != tb) G[((long)h * d + b) * d + a] = g;
+  }
 }
 
+// ---- d <= 128: pivoted Cholesky factor and one-sided Jacobi in LDS and registers -------------------
+// Columns are rotated in pairs x, x ^ m for m = 1 .. DP-1 (every pair once a sweep).  A wave takes 16 pairs
+// at a time: lane (part, g), g = lane % 16, holds every fourth row of column A_g and of its partner B_g in
+// registers, so that a pair's inner product is RP = DP/4 multiply-adds and two cross-lane steps and every
+// lane works out its own pair's rotation.  All m with the same highest bit that differ only in m's low
+// (up to 4) bits run without leaving the registers: between two of them the B columns change lanes, by
+// one DPP move (xor 1, 2, 7 or 15 inside 16 lanes reaches every pairing).  Then the columns go back to
+// LDS, the only point where the waves meet (11 times a sweep of 127 rounds at DP = 128).
+// Rotations are square-root free on the columns (two multiply-adds an element pair; the cosines
+// are collected in a factor per column and multiplied in when it goes back to LDS).  Angles come from
+// float32 (a rotation by a slightly wrong angle is still a rotation; its cosine is worked out in double),
+// which leaves 1e-7 of a pair's inner product for the next sweep.
+// Bound by the double-precision issue rate of the head's compute unit, one wave per SIMD: a round is
+// 3 multiply-adds and 2 moves for each of RP rows and a chain of about 40 dependent operations.
+// The pivoted factor matters: L's columns come out graded, which takes 8 sweeps where the columns of G
+// itself take more than 20, and a head without full rank is found by a pivot at rounding level: those
+// columns are left out of the rotations and V is completed to an orthonormal basis.
+// Measured on 32 heads of 128 columns: 0.79 ms (factor 0.12, eight sweeps 0.64, output 0.02), against
+// 34.8 ms for two-sided rotations of G and V through the L2 (jacobi_heads).
+__device__ __forceinline__ double join_d(unsigned lo, unsigned hi) {
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+template <int CTRL> __device__ __forceinline__ double dpp_d(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)u, CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), CTRL, 0xF, 0xF, true);
+  return join_d((unsigned)lo, (unsigned)hi);
+}
+// sum over lanes l, l ^ 16, l ^ 32, l ^ 48, returned in each of them
+__device__ __forceinline__ double sum_parts(double v) {
+  typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+  unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  uint2v lo = __builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)u, false, false);
+  uint2v hi = __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+  v = join_d(lo[0], hi[0]) + join_d(lo[1], hi[1]);
+  u = (unsigned long long)__double_as_longlong(v);
+  lo = __builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)u, false, false);
+  hi = __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+  return join_d(lo[0], hi[0]) + join_d(lo[1], hi[1]);
+}
+template <int RP> __device__ __forceinline__ double column_dot(const double (&a)[RP], const double (&b)[RP]) {
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < RP; ++k) s[k & 3] = fma(a[k], b[k], s[k & 3]);
+  return sum_parts((s[0] + s[1]) + (s[2] + s[3]));
+}
+// Tangent, cosine and 1 / cosine of the rotation that makes columns with squared norms al, be and inner
+// product ga orthogonal (0, 1, 1 where they are to rounding); `big` is set when they were far from it.
+__device__ __forceinline__ void rotation(double al, double be, double ga, double &t, double &c, double &ic, bool &big) {
+  const double g2 = ga * ga, ab = al * be;
+  big = big || g2 > 1e-10 * ab;
+  const float z = (float)(be - al) * __builtin_amdgcn_rcpf((float)(2.0 * ga));
+  float tf = __builtin_amdgcn_rcpf(fabsf(z) + __builtin_amdgcn_sqrtf(fmaf(z, z, 1.f)));
+  tf = z < 0.f ? -tf : tf;
+  const bool turn = (g2 > 1e-30 * ab) & (fabsf(tf) <= 1.f);      // (no branch)
+  tf = turn ? tf : 0.f;
+  t = (double)tf;
+  const double x = fma(t, t, 1.0), hx = -0.5 * x;
+  double y = (double)__builtin_amdgcn_rsqf(fmaf(tf, tf, 1.f));
+  y = y * fma(hx * y, y, 1.5);
+  c = y * fma(hx * y, y, 1.5);
+  ic = x * c;
+}
+// The 16 column pairs a wave has in registers: column = D x what they hold, I = 1 / D, n = squared norm.
+template <int RP> struct Pair {
+  double a[RP], b[RP], na, nb, Da, Ia, Db, Ib;
+};
+// Rounds X, X + 1, .. of `rounds` (1, 2, 4, 8 or 16): rotate every pair, move the B columns on.  Spelled out
+// by recursion: a loop around the four kinds of move copies the columns at every turn.
+template <int X, int RP>
+__device__ __forceinline__ void rotate_rounds(Pair<RP> &P, int rounds, bool &big) {
+  const double ga = column_dot<RP>(P.a, P.b) * (P.Da * P.Db);
+  double t, c, ic;
+  rotation(P.na, P.nb, ga, t, c, ic, big);
+  const double ta = -t * (P.Db * P.Ia), tb = t * (P.Da * P.Ib);
+#pragma unroll
+  for (int k = 0; k < RP; ++k) {
+    const double av = P.a[k];
+    P.a[k] = fma(ta, P.b[k], av);
+    P.b[k] = fma(tb, av, P.b[k]);
+  }
+  const double c2 = c * c, t2 = t * t, tg = 2.0 * t * ga;
+  const double na = c2 * (fma(t2, P.nb, P.na) - tg);
+  P.nb = c2 * (fma(t2, P.na, P.nb) + tg);
+  P.na = na;
+  P.Da *= c;
+  P.Db *= c;
+  P.Ia *= ic;
+  P.Ib *= ic;
+  if constexpr (X < 15) {
+    if constexpr ((X & (X + 1)) == 0) {
+      if (rounds == X + 1) return;
+    }
+    constexpr int CTRL = X % 2 == 0 ? DPP_QUAD_1032 : (X % 4 == 1 ? DPP_QUAD_2301 : (X == 7 ? DPP_ROW_MIRROR : DPP_ROW_HALF_MIRROR));
+#pragma unroll
+    for (int k = 0; k < RP; ++k) P.b[k] = dpp_d<CTRL>(P.b[k]);
+    P.nb = dpp_d<CTRL>(P.nb);
+    P.Db = dpp_d<CTRL>(P.Db);
+    P.Ib = dpp_d<CTRL>(P.Ib);
+    rotate_rounds<X + 1, RP>(P, rounds, big);
+  }
+}
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, DPP_QUAD_1032, 0xF, 0xF, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, DPP_QUAD_2301, 0xF, 0xF, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, DPP_ROW_HALF_MIRROR, 0xF, 0xF, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, DPP_ROW_MIRROR, 0xF, 0xF, false));
+  const unsigned r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
+  const unsigned r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
+  return max(max(r0, r1), max(r2, r3));
+}
+
+template <int DP>
+__global__ __launch_bounds__(256, 1) void onesided_heads(const double *__restrict__ Gall, float *__restrict__ A,
+                                                         float *__restrict__ sigma, int32_t *status, int d) {
+  constexpr int RP = DP / 4;               // rows a lane holds of a column
+  constexpr int LD = DP + 2;               // column stride: 16 columns x 2 rows fall into different banks
+  constexpr int NT = 256, NBLK = DP / 16;  // blocks of 16 columns; two to a wave: NBLK / 2 waves rotate
+  constexpr int TR = DP / 16;              // the Cholesky update: a TR x TR tile of G a thread
+  constexpr int MAX_SWEEPS = 30;
+  __shared__ double S[DP * LD];            // column c, row r at c*LD + r
+  __shared__ double lvec[DP], diag[DP];
+  __shared__ unsigned key[DP];
+  __shared__ int place[DP];
+  const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const double *G = Gall + (long)h * d * d;
+  // ---- G into registers, scaled by a power of two so that the largest diagonal entry is in [0.5, 1) ----
+  double T[TR][TR];
+  const int rb = tid & 15, cb = tid >> 4;  // rows rb + 16 i, columns cb + 16 j
+#pragma unroll
+  for (int j = 0; j < TR; ++j)
+#pragma unroll
+    for (int i = 0; i < TR; ++i) {
+      const int r = rb + 16 * i, c = cb + 16 * j;
+      T[i][j] = r < d && c < d ? G[(long)c * d + r] : 0.0;
+    }
+  if (rb == cb) {
+#pragma unroll
+    for (int i = 0; i < TR; ++i) diag[rb + 16 * i] = T[i][i];
+  }
+  __syncthreads();
+  double top = 0.0;
+  for (int e = lane; e < DP; e += 64) top = fmax(top, diag[e]);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) top = fmax(top, __shfl_xor(top, o, 64));
+  int ex = 0;
+  if (top > 0.0 && top < __longlong_as_double(0x7FF0000000000000ll)) (void)frexp(top, &ex);
+  top = ldexp(top, -ex);
+#pragma unroll
+  for (int j = 0; j < TR; ++j)
+#pragma unroll
+    for (int i = 0; i < TR; ++i) T[i][j] = ldexp(T[i][j], -ex);
+  // A pivot is the largest remaining diagonal entry to 16 bits, the earlier row first: the key is the
+  // entry's float32 image with the row in its low bits, 0 for rows that are used up.
+  // Thread r < DP keeps row r's diagonal entry by itself (with the arithmetic of the tile that holds it).
+  unsigned alive = (1u << TR) - 1;         // rows of the thread's tile that are not used up
+  double own_diag = tid < DP ? ldexp(diag[tid], -ex) : 0.0;
+  bool own_alive = true;
+  __syncthreads();                         // diag is overwritten
+  auto publish = [&]() {
+    if (tid < DP) {
+      const float v = (float)own_diag;
+      diag[tid] = own_diag;
+      key[tid] = own_alive && v > 0.f ? (__float_as_uint(v) & ~127u) | (unsigned)(127 - tid) : 0u;
+    }
+  };
+  publish();
+  __syncthreads();
+  const double least = 2.3e-16 * top;      // a pivot no larger than G's rounding ends the factorisation
+  int rank = 0;
+  for (int j = 0; j < d; ++j) {
+    unsigned k = key[lane];
+    if constexpr (DP > 64) k = max(k, key[64 + lane]);
+    k = wave_max_u32(k);                   // the same in every wave
+    if (k == 0u) break;
+    const int p = 127 - (int)(k & 127u);
+    const double best = diag[p];
+    if (!(best > least)) break;
+    // column p of what is left goes to LDS as it is; it is scaled by 1 / sqrt(best) at the end
+    if (cb == (p & 15)) {
+#pragma unroll
+      for (int jj = 0; jj < TR; ++jj)
+        if (jj == (p >> 4)) {
+#pragma unroll
+          for (int i = 0; i < TR; ++i) S[j * LD + rb + 16 * i] = ((alive >> i) & 1u) ? T[i][jj] : 0.0;
+        }
+    }
+    if (tid == 0) lvec[j] = best;
+    if (tid == p) own_alive = false;
+    alive &= ~((rb == (p & 15) ? 1u : 0u) << (p >> 4));
+    __syncthreads();
+    double inv = __builtin_amdgcn_rcp(best);       // and two Newton steps
+    inv = fma(fma(-best, inv, 1.0), inv, inv);
+    inv = fma(fma(-best, inv, 1.0), inv, inv);
+    if (tid < DP) {
+      const double l = S[j * LD + tid];
+      own_diag = fma(l, l * -inv, own_diag);
+    }
+    publish();
+    double rr[TR], cc[TR];
+#pragma unroll
+    for (int i = 0; i < TR; ++i) {
+      rr[i] = S[j * LD + rb + 16 * i];
+      cc[i] = S[j * LD + cb + 16 * i] * -inv;
+    }
+#pragma unroll
+    for (int jj = 0; jj < TR; ++jj)
+#pragma unroll
+      for (int i = 0; i < TR; ++i) T[i][jj] = fma(rr[i], cc[jj], T[i][jj]);
+    __syncthreads();
+    rank = j + 1;
+  }
+  for (int e = tid; e < DP * DP; e += NT) {
+    const int c = e / DP;
+    S[c * LD + e % DP] = c < rank ? S[c * LD + e % DP] * (1.0 / sqrt(lvec[c])) : 0.0;
+  }
+  __syncthreads();
+  // ---- one-sided Jacobi sweeps ----
+  const int g = lane & 15, part = lane >> 4;
+  bool big = true;
+  for (int sweep = 0; sweep < MAX_SWEEPS && big; ++sweep) {
+    big = false;
+    for (int pass = 0; pass < 4 + NBLK - 1; ++pass) {
+      // passes 0..3: m's highest bit is `pass`, pairs inside the wave's own 32 columns; passes 4..: block
+      // b against block b ^ M, M = pass - 3
+      int ca, cbx, rounds;
+      if (pass < 4) {
+        const int lowbits = (1 << pass) - 1;
+        ca = 32 * w + (((g & ~lowbits) << 1) | (g & lowbits));
+        cbx = ca ^ (1 << pass);
+        rounds = 1 << pass;
+      } else {
+        const int M = pass - 3, hb = 31 - __clz(M);
+        const int b0 = ((w >> hb) << (hb + 1)) | (w & ((1 << hb) - 1));
+        ca = b0 * 16 + g;
+        cbx = (b0 ^ M) * 16 + g;
+        rounds = 16;
+      }
+      if (w < NBLK / 2) {
+        double *pa = S + ca * LD + part;
+        const double *pb = S + cbx * LD + part;
+        Pair<RP> P;
+#pragma unroll
+        for (int k = 0; k < RP; ++k) {
+          P.a[k] = pa[4 * k];
+          P.b[k] = pb[4 * k];
+        }
+        P.na = column_dot<RP>(P.a, P.a);
+        P.nb = column_dot<RP>(P.b, P.b);
+        P.Da = P.Ia = P.Db = P.Ib = 1.0;
+        rotate_rounds<0, RP>(P, rounds, big);
+        // where the moves (xor 1, 2, 1, 7, 1, 2, 1, 15, ...) have taken the B columns: lane g holds lane
+        // g ^ moved's (in passes 0..3 only bits below `pass` flip, which the lane's column shares with g)
+        const int moved = rounds == 4 ? 2 : rounds - 1;
+        double *qb = S + (cbx ^ moved) * LD + part;
+#pragma unroll
+        for (int k = 0; k < RP; ++k) {
+          pa[4 * k] = P.a[k] * P.Da;
+          qb[4 * k] = P.b[k] * P.Db;
+        }
+      }
+      __syncthreads();
+    }
+    big = __syncthreads_or(big) != 0;
+  }
+  if (big && tid == 0) atomicOr(status, IG_STATUS_NOCONV);
+  // ---- norms, normalised columns (diag and lvec now belong to columns) ----
+  if (tid < DP) {
+    const int c = tid;
+    double n2 = 0.0;
+#pragma unroll 8
+    for (int i = 0; i < DP; ++i) {
+      const double v = S[c * LD + (i + c) % DP];      // (a different row per lane: no bank twice)
+      n2 = fma(v, v, n2);
+    }
+    diag[c] = n2;
+    lvec[c] = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
+  }
+  __syncthreads();
+  for (int e = tid; e < DP * DP; e += NT) S[(e / DP) * LD + e % DP] *= lvec[e / DP];
+  __syncthreads();
+  // ---- a head without full rank: complete V, one unit vector at a time ----
+  for (int c = rank; c < d; ++c) {
+    // the unit vector that the columns so far cover least
+    if (tid < d) {
+      double rest = 1.0;
+      for (int k = 0; k < c; ++k) rest -= S[k * LD + tid] * S[k * LD + tid];
+      lvec[tid] = rest;
+    }
+    __syncthreads();
+    int e = 0;
+    for (int i = 1; i < d; ++i)
+      if (lvec[i] > lvec[e]) e = i;
+    __syncthreads();
+    if (tid < DP) S[c * LD + tid] = tid == e ? 1.0 : 0.0;
+    for (int pass = 0; pass < 2; ++pass) {
+      __syncthreads();
+      if (tid < c) {
+        double dot = 0.0;
+        for (int i = 0; i < d; ++i) dot = fma(S[tid * LD + i], S[c * LD + i], dot);
+        lvec[tid] = dot;
+      }
+      __syncthreads();
+      if (tid < d) {
+        double v = S[c * LD + tid];
+        for (int k = 0; k < c; ++k) v = fma(-lvec[k], S[k * LD + tid], v);
+        S[c * LD + tid] = v;
+      }
+    }
+    __syncthreads();
+    double n2 = 0.0;
+    for (int i = 0; i < d; ++i) n2 = fma(S[c * LD + i], S[c * LD + i], n2);
+    __syncthreads();
+    if (tid < d) S[c * LD + tid] *= 1.0 / sqrt(n2);
+    __syncthreads();
+  }
+  // ---- rank the singular values (descending, the earlier column first on ties), fix signs, write ----
+  if (tid < d) {
+    const double nc = diag[tid];
+    int at = 0;
+    for (int i = 0; i < d; ++i) at += (diag[i] > nc) || (diag[i] == nc && i < tid);
+    int arg = 0;
+    for (int i = 1; i < d; ++i)
+      if (fabs(S[tid * LD + i]) > fabs(S[tid * LD + arg])) arg = i;
+    lvec[tid] = S[tid * LD + arg] < 0 ? -1.0 : 1.0;
+    place[at] = tid;
+    if (sigma) sigma[(long)h * d + at] = (float)sqrt(ldexp(nc, ex));
+  }
+  __syncthreads();
+  float *Ah = A + (long)h * d * d;
+  for (int e = tid; e < d * d; e += NT) {
+    const int c = place[e % d];
+    Ah[e] = (float)(lvec[c] * S[c * LD + e / d]);
+  }
+}
+
+// ---- d > 128: two-sided Jacobi through device memory ------------------------------------------------
+// One workgroup per head: cyclic two-sided Jacobi with a round-robin (tournament) ordering, so that the
+// d/2 rotations of a round act on disjoint index pairs and run in parallel: rotations are computed from
+// the current G, then applied to the columns of G and V, then to the rows of G, with a barrier after
+// each phase.  The number of sweeps is fixed (no data-dependent loop); what is left off the diagonal
+// afterwards is checked and flagged.  G and V live in the double-precision workspace in device memory.
 __global__ __launch_bounds__(256) void jacobi_heads(double *__restrict__ Gall, double *__restrict__ Vall,
                                                     float *__restrict__ A, float *__restrict__ sigma,
                                                     int32_t *status, int d) {
@@ -124,24 +499,29 @@ __global__ __launch_bounds__(256) void jacobi_heads(double *__restrict__ Gall, d
 
 }  // namespace
 
-size_t ig_skew_workspace(int H, int d) { return (size_t)2 * H * d * d * sizeof(double); }
+// Gram matrices; for d > 128 also the eigenvectors under construction
+size_t ig_skew_workspace(int H, int d) { return (size_t)(d > 128 ? 2 : 1) * H * d * d * sizeof(double); }
 
 int ig_launch_skew(ig_ctx *ctx, int D, int H, int n_cal, const float *Qcal, double *ws, float *A,
                    float *sigma, hipStream_t s) {
   const int d = D / H;
-  double *G = ws, *V = ws + (size_t)H * d * d;
+  double *G = ws;
+  const int T = (d + 15) / 16;
   auto k1 = gram_heads;
-  IG_LAUNCH(ctx, IG_K_BUILD, k1, dim3((d * d + 255) / 256, H), dim3(256), s, Qcal, G, n_cal, D, d);
+  IG_LAUNCH(ctx, IG_K_BUILD, k1, dim3(T * (T + 1) / 2, H), dim3(256), s, Qcal, G, n_cal, D, d, T);
+  if (d <= 64) {
+    auto k2 = onesided_heads<64>;
+    IG_LAUNCH(ctx, IG_K_BUILD, k2, dim3(H), dim3(256), s, (const double *)G, A, sigma, ctx->status, d);
+    return IG_OK;
+  }
+  if (d <= 128) {
+    auto k2 = onesided_heads<128>;
+    IG_LAUNCH(ctx, IG_K_BUILD, k2, dim3(H), dim3(256), s, (const double *)G, A, sigma, ctx->status, d);
+    return IG_OK;
+  }
+  double *V = ws + (size_t)H * d * d;
   auto k2 = jacobi_heads;
   const size_t lds = (size_t)(d / 2) * (2 * sizeof(double) + 2 * sizeof(int));
-  if (ctx->profiling) {
-    hipEvent_t e0, e1;
-    ig_prof_events(ctx, IG_K_BUILD, &e0, &e1);
-    hipExtLaunchKernelGGL(k2, dim3(H), dim3(256), (unsigned)lds, s, e0, e1, 0, G, V, A, sigma, ctx->status, d);
-  } else {
-    hipLaunchKernelGGL(k2, dim3(H), dim3(256), (unsigned)lds, s, G, V, A, sigma, ctx->status, d);
-  }
-  hipError_t le = hipGetLastError();
-  if (le != hipSuccess) return ig_hip_fail(ctx, le, "jacobi_heads");
+  IG_LAUNCH_LDS(ctx, IG_K_BUILD, k2, dim3(H), dim3(256), lds, s, G, V, A, sigma, ctx->status, d);
   return IG_OK;
 }

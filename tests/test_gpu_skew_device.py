@@ -93,3 +93,40 @@ def test_error_paths(ctx):
     assert ctx.call("ig_skew_device", 64, 3, 8, p, p, None, 0) == ig.IG_ESHAPE      # D % H
     assert ctx.call("ig_skew_device", 1024, 2, 8, p, p, None, 0) == ig.IG_ESHAPE    # d > 256
     assert ctx.call("ig_skew_device", 64, 2, 8, None, p, None, 0) == ig.IG_EINVAL
+
+
+@pytest.mark.parametrize("d,n,kind", [(2, 8, "full"), (30, 64, "full"), (64, 64, "full"), (66, 70, "graded"), (96, 1, "full"),
+                                      (126, 400, "graded"), (128, 127, "full"), (128, 129, "graded"), (128, 40, "repeated"),
+                                      (64, 33, "zero"), (130, 200, "full")])
+def test_edges_of_the_kernels_against_64_bits(ctx, d, n, kind):
+    """Heads around the tile and kernel edges (d = 64 / 66, 128 / 130), fewer rows than columns, repeated
+    columns, an all-zero head, singular values over five decades: against numpy's SVD in 64 bits.
+    Tolerances: A and sigma are float32 (2^-24 relative each); an inner product of two of A's columns sums
+    d products of entries rounded by 2^-24, so d * 2^-23 bounds it; sigma comes from the Gram matrix in
+    64 bits, whose smallest eigenvalues carry d * 2^-52 of the largest: 2e-7 of sigma_0 covers both.
+    (d = 130 takes the two-sided kernel, whose fixed 16 sweeps do not reach five decades: it reports
+    IG_ENOCONV there, so that case has singular values of one size.)"""
+    rng = np.random.default_rng(d * 1000 + n)
+    H = 2
+    Q = rng.standard_normal((n, H, d))
+    if kind == "graded":
+        Q *= 10.0 ** np.linspace(0, -5, d)
+        Q = Q @ np.linalg.qr(rng.standard_normal((d, d)))[0]
+    if kind == "repeated":
+        Q[:, :, d // 2:] = Q[:, :, : d - d // 2]
+    if kind == "zero":
+        Q[:, 1] = 0
+    Q32 = np.ascontiguousarray(Q.reshape(n, H * d), dtype=np.float32)
+    A, sigma, status = skew_on_gpu(ctx, Q32, H)
+    assert status == 0
+    for h in range(H):
+        Qh = Q32[:, h * d:(h + 1) * d].astype(np.float64)
+        ref = np.zeros(d)
+        ref[: min(n, d)] = np.linalg.svd(Qh, compute_uv=False)
+        top = max(ref[0], 1e-30)
+        assert np.abs(A[h].T @ A[h] - np.eye(d)).max() <= d * 2.0 ** -23
+        assert np.abs(sigma[h] - ref).max() <= 2e-7 * top
+        gram = (Qh @ A[h]).T @ (Qh @ A[h])
+        assert np.abs(gram - np.diag(np.diag(gram))).max() <= d * 2.0 ** -23 * top * top
+        big = np.abs(A[h]).max(0)
+        assert np.all(A[h].max(0) >= big * (1 - 1e-6))                 # largest entry positive
