@@ -3,9 +3,9 @@
 //
 // Two kernels, both with a fixed summation order (no floating-point atomics, so a run repeats
 // bit for bit):
-//   column_abs_sums   a workgroup takes 256 consecutive columns and one of ROW_CHUNKS row ranges;
-//                     thread c walks its column down the range (a wave reads 64 consecutive
-//                     elements of a row: coalesced) and writes one partial sum
+//   column_abs_sums   a lane takes VEC consecutive columns (8-byte loads in half precision, 16-byte in
+//                     float32) and one of ROW_CHUNKS row ranges, walks it down and writes one partial
+//                     sum per column
 //   top_columns       one workgroup per head: adds the ROW_CHUNKS partial sums of each column in
 //                     order, ranks the d columns (column j beats c when its sum is larger, or
 //                     equal with j < c), keeps ranks < r and writes them in ascending order
@@ -15,46 +15,99 @@ namespace {
 
 constexpr int ROW_CHUNKS = 32;
 
-template <typename T>
-__global__ __launch_bounds__(256) void column_abs_sums(const T *__restrict__ Qs, const T *__restrict__ Ks,
-                                                       float *__restrict__ part, int n, int D) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
+// HBM-bound (the rows are read once).  What it takes is bytes in flight: the grid is small (D columns
+// x 32 ranges), so a lane issues the loads of 16 rows of both matrices before it adds the first, in the
+// row order of the plain loop.  2048 rows of 4096 half columns, queries and keys (33.5 MB): 55 us with
+// 2-byte loads one row at a time, 13 us so.  Arrays whose rows or addresses do not allow the wide
+// loads go one column a lane.
+template <typename T, int VEC>
+__global__ __launch_bounds__(64) void column_abs_sums(const T *__restrict__ Qs, const T *__restrict__ Ks,
+                                                      float *__restrict__ part, int n, int D) {
+  typedef T vec __attribute__((ext_vector_type(VEC)));
+  constexpr int U = 16;
+  const int c = (blockIdx.x * 64 + threadIdx.x) * VEC;
   const int chunk = blockIdx.y;
   const int rows_per = (n + ROW_CHUNKS - 1) / ROW_CHUNKS;
   const int i0 = chunk * rows_per, i1 = min(n, i0 + rows_per);
   if (c >= D) return;
-  float acc = 0.f;
-  for (int i = i0; i < i1; ++i) {
-    acc += fabsf((float)Qs[(long)i * D + c]);
-    if (Ks) acc += fabsf((float)Ks[(long)i * D + c]);
+  const T *Kp = Ks ? Ks : Qs;                // (without keys: read and not added)
+  float acc[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+  for (int i = i0; i < i1; i += U) {
+    vec q[U], k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long at = (long)min(i + u, i1 - 1) * D + c;      // past the end: the last row again, not added
+      q[u] = *reinterpret_cast<const vec *>(Qs + at);
+      k[u] = *reinterpret_cast<const vec *>(Kp + at);
+    }
+    __builtin_amdgcn_sched_barrier(0);       // (the compiler would trade loads in flight for registers)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i + u < i1) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          acc[e] += fabsf((float)q[u][e]);
+          if (Ks) acc[e] += fabsf((float)k[u][e]);
+        }
+      }
+    }
   }
-  part[(long)chunk * D + c] = acc;
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) part[(long)chunk * D + c + e] = acc[e];
 }
 
-__global__ __launch_bounds__(256) void top_columns(const float *__restrict__ part, int32_t *__restrict__ idx,
-                                                   int d, int D, int r) {
-  __shared__ float sum[256];
-  __shared__ int keep[256];
-  __shared__ int wave_tot[4];
-  const int h = blockIdx.x, c = threadIdx.x, lane = c & 63, w = c >> 6;
-  float v = -1.f;                       // sums are >= 0: unused lanes never win
-  if (c < d) {
-    v = 0.f;
-    for (int k = 0; k < ROW_CHUNKS; ++k) v += part[(long)k * D + h * d + c];
+// One workgroup per head and a chain of dependent steps: the ROW_CHUNKS partial sums of a column in flight
+// at once, the d * d comparisons spread over PARTS threads a column (3 us on 32 heads of 128
+// columns; 6.3 us with one load after another and d comparisons a thread).
+template <int DP>      // columns, rounded up to 64, 128 or 256
+__global__ __launch_bounds__(1024) void top_columns(const float *__restrict__ part, int32_t *__restrict__ idx,
+                                                    int d, int D, int r) {
+  constexpr int PARTS = 1024 / DP, PER = DP / PARTS;
+  __shared__ __align__(16) float sum[DP];
+  __shared__ int below[PARTS][DP];
+  __shared__ int wave_tot[DP / 64];
+  const int h = blockIdx.x, c = threadIdx.x % DP, p = threadIdx.x / DP, lane = threadIdx.x & 63;
+  if (p == 0) {
+    float v[ROW_CHUNKS];
+    const float *col = part + h * d + min(c, d - 1);
+#pragma unroll
+    for (int k = 0; k < ROW_CHUNKS; ++k) v[k] = col[(long)k * D];
+    __builtin_amdgcn_sched_barrier(0);
+    float acc = 0.f;
+#pragma unroll
+    for (int k = 0; k < ROW_CHUNKS; ++k) acc += v[k];
+    sum[c] = c < d ? acc : -1.f;             // sums are >= 0: columns past d never win
   }
-  sum[c] = v;
   __syncthreads();
-  int rank = 0;
-  if (c < d)
-    for (int j = 0; j < d; ++j) rank += (sum[j] > v) || (sum[j] == v && j < c);
-  const bool kept = c < d && rank < r;
-  keep[c] = kept;
-  const unsigned long long bal = __ballot(kept);
-  if (lane == 0) wave_tot[w] = __popcll(bal);
+  // columns that beat column c: a larger sum, or an equal one further left
+  const float v = sum[c];
+  int n = 0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int j = p * PER + u;
+    const float o = sum[j];
+    n += (o > v) || (o == v && j < c);
+  }
+  below[p][c] = n;
   __syncthreads();
-  int pos = lanes_below(bal);
-  for (int k = 0; k < w; ++k) pos += wave_tot[k];
-  if (kept) idx[h * r + pos] = c;
+  bool kept = false;
+  unsigned long long bal = 0;
+  if (p == 0) {
+    int rank = 0;
+#pragma unroll
+    for (int k = 0; k < PARTS; ++k) rank += below[k][c];
+    kept = c < d && rank < r;
+    bal = __ballot(kept);
+    if (lane == 0) wave_tot[c / 64] = __popcll(bal);
+  }
+  __syncthreads();
+  if (kept) {
+    int pos = lanes_below(bal);
+    for (int k = 0; k < c / 64; ++k) pos += wave_tot[k];
+    idx[h * r + pos] = c;
+  }
 }
 
 }  // namespace
@@ -62,16 +115,26 @@ __global__ __launch_bounds__(256) void top_columns(const float *__restrict__ par
 int ig_launch_partial_index(ig_ctx *ctx, int dtype, int H, int d, int n, const void *Qs, const void *Ks,
                             int r, float *part, int32_t *idx, hipStream_t s) {
   const int D = H * d;
-  dim3 grid((D + 255) / 256, ROW_CHUNKS), block(256);
-  if (dtype == IG_F16) {
-    auto k = column_abs_sums<half_t>;
-    IG_LAUNCH(ctx, IG_K_BUILD, k, grid, block, s, (const half_t *)Qs, (const half_t *)Ks, part, n, D);
-  } else {
-    auto k = column_abs_sums<float>;
-    IG_LAUNCH(ctx, IG_K_BUILD, k, grid, block, s, (const float *)Qs, (const float *)Ks, part, n, D);
+  const size_t align = (size_t)D * ig_elem_bytes(dtype) | (uintptr_t)Qs | (uintptr_t)Ks;
+#define SUMS(T, VEC)                                                                               \
+  {                                                                                                \
+    auto k = column_abs_sums<T, VEC>;                                                              \
+    IG_LAUNCH(ctx, IG_K_BUILD, k, dim3((D + 64 * VEC - 1) / (64 * VEC), ROW_CHUNKS), dim3(64), s,  \
+              (const T *)Qs, (const T *)Ks, part, n, D);                                           \
   }
-  auto k2 = top_columns;
-  IG_LAUNCH(ctx, IG_K_BUILD, k2, dim3(H), dim3(256), s, (const float *)part, idx, d, D, r);
+  if (dtype == IG_F16) {
+    if (align % 8 == 0) SUMS(half_t, 4) else SUMS(half_t, 1)
+  } else {
+    if (align % 16 == 0) SUMS(float, 4) else SUMS(float, 1)
+  }
+#undef SUMS
+#define TOP(DP)                                                                                    \
+  {                                                                                                \
+    auto k2 = top_columns<DP>;                                                                     \
+    IG_LAUNCH(ctx, IG_K_BUILD, k2, dim3(H), dim3(1024), s, (const float *)part, idx, d, D, r);     \
+  }
+  if (d <= 64) TOP(64) else if (d <= 128) TOP(128) else TOP(256)
+#undef TOP
   return IG_OK;
 }
 

@@ -77,3 +77,29 @@ def test_error_paths(ctx):
     assert call(ig.IG_F32, 2, 64, 4, None, None, 0.3, p, 0) == ig.IG_EINVAL
     assert call(ig.IG_F32, 2, 64, 4, p, None, 0.0, p, 0) == ig.IG_EINVAL
     assert call(ig.IG_F32, 2, 2, 4, p, None, 0.3, p, 0) == ig.IG_ESHAPE         # floor(0.3 * 2) = 0
+
+
+@pytest.mark.parametrize("dtype,H,d,n", [("f16", 3, 64, 100), ("f16", 3, 7, 33), ("f32", 2, 128, 31), ("f32", 5, 3, 600)])
+def test_arrays_of_any_alignment_give_the_same_columns(ctx, dtype, H, d, n):
+    """Wide loads need 8- or 16-byte rows and addresses; the same rows one element further in memory, and
+    rows of odd length, take the one-column-a-lane form, which adds in the same order: equal results."""
+    import paper_2406_19707_amd as ig
+    rng = np.random.default_rng(n + d)
+    tdt = torch.float16 if dtype == "f16" else torch.float32
+    code = ig.IG_F16 if dtype == "f16" else ig.IG_F32
+    Q, K = (torch.from_numpy(rng.standard_normal((n, H * d))).to(tdt) for _ in range(2))
+    got = []
+    for shift in (0, 1):
+        bufs = [torch.zeros(n * H * d + 8, dtype=tdt, device="cuda") for _ in range(2)]
+        q, k = (b[shift: shift + n * H * d] for b in bufs)
+        q.copy_(Q.reshape(-1)), k.copy_(K.reshape(-1))
+        idx = torch.full((H, int(0.4 * d)), -1, dtype=torch.int32, device="cuda")
+        ctx.ig_partial_index_device(code, H, d, n, q, k, 0.4, idx)
+        torch.cuda.synchronize()
+        got.append(idx.cpu().numpy())
+    assert np.array_equal(got[0], got[1])
+    sums = np.abs(Q.double().numpy()).sum(0) + np.abs(K.double().numpy()).sum(0)
+    for h in range(H):
+        c = sums[h * d:(h + 1) * d]
+        cut = np.sort(c)[::-1][got[0].shape[1] - 1]
+        assert np.all(c[got[0][h]] >= cut * (1 - 1e-5))
