@@ -64,6 +64,26 @@ struct ProjGeom {
 };
 ProjGeom ig_proj_geom(const ig_desc *d);
 
+// Division by a number fixed at launch, worked out on the host: n / d for 0 <= n < 2^31 as one 64-bit
+// product and a shift, on the scalar unit where n is uniform.  A kernel's own 32-bit division is some
+// thirty dependent vector instructions: cheap once, but the attention's grids are mostly workgroups that
+// do nothing else.
+struct FastDiv {
+  unsigned m, sh, d;
+  __host__ __device__ __forceinline__ int div(int n) const {
+    return (int)(((unsigned long long)(unsigned)n * m) >> sh);
+  }
+  __host__ __device__ __forceinline__ int mod(int n) const { return n - div(n) * (int)d; }
+};
+static inline FastDiv ig_fast_div(int d) {
+  // m = ceil(2^(31+s) / d) with 2^s the next power of two: n * (m*d - 2^(31+s)) < 2^31 * 2^s, so the
+  // quotient is exact, and m stays below 2^32
+  unsigned s = 0;
+  while ((1ull << s) < (unsigned long long)d) ++s;
+  const unsigned long long p = 1ull << (31 + s);
+  return FastDiv{(unsigned)((p + d - 1) / d), 31 + s, (unsigned)d};
+}
+
 struct ProfRec {
   int which;
   hipEvent_t e0, e1;
@@ -240,6 +260,16 @@ __device__ __forceinline__ void rope_sincos(double ang, double *sn, double *cs) 
   *sn = q == 0 ? s : (q == 1 ? c : (q == 2 ? -s : -c));
   *cs = q == 0 ? c : (q == 1 ? -s : (q == 2 ? -c : s));
 }
+// ---- keeping loads where they are issued ----------------------------------------------------------
+// A load whose only use is under a condition is moved down to that use by the compiler, which turns a
+// batch of loads into a chain of round trips.  Naming the loaded value here, unconditionally and after
+// the batch, keeps the load up there (no instruction is emitted).
+template <typename V> __device__ __forceinline__ void keep_loaded(V &v) {
+  typedef int int4v __attribute__((ext_vector_type(4)));
+  static_assert(sizeof(V) == 16, "four registers");
+  asm volatile("" : "+v"(*reinterpret_cast<int4v *>(&v)));
+}
+
 // ---- wave helpers -------------------------------------------------------------------------------
 // Cross-lane moves inside a 16-lane row through DPP (no LDS crossbar traffic).
 template <int CTRL> __device__ __forceinline__ float dpp_move(float v) {

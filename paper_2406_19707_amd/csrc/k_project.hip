@@ -87,20 +87,23 @@ template <int NB>
 __global__ __launch_bounds__(256) void project_mfma(const half8 *__restrict__ blob,
                                                     const half_t *__restrict__ x,
                                                     float *__restrict__ part, int B, int D,
-                                                    int nCblk, int nKblk, int kb_per, int KS,
-                                                    int Bpad, int Cpad) {
-  const int lane = threadIdx.x & 63;
-  const long gw = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (gw >= (long)nCblk * KS) return;
-  const int cblk = gw % nCblk, ks = gw / nCblk;
-  const int nb0 = blockIdx.y * NB;
+                                                    int nCblk, int nKblk, int kb_per, int Bpad,
+                                                    int Cpad) {
+  // grid (column blocks / 4, KS, batch blocks / NB): nothing to divide before the first load goes out
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int cblk = blockIdx.x * 4 + w, ks = blockIdx.y;
+  if (cblk >= nCblk) return;
+  const int nb0 = blockIdx.z * NB;
   const int n = lane & 15, kg = lane >> 4;
   const int kb0 = ks * kb_per, kb1 = min(nKblk, kb0 + kb_per);
   floatx4 acc[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
   const half8 *wp = blob + ((long)cblk * nKblk) * 64 + lane;
-  const half8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+  // (lanes of a batch row past the last read the last row: a row of x only reaches its own row of the result)
+  const half_t *xp[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) xp[i] = x + (long)min((nb0 + i) * 16 + n, B - 1) * D + kg * 8;
   // K blocks are taken KB at a time: all weight pieces and x fragments of a batch are loaded before
   // the first MFMA, so a wave keeps KB * (1 + NB) KiB in flight (a block past the end is clamped
   // to the last one and its MFMA skipped).
@@ -113,13 +116,15 @@ __global__ __launch_bounds__(256) void project_mfma(const half8 *__restrict__ bl
       a[t] = wp[(long)kbt * 64];
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
-        const int row = (nb0 + i) * 16 + n;
-        bfrag[i][t] = zero;
-        if (row < B) bfrag[i][t] = *reinterpret_cast<const half8 *>(x + (long)row * D + kbt * 32 + kg * 8);
+        bfrag[i][t] = *reinterpret_cast<const half8 *>(xp[i] + kbt * 32);
       }
     }
+    __builtin_amdgcn_sched_barrier(0);   // (the compiler would trade loads in flight for registers)
 #pragma unroll
     for (int t = 0; t < KB; ++t) {
+      keep_loaded(a[t]);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) keep_loaded(bfrag[i][t]);
       if (kb + t < kb1) {
 #pragma unroll
         for (int i = 0; i < NB; ++i)
@@ -130,7 +135,7 @@ __global__ __launch_bounds__(256) void project_mfma(const half8 *__restrict__ bl
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     int row = (nb0 + i) * 16 + n;
-    if (row < Bpad) {
+    if (row < B) {                        // (the padding rows' sums are never read)
       float *o = part + ((long)ks * Bpad + row) * Cpad + cblk * 16 + kg * 4;
       *reinterpret_cast<floatx4 *>(o) = acc[i];
     }
@@ -150,7 +155,7 @@ __global__ __launch_bounds__(256) void project_mfma_shared(const half8 *__restri
                                                            const half_t *__restrict__ x,
                                                            float *__restrict__ part, int B, int D,
                                                            int nCblk, int nKblk, int kb_per, int Bpad,
-                                                           int Cpad) {
+                                                           int Cpad, FastDiv by_ppr) {
   extern __shared__ uint4 xs[];                       // [NB*16 rows][kb_per*4 + 1] 16-byte pieces
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int ks = blockIdx.y;
@@ -160,29 +165,31 @@ __global__ __launch_bounds__(256) void project_mfma_shared(const half8 *__restri
   const int n = lane & 15, kg = lane >> 4;
   const int kb0 = ks * kb_per, kb1 = min(nKblk, kb0 + kb_per);
   const int nkb = kb1 - kb0;
-  // x rows of the slice (rows past B are zero): loaded first, because they are needed first -- a
-  // wave's loads return in the order it issued them -- then the weight pieces of the whole K slice
+  // x rows of the slice: loaded first, because they are needed first -- a wave's loads return in the
+  // order it issued them -- then the weight pieces of the whole K slice.  (Rows past the last read the
+  // last row, which only reaches rows of the result that are not written; pieces past a short last slice
+  // read its last piece, which no product takes.)
   const int ppr = kb_per * 4, stride = ppr + 1;       // 16-byte pieces per row, padded stride
   const int pieces = NB * 16 * ppr;
   constexpr int XPT = NB * 16 * PKB * 4 / 256;         // x pieces per thread at most
   uint4 xv[XPT];
+  int at[XPT];                                        // where the piece goes in xs
 #pragma unroll
   for (int u = 0; u < XPT; ++u) {
     const int p = threadIdx.x + u * 256;
-    const int row = p / ppr, c = p - row * ppr;
-    xv[u] = make_uint4(0, 0, 0, 0);
-    if (p < pieces && row < B && kb0 * 4 + c < nKblk * 4)
-      xv[u] = *reinterpret_cast<const uint4 *>(x + (long)row * D + (long)kb0 * 32 + c * 8);
+    const int row = by_ppr.div(p), c = p - row * ppr;
+    at[u] = row * stride + c;
+    xv[u] = *reinterpret_cast<const uint4 *>(x + (long)min(row, B - 1) * D + (long)kb0 * 32 + min(c, nkb * 4 - 1) * 8);
   }
   half8 a[PKB];
   const half8 *wp = blob + ((long)cblk * nKblk + kb0) * 64 + lane;
 #pragma unroll
   for (int t = 0; t < PKB; ++t) a[t] = wp[(long)min(t, nkb - 1) * 64];
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int u = 0; u < XPT; ++u) {
-    const int p = threadIdx.x + u * 256;
-    const int row = p / ppr, c = p - row * ppr;
-    if (p < pieces) xs[row * stride + c] = xv[u];
+    keep_loaded(xv[u]);
+    if ((int)threadIdx.x + u * 256 < pieces) xs[at[u]] = xv[u];
   }
   __syncthreads();
   if (!live) return;
@@ -191,6 +198,7 @@ __global__ __launch_bounds__(256) void project_mfma_shared(const half8 *__restri
   for (int i = 0; i < NB; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int t = 0; t < PKB; ++t) {
+    keep_loaded(a[t]);
     if (t < nkb) {
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
@@ -202,37 +210,55 @@ __global__ __launch_bounds__(256) void project_mfma_shared(const half8 *__restri
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     const int row = i * 16 + n;
-    if (row < Bpad) {
+    if (row < B) {
       float *o = part + ((long)ks * Bpad + row) * Cpad + cblk * 16 + kg * 4;
       *reinterpret_cast<floatx4 *>(o) = acc[i];
     }
   }
 }
 
-// One thread per output column, 16 batch rows per pass, K rows [ks*kb_per, ...).
-template <typename T>
+// One thread per output column, NR batch rows per pass, K rows [ks*kb_per, ...).  Weight-read bound on
+// paper; on the small shapes that come here it is a chain of round trips, so the weight elements of U rows
+// of K are in flight before the first is used, and only the batch rows that exist are multiplied (NR, a
+// power of two up to 16).  The x entries are wave-uniform: scalar loads.  (256 x 76 float32 weight, one
+// sequence: 2.6 us, against 6.7 us with one row of K after another and 16 batch rows always.)
+template <typename T, int NR>
 __global__ __launch_bounds__(64) void project_fma(const T *__restrict__ blob, const T *__restrict__ x,
                                                   float *__restrict__ part, int B, int D, int kb_per,
                                                   int Bpad, int Cpad) {
+  constexpr int U = 16;
   const int c = blockIdx.x * 64 + threadIdx.x;
   const int ks = blockIdx.y;
-  const int n0 = blockIdx.z * 16;
+  const int n0 = blockIdx.z * NR;
   if (c >= Cpad) return;
   const int k0 = ks * kb_per, k1 = min(D, k0 + kb_per);
-  float acc[16];
+  float acc[NR];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-  for (int k = k0; k < k1; ++k) {
-    float wv = (float)blob[(long)k * Cpad + c];
+  for (int i = 0; i < NR; ++i) acc[i] = 0.f;
+  const T *xr[NR];                        // (rows past the last read the last row; their sums are not written)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      int row = n0 + i;
-      float xv = (row < B) ? (float)x[(long)row * D + k] : 0.f;
-      acc[i] = fmaf(xv, wv, acc[i]);
+  for (int i = 0; i < NR; ++i) xr[i] = x + (long)min(n0 + i, B - 1) * D;
+  for (int k = k0; k < k1; k += U) {
+    T wv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) wv[u] = blob[(long)min(k + u, k1 - 1) * Cpad + c];
+    if (k + U <= k1) {
+#pragma unroll
+      for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[i] = fmaf((float)xr[i][k + u], (float)wv[u], acc[i]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (k + u < k1) {
+#pragma unroll
+          for (int i = 0; i < NR; ++i) acc[i] = fmaf((float)xr[i][k + u], (float)wv[u], acc[i]);
+        }
     }
   }
 #pragma unroll
-  for (int i = 0; i < 16; ++i) part[((long)ks * Bpad + n0 + i) * Cpad + c] = acc[i];
+  for (int i = 0; i < NR; ++i)
+    if (n0 + i < B) part[((long)ks * Bpad + n0 + i) * Cpad + c] = acc[i];
 }
 
 // ---- index-only partial weight ------------------------------------------------------------------
@@ -330,7 +356,7 @@ __global__ __launch_bounds__(256) void project_columns(const T *__restrict__ W, 
     const int b = i / r, j = i % r;
     const int row = n0 + b;
     const int col = min(max(idx[h * r + j], 0), d - 1);
-    if (row < Bpad) part[((long)ks * Bpad + row) * Cpad + h * r + j] = red[b * 512 + col];
+    if (row < B) part[((long)ks * Bpad + row) * Cpad + h * r + j] = red[b * 512 + col];
   }
 }
 
@@ -360,22 +386,28 @@ __global__ __launch_bounds__(256) void project_columns_mfma(const half_t *__rest
   for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const half8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
   const half_t *wp = W + (long)cb * 128 + n * 8;
   // two steps per pass: 16 row loads of a lane are in flight before the first MFMA
   for (int kb = k0 + w * 32; kb < k1; kb += 256) {
     half8 rows[2][8], xf[2][NB];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const int kt = kb + t * 128 + kg * 8;
-      const bool ok = kt < k1;
+      // (a step past the slice reads its last 32 rows again and is not multiplied; lanes of a batch row
+      // past the last read the last row, which only reaches rows of the result that are not written)
+      const int kt = min(kb + t * 128, k1 - 32) + kg * 8;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) rows[t][e] = ok ? *reinterpret_cast<const half8 *>(wp + (long)(kt + e) * D) : zero;
+      for (int e = 0; e < 8; ++e) rows[t][e] = *reinterpret_cast<const half8 *>(wp + (long)(kt + e) * D);
 #pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const int row = (nb0 + i) * 16 + n;
-        xf[t][i] = (ok && row < B) ? *reinterpret_cast<const half8 *>(x + (long)row * D + kt) : zero;
-      }
+      for (int i = 0; i < NB; ++i)
+        xf[t][i] = *reinterpret_cast<const half8 *>(x + (long)min((nb0 + i) * 16 + n, B - 1) * D + kt);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) keep_loaded(rows[t][e]);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) keep_loaded(xf[t][i]);
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -414,7 +446,7 @@ __global__ __launch_bounds__(256) void project_columns_mfma(const half_t *__rest
     if (col < 0 || col >= 128) continue;
     for (int b = 0; b < NB * 16; ++b) {
       const int row = nb0 * 16 + b;
-      if (row < Bpad) part[((long)ks * Bpad + row) * Cpad + i] = red[b * RS + col];
+      if (row < B) part[((long)ks * Bpad + row) * Cpad + i] = red[b * RS + col];
     }
   }
 }
@@ -425,17 +457,20 @@ __global__ __launch_bounds__(256) void project_columns_mfma(const half_t *__rest
 //         pos[b]*theta^(-2c/d) (angle in double: positions reach 1e5 where float loses the phase);
 //         q_p[b,h,k] = sum_c q_rot[c] * A_p[h][c][k]
 // (Section 4.3 "Decoding Stage" for models whose skew cannot be folded into W_Q.)
+// A chain of dependent steps: 5.6 us for 160 heads of 128 columns while the compiler put conditions around
+// its loads (one round trip after another), 4.8 us with every load of a thread in flight at once.
 __global__ __launch_bounds__(256) void finalize_query(const float *__restrict__ part,
                                                       const float *__restrict__ bias,
                                                       const float *__restrict__ A_p,
                                                       const int32_t *__restrict__ pos,
                                                       float *__restrict__ q_p, int H, int d, int r,
                                                       int KS, long ks_stride, int Cpad, int rope,
-                                                      double freq_step /* -(2/d) log2(theta) */) {
+                                                      double freq_step /* -(2/d) log2(theta) */,
+                                                      FastDiv by_H, FastDiv by_r, int G, int per) {
   __shared__ float q[512];
   __shared__ float qr[512];
   __shared__ float psum[256];
-  const int bh = blockIdx.x, b = bh / H, h = bh % H;
+  const int bh = blockIdx.x, b = by_H.div(bh), h = bh - b * H;
   const int t = threadIdx.x;
   if (!rope) {
     // split-K partial sums: all loads of a column issued together, added in a fixed order
@@ -443,10 +478,10 @@ __global__ __launch_bounds__(256) void finalize_query(const float *__restrict__ 
       const float *p = part + (long)b * Cpad + (long)h * r + c;
       float v[IG_KS_MAX];
 #pragma unroll
-      for (int s = 0; s < IG_KS_MAX; ++s) v[s] = (s < KS) ? p[s * ks_stride] : 0.f;
+      for (int s = 0; s < IG_KS_MAX; ++s) v[s] = p[(long)min(s, KS - 1) * ks_stride];
       float acc = bias ? bias[h * r + c] : 0.f;
 #pragma unroll
-      for (int s = 0; s < IG_KS_MAX; ++s) acc += v[s];
+      for (int s = 0; s < IG_KS_MAX; ++s) acc += s < KS ? v[s] : 0.f;
       q_p[(long)bh * r + c] = acc;
     }
     return;
@@ -454,58 +489,65 @@ __global__ __launch_bounds__(256) void finalize_query(const float *__restrict__ 
   // Rotary model.  The block is one chain of dependent steps, so everything it reads is put in
   // flight before the first step: the partial sums of its (up to two) columns, the position, and
   // the thread's rows of A_p, which do not depend on the query at all.
-  float v[2][IG_KS_MAX], bs[2];
+  // (Addresses are clamped and surplus values dropped where they are used: a condition around a load
+  // becomes a branch, and loads behind branches were issued one round trip after another.  The second
+  // column of a thread exists for d > 256 only.)
+  float v[IG_KS_MAX], v2[IG_KS_MAX], bs, bs2 = 0.f;
+  {
+    const float *p = part + (long)b * Cpad + (long)h * d;
+    const int c = min(t, d - 1);
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int c = t + 256 * u;
+    for (int s = 0; s < IG_KS_MAX; ++s) v[s] = p[(long)min(s, KS - 1) * ks_stride + c];
+    bs = *(bias ? bias + h * d + c : p);
+    if (d > 256) {
+      const int c2 = min(t + 256, d - 1);
 #pragma unroll
-    for (int s = 0; s < IG_KS_MAX; ++s) v[u][s] = 0.f;
-    bs[u] = 0.f;
-    if (c < d) {
-      const float *p = part + (long)b * Cpad + (long)h * d + c;
-#pragma unroll
-      for (int s = 0; s < IG_KS_MAX; ++s)
-        if (s < KS) v[u][s] = p[s * ks_stride];
-      if (bias) bs[u] = bias[h * d + c];
+      for (int s = 0; s < IG_KS_MAX; ++s) v2[s] = p[(long)min(s, KS - 1) * ks_stride + c2];
+      if (bias) bs2 = bias[h * d + c2];
     }
   }
   const int position = pos[b];
   // q_p[k] = sum_c qr[c] * A_p[h][c][k]: the threads are G groups of r; group g sums its share of
   // the rows c for output k (reads of A_p coalesce over k), then the groups are added in order
-  const int G = 256 / r;                      // r <= 256
-  const int k = t % r, g = t / r;
-  const int per = (d + G - 1) / G;
+  // (G = 256 / r, r <= 256; per = ceil(d / G) rows each)
+  const int g = by_r.div(t), k = t - g * r;
   const int c0 = g < G ? min(d, g * per) : d, c1 = g < G ? min(d, (g + 1) * per) : d;
   constexpr int PF = 24;
   const float *ap = A_p + (long)h * d * r + k;
   float apf[PF];
 #pragma unroll
-  for (int i = 0; i < PF; ++i) {
-    apf[i] = 0.f;
-    if (c0 + i < c1) apf[i] = ap[(long)(c0 + i) * r];
-  }
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int c = t + 256 * u;
-    float acc = bs[u];
-#pragma unroll
-    for (int s = 0; s < IG_KS_MAX; ++s) acc += v[u][s];
-    if (c < d) q[c] = acc;
-  }
-  __syncthreads();
+  for (int i = 0; i < PF; ++i) apf[i] = ap[(long)min(c0 + i, d - 1) * r];
+  __builtin_amdgcn_sched_barrier(0);
+  // the angle's frequency depends on nothing that is loaded (d <= 512: one pair a thread)
   const int half = d / 2;
-  for (int c = t; c < half; c += 256) {
-    double sn, cs;
-    rope_sincos((double)position * exp2((double)c * freq_step), &sn, &cs);
-    float a = q[c], bb = q[c + half];
-    qr[c] = (float)((double)a * cs - (double)bb * sn);
-    qr[c + half] = (float)((double)bb * cs + (double)a * sn);
+  const double freq = exp2((double)t * freq_step);
+  {
+    float acc = bias ? bs : 0.f;
+#pragma unroll
+    for (int s = 0; s < IG_KS_MAX; ++s) acc += s < KS ? v[s] : 0.f;
+    if (t < d) q[t] = acc;
+  }
+  if (d > 256) {
+    float acc = bs2;
+#pragma unroll
+    for (int s = 0; s < IG_KS_MAX; ++s) acc += s < KS ? v2[s] : 0.f;
+    if (t + 256 < d) q[t + 256] = acc;
+  }
+  double sn, cs;
+  rope_sincos((double)position * freq, &sn, &cs);
+  __syncthreads();
+  if (t < half) {
+    float a = q[t], bb = q[t + half];
+    qr[t] = (float)((double)a * cs - (double)bb * sn);
+    qr[t + half] = (float)((double)bb * cs + (double)a * sn);
   }
   __syncthreads();
   float acc = 0.f;
 #pragma unroll
-  for (int i = 0; i < PF; ++i)
-    if (c0 + i < c1) acc = fmaf(qr[c0 + i], apf[i], acc);
+  for (int i = 0; i < PF; ++i) {               // (a condition around the LDS read would be a branch)
+    const float next = fmaf(qr[min(c0 + i, d - 1)], apf[i], acc);
+    acc = c0 + i < c1 ? next : acc;
+  }
   for (int c = c0 + PF; c < c1; ++c) acc = fmaf(qr[c], ap[(long)c * r], acc);
   psum[t] = acc;
   __syncthreads();
@@ -545,42 +587,44 @@ int ig_launch_project(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, const vo
                       const void *wq, float *part, hipStream_t s) {
   const int D = d->H * d->d;
   if (g.mfma) {
-    long waves = (long)g.nCblk * g.KS;
+    const unsigned cols = (unsigned)((g.nCblk + 3) / 4);
     dim3 block(256);
     if (g.NBtot == 1) {
       auto k = project_mfma<1>;
-      IG_LAUNCH(ctx, IG_K_PROJECT, k, dim3((unsigned)((waves + 3) / 4), 1), block, s,
-                (const half8 *)wq, (const half_t *)x, part, (int)d->B, D, g.nCblk, g.nKblk, g.kb_per,
-                g.KS, g.Bpad, g.Cpad);
+      IG_LAUNCH(ctx, IG_K_PROJECT, k, dim3(cols, g.KS), block, s, (const half8 *)wq, (const half_t *)x,
+                part, (int)d->B, D, g.nCblk, g.nKblk, g.kb_per, g.Bpad, g.Cpad);
     } else if (g.NBtot == 2 && g.kb_per <= 16) {
       // 17..32 batch rows: x fragments through LDS, a wave's whole K slice of weights in flight
       auto k = project_mfma_shared<2, 16>;
       const size_t lds = (size_t)32 * (g.kb_per * 4 + 1) * 16;
-      const dim3 grid((unsigned)((g.nCblk + 3) / 4), (unsigned)g.KS);
+      const dim3 grid(cols, (unsigned)g.KS);
       IG_LAUNCH_LDS(ctx, IG_K_PROJECT, k, grid, block, lds, s, (const half8 *)wq, (const half_t *)x, part,
-                    (int)d->B, D, g.nCblk, g.nKblk, g.kb_per, g.Bpad, g.Cpad);
+                    (int)d->B, D, g.nCblk, g.nKblk, g.kb_per, g.Bpad, g.Cpad, ig_fast_div(g.kb_per * 4));
     } else if (g.NBtot == 2) {
       auto k = project_mfma<2>;
-      IG_LAUNCH(ctx, IG_K_PROJECT, k, dim3((unsigned)((waves + 3) / 4), 1), block, s,
-                (const half8 *)wq, (const half_t *)x, part, (int)d->B, D, g.nCblk, g.nKblk, g.kb_per,
-                g.KS, g.Bpad, g.Cpad);
+      IG_LAUNCH(ctx, IG_K_PROJECT, k, dim3(cols, g.KS), block, s, (const half8 *)wq, (const half_t *)x,
+                part, (int)d->B, D, g.nCblk, g.nKblk, g.kb_per, g.Bpad, g.Cpad);
     } else {
       auto k = project_mfma<4>;
-      IG_LAUNCH(ctx, IG_K_PROJECT, k, dim3((unsigned)((waves + 3) / 4), (unsigned)((g.NBtot + 3) / 4)),
-                block, s, (const half8 *)wq, (const half_t *)x, part, (int)d->B, D, g.nCblk, g.nKblk,
-                g.kb_per, g.KS, g.Bpad, g.Cpad);
+      IG_LAUNCH(ctx, IG_K_PROJECT, k, dim3(cols, g.KS, (unsigned)((g.NBtot + 3) / 4)), block, s,
+                (const half8 *)wq, (const half_t *)x, part, (int)d->B, D, g.nCblk, g.nKblk, g.kb_per,
+                g.Bpad, g.Cpad);
     }
   } else {
-    dim3 grid((g.Cpad + 63) / 64, g.KS, g.NBtot), block(64);
+    const int nr = d->B > 8 ? 16 : (d->B > 4 ? 8 : (d->B > 2 ? 4 : d->B));
+    dim3 grid((g.Cpad + 63) / 64, g.KS, (d->B + nr - 1) / nr), block(64);
+#define FMA_CASE(T, NR)                                                                            \
+  if (nr == NR) {                                                                                  \
+    auto k = project_fma<T, NR>;                                                                   \
+    IG_LAUNCH(ctx, IG_K_PROJECT, k, grid, block, s, (const T *)wq, (const T *)x, part, (int)d->B,  \
+              D, g.kb_per, g.Bpad, g.Cpad);                                                        \
+  }
     if (d->dtype == IG_F16) {
-      auto k = project_fma<half_t>;
-      IG_LAUNCH(ctx, IG_K_PROJECT, k, grid, block, s, (const half_t *)wq, (const half_t *)x, part,
-                (int)d->B, D, g.kb_per, g.Bpad, g.Cpad);
+      FMA_CASE(half_t, 1) FMA_CASE(half_t, 2) FMA_CASE(half_t, 4) FMA_CASE(half_t, 8) FMA_CASE(half_t, 16)
     } else {
-      auto k = project_fma<float>;
-      IG_LAUNCH(ctx, IG_K_PROJECT, k, grid, block, s, (const float *)wq, (const float *)x, part,
-                (int)d->B, D, g.kb_per, g.Bpad, g.Cpad);
+      FMA_CASE(float, 1) FMA_CASE(float, 2) FMA_CASE(float, 4) FMA_CASE(float, 8) FMA_CASE(float, 16)
     }
+#undef FMA_CASE
   }
   return IG_OK;
 }
@@ -664,6 +708,7 @@ int ig_launch_finalize(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, const f
   auto k = finalize_query;
   IG_LAUNCH(ctx, IG_K_FINALIZE, k, dim3(d->B * d->H), dim3(256), s, part, bias, A_p, pos, q_p,
             (int)d->H, (int)d->d, (int)d->r, g.KS, (long)g.Bpad * g.Cpad, g.Cpad, (int)d->rope,
-            d->rope ? -2.0 / (double)d->d * log2((double)d->rope_theta) : 0.0);
+            d->rope ? -2.0 / (double)d->d * log2((double)d->rope_theta) : 0.0, ig_fast_div(d->H),
+            ig_fast_div(d->r), 256 / d->r, (d->d + 256 / d->r - 1) / (256 / d->r));
   return IG_OK;
 }
