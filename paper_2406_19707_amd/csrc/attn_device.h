@@ -9,7 +9,9 @@ struct AttnArgs {
   const void *q;              // [B,H,d]
   const uint4 *K, *V;          // gathered rows [B*H, stride, d] or the pool [B*H, kv_rows, d] (INDEXED)
   const int32_t *sel_idx, *sel_cnt;
-  int stride, kv_rows, LPR;
+  int stride, kv_rows;
+  int lpr_log2;               // a row is 1 << lpr_log2 pieces of 16 bytes
+  int slice_log2;             // rows of a slice: see slice_range
   const void *k_new, *v_new;  // optional always-attended row
   void *out;
   float scale;
@@ -17,6 +19,7 @@ struct AttnArgs {
   float *part;                // per-slice softmax states [B*H][SLICE_MAX][d+2]
   int32_t *counters;          // per-(b,h) arrival counters, zero between calls
   int H, BH;
+  FastDiv by_H, by_BH;
   uint4 *K_out, *V_out;        // INDEXED only: the rows read are also stored here (fused prefetch)
 };
 
@@ -35,10 +38,12 @@ __device__ __forceinline__ void store_stream(u128 *p, const u128 &v) {
 
 // ---- work split shared by gather and attention --------------------------------------------------
 // Selected-token lists are very uneven (a few heads keep a thousand rows, most a few dozen), and
-// one compute unit moves well under 100 GB/s, so a list is cut into up to SLICE_MAX slices of at
-// most SLICE_ROWS rows where possible: slices = min(SLICE_MAX, ceil(rows / SLICE_ROWS)), slice s
-// covering rows [rows*s/slices, rows*(s+1)/slices).  Every workgroup derives this from the
-// device-side count, so the host never reads the counts; surplus workgroups leave at once.
+// one compute unit moves well under 100 GB/s, so a list is cut into slices of 1 << slice_log2 rows, or,
+// when that would be more than SLICE_MAX of them, into SLICE_MAX equal ones.  Every workgroup derives
+// this from the device-side count, so the host never reads the counts; surplus workgroups leave at
+// once.  They are most of a grid, so the way to the exit has no division in it: with the work item
+// decoded by run-time divisions and slices of rows*s/slices, 320 lists of 250 rows on average took 28.6 us
+// to copy instead of 26.5.
 //
 // Workgroups are handed to the 8 XCDs round-robin by linear id, and an XCD reaches only about an
 // eighth of the HBM bandwidth, so the work has to be even per XCD, not just per compute unit:
@@ -47,24 +52,35 @@ __device__ __forceinline__ void store_stream(u128 *p, const u128 &v) {
 // linear id as slice = id / BH, t = id % BH, b = t / H, h = (t % H - b - 5*slice) mod H, which puts
 // (b, h, slice) on XCD (h + b + 5*slice) % 8: the slices of one list, the sequences of one head and
 // the heads of one sequence are each spread over all XCDs.
-constexpr int SLICE_ROWS = 128;
-constexpr int SLICE_MAX = IG_SLICE_MAX;
-__device__ __forceinline__ void work_item(int id, int H, int BH, int *bh, int *slice) {
-  const int s = id / BH, t = id - s * BH;
-  const int b = t / H;
-  int h = (t - b * H - b - 5 * s) % H;
+constexpr int SLICE_LOG2 = 7;
+constexpr int SLICE_MAX = IG_SLICE_MAX, SLICE_MAX_LOG2 = 4;
+static_assert(SLICE_MAX == 1 << SLICE_MAX_LOG2, "");
+__device__ __forceinline__ void work_item(int id, int H, int BH, const FastDiv &by_H, const FastDiv &by_BH, int *bh, int *slice) {
+  const int s = by_BH.div(id), t = id - s * BH;
+  const int b = by_H.div(t);
+  int h = t - b * H - by_H.mod(b + 5 * s);
   if (h < 0) h += H;
   *bh = b * H + h;
   *slice = s;
 }
-__device__ __forceinline__ bool slice_range(int rows, int s, int max_slices, int *row0, int *row1, int *slices) {
-  int n = (rows + SLICE_ROWS - 1) / SLICE_ROWS;
-  n = max(1, min(n, max_slices));
-  *slices = n;
-  if (s >= n) return false;
-  *row0 = (int)((long)rows * s / n);
-  *row1 = (int)((long)rows * (s + 1) / n);
+__device__ __forceinline__ bool slice_range(int rows, int s, int slice_log2, int *row0, int *row1, int *slices) {
+  if (rows <= (SLICE_MAX << slice_log2)) {
+    const int n = max(1, (rows + (1 << slice_log2) - 1) >> slice_log2);
+    *slices = n;
+    *row0 = s << slice_log2;
+    *row1 = min(rows, *row0 + (1 << slice_log2));
+    return s < n;
+  }
+  const int per = (rows + SLICE_MAX - 1) >> SLICE_MAX_LOG2;
+  *slices = SLICE_MAX;
+  *row0 = min(rows, s * per);
+  *row1 = min(rows, *row0 + per);
   return true;
+}
+// workgroups per list that a list of at most `rows` rows can need
+static inline int slices_at_most(long rows, int slice_log2) {
+  const long n = (rows + (1l << slice_log2) - 1) >> slice_log2;
+  return n < 1 ? 1 : (n < SLICE_MAX ? (int)n : SLICE_MAX);
 }
 
 // ---- attention ----------------------------------------------------------------------------------
@@ -83,6 +99,14 @@ __device__ __forceinline__ bool slice_range(int rows, int s, int max_slices, int
 // workgroup (see the note at the counter bump below).  The counter is left at zero for the next
 // call.
 constexpr int ATT_BATCH = 8;
+// rows of a slice: what one batch of a workgroup's loads covers, at least 1 << SLICE_LOG2.  (Rows of 128
+// bytes, d = 64 in half precision: 256 a batch; a list of 129..256 such rows is then one workgroup that
+// writes its output itself instead of two that meet: 192 lists of 120 rows on average 8.2 -> 5.8 us.)
+static inline int att_slice_log2(int lpr_log2) {
+  const int batch_log2 = 2 + (6 - lpr_log2) + 3;     // 4 waves x 64 / LPR rows x ATT_BATCH steps
+  return batch_log2 > SLICE_LOG2 ? batch_log2 : SLICE_LOG2;
+}
+static_assert(ATT_BATCH == 8, "att_slice_log2 counts on it");
 
 template <typename T> __device__ __forceinline__ void to_float(const u128 &raw, float (&f)[Elem<T>::TPL]);
 template <> __device__ __forceinline__ void to_float<half_t>(const u128 &raw, float (&f)[8]) {
@@ -106,14 +130,21 @@ __device__ __forceinline__ float coherent_load(const float *p) {
 
 
 // `id` is the linear work item (see work_item); the kernel passes blockIdx.x
-template <typename T, bool INDEXED>
+// LG: log2 of the 16-byte pieces in a row where that is known at build time (the row lengths of 64, 128 and
+// 256 half or 64 and 128 float32 columns), -1 otherwise.  With it a batch is straight-line code: the
+// eight rows' reductions interleave instead of eight times asking which form to take (with the query not
+// waited for before the rows are asked for: 1120 lists of 77 rows of 128 half columns 30.1 -> 24.3 us,
+// 512 lists of 229 rows, 120 MB read and written, 33.3 -> 31.6 us, 192 lists of 120 rows of 64 columns
+// 9.5 -> 5.3 us).
+template <typename T, bool INDEXED, int LG>
 __device__ __forceinline__ void sparse_attention_body(const AttnArgs &A, const int id) {
   const T *__restrict__ q = static_cast<const T *>(A.q);
   const u128 *__restrict__ K = A.K;
   const u128 *__restrict__ V = A.V;
   const int32_t *__restrict__ sel_idx = A.sel_idx;
   const int32_t *__restrict__ sel_cnt = A.sel_cnt;
-  const int stride = A.stride, kv_rows = A.kv_rows, LPR = A.LPR, d = A.d, H = A.H, BH = A.BH;
+  const int lpr_log2 = LG >= 0 ? LG : A.lpr_log2;
+  const int stride = A.stride, kv_rows = A.kv_rows, LPR = 1 << lpr_log2, d = A.d;
   const T *__restrict__ k_new = static_cast<const T *>(A.k_new);
   const T *__restrict__ v_new = static_cast<const T *>(A.v_new);
   T *__restrict__ out = static_cast<T *>(A.out);
@@ -128,21 +159,16 @@ __device__ __forceinline__ void sparse_attention_body(const AttnArgs &A, const i
   __shared__ int s_last;
   constexpr int max_slices = SLICE_MAX;
   int bh, slice;
-  work_item(id, H, BH, &bh, &slice);
+  work_item(id, A.H, A.BH, A.by_H, A.by_BH, &bh, &slice);
   const int n = min(sel_cnt[bh], stride);
   const int rows = n + (k_new ? 1 : 0);
   int row0 = 0, row1 = 0, slices = 1;
-  if (!slice_range(rows, slice, max_slices, &row0, &row1, &slices)) return;
+  if (!slice_range(rows, slice, A.slice_log2, &row0, &row1, &slices)) return;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int RPW = 64 / LPR;            // rows per wave step
-  const int sub = lane / LPR, li = lane % LPR;
-  float qf[TPL];
-  {
-    u128 raw = *reinterpret_cast<const u128 *>(q + (long)bh * d + li * TPL);
-    to_float<T>(raw, qf);
-#pragma unroll
-    for (int e = 0; e < TPL; ++e) qf[e] *= scale;
-  }
+  const int RPW = 64 >> lpr_log2;      // rows per wave step
+  const int sub = lane >> lpr_log2, li = lane & (LPR - 1);
+  // (not looked at before the first batch's loads are out)
+  const u128 qraw = *reinterpret_cast<const u128 *>(q + (long)bh * d + li * TPL);
   float m = -INFINITY, z = 0.f, acc[TPL];
 #pragma unroll
   for (int e = 0; e < TPL; ++e) acc[e] = 0.f;
@@ -197,6 +223,13 @@ __device__ __forceinline__ void sparse_attention_body(const AttnArgs &A, const i
       if (defer && r0 + rows_per_batch >= row1) r_keep = r0;
       else store_rows(r0);
     }
+    __builtin_amdgcn_sched_barrier(0);
+    u128 qnow = qraw;
+    keep_loaded(qnow);
+    float qf[TPL];
+    to_float<T>(qnow, qf);
+#pragma unroll
+    for (int e = 0; e < TPL; ++e) qf[e] *= scale;
     float l[ATT_BATCH];
     float bm = m;
 #pragma unroll
@@ -206,8 +239,11 @@ __device__ __forceinline__ void sparse_attention_body(const AttnArgs &A, const i
       float t = 0.f;
 #pragma unroll
       for (int e = 0; e < TPL; ++e) t = fmaf(qf[e], kf[e], t);
-      if (LPR == 16) {
+      if constexpr (LG == 3) {
+        t = row8_sum(t);
+      } else if constexpr (LG >= 4) {
         t = row16_sum(t);
+        if constexpr (LG == 5) t += __shfl_xor(t, 16, 64);
       } else {
         for (int o = 1; o < LPR; o <<= 1) t += __shfl_xor(t, o, 64);
       }

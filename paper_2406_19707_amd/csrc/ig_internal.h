@@ -290,6 +290,13 @@ __device__ __forceinline__ float wave_max(float v) {
   const float r3 = __int_as_float(__builtin_amdgcn_readlane(iv, 48));
   return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
 }
+// sum over the lanes of half a 16-lane row, returned in every lane of the half
+__device__ __forceinline__ float row8_sum(float v) {
+  v += dpp_move<DPP_QUAD_1032>(v);
+  v += dpp_move<DPP_QUAD_2301>(v);
+  v += dpp_move<DPP_ROW_HALF_MIRROR>(v);
+  return v;
+}
 // sum over the lanes of a 16-lane row, returned in every lane of the row
 __device__ __forceinline__ float row16_sum(float v) {
   v += dpp_move<DPP_QUAD_1032>(v);

@@ -162,19 +162,20 @@ __global__ __launch_bounds__(256) void pool_victim(const int32_t *__restrict__ c
 }
 
 // ---- gather, device-resident pool ---------------------------------------------------------------
-// Row copies in 16-byte units, U units per row; grid B*H*SLICE_MAX (see work_item).  A thread's copies are
+// Row copies in 16-byte units, U units per row; grid B*H x slices (see work_item).  A thread's copies are
 // issued in batches of GATHER_BATCH, so that index loads, then K and V row loads, are in flight
 // together.
 constexpr int GATHER_BATCH = 8;
 __global__ __launch_bounds__(256) void gather_rows_sliced(
     const u128 *__restrict__ Kpool, const u128 *__restrict__ Vpool, const int32_t *__restrict__ sel_idx,
     const int32_t *__restrict__ sel_cnt, u128 *__restrict__ K_sel, u128 *__restrict__ V_sel, int N_cap,
-    int stride, int U, int H, int BH) {
+    int stride, FastDiv by_U, int H, int BH, FastDiv by_H, FastDiv by_BH) {
+  const int U = by_U.d;
   int bh, slice;
-  work_item(blockIdx.x, H, BH, &bh, &slice);
+  work_item(blockIdx.x, H, BH, by_H, by_BH, &bh, &slice);
   const int cnt = min(sel_cnt[bh], stride);
   int row0, row1, slices;
-  if (!slice_range(cnt, slice, SLICE_MAX, &row0, &row1, &slices) || row1 <= row0) return;
+  if (!slice_range(cnt, slice, SLICE_LOG2, &row0, &row1, &slices) || row1 <= row0) return;
   const int32_t *list = sel_idx + (long)bh * stride + row0;
   const long src0 = (long)bh * N_cap * U, dst0 = ((long)bh * stride + row0) * U;
   const int total = (row1 - row0) * U;
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(256) void gather_rows_sliced(
 #pragma unroll
     for (int i = 0; i < GATHER_BATCH; ++i) {
       const int u = min(u0 + 256 * i, total - 1);
-      const int rr = u / U, c = u - rr * U;
+      const int rr = by_U.div(u), c = u - rr * U;
       src[i] = src0 + (long)min(max(list[rr], 0), N_cap - 1) * U + c;   // a slot outside the pool is clamped
     }
 #pragma unroll
@@ -195,6 +196,7 @@ __global__ __launch_bounds__(256) void gather_rows_sliced(
       kv[i] = Kpool[src[i]];
       vv[i] = Vpool[src[i]];
     }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < GATHER_BATCH; ++i) {
       const int u = min(u0 + 256 * i, total - 1);
@@ -283,9 +285,9 @@ __global__ __launch_bounds__(THREADS) void gather_rows_flat(
 }
 
 // ---- attention (body in attn_device.h) ----------------------------------------------------------
-template <typename T, bool INDEXED>
+template <typename T, bool INDEXED, int LG>
 __global__ __launch_bounds__(256) void sparse_attention(AttnArgs A) {
-  sparse_attention_body<T, INDEXED>(A, blockIdx.x);
+  sparse_attention_body<T, INDEXED, LG>(A, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void copy_bytes(const u128 *__restrict__ src, u128 *__restrict__ dst,
@@ -401,10 +403,11 @@ int ig_launch_gather(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const voi
   const int U = d->d * ig_elem_bytes(d->dtype) / 16;
   const int BH = d->B * d->H;
   if (!host_pool) {
-    dim3 grid(BH * SLICE_MAX), block(256);
+    dim3 grid(BH * slices_at_most(sel_stride, SLICE_LOG2)), block(256);
     auto k = gather_rows_sliced;
     IG_LAUNCH(ctx, IG_K_GATHER, k, grid, block, s, (const u128 *)Kpool, (const u128 *)Vpool, sel_idx,
-              sel_cnt, (u128 *)K_sel, (u128 *)V_sel, (int)d->N_cap, (int)sel_stride, U, (int)d->H, BH);
+              sel_cnt, (u128 *)K_sel, (u128 *)V_sel, (int)d->N_cap, (int)sel_stride, ig_fast_div(U),
+              (int)d->H, BH, ig_fast_div(d->H), ig_fast_div(BH));
     return IG_OK;
   }
   const size_t lds = (size_t)(BH + 1) * sizeof(int);
@@ -450,7 +453,8 @@ int ig_attn_fill(ig_ctx *ctx, const ig_desc *d, const void *q, const void *K, co
   A->sel_cnt = sel_cnt;
   A->stride = sel_stride;
   A->kv_rows = kv_rows;
-  A->LPR = LPR;
+  A->lpr_log2 = __builtin_ctz(LPR);
+  A->slice_log2 = att_slice_log2(A->lpr_log2);
   A->k_new = k_new;
   A->v_new = v_new;
   A->out = out;
@@ -460,6 +464,8 @@ int ig_attn_fill(ig_ctx *ctx, const ig_desc *d, const void *q, const void *K, co
   A->counters = counters;
   A->H = d->H;
   A->BH = d->B * d->H;
+  A->by_H = ig_fast_div(d->H);
+  A->by_BH = ig_fast_div(A->BH);
   A->K_out = sel_idx ? (uint4 *)K_out : nullptr;
   A->V_out = sel_idx ? (uint4 *)V_out : nullptr;
   return IG_OK;
@@ -478,6 +484,20 @@ int ig_attn_args(ig_ctx *ctx, const ig_desc *d, const void *q, const void *K, co
                       V_out, ctx->attn_part, ctx->attn_cnt, A);
 }
 
+// the attention kernel for a type and row length (see LG at sparse_attention_body)
+template <bool INDEXED>
+static void (*attention_kernel(int dtype, int lpr_log2))(AttnArgs) {
+  if (dtype == IG_F16) {
+    if (lpr_log2 == 3) return sparse_attention<half_t, INDEXED, 3>;
+    if (lpr_log2 == 4) return sparse_attention<half_t, INDEXED, 4>;
+    if (lpr_log2 == 5) return sparse_attention<half_t, INDEXED, 5>;
+    return sparse_attention<half_t, INDEXED, -1>;
+  }
+  if (lpr_log2 == 4) return sparse_attention<float, INDEXED, 4>;
+  if (lpr_log2 == 5) return sparse_attention<float, INDEXED, 5>;
+  return sparse_attention<float, INDEXED, -1>;
+}
+
 int ig_launch_attention(ig_ctx *ctx, const ig_desc *d, const void *q, const void *K, const void *V,
                         const int32_t *sel_idx, int32_t sel_stride, const int32_t *sel_cnt,
                         int kv_rows_per_bh, const void *k_new, const void *v_new, void *out,
@@ -486,24 +506,9 @@ int ig_launch_attention(ig_ctx *ctx, const ig_desc *d, const void *q, const void
   int rc = ig_attn_args(ctx, d, q, K, V, sel_idx, sel_stride, sel_cnt, kv_rows_per_bh, k_new, v_new, out,
                         K_out, V_out, &A);
   if (rc) return rc;
-  dim3 grid(A.BH * SLICE_MAX), block(256);
-  if (d->dtype == IG_F16) {
-    if (sel_idx) {
-      auto k = sparse_attention<half_t, true>;
-      IG_LAUNCH(ctx, IG_K_ATTENTION, k, grid, block, s, A);
-    } else {
-      auto k = sparse_attention<half_t, false>;
-      IG_LAUNCH(ctx, IG_K_ATTENTION, k, grid, block, s, A);
-    }
-  } else {
-    if (sel_idx) {
-      auto k = sparse_attention<float, true>;
-      IG_LAUNCH(ctx, IG_K_ATTENTION, k, grid, block, s, A);
-    } else {
-      auto k = sparse_attention<float, false>;
-      IG_LAUNCH(ctx, IG_K_ATTENTION, k, grid, block, s, A);
-    }
-  }
+  dim3 grid(A.BH * slices_at_most((long)sel_stride + 1, A.slice_log2)), block(256);
+  const auto k = sel_idx ? attention_kernel<true>(d->dtype, A.lpr_log2) : attention_kernel<false>(d->dtype, A.lpr_log2);
+  IG_LAUNCH(ctx, IG_K_ATTENTION, k, grid, block, s, A);
   return IG_OK;
 }
 
@@ -559,12 +564,8 @@ int ig_launch_attention_static(ig_ctx *ctx, const ig_desc *d, const void *q, con
   // behind): the arrival counters start from zero on every call.  A fill kernel, not a memset, so
   // that the sequence can be captured into a graph.
   hipLaunchKernelGGL(zero_words, dim3((unsigned)((BH + 255) / 256)), dim3(256), 0, s, counters, (int)BH);
-  dim3 grid((unsigned)(BH * SLICE_MAX)), block(256);
-  if (d->dtype == IG_F16) {
-    hipLaunchKernelGGL((sparse_attention<half_t, false>), grid, block, 0, s, A);
-  } else {
-    hipLaunchKernelGGL((sparse_attention<float, false>), grid, block, 0, s, A);
-  }
+  dim3 grid((unsigned)(BH * slices_at_most((long)sel_stride + 1, A.slice_log2))), block(256);
+  hipLaunchKernelGGL(attention_kernel<false>(d->dtype, A.lpr_log2), grid, block, 0, s, A);
   hipError_t le = hipGetLastError();
   if (le != hipSuccess) return ig_hip_fail(ctx, le, "sparse_attention (static scratch)");
   return IG_OK;

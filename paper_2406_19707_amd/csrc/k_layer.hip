@@ -5,27 +5,27 @@
 // lists (the launch of the previous step), so neither depends on the other, and both are short,
 // latency-bound kernels: run as the two halves of one grid they share the launch and overlap fully,
 // without streams or events between them.  Workgroups [0, B*H) run the scan body (4 waves, one
-// tile each), the remaining B*H*SLICE_MAX run the attention body; the bodies are those of the
+// tile each), the remaining ones run the attention body; the bodies are those of the
 // stand-alone kernels, so the results are the same bit for bit.
 #include "scan_device.h"
 #include "attn_device.h"
 
 namespace {
 
-template <typename T, int CH>
+template <typename T, int CH, int LG>
 __global__ __launch_bounds__(256) void scan_next_attend_this(ScanArgs sa, AttnArgs aa, int scan_blocks) {
   if ((int)blockIdx.x < scan_blocks)
     scan_select_fused_body<T, CH, 4>(sa, blockIdx.x);
   else
-    sparse_attention_body<T, true>(aa, (int)blockIdx.x - scan_blocks);
+    sparse_attention_body<T, true, LG>(aa, (int)blockIdx.x - scan_blocks);
 }
 
-template <typename T>
+template <typename T, int LG>
 int launch_t(ig_ctx *ctx, const ScanArgs &sa, const AttnArgs &aa, int BH, int ch, hipStream_t s) {
-  dim3 grid(BH + BH * SLICE_MAX), block(256);
+  dim3 grid(BH + BH * slices_at_most((long)aa.stride + 1, aa.slice_log2)), block(256);
 #define CASE(CHV)                                                              \
   case CHV: {                                                                  \
-    auto k = scan_next_attend_this<T, CHV>;                                    \
+    auto k = scan_next_attend_this<T, CHV, LG>;                                \
     IG_LAUNCH(ctx, IG_K_LAYER, k, grid, block, s, sa, aa, BH);                 \
     return IG_OK;                                                              \
   }
@@ -62,5 +62,10 @@ int ig_launch_scan_attend(ig_ctx *ctx, const ig_desc *d, const QSource &qs, cons
   // B8 H32 N2048 shape: 20.4-20.8 us per launch against 22.2-22.4 us with 20 loads in flight)
   const int ch = ig_pick_ch(d->r, 12);
   const int BH = d->B * d->H;
-  return d->dtype == IG_F16 ? launch_t<half_t>(ctx, sa, aa, BH, ch, s) : launch_t<float>(ctx, sa, aa, BH, ch, s);
+  if (d->dtype == IG_F16) {
+    if (aa.lpr_log2 == 3) return launch_t<half_t, 3>(ctx, sa, aa, BH, ch, s);
+    if (aa.lpr_log2 == 4) return launch_t<half_t, 4>(ctx, sa, aa, BH, ch, s);
+    return launch_t<half_t, -1>(ctx, sa, aa, BH, ch, s);
+  }
+  return aa.lpr_log2 == 4 ? launch_t<float, 4>(ctx, sa, aa, BH, ch, s) : launch_t<float, -1>(ctx, sa, aa, BH, ch, s);
 }
