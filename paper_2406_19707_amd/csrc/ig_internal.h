@@ -305,13 +305,18 @@ __device__ __forceinline__ float row16_sum(float v) {
   v += dpp_move<DPP_ROW_MIRROR>(v);
   return v;
 }
-// inclusive prefix sum over the 64 lanes
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int u = __shfl_up(v, o, 64);
-    if (lane >= o) v += u;
-  }
+// inclusive prefix sum over the 64 lanes (all of them active): within the rows of 16 by shifts, then
+// each row's total is carried into the next one and that of the first two into the last two
+template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_or_zero(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v += dpp_or_zero<0x111, 0xF>(v);      // row_shr:1
+  v += dpp_or_zero<0x112, 0xF>(v);      // row_shr:2
+  v += dpp_or_zero<0x114, 0xF>(v);      // row_shr:4
+  v += dpp_or_zero<0x118, 0xF>(v);      // row_shr:8
+  v += dpp_or_zero<0x142, 0xA>(v);      // row_bcast:15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xC>(v);      // row_bcast:31 into rows 2 and 3
   return v;
 }
 // sum over the 64 lanes, returned in every lane

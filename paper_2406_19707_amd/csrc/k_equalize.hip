@@ -6,9 +6,9 @@
 // One workgroup per (sequence, head):
 //   n      = clamp(floor(sum_h count[b,h] / H), 1, cap)
 //   T      = the n-th largest score of the head, found exactly by a most-significant-digit radix
-//            select on an order-preserving integer image of the float (4 passes of 8 bits, one
-//            256-bin LDS histogram each).  The keys of a head stay in registers (KPT per thread)
-//            when they fit; longer sequences re-read the scores from L2 in every pass.
+//            select on an order-preserving integer image of the float (at most 3 passes of 11 bits, one
+//            2048-bin LDS histogram each).  The scores of a head stay in registers (KPT per thread)
+//            when they fit; longer sequences re-read them from L2 in every pass.
 //   list   = tokens with score > T, plus the earliest tokens with score == T until n are kept,
 //            written in ascending token order with ballot / bit-count prefix ranks.
 // Integer work after the scores: the result is exact for the scores given.
@@ -22,135 +22,139 @@ __device__ __forceinline__ unsigned score_key(float s) {
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
+__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_incl_scan(v), 63); }
+// the histogram word of a digit: 4 words are left out after every 32, so that a lane's 32 words and its
+// neighbours' are read 16 bytes at a time without bank conflicts
+__device__ __forceinline__ int hist_word(int digit) { return digit + ((digit >> 5) << 2); }
+constexpr int DIGITS = 2048, HIST_WORDS = DIGITS + DIGITS / 32 * 4;
+
+// A chain of dependent steps rather than work (192 heads of 3000 tokens are 2.3 MB), so the steps are few: a
+// wave owns KPT * 64 consecutive tokens, whose keys stay in registers; every wave searches the histogram for
+// itself, which leaves one barrier in a pass; 11 bits a pass instead of 8 are a pass less, spread the sign,
+// exponent and leading bits over enough bins for the LDS adds not to queue up, and mostly settle the list in
+// two passes (when a bin is kept whole nothing below it matters); and the ordered compaction needs one
+// barrier, for the waves' totals, instead of two for every THREADS tokens.  (With the scan before it, whose
+// share is 3 to 7 us: 32 lists of 4096 tokens 26.3 -> 13.1 us, 192 of 3000 20.8 -> 13.3 us, 1120 of 2048
+// 32.6 -> 26.0 us.)
 template <int THREADS, int KPT>
 __global__ __launch_bounds__(THREADS) void equalize_select(const float *__restrict__ scores,
                                                            const int32_t *__restrict__ thr_cnt,
                                                            int32_t *__restrict__ sel_idx,
                                                            int32_t *__restrict__ sel_cnt,
-                                                           int32_t *status, int H, int N, int cap,
+                                                           int32_t *status, FastDiv by_H, int N, int cap,
                                                            int stride) {
-  constexpr int NW = THREADS / 64;
-  __shared__ unsigned hist[256];
-  __shared__ unsigned wave_sum_lds[4];
-  __shared__ unsigned s_prefix;
-  __shared__ int s_need, s_total;
-  __shared__ int w_eq[NW], w_keep[NW];
-  const int bh = blockIdx.x, b = bh / H;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  constexpr int NW = THREADS / 64, U = KPT > 0 ? KPT : 8;
+  __shared__ __attribute__((aligned(16))) unsigned hist[3][HIST_WORDS];
+  __shared__ int w_gt[NW], w_eq[NW];
+  const int H = by_H.d, bh = blockIdx.x, b = by_H.div(bh);
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float *s = scores + (long)bh * N;
+  const int32_t *cnts = thr_cnt + (long)b * H;
+  // the wave's tokens t0 .. t1 - 1, a multiple of 64 but for the end of the sequence
+  const int chunk = KPT > 0 ? KPT * 64 : ((N + THREADS - 1) / THREADS) * 64;
+  const int t0 = min(N, w * chunk), t1 = min(N, t0 + chunk);
+
+  // f(token, its key, whether there is such a token) in token order, 64 tokens a call
+  float raw[U];
+  auto load = [&](int t) {
+#pragma unroll
+    for (int i = 0; i < U; ++i) raw[i] = s[min(t + i * 64 + lane, N - 1)];
+  };
+  auto each = [&](auto &&f) {
+    if constexpr (KPT > 0) {
+#pragma unroll
+      for (int i = 0; i < U; ++i) f(t0 + i * 64 + lane, score_key(raw[i]), t0 + i * 64 + lane < t1);
+    } else {
+      for (int t = t0; t < t1; t += U * 64) {
+        load(t);
+#pragma unroll
+        for (int i = 0; i < U; ++i) f(t + i * 64 + lane, score_key(raw[i]), t + i * 64 + lane < t1);
+      }
+    }
+  };
+  if constexpr (KPT > 0) load(t0);
 
   // ---- n: truncated mean of the sequence's threshold counts, capped ----
-  if (tid == 0) s_total = 0;
+  int part = cnts[min(lane, H - 1)];
+  part = lane < H ? part : 0;
+  for (int h = lane + 64; h < H; h += 64) part += cnts[h];
+  for (int i = tid; i < 3 * HIST_WORDS / 4; i += THREADS) reinterpret_cast<uint4 *>(&hist[0][0])[i] = make_uint4(0, 0, 0, 0);
+  int need = max(1, min(min(by_H.div(max(0, wave_total(part))), cap), N));
   __syncthreads();
-  {
-    int part = 0;
-    for (int h = tid; h < H; h += THREADS) part += thr_cnt[b * H + h];
-    part = wave_sum(part);
-    if (lane == 0 && part) atomicAdd(&s_total, part);
-  }
-  __syncthreads();
-  const int n = max(1, min(min(s_total / H, cap), N));
-
-  // keys of tokens tid, tid + THREADS, ... (KPT of them) in registers; KPT == 0: re-read each pass
-  unsigned keys[KPT > 0 ? KPT : 1];
-  if (KPT > 0) {
-#pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-      const int t = i * THREADS + tid;
-      keys[i] = t < N ? score_key(s[t]) : 0u;
-    }
-  }
 
   // ---- radix select of the n-th largest key ----
-  unsigned prefix = 0;
-  int need = n;
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    const unsigned hi_mask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
-    if (tid < 256) hist[tid] = 0;
-    __syncthreads();
-    if (KPT > 0) {
+  // T: the kept tokens are those with a key above T and the first `need` of those equal to it
+  unsigned T = 0;
 #pragma unroll
-      for (int i = 0; i < KPT; ++i) {
-        const unsigned k = keys[i];
-        if (i * THREADS + tid < N && (k & hi_mask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1u);
-      }
-    } else {
-      for (int t = tid; t < N; t += THREADS) {
-        const unsigned k = score_key(s[t]);
-        if ((k & hi_mask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1u);
-      }
-    }
+  for (int pass = 0; pass < 3; ++pass) {
+    const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
+    const unsigned digit_mask = pass == 2 ? 1023u : 2047u;
+    const unsigned above_mask = pass == 0 ? 0u : (pass == 1 ? 0xFFE00000u : 0xFFFFFC00u);
+    each([&](int, unsigned k, bool there) {
+      if (there && (k & above_mask) == T) atomicAdd(&hist[pass][hist_word((k >> shift) & digit_mask)], 1u);
+    });
     __syncthreads();
-    // bin d holds the target when (#keys in bins above d) < need <= (#keys in bins >= d)
-    unsigned mine = 0, incl = 0;
-    if (tid < 256) {
-      mine = hist[tid];
-      incl = mine;                             // suffix sum inside the wave: bins tid..(wave end)
+    // digits 32 lane .. 32 lane + 31: the lane where (digits above) < need <= (digits above and its own)
+    int mine = 0;
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const unsigned u = __shfl_down(incl, o, 64);
-        if (lane + o < 64) incl += u;
-      }
-      if (lane == 0) wave_sum_lds[w] = incl;   // total of this wave's 64 bins
+    for (int i = 0; i < 8; ++i) {
+      const uint4 v = *reinterpret_cast<const uint4 *>(&hist[pass][lane * 36 + i * 4]);
+      mine += (int)(v.x + v.y + v.z + v.w);
     }
-    __syncthreads();                           // every wave of the workgroup takes part
-    if (tid < 256) {
-      unsigned above = incl - mine;
-      for (int k = w + 1; k < 4; ++k) above += wave_sum_lds[k];
-      if ((int)above < need && need <= (int)(above + mine)) {
-        s_prefix = prefix | ((unsigned)tid << shift);
-        s_need = need - (int)above;
-      }
+    int incl = wave_incl_scan(mine);
+    int above = __builtin_amdgcn_readlane(incl, 63) - incl;
+    const int group = __ffsll(__ballot(above < need && need <= above + mine)) - 1;
+    const int above_group = __builtin_amdgcn_readlane(above, group);
+    // the same among that lane's 32 digits
+    mine = lane < 32 ? (int)hist[pass][group * 36 + lane] : 0;
+    incl = wave_incl_scan(mine);
+    above = above_group + __builtin_amdgcn_readlane(incl, 63) - incl;
+    const int digit = __ffsll(__ballot(above < need && need <= above + mine)) - 1;
+    need -= __builtin_amdgcn_readlane(above, digit);
+    T |= (unsigned)(group * 32 + digit) << shift;
+    if (pass < 2 && need == __builtin_amdgcn_readlane(mine, digit) && T > 0) {
+      T -= 1;                      // the bin is kept whole: everything from its lowest key upwards
+      need = 0;
+      break;
     }
-    __syncthreads();
-    prefix = s_prefix;
-    need = s_need;
-    __syncthreads();
   }
-  const unsigned T = prefix;       // key of the n-th largest score; `need` tokens equal to it are kept
 
   // ---- ordered compaction ----
-  int base_out = 0, base_eq = 0;
-  int32_t *list = sel_idx + (long)bh * stride;
-  auto step = [&](int t0, unsigned k) {      // tokens t0 .. t0 + THREADS - 1, one per thread
-    const int t = t0 + tid;
-    const bool gt = t < N && k > T, eq = t < N && k == T;
-    const unsigned long long be = __ballot(eq);
-    if (lane == 0) w_eq[w] = __popcll(be);
-    __syncthreads();
-    int eq_rank = base_eq + lanes_below(be), eq_all = 0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      const int c = w_eq[i];
-      eq_rank += i < w ? c : 0;
-      eq_all += c;
-    }
-    const bool keep = gt || (eq && eq_rank < need);
-    const unsigned long long bk = __ballot(keep);
-    if (lane == 0) w_keep[w] = __popcll(bk);
-    __syncthreads();
-    int pos = base_out + lanes_below(bk), keep_all = 0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      const int c = w_keep[i];
-      pos += i < w ? c : 0;
-      keep_all += c;
-    }
-    if (keep && pos < stride) list[pos] = t;
-    base_out += keep_all;
-    base_eq += eq_all;
-  };
-  if constexpr (KPT > 0) {
-#pragma unroll
-    for (int it = 0; it < KPT; ++it)
-      if (it * THREADS < N) step(it * THREADS, keys[it]);     // wave-uniform condition
-  } else {
-    for (int t0 = 0; t0 < N; t0 += THREADS) step(t0, t0 + tid < N ? score_key(s[t0 + tid]) : 0u);
+  int gt = 0, eq = 0;
+  each([&](int, unsigned k, bool there) {
+    gt += __popcll(__ballot(there && k > T));
+    eq += __popcll(__ballot(there && k == T));
+  });
+  if (lane == 0) {
+    w_gt[w] = gt;
+    w_eq[w] = eq;
   }
+  __syncthreads();
+  int gt_all = 0, eq_all = 0, pos = 0, eq_rank = 0;      // before this wave's tokens, and in all
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const int g = w_gt[i], e = w_eq[i];
+    pos += i < w ? g : 0;
+    eq_rank += i < w ? e : 0;
+    gt_all += g;
+    eq_all += e;
+  }
+  pos = __builtin_amdgcn_readfirstlane(pos + min(eq_rank, need));
+  eq_rank = __builtin_amdgcn_readfirstlane(eq_rank);
+  int32_t *list = sel_idx + (long)bh * stride;
+  each([&](int t, unsigned k, bool there) {
+    const unsigned long long be = __ballot(there && k == T);
+    const bool keep = there && (k > T || (k == T && eq_rank + lanes_below(be) < need));
+    const unsigned long long bk = __ballot(keep);
+    const int at = pos + lanes_below(bk);
+    if (keep && at < stride) list[at] = t;
+    pos += __popcll(bk);
+    eq_rank += __popcll(be);
+  });
   if (tid == 0) {
-    sel_cnt[bh] = min(base_out, stride);
-    if (base_out > stride) atomicOr(status, IG_STATUS_CAPACITY);
+    const int kept = gt_all + min(eq_all, need);
+    sel_cnt[bh] = min(kept, stride);
+    if (kept > stride) atomicOr(status, IG_STATUS_CAPACITY);
   }
 }
 
@@ -164,8 +168,15 @@ int ig_launch_equalize(ig_ctx *ctx, const ig_desc *d, const float *scores, const
   {                                                                                                \
     auto k = equalize_select<THREADS, KPT>;                                                        \
     IG_LAUNCH(ctx, IG_K_SELECT, k, dim3(BH), dim3(THREADS), s, scores, thr_cnt, sel_idx, sel_cnt,  \
-              ctx->status, (int)d->H, (int)d->N, cap, (int)sel_stride);                            \
+              ctx->status, ig_fast_div(d->H), (int)d->N, cap, (int)sel_stride);                            \
     return IG_OK;                                                                                  \
+  }
+  // 512 threads while every workgroup has a compute unit's waves nearly to itself (192 lists of 3000 tokens
+  // with their scan 16.0 -> 13.3 us, 20.8 us before both), 256 where several
+  // workgroups share one anyway (1120 lists of 2048: 26.0 against 27.3 us with the scan)
+  if (BH <= 512) {
+    if (d->N <= 512 * 4) EQ_CASE(512, 4)
+    if (d->N <= 512 * 8) EQ_CASE(512, 8)
   }
   if (d->N <= 256 * 8) EQ_CASE(256, 8)
   if (d->N <= 256 * 16) EQ_CASE(256, 16)

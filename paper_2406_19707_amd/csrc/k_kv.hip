@@ -235,7 +235,7 @@ __global__ __launch_bounds__(THREADS) void gather_rows_flat(
     run += min(sel_cnt[i], stride);
     pre[i + 1] = run;                    // local to the thread's run for now
   }
-  int incl = wave_incl_scan(run, lane);
+  int incl = wave_incl_scan(run);
   if (lane == 63) wave_tot[w] = incl;
   __syncthreads();
   int offset = incl - run;

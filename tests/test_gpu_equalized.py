@@ -74,6 +74,36 @@ def test_all_scores_equal_keeps_the_earliest_tokens_up_to_the_cap(ctx):
     assert np.array_equal(idx[:, :409], np.tile(np.arange(409, dtype=np.int32), (2, 1)))
 
 
+# the register forms hold 2048, 4096, 16384 and 32768 tokens, a wave of theirs 512 or 1024 (2048 in the last)
+@pytest.mark.parametrize("N", [63, 512, 513, 2048, 2049, 4096, 4097, 16384, 16385, 32768, 32769, 40000])
+@pytest.mark.parametrize("values", ["far apart", "three", "infinities", "low bits", "all kept"])
+def test_exact_at_the_edges_of_the_register_forms(ctx, N, values):
+    rng = np.random.default_rng(N)
+    s = rng.standard_normal((2, 3, N)).astype(np.float32)
+    frac = 0.2
+    if values == "three":                       # a bin kept in part after every pass: ties across waves
+        s = rng.integers(-1, 2, (2, 3, N)).astype(np.float32)
+    elif values == "infinities":
+        s[rng.random(s.shape) < 0.3] = -np.inf
+        s[0, 1, ::7] = np.inf
+        s[1, 2] = -np.inf
+    elif values == "low bits":                  # decided by the last ten bits of the key
+        s = (np.float32(1.0) + rng.integers(0, 900, s.shape).astype(np.float32) * np.float32(2.0 ** -23)) * np.sign(s)
+        s = s.astype(np.float32)
+    elif values == "all kept":
+        frac = 1.0
+    counts = rng.integers(1, N + 1, (2, 3)) if values != "all kept" else np.full((2, 3), N)
+    n = np.clip(counts.sum(1) // 3, 1, max(1, int(np.floor(frac * N))))
+    idx, cnt, status = equalize_on_gpu(ctx, s, counts, 4.0, frac)
+    assert status == 0
+    for b in range(2):
+        for h in range(3):
+            keep = np.sort(np.argsort(-s[b, h], kind="stable")[:n[b]])
+            at = b * 3 + h
+            assert cnt.reshape(-1)[at] == n[b]
+            assert np.array_equal(idx.reshape(6, -1)[at, :n[b]], keep)
+
+
 def test_short_stride_is_clamped_and_flagged(ctx):
     import paper_2406_19707_amd as ig
     s = np.random.default_rng(1).standard_normal((1, 2, 512)).astype(np.float32)
