@@ -36,7 +36,7 @@ __global__ __launch_bounds__(1024) void scan_select_lds(ScanArgs a) {
   __shared__ float lds_s[LDS_SCORES];
   __shared__ float lds_max[NW];
   __shared__ int lds_cnt[NW];
-  const int bh = blockIdx.x, b = bh / a.H, h = bh % a.H;
+  const int bh = blockIdx.x, b = a.by_H.div(bh), h = bh - b * a.H;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const T *head = static_cast<const T *>(a.slab) + (long)bh * a.nTiles * a.r * TILE;
   typename SlabElem<T>::vec v[CH];
@@ -106,7 +106,7 @@ template <typename T, int CH>
 __global__ __launch_bounds__(256) void scan_tiles(ScanArgs a) {
   constexpr int TPL = SlabElem<T>::TPL;
   constexpr int TILE = IG_WAVE * TPL;
-  const int bh = blockIdx.y, b = bh / a.H, h = bh % a.H;
+  const int bh = blockIdx.y, b = a.by_H.div(bh), h = bh - b * a.H;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int tileno = blockIdx.x * 4 + w;
   if (tileno >= a.nValid) return;
@@ -627,32 +627,42 @@ struct RopeArgs {
 template <int PF>
 struct RopeLoads {
   float part[IG_KS_MAX];
+  double freq;           // theta^(-2t/d) of the thread's pair, worked out while the loads travel
   float bias;
   float apf[PF];
   int position;
 };
-template <int THREADS, int PF>
+template <int THREADS, int PF, int r>
 __device__ __forceinline__ void rope_issue(const ScanArgs &a, const RopeArgs &ra, int b, int h, RopeLoads<PF> &L) {
   // straight-line code, every load unconditional (addresses clamped, surplus values discarded
   // later): the compiler can then count exactly how many loads may still be outstanding at each
   // use, instead of waiting for all of them -- the slab window included -- after a branch
-  const int t = threadIdx.x, d = ra.d, r = a.r;
+  const int t = threadIdx.x, d = ra.d;
   const float *p = a.qsrc + (long)b * a.b_stride + (long)h * d + min(t, d - 1);
 #pragma unroll
   for (int s = 0; s < IG_KS_MAX; ++s) L.part[s] = p[(long)min(s, a.ks - 1) * a.ks_stride];
   L.bias = a.bias ? a.bias[h * d + min(t, d - 1)] : 0.f;
   L.position = ra.pos[b];
-  const int G = THREADS / r, k = t % r, g = min(t / r, G - 1);
+  constexpr int G = THREADS / r;
+  const int k = t % r, g = min(t / r, G - 1);
   const int per = (d + G - 1) / G;
   const int c0 = min(d, g * per);
   const float *ap = ra.A_p + (long)h * d * r + k;
 #pragma unroll
   for (int i = 0; i < PF; ++i) L.apf[i] = ap[(long)min(c0 + i, d - 1) * r];
 }
-template <int THREADS, int PF>
+// (behind the slab window's first loads: it waits for nothing)
+template <int PF>
+__device__ __forceinline__ void rope_frequency(const RopeArgs &ra, RopeLoads<PF> &L) {
+  L.freq = exp2((double)threadIdx.x * ra.freq_step);
+}
+// (LEAN: one LDS read after another instead of all of them in flight, for the kernels that also build
+// equalised lists and have no registers left: with the reads in flight they spill, and 384 pairs of 2048
+// tokens take 24.7 us instead of 22.8)
+template <int THREADS, int PF, int r, bool LEAN>
 __device__ __forceinline__ void rope_finish(const ScanArgs &a, const RopeArgs &ra, const RopeLoads<PF> &L,
                                             float *q_lds, float *qr_lds, float *psum, float *qp_lds) {
-  const int t = threadIdx.x, d = ra.d, r = a.r;
+  const int t = threadIdx.x, d = ra.d;
   {
     float acc = L.bias;
 #pragma unroll
@@ -663,19 +673,26 @@ __device__ __forceinline__ void rope_finish(const ScanArgs &a, const RopeArgs &r
   const int half = d / 2;
   if (t < half) {
     double sn, cs;
-    rope_sincos((double)L.position * exp2((double)t * ra.freq_step), &sn, &cs);
+    rope_sincos((double)L.position * L.freq, &sn, &cs);
     const float x0 = q_lds[t], x1 = q_lds[t + half];
     qr_lds[t] = (float)((double)x0 * cs - (double)x1 * sn);
     qr_lds[t + half] = (float)((double)x1 * cs + (double)x0 * sn);
   }
   __syncthreads();
-  const int G = THREADS / r, g = t / r;
+  constexpr int G = THREADS / r;
+  const int g = t / r;
   const int per = (d + G - 1) / G;
   const int c0 = g < G ? min(d, g * per) : d, c1 = g < G ? min(d, (g + 1) * per) : d;
   float acc = 0.f;
 #pragma unroll
-  for (int i = 0; i < PF; ++i)
-    if (c0 + i < c1) acc = fmaf(qr_lds[c0 + i], L.apf[i], acc);
+  for (int i = 0; i < PF; ++i) {
+    if constexpr (LEAN) {
+      if (c0 + i < c1) acc = fmaf(qr_lds[c0 + i], L.apf[i], acc);
+    } else {
+      const float next = fmaf(qr_lds[min(c0 + i, d - 1)], L.apf[i], acc);
+      acc = c0 + i < c1 ? next : acc;
+    }
+  }
   psum[t] = acc;
   __syncthreads();
   if (t < r) {
@@ -693,10 +710,11 @@ static inline bool rope_prologue_fits(int threads, int d, int r) {
 }
 
 template <typename T, int R, int NW, int TPW, int WIN, int MINW, bool ROPE, bool EQ>
-__global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, RopeArgs ra, EqArgs eq, int S, int BH, PairSync *sync, long spin_limit) {
+__global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, RopeArgs ra, EqArgs eq, int S, FastDiv by_8S, int BH, PairSync *sync, long spin_limit) {
   constexpr int TPL = SlabElem<T>::TPL;
   constexpr int TILE = IG_WAVE * TPL;
-  constexpr int NLOAD = TPW * R;              // 1 KiB loads of a wave with all its tiles valid
+  constexpr int NLOAD = TPW * R;              // 1 KiB loads of a wave with all its tiles valid (R > 0)
+  static_assert(R > 0 || !ROPE, "the rotary prologue prefetches a share of the columns fixed at build time");
   typedef typename SlabElem<T>::vec vec;
   __shared__ float lds_max[NW];
   __shared__ int lds_cnt[NW];
@@ -710,40 +728,51 @@ __global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, 
   // fetched into that XCD's L2 once instead of S times, while a pair's workgroups still start
   // within 8*S ids of each other.  (Only where bytes are fetched from changes with the hardware's
   // dispatch order, not the result.)
-  const int grp = blockIdx.x / (8 * S), rem = blockIdx.x - grp * 8 * S;
+  const int grp = by_8S.div(blockIdx.x), rem = blockIdx.x - grp * 8 * S;
   const int s = rem >> 3, bh = grp * 8 + (rem & 7);
   if (bh >= BH) return;                                   // the grid is rounded up to whole groups
-  const int b = bh / a.H, h = bh - b * a.H;
+  const int b = a.by_H.div(bh), h = bh - b * a.H;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int tile0 = s * (NW * TPW);                       // first tile of this workgroup
   const int my0 = tile0 + w * TPW;                        // first tile of this wave
   const int nact = max(0, min(TPW, a.nValid - my0));      // valid tiles of this wave (wave-uniform)
-  // a wave with fewer valid tiles re-reads its last valid one in their place (masked below), and a
-  // wave with none the pair's last valid tile, so the load sequence is the same for every wave
+  const char *const head = reinterpret_cast<const char *>(static_cast<const T *>(a.slab) + (long)bh * a.nTiles * (R > 0 ? R : a.r) * TILE);
+  constexpr int PLANE = TILE * (int)sizeof(T);            // bytes of one channel plane (1 KiB)
+  // R > 0: a wave with fewer valid tiles re-reads its last valid one in their place (masked below), and a
+  // wave with none the pair's last valid tile, so the load sequence is the same for every wave.  R == 0:
+  // the wave's valid tiles are one run of `nload` planes; the window's loads past its end read its last
+  // plane again.
   const char *tbase[TPW];
 #pragma unroll
   for (int i = 0; i < TPW; ++i)
-    tbase[i] = reinterpret_cast<const char *>(static_cast<const T *>(a.slab) +
-                                              ((long)bh * a.nTiles + min(my0 + max(0, min(i, nact - 1)), a.nValid - 1)) * R * TILE);
+    tbase[i] = head + (long)min(my0 + max(0, min(i, nact - 1)), a.nValid - 1) * (R > 0 ? R : a.r) * PLANE;
+  const int nload = max(nact, 1) * a.r;
   const int lane_off = lane * (int)sizeof(vec);
-  constexpr int PLANE = TILE * (int)sizeof(T);            // bytes of one channel plane (1 KiB)
   vec v[WIN];
   // the query's own loads go out first, so that they head the wave's memory queue
   QueryLoads ql;
-  RopeLoads<rope_pf(R)> rl;
-  if constexpr (ROPE) rope_issue<NW * 64, rope_pf(R)>(a, ra, b, h, rl);
+  constexpr int PF = rope_pf(R > 0 ? R : 64);
+  RopeLoads<PF> rl;
+  if constexpr (ROPE) rope_issue<NW * 64, PF, R>(a, ra, b, h, rl);
   else query_issue(a, b, h, lane, 0, ql);
   __builtin_amdgcn_sched_barrier(0);
   // (unconditional, like the query's loads: a branch here would make the compiler wait for the
   // whole window wherever the query is first used)
 #pragma unroll
-  for (int k = 0; k < WIN && k < NLOAD; ++k)
-    v[k] = *reinterpret_cast<const vec *>(tbase[k / R] + (k % R) * PLANE + lane_off);
+  for (int k = 0; k < WIN; ++k) {
+    if constexpr (R > 0) {
+      if (k < NLOAD) v[k] = *reinterpret_cast<const vec *>(tbase[k / R] + (k % R) * PLANE + lane_off);
+    } else {
+      v[k] = *reinterpret_cast<const vec *>(tbase[0] + (long)min(k, nload - 1) * PLANE + lane_off);
+    }
+  }
   __builtin_amdgcn_sched_barrier(0);
   float q_lane;
   __shared__ float q_lds[ROPE ? 256 : 1], qr_lds[ROPE ? 256 : 1], psum[ROPE ? NW * 64 : 1], qp_lds[ROPE ? 64 : 1];
   if constexpr (ROPE) {
-    rope_finish<NW * 64, rope_pf(R)>(a, ra, rl, q_lds, qr_lds, psum, qp_lds);
+    rope_frequency(ra, rl);
+    __builtin_amdgcn_sched_barrier(0);
+    rope_finish<NW * 64, PF, R, EQ>(a, ra, rl, q_lds, qr_lds, psum, qp_lds);
     q_lane = lane < R ? qp_lds[lane] * a.scale : 0.f;
   } else {
     q_lane = query_finish(a, ql);
@@ -753,17 +782,50 @@ __global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, 
   for (int i = 0; i < TPW; ++i)
 #pragma unroll
     for (int e = 0; e < TPL; ++e) sc[i][e] = 0.f;
-  if (nact > 0) {
-    const int qbits = __float_as_int(q_lane);
+  const int qbits = __float_as_int(q_lane);
+  if constexpr (R > 0) {
+    if (nact > 0) {
 #pragma unroll
-    for (int k = 0; k < NLOAD; ++k) {
-      const int i = k / R, j = k % R;
-      const float qj = __int_as_float(__builtin_amdgcn_readlane(qbits, j));
+      for (int k = 0; k < NLOAD; ++k) {
+        const int i = k / R, j = k % R;
+        const float qj = __int_as_float(__builtin_amdgcn_readlane(qbits, j));
 #pragma unroll
-      for (int e = 0; e < TPL; ++e) sc[i][e] = fmaf((float)v[k % WIN][e], qj, sc[i][e]);
-      if (k + WIN < NLOAD)
-        v[k % WIN] = *reinterpret_cast<const vec *>(tbase[(k + WIN) / R] + ((k + WIN) % R) * PLANE + lane_off);
-      __builtin_amdgcn_sched_barrier(0);     // keeps issue order = consumption order: WIN - 1 loads stay in flight
+        for (int e = 0; e < TPL; ++e) sc[i][e] = fmaf((float)v[k % WIN][e], qj, sc[i][e]);
+        if (k + WIN < NLOAD)
+          v[k % WIN] = *reinterpret_cast<const vec *>(tbase[(k + WIN) / R] + ((k + WIN) % R) * PLANE + lane_off);
+        __builtin_amdgcn_sched_barrier(0);     // keeps issue order = consumption order: WIN - 1 loads stay in flight
+      }
+    }
+  } else if (nact > 0) {
+    // the same stream with the channel count known only now: the window's turns are a loop, the finished
+    // tile's scores move to their registers where its last channel is reached, and what the turns past
+    // the last plane add is thrown away with `acc`
+    float acc[TPL];
+#pragma unroll
+    for (int e = 0; e < TPL; ++e) acc[e] = 0.f;
+    int i = 0, j = 0;
+    const char *next = tbase[0] + lane_off;
+    for (int k0 = 0; k0 < nload; k0 += WIN) {
+#pragma unroll
+      for (int u = 0; u < WIN; ++u) {
+        const float qj = __int_as_float(__builtin_amdgcn_readlane(qbits, j));
+#pragma unroll
+        for (int e = 0; e < TPL; ++e) acc[e] = fmaf((float)v[u][e], qj, acc[e]);
+        v[u] = *reinterpret_cast<const vec *>(next + (long)min(k0 + u + WIN, nload - 1) * PLANE);
+        __builtin_amdgcn_sched_barrier(0);
+        if (++j == a.r) {
+#pragma unroll
+          for (int ii = 0; ii < TPW; ++ii)
+            if (ii == i) {
+#pragma unroll
+              for (int e = 0; e < TPL; ++e) sc[ii][e] = acc[e];
+            }
+#pragma unroll
+          for (int e = 0; e < TPL; ++e) acc[e] = 0.f;
+          ++i;
+          j = 0;
+        }
+      }
     }
   }
   // mask, optional dump, workgroup maximum
@@ -820,10 +882,11 @@ __global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, 
         }
         float q2;
         if constexpr (ROPE) {
-          RopeLoads<rope_pf(R)> rl2;
-          rope_issue<NW * 64, rope_pf(R)>(a, ra, b, h2, rl2);
+          RopeLoads<PF> rl2;
+          rope_issue<NW * 64, PF, R>(a, ra, b, h2, rl2);
+          rope_frequency(ra, rl2);
           __syncthreads();
-          rope_finish<NW * 64, rope_pf(R)>(a, ra, rl2, q_lds, qr_lds, psum, qp_lds);
+          rope_finish<NW * 64, PF, R, EQ>(a, ra, rl2, q_lds, qr_lds, psum, qp_lds);
           q2 = lane < R ? qp_lds[lane] * a.scale : 0.f;
         } else {
           QueryLoads ql2;
@@ -996,25 +1059,29 @@ int launch_stream_one(ig_ctx *ctx, const ScanArgs &a, const RopeArgs *ra, const 
   dim3 grid((unsigned)((BH + 7) / 8 * 8 * S)), block(NW * 64);
   PairSync *sync = static_cast<PairSync *>(ctx->pair_sync);
   if (eq) {
-    if constexpr (TPW <= 2) {      // head-equalised lists: the forms with one workgroup per pair
+    if constexpr (TPW <= 2 && R > 0) {      // head-equalised lists: the forms with one workgroup per pair
       if (S != 1) return ig_fail(ctx, IG_ESHAPE, "scan: head-equalised lists need one workgroup per pair");
       if (ra) {
         auto k = scan_select_stream<T, R, NW, TPW, WIN, 3, true, true>;    // (few workgroups per compute unit here)
-        IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, *ra, *eq, S, BH, sync, ctx->spin_limit);
+        IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, *ra, *eq, S, ig_fast_div(8 * S), BH, sync, ctx->spin_limit);
       } else {
         auto k = scan_select_stream<T, R, NW, TPW, WIN, 4, false, true>;
-        IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, RopeArgs{}, *eq, S, BH, sync, ctx->spin_limit);
+        IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, RopeArgs{}, *eq, S, ig_fast_div(8 * S), BH, sync, ctx->spin_limit);
       }
       return IG_OK;
     }
-    return ig_fail(ctx, IG_ESHAPE, "scan: head-equalised lists are not built for %d tiles per wave", TPW);
+    return ig_fail(ctx, IG_ESHAPE, "scan: head-equalised lists are not built for %d tiles per wave and r = %d", TPW, a.r);
   }
   if (ra) {
-    auto k = scan_select_stream<T, R, NW, TPW, WIN, MINW, true, false>;
-    IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, *ra, EqArgs{}, S, BH, sync, ctx->spin_limit);
+    if constexpr (R > 0) {
+      auto k = scan_select_stream<T, R, NW, TPW, WIN, MINW, true, false>;
+      IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, *ra, EqArgs{}, S, ig_fast_div(8 * S), BH, sync, ctx->spin_limit);
+    } else {
+      return ig_fail(ctx, IG_ESHAPE, "scan: no rotary prologue for r = %d", a.r);
+    }
   } else {
     auto k = scan_select_stream<T, R, NW, TPW, WIN, MINW, false, false>;
-    IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, RopeArgs{}, EqArgs{}, S, BH, sync, ctx->spin_limit);
+    IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, RopeArgs{}, EqArgs{}, S, ig_fast_div(8 * S), BH, sync, ctx->spin_limit);
   }
   return IG_OK;
 }
@@ -1023,20 +1090,24 @@ template <typename T, int R>
 int launch_stream_r(ig_ctx *ctx, const ScanArgs &a, const RopeArgs *ra, const EqArgs *eq, int BH, int TPW, int S, hipStream_t s) {
   if (TPW == 1) return launch_stream_one<T, R, 4, 1, 8, 5>(ctx, a, ra, eq, BH, S, s);
   if (TPW == 2) return launch_stream_one<T, R, 4, 2, 8, 5>(ctx, a, ra, eq, BH, S, s);
-  if constexpr (R <= 32) {   // (with more channels the unrolled stream of 4 tiles no longer stays in registers)
+  if constexpr (R <= 32) {   // (with more channels the unrolled stream of 4 tiles no longer stays in registers; R == 0 is a loop)
     if (TPW == 4) return launch_stream_one<T, R, 4, 4, 8, 4>(ctx, a, ra, eq, BH, S, s);
   }
   return ig_fail(ctx, IG_ESHAPE, "scan: streaming form with %d tiles per wave is not built", TPW);
 }
 
+template <typename T>
 int launch_stream(ig_ctx *ctx, const ScanArgs &a, const RopeArgs *ra, const EqArgs *eq, int BH, int TPW, int S, hipStream_t s) {
   if (S < 1 || S > IG_SPLIT_MAX) return ig_fail(ctx, IG_ESHAPE, "scan: %d splits per pair", S);
   if (S > 1) {
     int rc = ig_ensure_zeroed(ctx, &ctx->pair_sync, &ctx->pair_sync_bytes, (size_t)BH * IG_PAIR_SYNC_BYTES);
     if (rc) return rc;
   }
-  if (a.r == 38) return launch_stream_r<half_t, 38>(ctx, a, ra, eq, BH, TPW, S, s);
-  if (a.r == 25) return launch_stream_r<half_t, 25>(ctx, a, ra, eq, BH, TPW, S, s);
+  if constexpr (sizeof(T) == 2) {
+    if (a.r == 38) return launch_stream_r<T, 38>(ctx, a, ra, eq, BH, TPW, S, s);
+    if (a.r == 25) return launch_stream_r<T, 25>(ctx, a, ra, eq, BH, TPW, S, s);
+  }
+  if (a.r <= 64) return launch_stream_r<T, 0>(ctx, a, ra, eq, BH, TPW, S, s);
   return ig_fail(ctx, IG_ESHAPE, "scan: streaming form is not built for r = %d", a.r);
 }
 
@@ -1089,9 +1160,9 @@ int launch_scan(ig_ctx *ctx, const ig_desc *d, ScanArgs &a, const QSource *rope,
   // otherwise one wave per tile so that long sequences spread over all compute units.
   int tpw = 0, S = 0;
   if (ig_scan_stream_form(d, &tpw, &S)) {
-    if (!rope) return launch_stream(ctx, a, nullptr, eq, BH, tpw, S, s);
+    if (!rope) return launch_stream<T>(ctx, a, nullptr, eq, BH, tpw, S, s);
     RopeArgs ra{rope->A_p, rope->pos, d->d, -2.0 / (double)d->d * log2((double)d->rope_theta)};
-    return launch_stream(ctx, a, &ra, eq, BH, tpw, S, s);
+    return launch_stream<T>(ctx, a, &ra, eq, BH, tpw, S, s);
   }
   if (rope) return ig_fail(ctx, IG_EINVAL, "scan: a rotary query source needs the streaming form");
   if (eq) return ig_fail(ctx, IG_EINVAL, "scan: head-equalised lists need the streaming form");
@@ -1125,14 +1196,19 @@ int launch_scan(ig_ctx *ctx, const ig_desc *d, ScanArgs &a, const QSource *rope,
 
 }  // namespace
 
-// The streaming form (rolling load window, one kernel, pairs split over workgroups when they are
-// long) takes half-precision slabs with the kept-channel counts it is built for, where it measured
-// faster than the forms below: sequences of up to 8 tiles with enough pairs to fill the chip (no
-// split), and every sequence beyond 16 tiles (8 tiles per workgroup, 16 when that would need more
-// than IG_SPLIT_MAX workgroups per pair and r <= 32; 4 when there are few pairs, to get more
-// workgroups).
+// The streaming form (rolling load window, one kernel, pairs split over workgroups when they are long or
+// few) where it measured faster than the forms below: for the kept-channel counts of the workloads in half
+// precision (r = 38 and 25, the whole stream unrolled) sequences of up to 8 tiles with enough pairs to fill
+// the chip and everything that is split; for any other r up to 64 and for float32 (the channel loop at run
+// time) what is split, with the exceptions below.  Splits take 4 or 8 tiles per workgroup, 16 when 8 would
+// need more than IG_SPLIT_MAX workgroups per pair (not for r = 38, whose unrolled stream of 4 tiles a wave
+// leaves the registers).
+// (half precision with the kept-channel counts that are template parameters)
+static bool built_in(const ig_desc *d) { return d->dtype == IG_F16 && (d->r == 38 || d->r == 25); }
+
 bool ig_scan_stream_form(const ig_desc *d, int *tpw, int *S) {
-  if (d->dtype != IG_F16 || (d->r != 38 && d->r != 25)) return false;
+  if (d->r > 64) return false;
+  const bool built = built_in(d);
   const int tile = ig_tile_tokens(d->dtype);
   const int nValid = (d->N + tile - 1) / tile;
   const int BH = d->B * d->H;
@@ -1140,37 +1216,44 @@ bool ig_scan_stream_form(const ig_desc *d, int *tpw, int *S) {
     // one tile per wave: about a tenth faster than the block-loading form up to a few hundred
     // pairs (9.3 against 10.5 us on 256 pairs of 2048 tokens); with a thousand pairs and more the
     // block-loading form with its fewer resident workgroups is ahead (31.8 against 32.8 us)
-    if (BH < 128 || BH > 512) return false;
+    if (!built || BH < 128 || BH > 512) return false;
     *tpw = 1;
     *S = 1;
     return true;
   }
-  if (nValid <= 8) {
-    if (BH < 128) return false;
+  if (nValid <= 8 && BH >= 128) {
+    if (!built) return false;
     *tpw = 2;
     *S = 1;
     return true;
   }
-  if (nValid <= 16) return false;
+  // From here on a pair is split.  5..16 tiles and too few pairs to fill the chip: one kernel instead of
+  // three (32 pairs of 4096 tokens: r = 38 13.5 -> 7.2 us, r = 19 13.0 -> 7.6 us, float32 12.8 -> 8.1 us);
+  // with 128 pairs and more the block-loading form, one workgroup per pair, is as fast or faster
+  // (9 tiles: 13.9 against 14.0 us on 128 pairs, 19.0 against 21.8 us on 256).
+  if (nValid <= 16 && BH >= 128) return false;
+  // Beyond 16 tiles, channel counts known only at run time: ahead of the LDS-parked form up to 256 pairs
+  // (16384 tokens, r = 19: 14.9 -> 9.0 us on 32 pairs, 21.0 -> 19.3 us on 128, but 29.9 -> 31.7 us on 256)
+  // and for few channels (r = 12: 25.0 -> 22.6 us on 256 pairs, 49.0 -> 44.0 us on 512).
+  if (!built && nValid > 16 && BH >= 256 && d->r > 16 && nValid * tile <= 32768) return false;
   int t = BH * ((nValid + 7) / 8) >= 512 ? 2 : 1;
   if ((nValid + 4 * t - 1) / (4 * t) > IG_SPLIT_MAX) t = 2;
   if ((nValid + 4 * t - 1) / (4 * t) > IG_SPLIT_MAX) t = 4;
-  if ((nValid + 4 * t - 1) / (4 * t) > IG_SPLIT_MAX || (t == 4 && d->r > 32)) return false;
+  if ((nValid + 4 * t - 1) / (4 * t) > IG_SPLIT_MAX || (t == 4 && built && d->r > 32)) return false;
   *tpw = t;
   *S = (nValid + 4 * t - 1) / (4 * t);
   return true;
 }
 
 // Shapes whose scan finishes a rotary model's partial query itself (from the full projection's
-// split-K sums) instead of reading it from the finalisation kernel: the streaming form with one
-// workgroup per pair, heads that fit its prologue.  Where a pair is split over S workgroups every
-// one of them would repeat the prologue (S times the work, and 2.5-3 us of latency at the start of
-// each): there the query is finished once, by the finalisation kernel, and the scan starts with it
-// (measured on 160 pairs of 32768 tokens, S = 8: scan 52.1 -> 49.7 us, the finalisation kernel adds
-// 4.8 us including its launch, the projection + scan sequence 65.3 -> 66.7 us).
+// split-K sums) instead of reading it from the finalisation kernel: the streaming form with a built-in
+// channel count, heads that fit its prologue.  Where a pair is split over S workgroups every one of them
+// repeats the prologue, behind its first slab loads; that costs the scan less than the finalisation kernel
+// and its launch (160 pairs of 32768 tokens, S = 8: scan 52.0 -> 53.6 us, the finalisation kernel's 4.8 us
+// gone, the whole rehearsal 66.2 -> 63.4 us).
 bool ig_scan_takes_rope(const ig_desc *d) {
   int tpw = 0, S = 0;
-  return d->rope && ig_scan_stream_form(d, &tpw, &S) && S == 1 && rope_prologue_fits(256, d->d, d->r);
+  return d->rope && built_in(d) && ig_scan_stream_form(d, &tpw, &S) && rope_prologue_fits(256, d->d, d->r);
 }
 
 // One workgroup per (b,h) and a single kernel when a pair fits 16 waves (scores stay in registers)
@@ -1199,6 +1282,7 @@ int ig_scan_args(ig_ctx *ctx, const ig_desc *d, const QSource &q, const void *sl
   a.b_stride = q.b_stride;
   a.ks = q.ks;
   a.H = d->H;
+  a.by_H = ig_fast_div(d->H);
   a.r = d->r;
   a.N = d->N;
   const int tile = ig_tile_tokens(d->dtype);
@@ -1225,10 +1309,11 @@ int ig_launch_scan_select(ig_ctx *ctx, const ig_desc *d, const QSource &q, const
 }
 
 // Shapes whose scan builds the head-equalised lists itself: the streaming form with one
-// workgroup per pair (every head's workgroup of a sequence then runs at the same time).
+// workgroup per pair (every head's workgroup of a sequence then runs at the same time), for the
+// channel counts that are built in.
 bool ig_scan_equalizes(const ig_desc *d) {
   int tpw = 0, S = 0;
-  return ig_scan_stream_form(d, &tpw, &S) && S == 1 && tpw <= 2 && (!d->rope || ig_scan_takes_rope(d));
+  return built_in(d) && ig_scan_stream_form(d, &tpw, &S) && S == 1 && tpw <= 2 && (!d->rope || ig_scan_takes_rope(d));
 }
 
 int ig_launch_scan_equalized(ig_ctx *ctx, const ig_desc *d, const QSource &q, const void *slab, int cap,

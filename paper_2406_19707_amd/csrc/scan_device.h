@@ -19,6 +19,7 @@ struct ScanArgs {
   long b_stride;
   int ks;
   int H, r, N;
+  FastDiv by_H;
   int nTiles;   // tiles allocated per (b,h): the slab's stride (from N_cap)
   int nValid;   // tiles that hold valid tokens (from N): the only ones read
   int sel_stride;
@@ -209,7 +210,7 @@ __device__ __forceinline__ void scan_select_fused_body(const ScanArgs &a, const 
   constexpr int TILE = IG_WAVE * TPL;
   __shared__ float lds_max[NW];
   __shared__ int lds_cnt[NW];
-  const int b = bh / a.H, h = bh % a.H;
+  const int b = a.by_H.div(bh), h = bh - b * a.H;
   // the wave index is made a scalar so that tile addresses stay in scalar registers
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const bool active = w < a.nValid;

@@ -106,3 +106,46 @@ def test_split_pairs_are_deterministic(ctx):
     for _ in range(10):
         idx, cnt = _speculate(ctx, up, c)
         assert np.array_equal(cnt, cnt0) and np.array_equal(idx, idx0)
+
+
+# ---- channel counts and types known only at run time; few pairs of 5..16 tiles ---------------------
+# (the form's rule: r <= 64, any type; a wave's stream is its valid tiles x r planes in turns of 8 loads, so
+# r below, at and above the window, r = 64, tiles with one token, waves with one or no valid tile)
+RUN_TIME = [
+    (2, "f16", 2, 4, 64, 2600, 2700, 0.3, 8.0, True),       # r 19, 6 tiles: 2 workgroups, the second half empty; bias
+    (2, "f16", 1, 3, 64, 4609, 4609, 1.0, 6.0, False),      # r 64, 10 tiles, the last with one token
+    (2, "f16", 1, 2, 64, 8192, 8192, 0.05, 6.0, False),     # r 3: less than one window a tile; 16 tiles
+    (2, "f16", 3, 5, 128, 4000, 4000, 0.3, 8.0, False),     # r 38, 8 tiles, 15 pairs
+    (2, "f32", 1, 4, 64, 1300, 1300, 0.3, 8.0, False),      # float32: 6 tiles of 256
+    (2, "f32", 2, 3, 16, 20000, 20000, 0.5, 4.0, True),     # float32, r 8, 79 tiles: 20 workgroups a pair
+    (2, "f16", 2, 8, 64, 16900, 17000, 0.2, 8.0, False),    # r 12, 34 tiles
+    (3, "f16", 1, 4, 64, 5000, 5000, 0.3, 20.0, False),     # rotary, r 19, 10 tiles
+    (3, "f16", 1, 4, 128, 5000, 5000, 0.3, 20.0, False),    # rotary, r 38, split: the scan finishes the query
+    (3, "f16", 2, 3, 64, 2700, 2700, 0.6, 20.0, True),      # the same, heads of 64 columns; bias
+]
+
+
+@pytest.mark.parametrize("cfg,dtype,B,H,d,N,N_cap,ratio,gain,bias", RUN_TIME)
+def test_run_time_channel_counts_against_the_oracle(ctx, cfg, dtype, B, H, d, N, N_cap, ratio, gain, bias):
+    w = wl.shrink(wl.WORKLOADS[cfg], B=B, H=H, d=d, N=N, ratio=ratio, dtype=dtype, n_cal=2 * d, heavy_count=24)
+    c = make_case(w, gain=gain, bias=bias, N_cap=N_cap)
+    check_case(ctx, c)
+
+
+@pytest.mark.parametrize("cfg,dtype,B,H,d,N,N_cap,ratio,gain,bias", RUN_TIME[:1] + RUN_TIME[4:7])
+def test_run_time_channel_counts_every_workgroup_alone(ctx, cfg, dtype, B, H, d, N, N_cap, ratio, gain, bias):
+    import paper_2406_19707_amd as ig
+    from ig_gpu import Uploaded
+    w = wl.shrink(wl.WORKLOADS[cfg], B=B, H=H, d=d, N=N, ratio=ratio, dtype=dtype, n_cal=2 * d, heavy_count=24)
+    c = make_case(w, gain=gain, bias=bias, N_cap=N_cap)
+    up = Uploaded(ctx, c)
+    idx0, cnt0 = _speculate(ctx, up, c)
+    ctx.ig_set_wait_limit(-1)
+    try:
+        got = [_speculate(ctx, up, c) for _ in range(2)]
+    finally:
+        ctx.ig_set_wait_limit(0)
+    got.append(_speculate(ctx, up, c))
+    assert ctx.ig_check_status() == ig.IG_OK
+    for idx, cnt in got:
+        assert np.array_equal(cnt, cnt0) and np.array_equal(idx, idx0)
