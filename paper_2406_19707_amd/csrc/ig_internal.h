@@ -325,6 +325,41 @@ __device__ __forceinline__ int wave_sum(int v) {
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
+// ---- radix selection of the n-th largest 32-bit key --------------------------------------------------
+// Three passes of 11, 11 and 10 bits, most significant first, with a histogram each.  Every wave searches
+// the histogram itself, so a pass has one barrier (between the adds and the search).
+// The histogram word of a digit: 4 words are left out after every 32, so that a lane's 32 words and its
+// neighbours' are read 16 bytes at a time without bank conflicts.
+constexpr int RADIX_DIGITS = 2048, RADIX_WORDS = RADIX_DIGITS + RADIX_DIGITS / 32 * 4;
+__device__ __forceinline__ int radix_word(int digit) { return digit + ((digit >> 5) << 2); }
+__device__ __forceinline__ constexpr int radix_shift(int pass) { return pass == 0 ? 21 : (pass == 1 ? 10 : 0); }
+// counts the key if its higher digits are those of T
+__device__ __forceinline__ void radix_add(unsigned *hist, int pass, unsigned key, unsigned T) {
+  const unsigned above = pass == 0 ? 0u : (pass == 1 ? 0xFFE00000u : 0xFFFFFC00u), digit = pass == 2 ? 1023u : 2047u;
+  if ((key & above) == T) atomicAdd(&hist[radix_word((key >> radix_shift(pass)) & digit)], 1u);
+}
+// The digit where the count of larger ones is below `need` and its own reaches it (all lanes active); `need`
+// becomes what is left to find among the keys with that digit, *whole says that this is all of them.
+__device__ __forceinline__ unsigned radix_digit(const unsigned *hist, int lane, int &need, bool *whole) {
+  int mine = 0;                    // digits 32 lane .. 32 lane + 31
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const uint4 v = *reinterpret_cast<const uint4 *>(hist + lane * 36 + i * 4);
+    mine += (int)(v.x + v.y + v.z + v.w);
+  }
+  int incl = wave_incl_scan(mine);
+  int above = __builtin_amdgcn_readlane(incl, 63) - incl;
+  const int group = __ffsll(__ballot(above < need && need <= above + mine)) - 1;
+  const int above_group = __builtin_amdgcn_readlane(above, group);
+  mine = lane < 32 ? (int)hist[group * 36 + lane] : 0;      // the same among that lane's 32 digits
+  incl = wave_incl_scan(mine);
+  above = above_group + __builtin_amdgcn_readlane(incl, 63) - incl;
+  const int digit = __ffsll(__ballot(above < need && need <= above + mine)) - 1;
+  need -= __builtin_amdgcn_readlane(above, digit);
+  *whole = need == __builtin_amdgcn_readlane(mine, digit);
+  return (unsigned)(group * 32 + digit);
+}
+
 // number of lanes below this one whose predicate is set, and the wave's total
 __device__ __forceinline__ int lanes_below(unsigned long long ballot) {
   return __builtin_amdgcn_mbcnt_hi((unsigned)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)ballot, 0));

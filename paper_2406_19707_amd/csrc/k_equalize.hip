@@ -23,11 +23,6 @@ __device__ __forceinline__ unsigned score_key(float s) {
 }
 
 __device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_incl_scan(v), 63); }
-// the histogram word of a digit: 4 words are left out after every 32, so that a lane's 32 words and its
-// neighbours' are read 16 bytes at a time without bank conflicts
-__device__ __forceinline__ int hist_word(int digit) { return digit + ((digit >> 5) << 2); }
-constexpr int DIGITS = 2048, HIST_WORDS = DIGITS + DIGITS / 32 * 4;
-
 // A chain of dependent steps rather than work (192 heads of 3000 tokens are 2.3 MB), so the steps are few: a
 // wave owns KPT * 64 consecutive tokens, whose keys stay in registers; every wave searches the histogram for
 // itself, which leaves one barrier in a pass; 11 bits a pass instead of 8 are a pass less, spread the sign,
@@ -44,7 +39,7 @@ __global__ __launch_bounds__(THREADS) void equalize_select(const float *__restri
                                                            int32_t *status, FastDiv by_H, int N, int cap,
                                                            int stride) {
   constexpr int NW = THREADS / 64, U = KPT > 0 ? KPT : 8;
-  __shared__ __attribute__((aligned(16))) unsigned hist[3][HIST_WORDS];
+  __shared__ __attribute__((aligned(16))) unsigned hist[3][RADIX_WORDS];
   __shared__ int w_gt[NW], w_eq[NW];
   const int H = by_H.d, bh = blockIdx.x, b = by_H.div(bh);
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -78,7 +73,7 @@ __global__ __launch_bounds__(THREADS) void equalize_select(const float *__restri
   int part = cnts[min(lane, H - 1)];
   part = lane < H ? part : 0;
   for (int h = lane + 64; h < H; h += 64) part += cnts[h];
-  for (int i = tid; i < 3 * HIST_WORDS / 4; i += THREADS) reinterpret_cast<uint4 *>(&hist[0][0])[i] = make_uint4(0, 0, 0, 0);
+  for (int i = tid; i < 3 * RADIX_WORDS / 4; i += THREADS) reinterpret_cast<uint4 *>(&hist[0][0])[i] = make_uint4(0, 0, 0, 0);
   int need = max(1, min(min(by_H.div(max(0, wave_total(part))), cap), N));
   __syncthreads();
 
@@ -87,32 +82,13 @@ __global__ __launch_bounds__(THREADS) void equalize_select(const float *__restri
   unsigned T = 0;
 #pragma unroll
   for (int pass = 0; pass < 3; ++pass) {
-    const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
-    const unsigned digit_mask = pass == 2 ? 1023u : 2047u;
-    const unsigned above_mask = pass == 0 ? 0u : (pass == 1 ? 0xFFE00000u : 0xFFFFFC00u);
     each([&](int, unsigned k, bool there) {
-      if (there && (k & above_mask) == T) atomicAdd(&hist[pass][hist_word((k >> shift) & digit_mask)], 1u);
+      if (there) radix_add(hist[pass], pass, k, T);
     });
     __syncthreads();
-    // digits 32 lane .. 32 lane + 31: the lane where (digits above) < need <= (digits above and its own)
-    int mine = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint4 v = *reinterpret_cast<const uint4 *>(&hist[pass][lane * 36 + i * 4]);
-      mine += (int)(v.x + v.y + v.z + v.w);
-    }
-    int incl = wave_incl_scan(mine);
-    int above = __builtin_amdgcn_readlane(incl, 63) - incl;
-    const int group = __ffsll(__ballot(above < need && need <= above + mine)) - 1;
-    const int above_group = __builtin_amdgcn_readlane(above, group);
-    // the same among that lane's 32 digits
-    mine = lane < 32 ? (int)hist[pass][group * 36 + lane] : 0;
-    incl = wave_incl_scan(mine);
-    above = above_group + __builtin_amdgcn_readlane(incl, 63) - incl;
-    const int digit = __ffsll(__ballot(above < need && need <= above + mine)) - 1;
-    need -= __builtin_amdgcn_readlane(above, digit);
-    T |= (unsigned)(group * 32 + digit) << shift;
-    if (pass < 2 && need == __builtin_amdgcn_readlane(mine, digit) && T > 0) {
+    bool whole;
+    T |= radix_digit(hist[pass], lane, need, &whole) << radix_shift(pass);
+    if (pass < 2 && whole && T > 0) {
       T -= 1;                      // the bin is kept whole: everything from its lowest key upwards
       need = 0;
       break;

@@ -389,52 +389,44 @@ __device__ __forceinline__ bool poll_heads(const unsigned long long *slots, int 
   }
 }
 
-// Key of the n-th largest valid score of the workgroup's tokens (4 waves; wave w holds tiles
-// w*TPW + i): most-significant-digit radix select, 4 passes of 8 bits, one 256-bin LDS histogram
-// each.  *need_out = how many tokens equal to that key are to be kept.
+template <int THREADS>
+__device__ __forceinline__ void radix_clear(unsigned *hist, int words) {
+  for (int i = threadIdx.x; i < words / 4; i += THREADS) reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0, 0, 0, 0);
+}
+// Radix selection among the valid scores a workgroup holds: one pass's histogram ...
 template <int TPL, int TPW>
-__device__ __forceinline__ unsigned nth_largest_key(const float (&sc)[TPW][TPL], const unsigned (&valid)[TPW], int n,
-                                                    unsigned *hist /*[256]*/, unsigned *wsum /*[4]*/,
-                                                    unsigned *s_prefix, int *s_need, int *need_out) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  unsigned prefix = 0;
-  int need = n;
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    const unsigned hi_mask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
-    hist[tid] = 0;
-    __syncthreads();
+__device__ __forceinline__ void radix_add_held(const float (&sc)[TPW][TPL], const unsigned (&valid)[TPW], int pass, unsigned T,
+                                               unsigned *hist) {
 #pragma unroll
-    for (int i = 0; i < TPW; ++i)
+  for (int i = 0; i < TPW; ++i)
 #pragma unroll
-      for (int e = 0; e < TPL; ++e) {
-        const unsigned k = eq_key(sc[i][e]);
-        if (((valid[i] >> e) & 1u) && (k & hi_mask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1u);
-      }
-    __syncthreads();
-    // bin d holds the target when (#keys in bins above d) < need <= (#keys in bins >= d)
-    const unsigned mine = hist[tid];
-    unsigned incl = mine;                     // suffix sum inside the wave: bins tid .. (wave end)
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned u = __shfl_down(incl, o, 64);
-      if (lane + o < 64) incl += u;
+    for (int e = 0; e < TPL; ++e)
+      if ((valid[i] >> e) & 1u) radix_add(hist, pass, eq_key(sc[i][e]), T);
+}
+// ... and the passes, the first histogram being counted already (and a barrier past): kept are the keys above
+// the one returned and the first *need of those equal to it.  Two histograms, both zeroed by the caller: the
+// last pass, which few lists need, clears the first one again.
+template <int TPL, int TPW, int THREADS>
+__device__ __forceinline__ unsigned nth_largest_key(const float (&sc)[TPW][TPL], const unsigned (&valid)[TPW], int lane,
+                                                    unsigned (*hist)[RADIX_WORDS], int *need) {
+  bool whole;
+  unsigned T = radix_digit(hist[0], lane, *need, &whole) << radix_shift(0);
+#pragma unroll 1
+  for (int pass = 1; pass < 3; ++pass) {
+    if (whole && T > 0) {      // the bin is kept whole: everything from its lowest key upwards
+      *need = 0;
+      return T - 1;
     }
-    if (lane == 0) wsum[w] = incl;
-    __syncthreads();
-    unsigned above = incl - mine;
-    for (int k = w + 1; k < 4; ++k) above += wsum[k];
-    if ((int)above < need && need <= (int)(above + mine)) {
-      *s_prefix = prefix | ((unsigned)tid << shift);
-      *s_need = need - (int)above;
+    unsigned *h = hist[pass & 1];
+    if (pass == 2) {           // (read for the last time before the barrier of pass 1)
+      radix_clear<THREADS>(h, RADIX_WORDS);
+      __syncthreads();
     }
+    radix_add_held<TPL, TPW>(sc, valid, pass, T, h);
     __syncthreads();
-    prefix = *s_prefix;
-    need = *s_need;
-    __syncthreads();
+    T |= radix_digit(h, lane, *need, &whole) << radix_shift(pass);
   }
-  *need_out = need;
-  return prefix;
+  return T;
 }
 
 // Ordered compaction of the tokens whose key exceeds T plus the first `need` tokens (in token
@@ -842,6 +834,8 @@ __global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, 
   }
   m = wave_max(m);
   if (lane == 0) lds_max[w] = m;
+  __shared__ __attribute__((aligned(16))) unsigned eq_hist[EQ ? 2 : 1][RADIX_WORDS];
+  if constexpr (EQ) radix_clear<NW * 64>(&eq_hist[0][0], 2 * RADIX_WORDS);
   __syncthreads();
   float mm = lds_max[0];
 #pragma unroll
@@ -849,15 +843,22 @@ __global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, 
   int32_t *list = a.sel_idx + (long)bh * a.sel_stride;
   if constexpr (EQ) {
     // ---- head-equalised lists (one workgroup per pair: S == 1) ----
-    static_assert(NW == 4, "the radix select's histogram scan is written for 4 waves");
-    __shared__ unsigned eq_hist[256], eq_wsum[4], eq_prefix;
-    __shared__ int eq_need;
     const int cnt = compact_tiles<TPL, NW, TPW>(sc, mm - a.alpha, a.N, 0, list, a.sel_stride, 0, lds_cnt, stage, w, lane, true);
     if (eq.thr_cnt && threadIdx.x == 0) eq.thr_cnt[bh] = cnt;
     unsigned long long *rec = eq.seq + (long)b * (a.H + 1);
+    if (threadIdx.x == 0)
+      __hip_atomic_store(&rec[h], PUBLISHED | (unsigned long long)(unsigned)cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the first pass of the selection needs no count: it is made while the other heads' counts arrive
+    unsigned valid[TPW];
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) {
+      const int t0 = (my0 + i) * TILE + lane * TPL;
+      valid[i] = 0;
+#pragma unroll
+      for (int e = 0; e < TPL; ++e) valid[i] |= ((i < nact && t0 + e < a.N) ? 1u : 0u) << e;
+    }
+    radix_add_held<TPL, TPW>(sc, valid, 0, 0, eq_hist[0]);
     if (w == 0) {
-      if (lane == 0)
-        __hip_atomic_store(&rec[h], PUBLISHED | (unsigned long long)(unsigned)cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       int total = 0;
       const bool ok = poll_heads(rec, a.H, lane, spin_limit, &total);
       if (lane == 0) {
@@ -897,17 +898,8 @@ __global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, 
         total += count_pair<T, NW>(a, b * a.H + h2, q2, m2 - a.alpha, lds_cnt);
       }
     }
-    const int n = max(1, min(min(total / a.H, eq.cap), a.N));
-    unsigned valid[TPW];
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int t0 = (my0 + i) * TILE + lane * TPL;
-      valid[i] = 0;
-#pragma unroll
-      for (int e = 0; e < TPL; ++e) valid[i] |= ((i < nact && t0 + e < a.N) ? 1u : 0u) << e;
-    }
-    int need = 0;
-    const unsigned Tkey = nth_largest_key<TPL, TPW>(sc, valid, n, eq_hist, eq_wsum, &eq_prefix, &eq_need, &need);
+    int need = max(1, min(min(total / a.H, eq.cap), a.N));
+    const unsigned Tkey = nth_largest_key<TPL, TPW, NW * 64>(sc, valid, lane, eq_hist, &need);
     const int all = compact_tiles_topn<TPL, NW, TPW>(sc, valid, Tkey, need, list, a.sel_stride, lds_cnt, stage, w, lane);
     if (threadIdx.x == 0) {
       a.sel_cnt[bh] = min(all, a.sel_stride);
