@@ -444,8 +444,8 @@ int ig_pool_replace_policy(ig_ctx *ctx, const ig_desc *d, int policy, const int3
                           (hipStream_t)stream);
 }
 
-static int project_partials(ig_ctx *ctx, const ig_desc *d, const void *x, const void *wq,
-                            const float *A_p, const int32_t *pos, ProjGeom *g, hipStream_t s) {
+static int project_ready(ig_ctx *ctx, const ig_desc *d, const void *x, const void *wq,
+                         const float *A_p, const int32_t *pos, ProjGeom *g) {
   if (!x || !wq) return ig_fail(ctx, IG_EINVAL, "x or wq is NULL");
   if (int rc0 = check_aligned(ctx, "projection", {x, wq})) return rc0;
   if (d->rope && (!A_p || !pos)) return ig_fail(ctx, IG_EINVAL, "rope mode needs A_p and pos");
@@ -453,6 +453,12 @@ static int project_partials(ig_ctx *ctx, const ig_desc *d, const void *x, const 
   if (rc) return rc;
   if ((rc = reserve_for(ctx, d, false))) return rc;
   *g = ig_proj_geom(d);
+  return IG_OK;
+}
+
+static int project_partials(ig_ctx *ctx, const ig_desc *d, const void *x, const void *wq,
+                            const float *A_p, const int32_t *pos, ProjGeom *g, hipStream_t s) {
+  if (int rc = project_ready(ctx, d, x, wq, A_p, pos, g)) return rc;
   return ig_launch_project(ctx, d, *g, x, wq, ctx->part, s);
 }
 
@@ -536,7 +542,10 @@ int ig_speculate(ig_ctx *ctx, const ig_desc *d, const void *x, const void *wq, c
   if ((rc = check_sel(ctx, sel_idx, sel_stride, sel_cnt))) return rc;
   ProjGeom g;
   hipStream_t s = (hipStream_t)stream;
-  if ((rc = project_partials(ctx, d, x, wq, A_p, pos, &g, s))) return rc;
+  if ((rc = project_ready(ctx, d, x, wq, A_p, pos, &g))) return rc;
+  if (ig_scan_takes_projection(d, g))
+    return ig_launch_project_scan(ctx, d, g, x, wq, bias, slab, sel_idx, sel_stride, sel_cnt, scores_opt, s);
+  if ((rc = ig_launch_project(ctx, d, g, x, wq, ctx->part, s))) return rc;
   if (d->rope && ig_scan_takes_rope(d)) {
     // rotary embedding and the partial skew sit between the projection and the scan: the scan's
     // workgroups work them out themselves while their first slab loads are in flight

@@ -190,6 +190,11 @@ struct QSource {
 };
 bool ig_scan_is_fused(const ig_desc *d);
 bool ig_scan_takes_rope(const ig_desc *d);
+// small folded models: projection and scan in one kernel
+bool ig_scan_takes_projection(const ig_desc *d, const ProjGeom &g);
+int ig_launch_project_scan(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, const void *x, const void *wq,
+                           const float *bias, const void *slab, int32_t *sel_idx, int32_t sel_stride,
+                           int32_t *sel_cnt, float *scores_opt, hipStream_t s);
 bool ig_scan_equalizes(const ig_desc *d);
 int ig_launch_scan_equalized(ig_ctx *ctx, const ig_desc *d, const QSource &q, const void *slab, int cap,
                              int32_t *sel_idx, int32_t sel_stride, int32_t *sel_cnt, int32_t *thr_cnt_opt,

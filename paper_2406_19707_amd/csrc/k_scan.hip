@@ -22,6 +22,69 @@ __global__ __launch_bounds__(NW * 64) void scan_select_fused(ScanArgs a) {
   scan_select_fused_body<T, CH, NW>(a, blockIdx.x);
 }
 
+// The same for small models, with the projection in the workgroup too: a head's r columns of the weight are a
+// few tens of KB there, and reading them again for every sequence costs less than the launch and the chain
+// of a kernel before this one (one layer of 4 heads, 256 model columns, 512 tokens: 5.0 -> 4.6 us on the GPU,
+// 9.2 -> 5.5 us from call to call).  Thread (split, channel) adds its rows of the weight in the order of
+// project_fma, behind the wave's slab loads, which are on their way meanwhile; the splits are added from
+// LDS in the order of query_finish: the same query, bit for bit.
+struct ProjectArgs {
+  const void *x, *blob;
+  int D, kb_per, Cpad;
+  FastDiv by_r;
+};
+template <typename T, int CH>
+__global__ __launch_bounds__(256) void project_scan_select(ScanArgs a, ProjectArgs p) {
+  constexpr int TPL = SlabElem<T>::TPL, U = 16;
+  constexpr int TILE = IG_WAVE * TPL;
+  __shared__ float part[IG_KS_MAX * 64];
+  const int bh = blockIdx.x, b = a.by_H.div(bh), h = bh - b * a.H;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const bool active = w < a.nValid;
+  const T *tile = static_cast<const T *>(a.slab) + ((long)bh * a.nTiles + (active ? w : 0)) * a.r * TILE;
+  typename SlabElem<T>::vec v[CH];
+  load_block<T, CH>(tile, a.r, 0, lane, v);
+  __builtin_amdgcn_sched_barrier(0);
+  const T *x = static_cast<const T *>(p.x) + (long)b * p.D;
+  const T *blob = static_cast<const T *>(p.blob) + h * a.r;
+  for (int i = threadIdx.x; i < a.ks * a.r; i += 256) {
+    const int s = p.by_r.div(i), j = i - s * a.r;
+    const int k0 = s * p.kb_per, k1 = min(p.D, k0 + p.kb_per);
+    float sum = 0.f;
+    for (int k = k0; k < k1; k += U) {
+      T wv[U], xv[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int kk = min(k + u, k1 - 1);
+        wv[u] = blob[(long)kk * p.Cpad + j];
+        xv[u] = x[kk];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const float next = fmaf((float)xv[u], (float)wv[u], sum);
+        sum = k + u < k1 ? next : sum;
+      }
+    }
+    part[i] = sum;
+  }
+  __syncthreads();
+  const int j = min(lane, a.r - 1);
+  float q = a.bias ? a.bias[h * a.r + j] : 0.f;
+#pragma unroll
+  for (int s = 0; s < IG_KS_MAX; ++s) {
+    const float t = part[min(s, a.ks - 1) * a.r + j];
+    q += s < a.ks ? t : 0.f;
+  }
+  const float qv[4] = {lane < a.r ? q * a.scale : 0.f, 0.f, 0.f, 0.f};
+  float acc[TPL];
+#pragma unroll
+  for (int e = 0; e < TPL; ++e) acc[e] = 0.f;
+#pragma unroll
+  for (int i = 0; i < CH; ++i) keep_loaded(v[i]);
+  if (active) scan_tile_given_q<T, CH>(a, tile, lane, v, qv, acc);
+  select_held<T, 4>(a, bh, acc, active, w, lane);
+}
+
 // Sequences of up to LDS_SCORES tokens that do not fit 16 waves at once: still one workgroup of
 // 16 waves per (b,h); wave w scans tiles w, w + 16, ... and parks the scores in LDS (4 B/token,
 // 128 KiB), so that the threshold pass needs neither a score buffer in memory nor further
@@ -1145,6 +1208,22 @@ int launch_tiles(ig_ctx *ctx, const ScanArgs &a, int BH, int ch, hipStream_t s) 
 }
 
 template <typename T>
+int launch_project_scan(ig_ctx *ctx, const ig_desc *d, const ScanArgs &a, const ProjectArgs &p, hipStream_t s) {
+  dim3 grid(d->B * d->H), block(256);
+#define CASE(CHV)                                                              \
+  case CHV: {                                                                  \
+    auto k = project_scan_select<T, CHV>;                                      \
+    IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, p);                        \
+    return IG_OK;                                                              \
+  }
+  switch (pick_ch(d->r, 20)) {
+    CASE(4) CASE(8) CASE(12) CASE(16) CASE(20)
+    default: return ig_fail(ctx, IG_ESHAPE, "scan: unsupported channel block %d", pick_ch(d->r, 20));
+  }
+#undef CASE
+}
+
+template <typename T>
 int launch_scan(ig_ctx *ctx, const ig_desc *d, ScanArgs &a, const QSource *rope, const EqArgs *eq, hipStream_t s) {
   const int BH = d->B * d->H;
   const int nTiles = a.nValid;     // the work, not the capacity, picks the kernel
@@ -1257,6 +1336,31 @@ bool ig_scan_is_fused(const ig_desc *d) {
   const int BH = d->B * d->H;
   if (nTiles > 16) return nTiles * tile <= 32768 && BH >= 64;     // scores parked in LDS, one workgroup per pair
   return BH >= 128 || nTiles <= 4;
+}
+
+// Shapes whose scan multiplies the weight itself (folded models on the FMA projection, one workgroup of four
+// tiles at most per pair): where a head's columns of the weight are at most PROJECT_IN_SCAN_BYTES.  Up to
+// there a workgroup's share of the weight is one or two round trips (19 KB, 512 tokens: 5.0 -> 4.6 us for 4
+// heads, 6.8 -> 4.8 us for 16 sequences); at 38 KB it takes longer than the kernel it replaces (8 heads, one
+// sequence 5.3 -> 6.2 us).
+constexpr long PROJECT_IN_SCAN_BYTES = 32768;
+bool ig_scan_takes_projection(const ig_desc *d, const ProjGeom &g) {
+  int tpw = 0, S = 0;
+  const int tile = ig_tile_tokens(d->dtype);
+  return !d->rope && !g.mfma && d->r <= 64 && (d->N + tile - 1) / tile <= 4 && !ig_scan_stream_form(d, &tpw, &S) &&
+         (long)d->H * d->d * d->r * ig_elem_bytes(d->dtype) <= PROJECT_IN_SCAN_BYTES;
+}
+
+int ig_launch_project_scan(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, const void *x, const void *wq,
+                           const float *bias, const void *slab, int32_t *sel_idx, int32_t sel_stride,
+                           int32_t *sel_cnt, float *scores_opt, hipStream_t s) {
+  if (!ig_scan_takes_projection(d, g)) return ig_fail(ctx, IG_EINVAL, "scan: this shape does not multiply the weight itself");
+  ScanArgs a;
+  QSource q{nullptr, g.KS, 0, 0, bias};
+  int rc = ig_scan_args(ctx, d, q, slab, sel_idx, sel_stride, sel_cnt, scores_opt, &a);
+  if (rc) return rc;
+  ProjectArgs p{x, wq, d->H * d->d, g.kb_per, g.Cpad, ig_fast_div(d->r)};
+  return d->dtype == IG_F16 ? launch_project_scan<half_t>(ctx, d, a, p, s) : launch_project_scan<float>(ctx, d, a, p, s);
 }
 
 int ig_scan_args(ig_ctx *ctx, const ig_desc *d, const QSource &q, const void *slab, int32_t *sel_idx,

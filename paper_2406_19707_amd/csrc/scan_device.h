@@ -203,22 +203,15 @@ __device__ __forceinline__ int compact_block(const float (&sc)[TPL], int t0, int
   return all;
 }
 
-// One workgroup per (b,h); wave w scans tile w (nValid <= NW) and keeps its scores in registers.
-template <typename T, int CH, int NW>
-__device__ __forceinline__ void scan_select_fused_body(const ScanArgs &a, const int bh) {
+// Threshold and list of a pair whose scores are in the registers of the one workgroup that scanned it
+// (wave w holds tile w).
+template <typename T, int NW>
+__device__ __forceinline__ void select_held(const ScanArgs &a, const int bh, float (&acc)[SlabElem<T>::TPL],
+                                            const bool active, const int w, const int lane) {
   constexpr int TPL = SlabElem<T>::TPL;
   constexpr int TILE = IG_WAVE * TPL;
   __shared__ float lds_max[NW];
   __shared__ int lds_cnt[NW];
-  const int b = a.by_H.div(bh), h = bh - b * a.H;
-  // the wave index is made a scalar so that tile addresses stay in scalar registers
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const bool active = w < a.nValid;
-  const T *tile = static_cast<const T *>(a.slab) + ((long)bh * a.nTiles + (active ? w : 0)) * a.r * TILE;
-  float acc[TPL];
-#pragma unroll
-  for (int e = 0; e < TPL; ++e) acc[e] = 0.f;
-  if (active) scan_tile<T, CH>(a, tile, b, h, lane, acc);
   const int t0 = w * TILE;
   float m = -INFINITY;
 #pragma unroll
@@ -241,6 +234,23 @@ __device__ __forceinline__ void scan_select_fused_body(const ScanArgs &a, const 
     a.sel_cnt[bh] = min(all, a.sel_stride);
     if (all > a.sel_stride) atomicOr(a.status, IG_STATUS_CAPACITY);
   }
+}
+
+// One workgroup per (b,h); wave w scans tile w (nValid <= NW) and keeps its scores in registers.
+template <typename T, int CH, int NW>
+__device__ __forceinline__ void scan_select_fused_body(const ScanArgs &a, const int bh) {
+  constexpr int TPL = SlabElem<T>::TPL;
+  constexpr int TILE = IG_WAVE * TPL;
+  const int b = a.by_H.div(bh), h = bh - b * a.H;
+  // the wave index is made a scalar so that tile addresses stay in scalar registers
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const bool active = w < a.nValid;
+  const T *tile = static_cast<const T *>(a.slab) + ((long)bh * a.nTiles + (active ? w : 0)) * a.r * TILE;
+  float acc[TPL];
+#pragma unroll
+  for (int e = 0; e < TPL; ++e) acc[e] = 0.f;
+  if (active) scan_tile<T, CH>(a, tile, b, h, lane, acc);
+  select_held<T, NW>(a, bh, acc, active, w, lane);
 }
 
 }  // namespace

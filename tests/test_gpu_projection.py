@@ -77,3 +77,47 @@ def test_partial_query_against_float64(ctx, dtype, H, d, r, rope, bias, B):
         ref, bound = (q[:, cols] + b64).reshape(B, H, r), (eps * (mag[:, cols] + np.abs(b64))).reshape(B, H, r)
     for o in outs:
         assert np.all(np.abs(o.cpu().numpy().astype(np.float64) - ref) <= bound)
+
+
+# Small folded models: one kernel multiplies the weight, scans and selects (ig_speculate), with the sums of
+# the three in the same order as the separate calls: the same scores and lists, bit for bit.  On both sides
+# of its limits (32768 bytes of a head's weight columns, r = 64, four tiles).
+@pytest.mark.parametrize("dtype,B,H,d,r,N,bias", [
+    ("f32", 1, 4, 64, 19, 512, False), ("f32", 3, 4, 64, 19, 1024, True), ("f32", 2, 3, 8, 1, 1, True),
+    ("f32", 2, 8, 64, 19, 700, True), ("f32", 1, 4, 48, 48, 257, False), ("f32", 1, 3, 64, 64, 1024, True),
+    ("f32", 1, 3, 64, 64, 1025, False), ("f32", 5, 2, 80, 51, 300, True), ("f32", 5, 2, 80, 52, 300, False), ("f32", 1, 2, 128, 65, 300, False),
+    ("f16", 2, 3, 80, 24, 700, True), ("f16", 40, 1, 8, 8, 2048, False), ("f16", 2, 5, 72, 64, 513, True),
+    ("f16", 1, 3, 8, 3, 2049, False)])
+def test_small_models_project_in_the_scan(ctx, dtype, B, H, d, r, N, bias):
+    import paper_2406_19707_amd as ig
+    print(f"case {dtype} B{B} H{H} d{d} r{r} N{N}", flush=True)
+    torch.manual_seed(B + H * d + N)
+    t, D = (torch.float16 if dtype == "f16" else torch.float32), H * d
+    desc = ig.IgDesc(B=B, H=H, d=d, r=r, N=N, N_cap=N + 300, dtype=ig.IG_F16 if dtype == "f16" else ig.IG_F32, scale=0.4, alpha=3.0)
+    W = (torch.randn(D, D, device="cuda") / D ** 0.5).to(t)
+    idx = torch.stack([torch.randperm(d, device="cuda")[:r].sort().values for _ in range(H)]).to(torch.int32).contiguous()
+    bv = torch.randn(H * r, device="cuda") if bias else None
+    x, K = torch.randn(B, D, device="cuda").to(t), torch.randn(B, H, N + 300, d, device="cuda").to(t)
+    wq = torch.empty(ig.ig_wq_bytes(desc), dtype=torch.uint8, device="cuda")
+    slab = torch.empty(ig.ig_slab_bytes(desc), dtype=torch.uint8, device="cuda")
+    ctx.ig_wq_build(desc, W, idx, wq)
+    ctx.ig_slab_build(desc, K, ig.IG_MEM_DEVICE, idx, slab)
+
+    def lists(stride, run):
+        sel = torch.full((B * H, stride), -1, dtype=torch.int32, device="cuda")
+        cnt = torch.full((B * H,), -1, dtype=torch.int32, device="cuda")
+        scores = torch.full((B, H, N), float("nan"), device="cuda")
+        run(sel, stride, cnt, scores)
+        torch.cuda.synchronize()
+        return sel.cpu().numpy(), cnt.cpu().numpy(), scores.cpu().numpy(), ctx.ig_check_status()
+
+    def apart(sel, stride, cnt, scores):
+        q_p = torch.zeros((B, H, r), device="cuda")
+        ctx.ig_project(desc, x, wq, bv, None, None, q_p)
+        ctx.ig_scan_select(desc, q_p, slab, sel, stride, cnt, scores)
+
+    for stride in (N, max(1, N // 7)):
+        one = lists(stride, lambda *a: ctx.ig_speculate(desc, x, wq, bv, None, None, slab, *a))
+        two = lists(stride, apart)
+        assert one[3] == two[3] and all(np.array_equal(u, v) for u, v in zip(one[:3], two[:3]))
+        assert np.all(one[1] >= 1)
