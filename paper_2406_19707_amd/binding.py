@@ -162,13 +162,30 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# torch's current-stream handle without the Stream object around it: torch.cuda.current_stream() builds
+# one on every call (2.6 us measured, against 0.2 us for the two lookups here), which on the small calls
+# is as much as a kernel launch.  Looked up on every call, like the object: nothing is remembered.
+_raw_stream = _raw_device = None
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _raw_stream is not None:
+            return _raw_stream(_raw_device())
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
+
+
+def _current_stream():
+    global _raw_stream, _raw_device
+    import torch
+    handle = torch.cuda.current_stream().cuda_stream          # initialises the device if nothing has yet
+    raw, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is not None and dev is not None:
+        _raw_device, _raw_stream = dev, raw
+    return handle
 
 
 def _host_f32(a):
