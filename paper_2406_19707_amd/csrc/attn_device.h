@@ -332,40 +332,34 @@ __device__ __forceinline__ void sparse_attention_body(const AttnArgs &A, const i
   if (w != 0) return;
   if (s_last) {
     // wave 0 of the last arrival: lane c owns output channels c, c + 64, ...; all loads of a pass
-    // (independent, predicated on the slice count) are issued before any is used
+    // (independent, slices past the last read it again) are issued before any is used
     const float *all = part + (long)bh * max_slices * (d + 2);
-    float mk[SLICE_MAX], zk[SLICE_MAX];
-#pragma unroll
-    for (int k = 0; k < SLICE_MAX; ++k) {
-      mk[k] = -INFINITY;
-      zk[k] = 0.f;
-      if (k < slices) {
-        mk[k] = coherent_load(all + (long)k * (d + 2));
-        zk[k] = coherent_load(all + (long)k * (d + 2) + 1);
-      }
-    }
+    static_assert(SLICE_MAX == 16, "lane k of a 16-lane row has slice k's maximum and normaliser");
+    const float *state = all + (long)min(lane, slices - 1) * (d + 2);
     constexpr int CPP = 2;               // channels per lane and pass
-    for (int c0 = lane; c0 < d; c0 += 64 * CPP) {
-      float ak[CPP][SLICE_MAX];
+    for (int c0 = lane; c0 - lane < d; c0 += 64 * CPP) {   // (all lanes stay: they hold the weights)
+      float mk = coherent_load(state), zk = coherent_load(state + 1), ak[CPP][SLICE_MAX];
 #pragma unroll
       for (int q = 0; q < CPP; ++q)
 #pragma unroll
-        for (int k = 0; k < SLICE_MAX; ++k) {
-          const int c = c0 + 64 * q;
-          ak[q][k] = (k < slices && c < d) ? coherent_load(all + (long)k * (d + 2) + 2 + c) : 0.f;
-        }
-      float MM = -INFINITY;
-#pragma unroll
-      for (int k = 0; k < SLICE_MAX; ++k) MM = fmaxf(MM, mk[k]);
-      float zz = 0.f;
-#pragma unroll
-      for (int k = 0; k < SLICE_MAX; ++k) zz += zk[k] * exp_or_zero(mk[k], MM);
+        for (int k = 0; k < SLICE_MAX; ++k)
+          ak[q][k] = coherent_load(all + (long)min(k, slices - 1) * (d + 2) + 2 + min(c0 + 64 * q, d - 1));
+      __builtin_amdgcn_sched_barrier(0);
+      // (One lane a slice works out its weight, and the loop below reads them one by one.  With every slice's
+      // maximum, normaliser and weight in every lane this merge set the kernel's registers, 144 instead of 117,
+      // three waves a SIMD instead of four: 1120 lists of 77 rows 26.2 -> 23.4 us.)
+      mk = lane < slices ? mk : -INFINITY;
+      zk = lane < slices ? zk : 0.f;
+      const float wk = exp_or_zero(mk, wave_max(mk));
+      const int wbits = __float_as_int(wk);
+      const float zs = row16_sum(zk * wk);     // (lanes 16 and up hold zeros)
+      const float zz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(zs), 0));
 #pragma unroll
       for (int q = 0; q < CPP; ++q) {
         const int c = c0 + 64 * q;
         float a = 0.f;
 #pragma unroll
-        for (int k = 0; k < SLICE_MAX; ++k) a += ak[q][k] * exp_or_zero(mk[k], MM);
+        for (int k = 0; k < SLICE_MAX; ++k) a = fmaf(k < slices ? ak[q][k] : 0.f, __int_as_float(__builtin_amdgcn_readlane(wbits, k)), a);
         if (c < d) out[(long)bh * d + c] = (T)(zz > 0.f ? a / zz : 0.f);
       }
     }
