@@ -418,7 +418,8 @@ int ig_decode_step_overlapped(ig_ctx *ctx, const ig_desc *desc, int n_layers, co
                               int pool_space, int n_sets, const ig_buffer_set *sets, int32_t sel_stride,
                               void *main_stream, void *side_stream);
 
-/* Long sequences are scanned by several workgroups per (sequence, head), which meet through device
+/* Long sequences, and sequences of more than 4 tiles (2048 half or 1024 float32 tokens) when there are
+ * few (sequence, head) pairs, are scanned by several workgroups per pair, which meet through device
  * memory; each waits for its partners at most `ticks` periods of the GPU's 100 MHz clock (10 ns)
  * and then finishes the pair on its own (slower, same result bit for bit).  0 restores the
  * default (20 ms); a negative value makes every such workgroup take the self-sufficient route
