@@ -57,9 +57,9 @@ int ig_launch_scan_attend(ig_ctx *ctx, const ig_desc *d, const QSource &qs, cons
   if ((rc = ig_attn_args(ctx, d, q, Kpool, Vpool, sel_idx, sel_stride, sel_cnt, d->N_cap, k_new, v_new, out,
                          K_sel, V_sel, &aa)))
     return rc;
-  // at most 12 channel loads in flight per wave: the scan half then needs fewer registers than
-  // the attention half, so the joint kernel keeps the attention's occupancy (measured on the
-  // B8 H32 N2048 shape: 20.4-20.8 us per launch against 22.2-22.4 us with 20 loads in flight)
+  // at most 12 channel loads in flight per wave: the scan half then fits the attention half's occupancy
+  // (B8 H32 N2048 shape: 22.2-22.4 us per launch with 20 loads in flight where 12 took 20.4-20.8; with
+  // the attention as it is now 12 take 18.5)
   const int ch = ig_pick_ch(d->r, 12);
   const int BH = d->B * d->H;
   if (d->dtype == IG_F16) {
