@@ -79,12 +79,18 @@ __global__ __launch_bounds__(256) void gram_heads(const float *__restrict__ Qcal
 // are collected in a factor per column and multiplied in when it goes back to LDS).  Angles come from
 // float32 (a rotation by a slightly wrong angle is still a rotation; its cosine is worked out in double),
 // which leaves 1e-7 of a pair's inner product for the next sweep.
+// The sweeps end with one that met no pair further from orthogonal than a cosine of 1e-13, where rounding
+// leaves 1e-15.  Nothing coarser will do: columns whose norms differ by less than their cosine are still
+// turned by large angles, which carries what a later pair has left into a pair that was done already, and
+// nearly equal singular values make their columns of V as much worse as they are close.  (With an end at a
+// cosine of 1e-5, which is one sweep less, 128 singular values within 1e-3 of each other left A^T A 2.8e-7
+// from the identity and moved entries of V by 1e-3.)
 // Bound by the double-precision issue rate of the head's compute unit, one wave per SIMD: a round is
 // 3 multiply-adds and 2 moves for each of RP rows and a chain of about 40 dependent operations.
-// The pivoted factor matters: L's columns come out graded, which takes 8 sweeps where the columns of G
+// The pivoted factor matters: L's columns come out graded, which takes 9 sweeps where the columns of G
 // itself take more than 20, and a head without full rank is found by a pivot at rounding level: those
 // columns are left out of the rotations and V is completed to an orthonormal basis.
-// Measured on 32 heads of 128 columns: 0.79 ms (factor 0.12, eight sweeps 0.64, output 0.02), against
+// Measured on 32 heads of 128 columns: 0.87 ms (factor 0.12, nine sweeps 0.72, output 0.02), against
 // 34.8 ms for two-sided rotations of G and V through the L2 (jacobi_heads).
 __device__ __forceinline__ double join_d(unsigned lo, unsigned hi) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
@@ -114,12 +120,13 @@ template <int RP> __device__ __forceinline__ double column_dot(const double (&a)
   return sum_parts((s[0] + s[1]) + (s[2] + s[3]));
 }
 // Tangent, cosine and 1 / cosine of the rotation that makes columns with squared norms al, be and inner
-// product ga orthogonal (0, 1, 1 where they are to rounding); `big` is set when they were far from it.
+// product ga orthogonal (0, 1, 1 where they are to rounding); `big` is set when they were not nearly so.
 __device__ __forceinline__ void rotation(double al, double be, double ga, double &t, double &c, double &ic, bool &big) {
   const double g2 = ga * ga, ab = al * be;
-  big = big || g2 > 1e-10 * ab;
-  const float z = (float)(be - al) * __builtin_amdgcn_rcpf((float)(2.0 * ga));
-  float tf = __builtin_amdgcn_rcpf(fabsf(z) + __builtin_amdgcn_sqrtf(fmaf(z, z, 1.f)));
+  big = big || g2 > 1e-26 * ab;
+  const float z = (float)(be - al) * __builtin_amdgcn_rcpf((float)(2.0 * ga)), az = fabsf(z);
+  // (z^2 leaves float32's range where one column is far shorter than the other)
+  float tf = __builtin_amdgcn_rcpf(az + (az < 1e9f ? __builtin_amdgcn_sqrtf(fmaf(z, z, 1.f)) : az));
   tf = z < 0.f ? -tf : tf;
   const bool turn = (g2 > 1e-30 * ab) & (fabsf(tf) <= 1.f);      // (no branch)
   tf = turn ? tf : 0.f;

@@ -95,15 +95,20 @@ def test_error_paths(ctx):
     assert ctx.call("ig_skew_device", 64, 2, 8, None, p, None, 0) == ig.IG_EINVAL
 
 
+ROUNDED = 1.01 * 2.0 ** -23
+
+
 @pytest.mark.parametrize("d,n,kind", [(2, 8, "full"), (30, 64, "full"), (64, 64, "full"), (66, 70, "graded"), (96, 1, "full"),
                                       (126, 400, "graded"), (128, 127, "full"), (128, 129, "graded"), (128, 40, "repeated"),
                                       (64, 33, "zero"), (130, 200, "full")])
 def test_edges_of_the_kernels_against_64_bits(ctx, d, n, kind):
     """Heads around the tile and kernel edges (d = 64 / 66, 128 / 130), fewer rows than columns, repeated
     columns, an all-zero head, singular values over five decades: against numpy's SVD in 64 bits.
-    Tolerances: A and sigma are float32 (2^-24 relative each); an inner product of two of A's columns sums
-    d products of entries rounded by 2^-24, so d * 2^-23 bounds it; sigma comes from the Gram matrix in
-    64 bits, whose smallest eigenvalues carry d * 2^-52 of the largest: 2e-7 of sigma_0 covers both.
+    Tolerances: A and sigma are float32 (2^-24 relative each).  Rounding moves a column of A by at most
+    2^-24 of its length, so an inner product of two of them, and one through Q^T Q against sigma_0^2, by
+    at most 2^-23; ROUNDED is that and 1 % for the arithmetic before the rounding.  sigma comes from the
+    Gram matrix in 64 bits, whose smallest eigenvalues carry d * 2^-52 of the largest: 2e-7 of sigma_0
+    covers both.
     (d = 130 takes the two-sided kernel, whose fixed 16 sweeps do not reach five decades: it reports
     IG_ENOCONV there, so that case has singular values of one size.)"""
     rng = np.random.default_rng(d * 1000 + n)
@@ -124,9 +129,40 @@ def test_edges_of_the_kernels_against_64_bits(ctx, d, n, kind):
         ref = np.zeros(d)
         ref[: min(n, d)] = np.linalg.svd(Qh, compute_uv=False)
         top = max(ref[0], 1e-30)
-        assert np.abs(A[h].T @ A[h] - np.eye(d)).max() <= d * 2.0 ** -23
+        assert np.abs(A[h].T @ A[h] - np.eye(d)).max() <= ROUNDED
         assert np.abs(sigma[h] - ref).max() <= 2e-7 * top
         gram = (Qh @ A[h]).T @ (Qh @ A[h])
-        assert np.abs(gram - np.diag(np.diag(gram))).max() <= d * 2.0 ** -23 * top * top
+        assert np.abs(gram - np.diag(np.diag(gram))).max() <= ROUNDED * top * top
         big = np.abs(A[h]).max(0)
         assert np.all(A[h].max(0) >= big * (1 - 1e-6))                 # largest entry positive
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("spread", [1e-1, 1e-2, 1e-3, 1e-4, 0.0])
+def test_close_singular_values(ctx, d, spread):
+    """Singular values within `spread` of each other, as near-orthonormal queries and a flat noise floor have
+    them: the rotations of the last sweeps are large there however small the inner products are.  A must
+    be as orthogonal as elsewhere, and each column the right singular vector: a vector is settled to
+    the rounding of the matrix it comes from (d * 2^-52 of the largest eigenvalue, here and in numpy) over
+    the distance of its eigenvalue to the next, a factor 2 under the singular values' own."""
+    n, H = 4 * d, 2
+    rng = np.random.default_rng(int(1e4 * spread) + d)
+    heads = []
+    for _ in range(H):
+        U, W = np.linalg.qr(rng.standard_normal((n, d)))[0], np.linalg.qr(rng.standard_normal((d, d)))[0]
+        heads.append((U * (1.0 + spread * np.linspace(1.0, 0.0, d))) @ W.T)
+    Q32 = np.ascontiguousarray(np.concatenate(heads, 1), dtype=np.float32)
+    A, sigma, status = skew_on_gpu(ctx, Q32, H)
+    assert status == 0
+    for h in range(H):
+        Qh = Q32[:, h * d:(h + 1) * d].astype(np.float64)
+        _, s, Vt = np.linalg.svd(Qh, full_matrices=False)
+        print(f"case d{d} spread {spread} head {h}: A^T A - I {np.abs(A[h].T @ A[h] - np.eye(d)).max():.2e}", flush=True)
+        assert np.abs(A[h].T @ A[h] - np.eye(d)).max() <= ROUNDED
+        assert np.abs(sigma[h] - s).max() <= 2.0 ** -23 * s[0]
+        gram = (Qh @ A[h]).T @ (Qh @ A[h])
+        assert np.abs(gram - np.diag(np.diag(gram))).max() <= ROUNDED * s[0] ** 2
+        gap = np.minimum(np.abs(np.diff(s, prepend=np.inf)), np.abs(np.diff(s, append=-np.inf))) / s[0]
+        V = Vt.T * np.sign(Vt.T[np.abs(A[h]).argmax(0), np.arange(d)])
+        settled = 2.0 ** -24 + 2 * d * 2.0 ** -52 / (2 * gap)
+        assert np.all(np.abs(A[h] - V).max(0) <= settled), (np.abs(A[h] - V).max(0) / settled).max()
