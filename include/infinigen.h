@@ -52,7 +52,8 @@ enum {
   IG_EDTYPE = 3,    /* unknown dtype */
   IG_ECAPACITY = 4, /* a selected-token list did not fit in sel_stride (reported by ig_check_status) */
   IG_EHIP = 5,      /* a HIP runtime call failed; message holds hipGetErrorString */
-  IG_ENOCONV = 6,   /* Jacobi sweeps exceeded their cap in ig_skew_offline */
+  IG_ENOCONV = 6,   /* ig_skew_offline's sweeps exceeded their cap; ig_skew_device's result failed its check
+                       (reported by ig_check_status) */
   IG_ENOMEM = 7
 };
 
@@ -143,9 +144,12 @@ int ig_apply_skew(ig_ctx *ctx, int H, int d, int n, const float *X, const float 
 int ig_rope_rows(ig_ctx *ctx, int n, int H, int d, const int32_t *pos, double theta, float *q);
 
 /* Offline skewing on the GPU: the same A [H,d,d] and sigma [H,d] (may be NULL) as ig_skew_offline,
- * from device arrays (Qcal float32 [n_cal, D]); d even, at most 256.  All arithmetic in double;
- * a fixed number of parallel Jacobi sweeps; if they leave off-diagonal mass above tolerance the
- * next ig_check_status returns IG_ENOCONV.  Allocates a double-precision workspace on first use.
+ * from device arrays (Qcal float32 [n_cal, D]); d even, at most 256.  Sums and rotations in double.
+ * d <= 128: one-sided Jacobi sweeps on a Cholesky factor, as many as it takes to reach rounding level
+ * (at most 30); d > 128: a fixed number of two-sided sweeps.  The result is checked: when columns of
+ * A are not orthogonal to 1e-9 (d > 128: when off-diagonal mass above 1e-9 of the largest eigenvalue
+ * is left), or a head's queries hold a NaN or an infinity, the next ig_check_status returns
+ * IG_ENOCONV.  Allocates a double-precision workspace on first use.
  * The weights are skewed by the caller (W~ = W * blockdiag(A)), a plain batched product. */
 int ig_skew_device(ig_ctx *ctx, int D, int H, int n_cal, const float *Qcal, float *A, float *sigma,
                    void *stream);

@@ -267,7 +267,7 @@ int ig_check_status(ig_ctx *ctx) {
   if (st & IG_STATUS_CAPACITY)
     return ig_fail(ctx, IG_ECAPACITY, "a selected-token list was longer than sel_stride and was clamped");
   if (st & IG_STATUS_NOCONV)
-    return ig_fail(ctx, IG_ENOCONV, "ig_skew_device: the Jacobi sweeps left off-diagonal mass above tolerance");
+    return ig_fail(ctx, IG_ENOCONV, "ig_skew_device: the Jacobi sweeps left off-diagonal mass above tolerance, or the queries were not finite");
   return IG_OK;
 }
 

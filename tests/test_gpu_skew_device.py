@@ -166,3 +166,22 @@ def test_close_singular_values(ctx, d, spread):
         V = Vt.T * np.sign(Vt.T[np.abs(A[h]).argmax(0), np.arange(d)])
         settled = 2.0 ** -24 + 2 * d * 2.0 ** -52 / (2 * gap)
         assert np.all(np.abs(A[h] - V).max(0) <= settled), (np.abs(A[h] - V).max(0) / settled).max()
+
+
+@pytest.mark.parametrize("d", [64, 128, 130])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_queries_that_are_not_finite_are_reported(ctx, d, bad):
+    """As ig_skew_offline reports them; the other heads are not touched by it."""
+    import paper_2406_19707_amd as ig
+    rng = np.random.default_rng(d)
+    n, H = 200, 3
+    Q = rng.standard_normal((n, H * d)).astype(np.float32)
+    A0, sigma0, status = skew_on_gpu(ctx, Q, H)
+    assert status == ig.IG_OK
+    Q[7, d + 5] = bad
+    print(f"case d{d} {bad}", flush=True)
+    A, sigma, status = skew_on_gpu(ctx, Q, H)
+    assert status == ig.IG_ENOCONV and ctx.ig_check_status() == ig.IG_OK
+    assert np.array_equal(A[[0, 2]], A0[[0, 2]]) and np.array_equal(sigma[[0, 2]], sigma0[[0, 2]])
+    if d <= 128:
+        assert np.isnan(A[1]).all() and np.isnan(sigma[1]).all()
