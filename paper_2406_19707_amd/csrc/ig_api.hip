@@ -710,14 +710,15 @@ int ig_layer_step(ig_ctx *ctx, const ig_desc *d, const void *x, const void *wq, 
   hipStream_t s = (hipStream_t)stream;
   if ((rc = project_partials(ctx, d, x, wq, A_p, pos, &g, s))) return rc;
   QSource qs{ctx->part, g.KS, (long)g.Bpad * g.Cpad, (long)g.Cpad, bias};
-  if (d->rope && ig_scan_takes_rope(d)) {
+  const bool joint = ig_layer_step_is_joint(d);
+  if (d->rope && !joint && ig_scan_takes_rope(d)) {      // (the joint launch's scan takes finished queries only)
     qs.A_p = A_p;
     qs.pos = pos;
   } else if (d->rope) {
     if ((rc = ig_launch_finalize(ctx, d, g, ctx->part, bias, A_p, pos, ctx->qp, s))) return rc;
     qs = QSource{ctx->qp, 1, 0, (long)d->H * d->r, nullptr};
   }
-  if (!ig_layer_step_is_joint(d)) {
+  if (!joint) {
     // other shapes: the two launches one after the other
     if ((rc = ig_launch_scan_select(ctx, d, qs, slab, sel_idx_next, sel_stride, sel_cnt_next, nullptr, s))) return rc;
     return ig_launch_attention(ctx, d, q, Kpool, Vpool, sel_idx, sel_stride, sel_cnt, d->N_cap, k_new,

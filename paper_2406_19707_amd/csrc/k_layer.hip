@@ -50,6 +50,7 @@ int ig_launch_scan_attend(ig_ctx *ctx, const ig_desc *d, const QSource &qs, cons
                           const void *Kpool, const void *Vpool, const int32_t *sel_idx,
                           const int32_t *sel_cnt, int32_t sel_stride, const void *k_new,
                           const void *v_new, void *out, void *K_sel, void *V_sel, hipStream_t s) {
+  if (qs.A_p) return ig_fail(ctx, IG_EINVAL, "layer step: the joint launch takes no rotary query source");
   ScanArgs sa;
   int rc = ig_scan_args(ctx, d, qs, slab, sel_idx_next, sel_stride, sel_cnt_next, nullptr, &sa);
   if (rc) return rc;

@@ -75,6 +75,13 @@ def test_rotary_joint_launch(ctx):
     check_layer_step(ctx, w, gain=24.0, with_new_row=True)
 
 
+@pytest.mark.parametrize("cfg,N,new_row", [(3, 2000, True), (5, 700, False)])
+def test_rotary_joint_launch_of_many_pairs(ctx, cfg, N, new_row):
+    # 8 x 16 = 128 pairs with r = 38 and 25: ig_speculate's scan would finish the rotary query itself here
+    w = wl.shrink(wl.WORKLOADS[cfg], B=8, H=16, N=N, heavy_count=20)
+    check_layer_step(ctx, w, gain=24.0, with_new_row=new_row)
+
+
 def test_f32_joint_launch(ctx):
     w = wl.shrink(wl.WORKLOADS[1], B=2, H=4, N=900, heavy_count=10)      # 4 tiles of 256 floats
     check_layer_step(ctx, w, gain=8.0)
