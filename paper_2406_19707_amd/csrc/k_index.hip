@@ -78,7 +78,9 @@ __global__ __launch_bounds__(1024) void top_columns(const float *__restrict__ pa
     float acc = 0.f;
 #pragma unroll
     for (int k = 0; k < ROW_CHUNKS; ++k) acc += v[k];
-    sum[c] = c < d ? acc : -1.f;             // sums are >= 0: columns past d never win
+    // sums are >= 0: columns past d never win; one that is NaN ranks as infinite (compared as it is it would
+    // be beaten by none and beat none, and more than r columns would be kept)
+    sum[c] = c < d ? (acc >= 0.f ? acc : INFINITY) : -1.f;
   }
   __syncthreads();
   // columns that beat column c: a larger sum, or an equal one further left

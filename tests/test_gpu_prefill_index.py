@@ -103,3 +103,27 @@ def test_arrays_of_any_alignment_give_the_same_columns(ctx, dtype, H, d, n):
         c = sums[h * d:(h + 1) * d]
         cut = np.sort(c)[::-1][got[0].shape[1] - 1]
         assert np.all(c[got[0][h]] >= cut * (1 - 1e-5))
+
+
+@pytest.mark.parametrize("H,d", [(3, 64), (2, 128), (2, 250)])
+def test_rows_with_nan_or_infinity_keep_r_columns(ctx, H, d):
+    """Columns whose sum is NaN or infinite are kept first, the earlier ones before the later, and never more
+    than r: nothing is written past a head's entries."""
+    import paper_2406_19707_amd as ig
+    n, r = 40, d // 4
+    rng = np.random.default_rng(d)
+    Q = rng.standard_normal((n, H, d)).astype(np.float32)
+    Q[3, 0, [1, d // 2, d - 1]] = np.nan              # fewer than r
+    Q[5, 0, 7] = np.inf
+    Q[0, H - 1, d // 8:] = np.nan                     # more than r
+    buf = torch.full((H * r + 256,), -7, dtype=torch.int32, device="cuda")
+    print(f"case H{H} d{d} r{r}", flush=True)
+    ctx.ig_partial_index_device(ig.IG_F32, H, d, n, torch.from_numpy(Q.reshape(n, H * d)).cuda(), None, 0.25, buf)
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy()
+    assert np.all(got[H * r:] == -7)
+    sums = np.abs(Q.astype(np.float64)).sum(0)
+    sums[~np.isfinite(sums)] = np.inf
+    for h in range(H):
+        want = np.sort(np.argsort(-sums[h], kind="stable")[:r])
+        assert np.array_equal(got[h * r:(h + 1) * r], want), h
