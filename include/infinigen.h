@@ -21,7 +21,11 @@
  *  - Device calls enqueue work on the hipStream_t passed as `stream` (a void*; NULL = the null
  *    stream) and return without synchronising.  They never read device results on the host.
  *    Workspaces grow on the first call with a larger shape (this allocates); ig_reserve() sizes
- *    them ahead of time, after which the hot-path calls allocate nothing.
+ *    them ahead of time, after which the hot-path calls allocate nothing.  While `stream` is being
+ *    captured into a graph nothing is allocated either: a call that lacks a workspace returns
+ *    IG_EINVAL, except that a scan whose pairs would be split (see ig_set_wait_limit) takes a form that
+ *    needs none where there is one.  A graph keeps the addresses of the workspaces it was captured
+ *    with, so the largest shape is to be reserved before the capture.
  *  - Calls on one context must not overlap in time on different streams: they share workspaces.
  *  - dtype IG_F16: x, weights, K, V, q, out are IEEE half; IG_F32: float.  Partial queries,
  *    scores and all accumulation are float32 in both cases.  Index arrays are int32.

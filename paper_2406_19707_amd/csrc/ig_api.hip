@@ -23,17 +23,19 @@ int ig_hip_fail(ig_ctx *ctx, hipError_t e, const char *what) {
   return ig_fail(ctx, IG_EHIP, "%s: %s", what, hipGetErrorString(e));
 }
 
+bool ig_capturing(const ig_ctx *ctx) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return ctx->call_stream && hipStreamIsCapturing(ctx->call_stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
 int ig_ensure(ig_ctx *ctx, void **p, size_t *have, size_t need) {
   if (*have >= need && *p) return IG_OK;
   // Growing means hipMalloc, and for a buffer in use also a device-wide wait and a hipFree: none of
   // them may happen while the call's stream is being captured into a graph (the runtime would
   // invalidate the capture, and a replay would use the freed buffer).  Refuse instead.
-  if (ctx->call_stream) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(ctx->call_stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone)
-      return ig_fail(ctx, IG_EINVAL, "a workspace of %zu bytes would have to be allocated while the stream is being "
-                     "captured: call ig_reserve for the largest shape before the capture", need);
-  }
+  if (ig_capturing(ctx))
+    return ig_fail(ctx, IG_EINVAL, "a workspace of %zu bytes would have to be allocated while the stream is being "
+                   "captured: call ig_reserve for the largest shape before the capture", need);
   if (*p) {
     IG_HIP(ctx, hipDeviceSynchronize());   // earlier launches may still read the old buffer
     IG_HIP(ctx, hipFree(*p));

@@ -121,6 +121,8 @@ struct ig_ctx {
 
 int ig_fail(ig_ctx *ctx, int code, const char *fmt, ...);
 int ig_hip_fail(ig_ctx *ctx, hipError_t e, const char *what);
+// whether the stream of the entry point being served is being captured into a graph
+bool ig_capturing(const ig_ctx *ctx);
 int ig_ensure(ig_ctx *ctx, void **p, size_t *have, size_t need);
 int ig_ensure_zeroed(ig_ctx *ctx, void **p, size_t *have, size_t need);
 void ig_prof_events(ig_ctx *ctx, int which, hipEvent_t *e0, hipEvent_t *e1);

@@ -1230,7 +1230,13 @@ int launch_scan(ig_ctx *ctx, const ig_desc *d, ScanArgs &a, const QSource *rope,
   // One workgroup per (b,h) when it fits and there are enough (b,h) pairs to fill the chip;
   // otherwise one wave per tile so that long sequences spread over all compute units.
   int tpw = 0, S = 0;
-  if (ig_scan_stream_form(d, &tpw, &S)) {
+  bool stream = ig_scan_stream_form(d, &tpw, &S);
+  // A split needs the pairs' records.  Where they would have to be allocated under a capture, which is
+  // refused, the forms below serve the call with the same lists: one workgroup per pair without any
+  // workspace (64 pairs and more, up to 32768 tokens), or the three kernels if theirs are there.
+  if (stream && S > 1 && !rope && !eq && ctx->pair_sync_bytes < (size_t)BH * IG_PAIR_SYNC_BYTES && ig_capturing(ctx))
+    stream = false;
+  if (stream) {
     if (!rope) return launch_stream<T>(ctx, a, nullptr, eq, BH, tpw, S, s);
     RopeArgs ra{rope->A_p, rope->pos, d->d, -2.0 / (double)d->d * log2((double)d->rope_theta)};
     return launch_stream<T>(ctx, a, &ra, eq, BH, tpw, S, s);

@@ -109,3 +109,47 @@ def test_workspace_growth_under_capture_is_refused():
         assert torch.equal(sel_cnt, ref_cnt)
     ctx.close()
     build_ctx.close()
+
+
+@pytest.mark.parametrize("B,H,N", [(4, 16, 9000), (3, 40, 16384)])
+def test_scans_that_need_no_workspace_are_captured_without_ig_reserve(B, H, N):
+    """ig_scan_select, and ig_speculate_indexed where ig_project_indexed has run, on 64 to 255 pairs of more
+    than 16 tiles with r = 19: such pairs are split over workgroups that meet in a workspace, but a context
+    that has none yet can still capture the call, and the replays give the eager lists bit for bit."""
+    import paper_2406_19707_amd as ig
+    from ig_case import make_case
+    from ig_gpu import Uploaded
+    w = wl.shrink(wl.WORKLOADS[2], B=B, H=H, d=64, N=N, n_cal=128, heavy_count=24)
+    c = make_case(w, gain=8.0)
+    assert c.r == 19
+    eager = ig.Context(0)
+    up = Uploaded(eager, c)
+    d, BH = up.desc, B * H
+    print(f"case B{B} H{H} N{N} r{c.r}", flush=True)
+    q_p = torch.empty((B, H, c.r), device="cuda")
+    lists = lambda: (torch.zeros((BH, N), dtype=torch.int32, device="cuda"), torch.zeros(BH, dtype=torch.int32, device="cuda"))   # noqa: E731
+    (ref_idx, ref_cnt), (refi_idx, refi_cnt), (idx, cnt), (idx2, cnt2) = (lists() for _ in range(4))
+    eager.ig_project_indexed(d, up.x, up.W, up.idx, up.bias, q_p)
+    eager.ig_scan_select(d, q_p, up.slab, ref_idx, N, ref_cnt, None)
+    eager.ig_speculate_indexed(d, up.x, up.W, up.idx, up.bias, up.slab, refi_idx, N, refi_cnt, None)
+    fresh, projected = ig.Context(0), ig.Context(0)
+    projected.ig_project_indexed(d, up.x, up.W, up.idx, up.bias, q_p)
+    torch.cuda.synchronize()
+    held = fresh.ig_workspace_bytes(), projected.ig_workspace_bytes()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        fresh.ig_scan_select(d, q_p, up.slab, idx, N, cnt, None)
+        projected.ig_speculate_indexed(d, up.x, up.W, up.idx, up.bias, up.slab, idx2, N, cnt2, None)
+    assert held == (fresh.ig_workspace_bytes(), projected.ig_workspace_bytes())
+    for rep in range(3):
+        for t in (idx, cnt, idx2, cnt2):
+            t.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(cnt, ref_cnt) and torch.equal(cnt2, refi_cnt), rep
+        for i in range(BH):
+            assert torch.equal(idx[i, :cnt[i]], ref_idx[i, :cnt[i]]) and torch.equal(idx2[i, :cnt[i]], refi_idx[i, :cnt[i]]), (rep, i)
+    for k in (fresh, projected, eager):
+        assert k.ig_check_status() == ig.IG_OK
+        k.close()
