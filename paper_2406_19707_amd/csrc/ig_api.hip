@@ -748,9 +748,11 @@ int ig_decode_step_overlapped(ig_ctx *ctx, const ig_desc *d, int n_layers, const
   }
   while ((int)ctx->pipe_events.size() < 2 * n_layers) {
     hipEvent_t e;
-    // (both streams are this device's: nothing here has to be made visible to the host or another device, and
-    // without the system-scope fences of a record and a wait 3 layers of 64 heads take 189 us instead of 200)
-    IG_HIP(ctx, hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventDisableSystemFence));
+    // (With hipEventDisableSystemFence, 3 layers of 64 heads and 2048 tokens take 187 us instead of 199 issued
+    // back to back, but that flag is documented for events that only time things: what a wait on such an
+    // event makes visible, of a non-coherent host pool above all, is not stated.  With
+    // hipEventReleaseToDevice they take 200.)
+    IG_HIP(ctx, hipEventCreateWithFlags(&e, hipEventDisableTiming));
     ctx->pipe_events.push_back(e);
   }
   hipStream_t ms = (hipStream_t)main_stream, ss = (hipStream_t)side_stream;

@@ -229,6 +229,72 @@ def test_native_overlapped_step_matches_the_serial_layers(cfg, B, H, N, L, sets,
     ctx.close()
 
 
+COHERENT, NON_COHERENT = 0x40000000, 0x80000000        # hipHostMalloc flags
+
+
+@pytest.mark.parametrize("flags", [0, COHERENT, NON_COHERENT])
+def test_native_overlapped_step_reads_the_pool_as_last_written(flags):
+    """The prefetch on the side stream reads pinned memory that the CPU has rewritten since the last step and
+    that kernels on the main stream (ig_pool_replace) have written just before, whichever way the memory
+    was allocated: every layer's output against the serial calls on a device copy of the pool."""
+    import ctypes
+    import paper_2406_19707_amd as ig
+    from paper_2406_19707_amd.binding import lib
+    from ig_case import make_case
+    from ig_gpu import Uploaded
+    w = wl.shrink(wl.WORKLOADS[4], B=2, H=8, N=1500, n_cal=256, heavy_count=16)
+    L, BH = 3, w.B * w.H
+    ctx = ig.Context(0)
+    ups = [Uploaded(ctx, make_case(w, gain=12.0, layer=l)) for l in range(L)]
+    d = ups[0].desc
+    bytes_ = ups[0].K.numel() * 2
+    mem, pools = [], []
+    for _ in range(2 * L):
+        p = ctypes.c_void_p()
+        assert lib().hipHostMalloc(ctypes.byref(p), ctypes.c_size_t(bytes_), ctypes.c_uint(flags)) == 0
+        mem.append(p)
+        pools.append(torch.frombuffer((ctypes.c_char * bytes_).from_address(p.value), dtype=torch.float16).view(ups[0].K.shape))
+    Kp, Vp = pools[:L], pools[L:]
+    new = lambda *shape, dt: torch.zeros(shape, dtype=dt, device="cuda")                      # noqa: E731
+    sets = [dict(sel_idx=new(BH, w.N, dt=torch.int32), sel_cnt=new(BH, dt=torch.int32),
+                 K_sel=new(BH, w.N, w.d, dt=torch.float16), V_sel=new(BH, w.N, w.d, dt=torch.float16)) for _ in range(2)]
+    outs = [new(w.B, w.H, w.d, dt=torch.float16) for _ in range(L)]
+    bufs = (ig.IgBufferSet * 2)(*[ig.IgBufferSet(**{k: t.data_ptr() for k, t in st.items()}) for st in sets])
+    layers = (ig.IgLayerIO * L)(*[ig.IgLayerIO(x=u.x.data_ptr(), slab=u.slab.data_ptr(), q=u.q.data_ptr(), Kpool=k.data_ptr(),
+                                               Vpool=v.data_ptr(), k_new=None, v_new=None, out=o.data_ptr())
+                                  for u, k, v, o in zip(ups, Kp, Vp, outs)])
+    main, side = torch.cuda.Stream(), torch.cuda.Stream()
+    idx, cnt = new(BH, w.N, dt=torch.int32), new(BH, dt=torch.int32)
+    Ks, Vs, ref = new(BH, w.N, w.d, dt=torch.float16), new(BH, w.N, w.d, dt=torch.float16), new(w.B, w.H, w.d, dt=torch.float16)
+    g = torch.Generator().manual_seed(3)
+    rnd = lambda *shape: torch.randn(shape, generator=g).half()                               # noqa: E731
+    victims = [new(BH, dt=torch.int32) for _ in range(L)]
+    print(f"case flags {flags:#x} L{L} B{w.B} H{w.H} N{w.N}", flush=True)
+    for rep in range(6):
+        rows = [(rnd(w.B, w.H, w.d).cuda(), rnd(w.B, w.H, w.d).cuda()) for _ in range(L)]
+        torch.cuda.synchronize()
+        for l in range(L):                                   # the CPU's writes
+            if rep == 0:
+                Kp[l].copy_(ups[l].K.cpu())
+            Vp[l].copy_(rnd(*Vp[l].shape))
+        for l in range(L):                                   # the GPU's, into slots the last step selected
+            ctx.ig_pool_replace(d, victims[l], rows[l][0], rows[l][1], ups[l].idx, ups[l].slab, Kp[l], Vp[l],
+                                ig.IG_MEM_HOST_PINNED, None, main)
+        ctx.ig_decode_step_overlapped(d, layers, ups[0].wq, ups[0].bias, None, None, ig.IG_MEM_HOST_PINNED, bufs, w.N, main, side)
+        torch.cuda.synchronize()
+        assert ctx.ig_check_status() == ig.IG_OK
+        for l in range(L):
+            Kd, Vd = Kp[l].cuda(), Vp[l].cuda()
+            ctx.ig_speculate(d, ups[l].x, ups[0].wq, ups[0].bias, None, None, ups[l].slab, idx, w.N, cnt, None)
+            ctx.ig_gather_kv(d, Kd, Vd, ig.IG_MEM_DEVICE, idx, w.N, cnt, Ks, Vs)
+            ctx.ig_sparse_attention(d, ups[l].q, Ks, Vs, cnt, w.N, None, None, ref)
+            victims[l].copy_(idx[:, 0])
+            assert torch.equal(outs[l], ref), (rep, l)
+    ctx.close()
+    for p in mem:
+        assert lib().hipHostFree(p) == 0
+
+
 def test_native_overlapped_step_error_paths():
     import ctypes
     import paper_2406_19707_amd as ig
