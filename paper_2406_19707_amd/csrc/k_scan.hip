@@ -1277,11 +1277,34 @@ int launch_scan(ig_ctx *ctx, const ig_desc *d, ScanArgs &a, const QSource *rope,
 // few) where it measured faster than the forms below: for the kept-channel counts of the workloads in half
 // precision (r = 38 and 25, the whole stream unrolled) sequences of up to 8 tiles with enough pairs to fill
 // the chip and everything that is split; for any other r up to 64 and for float32 (the channel loop at run
-// time) what is split, with the exceptions below.  Splits take 4 or 8 tiles per workgroup, 16 when 8 would
+// time) what is split, where that pays.  Splits take 4 or 8 tiles per workgroup, 16 when 8 would
 // need more than IG_SPLIT_MAX workgroups per pair (not for r = 38, whose unrolled stream of 4 tiles a wave
 // leaves the registers).
 // (half precision with the kept-channel counts that are template parameters)
 static bool built_in(const ig_desc *d) { return d->dtype == IG_F16 && (d->r == 38 || d->r == 25); }
+
+// Whether splitting pairs of more than 16 tiles is ahead for a channel count known only at run time, whose
+// loop costs more than the unrolled stream's.  (Ratios: split / form it replaces, r = 3..64, both types.)
+static bool run_time_split_pays(const ig_desc *d, int nValid, int BH, int t, int splits) {
+  // too few workgroups with too long a stream each: the three kernels' one wave per tile fills the chip (2 and
+  // 4 pairs, 131072 half tokens, r = 12: 1.16, 1.11, r = 64: 1.80, 1.33; 8 pairs 0.85..1.03; one tile a wave:
+  // 4 pairs of 94..102 tiles, r = 64, 1.09..1.20)
+  if (BH * splits < 112 && (t == 1 ? splits > 20 && d->r > 40 : t > 2 || d->r > 20)) return false;
+  // beyond 32768 tokens the other form is the three kernels: 0.5..1.0
+  if (nValid * ig_tile_tokens(d->dtype) > 32768) return true;
+  // The other form is one workgroup per pair, its scores parked in LDS, one to a compute unit.  It leaves the
+  // chip idle with few pairs (64 pairs 0.55..0.95, 72 up to 1.08; 104 pairs of 48 tiles and more 0.70..1.03)
+  // and takes a second round for the 257th (320 pairs, r <= 16: 0.63..0.98).
+  // Just over 16 tiles its 16 waves go round twice for the one (18 tiles, r = 16 and 19, 80 and 96 pairs
+  // 0.80..0.87).
+  if (BH <= 72 || (BH <= 104 && nValid >= 48) || (BH > 256 && d->r <= 16)) return true;
+  if (BH <= 96 && nValid <= 20 && d->r <= 24) return true;
+  // In between it fills the chip, and what counts is the work a workgroup has besides its loads: little for few
+  // channels (r = 6, half precision, 128 pairs 0.68, 256 pairs 0.90; float32, 128 pairs 0.92, 160 pairs 1.00;
+  // r = 12, 96 pairs 0.91, 160 pairs 1.07; r = 19, 160 pairs 1.06, 192 pairs 1.09).
+  if (d->r <= 9) return d->dtype == IG_F16 || BH <= 128;
+  return d->r <= 12 ? BH <= 96 : (d->r <= 16 && BH <= 80);
+}
 
 bool ig_scan_stream_form(const ig_desc *d, int *tpw, int *S) {
   if (d->r > 64) return false;
@@ -1309,16 +1332,24 @@ bool ig_scan_stream_form(const ig_desc *d, int *tpw, int *S) {
   // with 128 pairs and more the block-loading form, one workgroup per pair, is as fast or faster
   // (9 tiles: 13.9 against 14.0 us on 128 pairs, 19.0 against 21.8 us on 256).
   if (nValid <= 16 && BH >= 128) return false;
-  // Beyond 16 tiles, channel counts known only at run time: ahead of the LDS-parked form up to 256 pairs
-  // (16384 tokens, r = 19: 14.9 -> 9.0 us on 32 pairs, 21.0 -> 19.3 us on 128, but 29.9 -> 31.7 us on 256)
-  // and for few channels (r = 12: 25.0 -> 22.6 us on 256 pairs, 49.0 -> 44.0 us on 512).
-  if (!built && nValid > 16 && BH >= 256 && d->r > 16 && nValid * tile <= 32768) return false;
   int t = BH * ((nValid + 7) / 8) >= 512 ? 2 : 1;
-  if ((nValid + 4 * t - 1) / (4 * t) > IG_SPLIT_MAX) t = 2;
+  if (!built && d->dtype == IG_F32) {
+    // (float32 tiles have half the tokens: a workgroup's own cost weighs more, so it is given more of them
+    // sooner: 32 pairs of 94..102 tiles, r = 12, 22 % slower than the three kernels with one tile a wave and
+    // 15..20 % faster with two; 256..384 pairs, r = 3, 20 % faster than the LDS-parked form with four a wave
+    // where two were 5..30 % slower)
+    t = BH * ((nValid + 3) / 4) > 512 ? 2 : 1;
+    if (d->r <= 9 && BH * ((nValid + 7) / 8) > 768) t = 4;
+  }
+  // (many partners for little work each: 16 pairs of 94..102 tiles 1.0 to 1.1 times the three kernels' time)
+  if (!built && t == 1 && (nValid + 3) / 4 > 20 && BH * ((nValid + 3) / 4) > 320) t = 2;
+  if ((nValid + 4 * t - 1) / (4 * t) > IG_SPLIT_MAX && t < 2) t = 2;
   if ((nValid + 4 * t - 1) / (4 * t) > IG_SPLIT_MAX) t = 4;
-  if ((nValid + 4 * t - 1) / (4 * t) > IG_SPLIT_MAX || (t == 4 && built && d->r > 32)) return false;
+  const int splits = (nValid + 4 * t - 1) / (4 * t);
+  if (splits > IG_SPLIT_MAX || (t == 4 && built && d->r > 32)) return false;
+  if (!built && nValid > 16 && !run_time_split_pays(d, nValid, BH, t, splits)) return false;
   *tpw = t;
-  *S = (nValid + 4 * t - 1) / (4 * t);
+  *S = splits;
   return true;
 }
 

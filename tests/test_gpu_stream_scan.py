@@ -119,6 +119,8 @@ RUN_TIME = [
     (2, "f32", 1, 4, 64, 1300, 1300, 0.3, 8.0, False),      # float32: 6 tiles of 256
     (2, "f32", 2, 3, 16, 20000, 20000, 0.5, 4.0, True),     # float32, r 8, 79 tiles: 20 workgroups a pair
     (2, "f16", 2, 8, 64, 16900, 17000, 0.2, 8.0, False),    # r 12, 34 tiles
+    (2, "f32", 10, 30, 16, 4200, 4200, 0.5, 4.0, False),    # float32, r 8, 300 pairs of 17 tiles: 4 tiles a wave, 2 workgroups a pair
+    (2, "f16", 8, 16, 64, 9000, 9000, 0.3, 8.0, True),      # r 19, 128 pairs of 18 tiles: one workgroup a pair
     (3, "f16", 1, 4, 64, 5000, 5000, 0.3, 20.0, False),     # rotary, r 19, 10 tiles
     (3, "f16", 1, 4, 128, 5000, 5000, 0.3, 20.0, False),    # rotary, r 38, split: the scan finishes the query
     (3, "f16", 2, 3, 64, 2700, 2700, 0.6, 20.0, True),      # the same, heads of 64 columns; bias
