@@ -169,13 +169,13 @@ constexpr int GATHER_BATCH = 8;
 __global__ __launch_bounds__(256) void gather_rows_sliced(
     const u128 *__restrict__ Kpool, const u128 *__restrict__ Vpool, const int32_t *__restrict__ sel_idx,
     const int32_t *__restrict__ sel_cnt, u128 *__restrict__ K_sel, u128 *__restrict__ V_sel, int N_cap,
-    int stride, FastDiv by_U, int H, int BH, FastDiv by_H, FastDiv by_BH) {
+    int stride, int slice_log2, FastDiv by_U, int H, int BH, FastDiv by_H, FastDiv by_BH) {
   const int U = by_U.d;
   int bh, slice;
   work_item(blockIdx.x, H, BH, by_H, by_BH, &bh, &slice);
   const int cnt = min(sel_cnt[bh], stride);
   int row0, row1, slices;
-  if (!slice_range(cnt, slice, SLICE_LOG2, &row0, &row1, &slices) || row1 <= row0) return;
+  if (!slice_range(cnt, slice, slice_log2, &row0, &row1, &slices) || row1 <= row0) return;
   const int32_t *list = sel_idx + (long)bh * stride + row0;
   const long src0 = (long)bh * N_cap * U, dst0 = ((long)bh * stride + row0) * U;
   const int total = (row1 - row0) * U;
@@ -403,10 +403,13 @@ int ig_launch_gather(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const voi
   const int U = d->d * ig_elem_bytes(d->dtype) / 16;
   const int BH = d->B * d->H;
   if (!host_pool) {
-    dim3 grid(BH * slices_at_most(sel_stride, SLICE_LOG2)), block(256);
+    // rows of a slice: 1 << SLICE_LOG2, but no more than two batches of a workgroup's copies (see att_slice_log2)
+    int slice_log2 = SLICE_LOG2;
+    while (slice_log2 > 4 && ((long)U << slice_log2) > 2 * 256 * GATHER_BATCH) --slice_log2;
+    dim3 grid(BH * slices_at_most(sel_stride, slice_log2)), block(256);
     auto k = gather_rows_sliced;
     IG_LAUNCH(ctx, IG_K_GATHER, k, grid, block, s, (const u128 *)Kpool, (const u128 *)Vpool, sel_idx,
-              sel_cnt, (u128 *)K_sel, (u128 *)V_sel, (int)d->N_cap, (int)sel_stride, ig_fast_div(U),
+              sel_cnt, (u128 *)K_sel, (u128 *)V_sel, (int)d->N_cap, (int)sel_stride, slice_log2, ig_fast_div(U),
               (int)d->H, BH, ig_fast_div(d->H), ig_fast_div(BH));
     return IG_OK;
   }
@@ -454,7 +457,7 @@ int ig_attn_fill(ig_ctx *ctx, const ig_desc *d, const void *q, const void *K, co
   A->stride = sel_stride;
   A->kv_rows = kv_rows;
   A->lpr_log2 = __builtin_ctz(LPR);
-  A->slice_log2 = att_slice_log2(A->lpr_log2);
+  A->slice_log2 = att_slice_log2(A->lpr_log2, d->B * d->H);
   A->k_new = k_new;
   A->v_new = v_new;
   A->out = out;

@@ -1,5 +1,5 @@
 """Lists at the edges of the row slices that fetch and attention are cut into (a batch of a workgroup's
-loads, at least 128 rows; 16 slices at most), for every row length the attention has a form for, against
+loads, or 128 rows, but no more than two batches; 16 slices at most), for every row length the attention has a form for, against
 float64.
 
 Bound of an attention output: a logit is a d-term float32 sum, scaled, and goes through exp, so it is off by
@@ -11,7 +11,7 @@ import torch
 
 pytestmark = pytest.mark.gpu
 
-ROWS = [0, 1, 2, 31, 127, 128, 129, 255, 256, 257, 511, 513, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 4500]
+ROWS = [0, 1, 2, 31, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 513, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 4300, 4500]
 
 
 @pytest.fixture(scope="module")
@@ -24,17 +24,26 @@ def ctx():
 
 
 @pytest.mark.parametrize("dtype,d", [("f16", 8), ("f16", 32), ("f16", 64), ("f16", 128), ("f16", 256), ("f16", 512),
-                                     ("f32", 4), ("f32", 32), ("f32", 64), ("f32", 128), ("f32", 256), ("f16", 96)])
+                                     ("f32", 4), ("f32", 32), ("f32", 64), ("f32", 128), ("f32", 256), ("f16", 96), ("f32", 512)])
 @pytest.mark.parametrize("stride,new_row", [(4500, True), (4500, False), (200, True)])
 def test_lists_at_slice_edges(ctx, dtype, d, stride, new_row):
+    check(ctx, dtype, d, stride, new_row, ROWS, 4500)
+
+
+def test_many_lists_of_long_rows(ctx):
+    # 1024-byte rows: 64 of them a slice up to 255 lists, 128 from there
+    check(ctx, "f32", 256, 300, True, [0, 1, 63, 64, 65, 127, 128, 129, 255, 256, 257, 300] * 22, 300)
+
+
+def check(ctx, dtype, d, stride, new_row, lengths, N):
     import paper_2406_19707_amd as ig
     print(f"case {dtype} d{d} stride {stride} new {new_row}", flush=True)
     rng = np.random.default_rng(d + stride)
     npdt, half = (np.float16, True) if dtype == "f16" else (np.float32, False)
-    B, H, N = 2, len(ROWS) // 2, 4500
+    B, H = 2, len(lengths) // 2
     q, kn, vn = (rng.standard_normal((B, H, d)).astype(npdt) for _ in range(3))
     K, V = (rng.standard_normal((B * H, N, d)).astype(npdt) for _ in range(2))
-    cnt = np.minimum(np.array(ROWS, np.int32)[rng.permutation(len(ROWS))], stride).astype(np.int32)
+    cnt = np.minimum(np.array(lengths, np.int32)[rng.permutation(len(lengths))], stride).astype(np.int32)
     idx = np.zeros((B * H, stride), np.int32)
     for i, n in enumerate(cnt):
         idx[i, :n] = np.sort(rng.choice(N, n, replace=False))
@@ -47,7 +56,7 @@ def test_lists_at_slice_edges(ctx, dtype, d, stride, new_row):
     fill = lambda: torch.full((B * H, stride, d), 7.0, dtype=tdt, device="cuda")  # noqa: E731
     Ks, Vs, Kf, Vf = fill(), fill(), fill(), fill()
     ctx.ig_gather_kv(desc, Kd, Vd, ig.IG_MEM_DEVICE, idxd, stride, cntd, Ks, Vs)
-    attend = d != 96                               # (rows of 16 * 2^k bytes only)
+    attend = d != 96 and (dtype, d) != ("f32", 512)   # (rows of 16 * 2^k bytes, at most 1024)
     outs = [torch.zeros((B, H, d), dtype=tdt, device="cuda") for _ in range(3)]
     if attend:
         ctx.ig_sparse_attention(desc, qd, Ks, Vs, cntd, stride, *new, outs[0])
