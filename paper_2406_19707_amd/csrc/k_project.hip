@@ -457,14 +457,40 @@ __global__ __launch_bounds__(256) void project_columns_mfma(const half_t *__rest
 //         pos[b]*theta^(-2c/d) (angle in double: positions reach 1e5 where float loses the phase);
 //         q_p[b,h,k] = sum_c q_rot[c] * A_p[h][c][k]
 // (Section 4.3 "Decoding Stage" for models whose skew cannot be folded into W_Q.)
-// A chain of dependent steps: 5.6 us for 160 heads of 128 columns while the compiler put conditions around
-// its loads (one round trip after another), 4.8 us with every load of a thread in flight at once.
+// finalize_folded takes a sequence's H*r columns in a row (5760 heads of 12 columns: one workgroup a head 6.5 us, so
+// 4.2).  finalize_query is a chain of dependent steps: 5.6 us for 160 heads of 128 columns while the compiler
+// put conditions around its loads (one round trip after another), 4.3 us with every load of a thread in flight.
+// KSM, PF: partial sums of a column and rows of A_p that a thread has in flight.  Loads past what there is, clamped
+// to the last, cost nothing while latency sets the time and something where the chip is full, so a launch
+// takes the smallest that fit: KS sums of 2, 4, 8, 12 or IG_KS_MAX, a share of the rows (d r / 256) of 8, 16 or 24.
+// (32 heads of 64 columns, 96 sequences, r = 6: 15.1 -> 8.2 us; 16 heads of 128, 80 sequences, r = 128: 13.8 ->
+// 9.0 us with the waves that have no pair to rotate out of the double arithmetic and 8 of the further rows at a time.)
+template <int KSM>
+__global__ __launch_bounds__(64) void finalize_folded(const float *__restrict__ part,
+                                                       const float *__restrict__ bias,
+                                                       float *__restrict__ q_p, int C, int KS,
+                                                       long ks_stride, int Cpad, FastDiv by_blocks) {
+  // (one wave a workgroup, so that few rows reach every compute unit: rows of 1024 columns, 80 of them, with four
+  // waves 2 us more)
+  const int b = by_blocks.div(blockIdx.x), c = by_blocks.mod(blockIdx.x) * 64 + threadIdx.x;
+  if (c >= C) return;
+  // split-K partial sums: all loads of a column issued together, added in a fixed order
+  const float *p = part + (long)b * Cpad + c;
+  float v[KSM];
+#pragma unroll
+  for (int s = 0; s < KSM; ++s) v[s] = p[(long)min(s, KS - 1) * ks_stride];
+  float acc = bias ? bias[c] : 0.f;
+#pragma unroll
+  for (int s = 0; s < KSM; ++s) acc += s < KS ? v[s] : 0.f;
+  q_p[(long)b * C + c] = acc;
+}
+template <int KSM, int PF>
 __global__ __launch_bounds__(256) void finalize_query(const float *__restrict__ part,
                                                       const float *__restrict__ bias,
                                                       const float *__restrict__ A_p,
                                                       const int32_t *__restrict__ pos,
                                                       float *__restrict__ q_p, int H, int d, int r,
-                                                      int KS, long ks_stride, int Cpad, int rope,
+                                                      int KS, long ks_stride, int Cpad,
                                                       double freq_step /* -(2/d) log2(theta) */,
                                                       FastDiv by_H, FastDiv by_r, int G, int per) {
   __shared__ float q[512];
@@ -472,37 +498,23 @@ __global__ __launch_bounds__(256) void finalize_query(const float *__restrict__ 
   __shared__ float psum[256];
   const int bh = blockIdx.x, b = by_H.div(bh), h = bh - b * H;
   const int t = threadIdx.x;
-  if (!rope) {
-    // split-K partial sums: all loads of a column issued together, added in a fixed order
-    for (int c = t; c < r; c += 256) {
-      const float *p = part + (long)b * Cpad + (long)h * r + c;
-      float v[IG_KS_MAX];
-#pragma unroll
-      for (int s = 0; s < IG_KS_MAX; ++s) v[s] = p[(long)min(s, KS - 1) * ks_stride];
-      float acc = bias ? bias[h * r + c] : 0.f;
-#pragma unroll
-      for (int s = 0; s < IG_KS_MAX; ++s) acc += s < KS ? v[s] : 0.f;
-      q_p[(long)bh * r + c] = acc;
-    }
-    return;
-  }
   // Rotary model.  The block is one chain of dependent steps, so everything it reads is put in
   // flight before the first step: the partial sums of its (up to two) columns, the position, and
   // the thread's rows of A_p, which do not depend on the query at all.
   // (Addresses are clamped and surplus values dropped where they are used: a condition around a load
   // becomes a branch, and loads behind branches were issued one round trip after another.  The second
   // column of a thread exists for d > 256 only.)
-  float v[IG_KS_MAX], v2[IG_KS_MAX], bs, bs2 = 0.f;
+  float v[KSM], v2[KSM], bs, bs2 = 0.f;
   {
     const float *p = part + (long)b * Cpad + (long)h * d;
     const int c = min(t, d - 1);
 #pragma unroll
-    for (int s = 0; s < IG_KS_MAX; ++s) v[s] = p[(long)min(s, KS - 1) * ks_stride + c];
+    for (int s = 0; s < KSM; ++s) v[s] = p[(long)min(s, KS - 1) * ks_stride + c];
     bs = *(bias ? bias + h * d + c : p);
     if (d > 256) {
       const int c2 = min(t + 256, d - 1);
 #pragma unroll
-      for (int s = 0; s < IG_KS_MAX; ++s) v2[s] = p[(long)min(s, KS - 1) * ks_stride + c2];
+      for (int s = 0; s < KSM; ++s) v2[s] = p[(long)min(s, KS - 1) * ks_stride + c2];
       if (bias) bs2 = bias[h * d + c2];
     }
   }
@@ -512,29 +524,29 @@ __global__ __launch_bounds__(256) void finalize_query(const float *__restrict__ 
   // (G = 256 / r, r <= 256; per = ceil(d / G) rows each)
   const int g = by_r.div(t), k = t - g * r;
   const int c0 = g < G ? min(d, g * per) : d, c1 = g < G ? min(d, (g + 1) * per) : d;
-  constexpr int PF = 24;
   const float *ap = A_p + (long)h * d * r + k;
   float apf[PF];
 #pragma unroll
   for (int i = 0; i < PF; ++i) apf[i] = ap[(long)min(c0 + i, d - 1) * r];
   __builtin_amdgcn_sched_barrier(0);
-  // the angle's frequency depends on nothing that is loaded (d <= 512: one pair a thread)
+  // the angle's frequency depends on nothing that is loaded (d <= 512: one pair a thread; waves without a pair
+  // skip the double arithmetic, which is most of the block's work where the chip is full)
   const int half = d / 2;
-  const double freq = exp2((double)t * freq_step);
+  double freq = 0.0, sn = 0.0, cs = 1.0;
+  if (t < half) freq = exp2((double)t * freq_step);
   {
     float acc = bias ? bs : 0.f;
 #pragma unroll
-    for (int s = 0; s < IG_KS_MAX; ++s) acc += s < KS ? v[s] : 0.f;
+    for (int s = 0; s < KSM; ++s) acc += s < KS ? v[s] : 0.f;
     if (t < d) q[t] = acc;
   }
   if (d > 256) {
     float acc = bs2;
 #pragma unroll
-    for (int s = 0; s < IG_KS_MAX; ++s) acc += s < KS ? v2[s] : 0.f;
+    for (int s = 0; s < KSM; ++s) acc += s < KS ? v2[s] : 0.f;
     if (t + 256 < d) q[t + 256] = acc;
   }
-  double sn, cs;
-  rope_sincos((double)position * freq, &sn, &cs);
+  if (t < half) rope_sincos((double)position * freq, &sn, &cs);
   __syncthreads();
   if (t < half) {
     float a = q[t], bb = q[t + half];
@@ -548,7 +560,16 @@ __global__ __launch_bounds__(256) void finalize_query(const float *__restrict__ 
     const float next = fmaf(qr[min(c0 + i, d - 1)], apf[i], acc);
     acc = c0 + i < c1 ? next : acc;
   }
-  for (int c = c0 + PF; c < c1; ++c) acc = fmaf(qr[c], ap[(long)c * r], acc);
+  for (int c = c0 + PF; c < c1; c += 8) {      // (heads kept nearly whole: 8 more rows at a time)
+    float more[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) more[i] = ap[(long)min(c + i, d - 1) * r];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float next = fmaf(qr[min(c + i, d - 1)], more[i], acc);
+      acc = c + i < c1 ? next : acc;
+    }
+  }
   psum[t] = acc;
   __syncthreads();
   if (t < r) {
@@ -705,10 +726,27 @@ int ig_launch_finalize(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, const f
                        const float *bias, const float *A_p, const int32_t *pos, float *q_p,
                        hipStream_t s) {
   if (d->rope && d->d > 512) return ig_fail(ctx, IG_ESHAPE, "rope: d = %d exceeds 512", d->d);
-  auto k = finalize_query;
+#define BY_KS(K)                                                                                   \
+  (g.KS <= 2 ? K(2) : (g.KS <= 4 ? K(4) : (g.KS <= 8 ? K(8) : (g.KS <= 12 ? K(12) : K(IG_KS_MAX)))))
+  const long ks_stride = (long)g.Bpad * g.Cpad;
+  if (!d->rope) {
+    const int C = d->H * d->r;
+#define FOLDED(KSM) finalize_folded<KSM>
+    auto k = BY_KS(FOLDED);
+#undef FOLDED
+    const int blocks = (C + 63) / 64;
+    IG_LAUNCH(ctx, IG_K_FINALIZE, k, dim3((unsigned)d->B * blocks), dim3(64), s, part, bias, q_p, C, g.KS, ks_stride,
+              g.Cpad, ig_fast_div(blocks));
+    return IG_OK;
+  }
+  const int G = 256 / d->r, per = (d->d + G - 1) / G;
+  auto pick = [&](auto k8, auto k16, auto k24) { return per <= 8 ? k8 : (per <= 16 ? k16 : k24); };
+#define QUERY(KSM) pick(finalize_query<KSM, 8>, finalize_query<KSM, 16>, finalize_query<KSM, 24>)
+  auto k = BY_KS(QUERY);
+#undef QUERY
+#undef BY_KS
   IG_LAUNCH(ctx, IG_K_FINALIZE, k, dim3(d->B * d->H), dim3(256), s, part, bias, A_p, pos, q_p,
-            (int)d->H, (int)d->d, (int)d->r, g.KS, (long)g.Bpad * g.Cpad, g.Cpad, (int)d->rope,
-            d->rope ? -2.0 / (double)d->d * log2((double)d->rope_theta) : 0.0, ig_fast_div(d->H),
-            ig_fast_div(d->r), 256 / d->r, (d->d + 256 / d->r - 1) / (256 / d->r));
+            (int)d->H, (int)d->d, (int)d->r, g.KS, ks_stride, g.Cpad,
+            -2.0 / (double)d->d * log2((double)d->rope_theta), ig_fast_div(d->H), ig_fast_div(d->r), G, per);
   return IG_OK;
 }

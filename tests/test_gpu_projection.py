@@ -30,8 +30,11 @@ def ctx():
     ("f16", 4, 64, 38, True, True),
     ("f16", 2, 512, 100, True, False),     # two columns a thread
     ("f32", 3, 320, 256, True, True),      # one group of 256 outputs, more rows than are fetched ahead
+    ("f16", 1, 64, 20, False, True),       # two partial sums
+    ("f16", 2, 64, 30, True, False),       # four; 8 rows of A_p a thread
+    ("f16", 3, 96, 96, True, True),        # 48 rows: 24 and three times 8
 ])
-@pytest.mark.parametrize("B", [1, 2, 3, 5, 8, 9, 16, 17, 32, 33, 65])
+@pytest.mark.parametrize("B", [1, 2, 3, 5, 8, 9, 16, 17, 32, 33, 65, 100])
 def test_partial_query_against_float64(ctx, dtype, H, d, r, rope, bias, B):
     import paper_2406_19707_amd as ig
     print(f"case {dtype} H{H} d{d} r{r} rope {rope} B{B}", flush=True)
