@@ -83,7 +83,7 @@ __global__ void wq_build_plain(const T *W, const int32_t *idx, T *blob, int D, i
 // Wave (cblk, ks): part[ks][n][cblk*16 + i] = sum over its K blocks of W^T-fragment x x-fragment.
 // A operand = weight piece (M side = 16 output columns), B operand = 16 batch rows of x.
 // Result lane l, register v -> column cblk*16 + 4*(l/16) + v, batch row l%16.
-template <int NB>
+template <int NB, int KB>
 __global__ __launch_bounds__(256) void project_mfma(const half8 *__restrict__ blob,
                                                     const half_t *__restrict__ x,
                                                     float *__restrict__ part, int B, int D,
@@ -107,7 +107,6 @@ __global__ __launch_bounds__(256) void project_mfma(const half8 *__restrict__ bl
   // K blocks are taken KB at a time: all weight pieces and x fragments of a batch are loaded before
   // the first MFMA, so a wave keeps KB * (1 + NB) KiB in flight (a block past the end is clamped
   // to the last one and its MFMA skipped).
-  constexpr int KB = NB == 1 ? 8 : (NB == 2 ? 6 : 4);
   for (int kb = kb0; kb < kb1; kb += KB) {
     half8 a[KB], bfrag[NB][KB];
 #pragma unroll
@@ -611,7 +610,7 @@ int ig_launch_project(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, const vo
     const unsigned cols = (unsigned)((g.nCblk + 3) / 4);
     dim3 block(256);
     if (g.NBtot == 1) {
-      auto k = project_mfma<1>;
+      auto k = project_mfma<1, 8>;
       IG_LAUNCH(ctx, IG_K_PROJECT, k, dim3(cols, g.KS), block, s, (const half8 *)wq, (const half_t *)x,
                 part, (int)d->B, D, g.nCblk, g.nKblk, g.kb_per, g.Bpad, g.Cpad);
     } else if (g.NBtot == 2 && g.kb_per <= 16) {
@@ -622,14 +621,23 @@ int ig_launch_project(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, const vo
       IG_LAUNCH_LDS(ctx, IG_K_PROJECT, k, grid, block, lds, s, (const half8 *)wq, (const half_t *)x, part,
                     (int)d->B, D, g.nCblk, g.nKblk, g.kb_per, g.Bpad, g.Cpad, ig_fast_div(g.kb_per * 4));
     } else if (g.NBtot == 2) {
-      auto k = project_mfma<2>;
+      auto k = project_mfma<2, 6>;
       IG_LAUNCH(ctx, IG_K_PROJECT, k, dim3(cols, g.KS), block, s, (const half8 *)wq, (const half_t *)x,
                 part, (int)d->B, D, g.nCblk, g.nKblk, g.kb_per, g.Bpad, g.Cpad);
     } else {
-      auto k = project_mfma<4>;
-      IG_LAUNCH(ctx, IG_K_PROJECT, k, dim3(cols, g.KS, (unsigned)((g.NBtot + 3) / 4)), block, s,
-                (const half8 *)wq, (const half_t *)x, part, (int)d->B, D, g.nCblk, g.nKblk, g.kb_per,
-                g.Bpad, g.Cpad);
+      // groups of up to 4 blocks of 16 batch rows, as even as they go: a block past the batch is read (its last
+      // row again) and multiplied like any other (5120 columns, 37 rows: 24.4 us as 4 blocks, 22.8 as 3, 20.4 with
+      // its K slice of 10 taken by 2)
+      const int groups = (g.NBtot + 3) / 4;
+      // K blocks at a time: as many of 4, 3 or 2 as leave the fewest loads past the slice, which many rows feel
+      int kb = 4;
+      for (int n = 3; n >= 2; --n)
+        if ((g.kb_per + n - 1) / n * n < (g.kb_per + kb - 1) / kb * kb) kb = n;
+      auto pick = [&](auto k4, auto k3, auto k2) { return kb == 4 ? k4 : (kb == 3 ? k3 : k2); };
+      auto k = (g.NBtot + groups - 1) / groups == 3 ? pick(project_mfma<3, 4>, project_mfma<3, 3>, project_mfma<3, 2>)
+                                                    : pick(project_mfma<4, 4>, project_mfma<4, 3>, project_mfma<4, 2>);
+      IG_LAUNCH(ctx, IG_K_PROJECT, k, dim3(cols, g.KS, (unsigned)groups), block, s, (const half8 *)wq,
+                (const half_t *)x, part, (int)d->B, D, g.nCblk, g.nKblk, g.kb_per, g.Bpad, g.Cpad);
     }
   } else {
     const int nr = d->B > 8 ? 16 : (d->B > 4 ? 8 : (d->B > 2 ? 4 : d->B));
@@ -684,8 +692,8 @@ int ig_launch_project_columns(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, 
   const int KS = ig_proj_columns_ks(d, &k_per);
   if (proj_columns_mfma(d)) {
     const int nbtot = (d->B + 15) / 16;
-    const int nb = nbtot == 1 ? 1 : (nbtot == 2 ? 2 : 4);
-    dim3 grid(D / 128, KS, (nbtot + nb - 1) / nb), block(256);
+    const int groups = (nbtot + 3) / 4, nb = (nbtot + groups - 1) / groups;      // (as in ig_launch_project)
+    dim3 grid(D / 128, KS, groups), block(256);
 #define PM_CASE(NB)                                                                                \
   {                                                                                                \
     auto k = project_columns_mfma<NB>;                                                             \
@@ -695,6 +703,7 @@ int ig_launch_project_columns(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, 
   }
     if (nb == 1) PM_CASE(1)
     if (nb == 2) PM_CASE(2)
+    if (nb == 3) PM_CASE(3)
     PM_CASE(4)
 #undef PM_CASE
   }
