@@ -339,7 +339,7 @@ int ig_slab_build(ig_ctx *ctx, const ig_desc *d, const void *Kpool, int pool_spa
   if ((rc = set_device(ctx))) return rc;
   const void *kp = nullptr;
   if ((rc = resolve_pool(ctx, Kpool, pool_space, &kp))) return rc;
-  return ig_launch_slab_build(ctx, d, kp, idx_dev, slab, (hipStream_t)stream);
+  return ig_launch_slab_build(ctx, d, kp, idx_dev, slab, pool_space == IG_MEM_HOST_PINNED, (hipStream_t)stream);
 }
 
 int ig_append_token(ig_ctx *ctx, const ig_desc *d, const void *k_new, const void *v_new,

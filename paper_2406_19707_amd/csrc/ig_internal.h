@@ -167,7 +167,7 @@ void ig_prof_events(ig_ctx *ctx, int which, hipEvent_t *e0, hipEvent_t *e1);
 int ig_launch_wq_build(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, const void *Wq,
                        const int32_t *idx, void *wq, hipStream_t s);
 int ig_launch_slab_build(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const int32_t *idx,
-                         void *slab, hipStream_t s);
+                         void *slab, bool host_pool, hipStream_t s);
 int ig_launch_project(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, const void *x,
                       const void *wq, float *part, hipStream_t s);
 // index-only partial weight: columns idx of the full weight W, same partial-sum layout

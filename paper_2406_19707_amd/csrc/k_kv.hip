@@ -14,7 +14,7 @@ namespace {
 // = 5.3 TB/s, the rate of a large copy, against 43.8 us with 32 tokens a workgroup and 2-byte accesses on
 // both sides of the LDS.
 // The LDS row is padded by 8 bytes: consecutive tokens of one column then fall two banks apart.
-template <typename T, int CHUNK>
+template <typename T, int CHUNK, int U>     // U: row units a thread has in flight
 __global__ __launch_bounds__(256) void slab_build(const T *__restrict__ Kpool,
                                                   const int32_t *__restrict__ idx,
                                                   T *__restrict__ slab, int H, int d, int r, int N,
@@ -23,7 +23,6 @@ __global__ __launch_bounds__(256) void slab_build(const T *__restrict__ Kpool,
   constexpr int TILE = IG_WAVE * SlabElem<T>::TPL;
   constexpr int VEC = 16 / sizeof(T);            // tokens of a 16-byte store
   constexpr int PAD = 8 / sizeof(T);
-  constexpr int U = 8;                           // row units a thread has in flight
   static_assert(TILE % CHUNK == 0 && CHUNK % VEC == 0, "a chunk lies inside one tile");
   extern __shared__ uint2 slab_lds[];            // [CHUNK][d + PAD] elements, then the kept columns [r]
   T *rows = reinterpret_cast<T *>(slab_lds);
@@ -325,29 +324,33 @@ int ig_launch_read(ig_ctx *ctx, const void *src, size_t bytes, hipStream_t s) {
 }
 
 int ig_launch_slab_build(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const int32_t *idx,
-                         void *slab, hipStream_t s) {
+                         void *slab, bool host_pool, hipStream_t s) {
   const int tile = ig_tile_tokens(d->dtype);
   const int nTiles = (d->N_cap + tile - 1) / tile;
   if (d->d > 256) return ig_fail(ctx, IG_ESHAPE, "slab build: d = %d exceeds 256", d->d);
-  // chunk of tokens by row length, so that it stays at about 32 KiB
+  // Chunk of tokens by row length, so that it stays at about 32 KiB, 8 loads a thread.  From a pinned pool 32 tokens,
+  // one load a thread at a time: requests over the link beyond what its latency covers only slow it down (8 pairs
+  // of 1500 tokens, 128 float32 columns, 6.1 MB: 116 us, with 32 KiB in flight a workgroup 144 us).
   const int esz = ig_elem_bytes(d->dtype), row = d->d * esz;
-  const int chunk = row <= 256 ? 128 : (row <= 512 ? 64 : 32);
+  const int chunk = host_pool ? 32 : (row <= 256 ? 128 : (row <= 512 ? 64 : 32));
   const size_t lds = (size_t)chunk * (row + 8) + (size_t)d->r * sizeof(int32_t);
   dim3 grid(nTiles * tile / chunk, d->B * d->H), block(256);
-#define SLAB(T, CHUNK)                                                                             \
-  if (chunk == CHUNK) {                                                                            \
-    auto k = slab_build<T, CHUNK>;                                                                 \
+#define SLAB(T, CHUNK, U)                                                                          \
+  {                                                                                                \
+    auto k = slab_build<T, CHUNK, U>;                                                              \
     IG_LAUNCH_LDS(ctx, IG_K_BUILD, k, grid, block, lds, s, (const T *)Kpool, idx, (T *)slab,       \
                   (int)d->H, (int)d->d, (int)d->r, (int)d->N, (int)d->N_cap, nTiles);              \
     return IG_OK;                                                                                  \
   }
   if (d->dtype == IG_F16) {
-    SLAB(half_t, 128)
-    SLAB(half_t, 64)
+    if (host_pool) SLAB(half_t, 32, 1)
+    if (chunk == 128) SLAB(half_t, 128, 8)
+    if (chunk == 64) SLAB(half_t, 64, 8)
   } else {
-    SLAB(float, 128)
-    SLAB(float, 64)
-    SLAB(float, 32)
+    if (host_pool) SLAB(float, 32, 1)
+    if (chunk == 128) SLAB(float, 128, 8)
+    if (chunk == 64) SLAB(float, 64, 8)
+    if (chunk == 32) SLAB(float, 32, 8)
   }
 #undef SLAB
   return ig_fail(ctx, IG_ESHAPE, "slab build: rows of %d bytes", row);
