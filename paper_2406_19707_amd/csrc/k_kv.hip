@@ -332,7 +332,12 @@ int ig_launch_slab_build(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const
   // one load a thread at a time: requests over the link beyond what its latency covers only slow it down (8 pairs
   // of 1500 tokens, 128 float32 columns, 6.1 MB: 116 us, with 32 KiB in flight a workgroup 144 us).
   const int esz = ig_elem_bytes(d->dtype), row = d->d * esz;
-  const int chunk = host_pool ? 32 : (row <= 256 ? 128 : (row <= 512 ? 64 : 32));
+  // Calls with less than a workgroup for every compute unit, which last as long as one workgroup, also take fewer
+  // tokens in each, and one load where that is all there is (2 pairs of 492 tokens, 64 half columns: 2.6 us with 128
+  // tokens, 2.0 so).
+  int chunk = host_pool ? 32 : (row <= 256 ? 128 : (row <= 512 ? 64 : 32));
+  while (chunk > 32 && (long)d->B * d->H * nTiles * (tile / chunk) < 256) chunk /= 2;
+  const bool one_load = chunk == 32 && row <= 128;
   const size_t lds = (size_t)chunk * (row + 8) + (size_t)d->r * sizeof(int32_t);
   dim3 grid(nTiles * tile / chunk, d->B * d->H), block(256);
 #define SLAB(T, CHUNK, U)                                                                          \
@@ -343,11 +348,12 @@ int ig_launch_slab_build(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const
     return IG_OK;                                                                                  \
   }
   if (d->dtype == IG_F16) {
-    if (host_pool) SLAB(half_t, 32, 1)
+    if (host_pool || one_load) SLAB(half_t, 32, 1)
     if (chunk == 128) SLAB(half_t, 128, 8)
     if (chunk == 64) SLAB(half_t, 64, 8)
+    if (chunk == 32) SLAB(half_t, 32, 8)
   } else {
-    if (host_pool) SLAB(float, 32, 1)
+    if (host_pool || one_load) SLAB(float, 32, 1)
     if (chunk == 128) SLAB(float, 128, 8)
     if (chunk == 64) SLAB(float, 64, 8)
     if (chunk == 32) SLAB(float, 32, 8)
