@@ -25,10 +25,21 @@ def ctx():
     ("f32", 4, 4, 31, 300), ("f32", 64, 19, 257, 257), ("f32", 68, 20, 64, 256), ("f32", 128, 38, 255, 600), ("f32", 256, 76, 33, 40)])
 @pytest.mark.parametrize("pinned", [False, True])
 def test_layout_byte_for_byte(ctx, dtype, d, r, N, N_cap, pinned):
+    check(ctx, dtype, d, r, N, N_cap, pinned, 2, 3)      # (fewer workgroups than compute units: 32 tokens each)
+
+
+# enough pairs for every compute unit: 128, 64 and 32 tokens a workgroup by the length of a row
+@pytest.mark.parametrize("dtype,d,r,N,N_cap", [
+    ("f16", 8, 1, 1, 1), ("f16", 64, 19, 127, 127), ("f16", 96, 28, 513, 700), ("f16", 128, 38, 128, 1100), ("f16", 136, 5, 65, 65),
+    ("f16", 256, 76, 512, 513), ("f32", 4, 4, 31, 300), ("f32", 64, 19, 257, 257), ("f32", 68, 20, 64, 256), ("f32", 256, 76, 33, 40)])
+def test_layout_of_many_pairs(ctx, dtype, d, r, N, N_cap):
+    check(ctx, dtype, d, r, N, N_cap, False, 16, 9)
+
+
+def check(ctx, dtype, d, r, N, N_cap, pinned, B, H):
     import paper_2406_19707_amd as ig
     print(f"case {dtype} d{d} r{r} N{N} cap{N_cap} pinned {pinned}", flush=True)
     rng = np.random.default_rng(d * 7 + r + N)
-    B, H = 2, 3
     npdt = np.float16 if dtype == "f16" else np.float32
     K = rng.standard_normal((B, H, N_cap, d)).astype(npdt)
     idx = np.stack([np.sort(rng.choice(d, r, replace=False)) for _ in range(H)]).astype(np.int32)
