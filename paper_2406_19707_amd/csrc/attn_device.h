@@ -100,12 +100,12 @@ static inline int slices_at_most(long rows, int slice_log2) {
 // call.
 constexpr int ATT_BATCH = 8;
 // rows of a slice: what one batch of a workgroup's loads covers, or 1 << SLICE_LOG2 where that is more, but no
-// more than two batches where lists are few.  (Rows of 128 bytes, d = 64 in half precision: 256 a batch; a list of 129..256 such
-// rows is then one workgroup that writes its output itself instead of two that meet: 192 lists of 120 rows on
-// average 8.2 -> 5.8 us.  Rows of 1024 bytes: 32 a batch; the first of two slices is full whatever is left for
-// the second, and one workgroup walking 128 rows sets the time of a list of 137: 32 such lists 18.5 -> 11.6 us.
-// With 256 lists and more every compute unit has one, and cutting lists of 100 rows in two only adds the meeting:
-// 512 of them 23.8 -> 25.8 us.)
+// more than two batches where lists are few.  (Rows of 128 bytes, d = 64 in half precision: 256 a batch; a list of
+// 129..256 such rows is then one workgroup that writes its output itself instead of two that meet: 192 lists of
+// 120 rows on average 8.2 -> 5.8 us.  Rows of 1024 bytes: 32 a batch; the first of two slices is full whatever is
+// left for the second, and one workgroup walking 128 rows sets the time of a list of 137: 32 such lists 18.5 ->
+// 11.6 us.  With 256 lists and more every compute unit has one, and cutting lists of 100 rows in two only adds the
+// meeting: 512 of them 23.8 -> 25.8 us.)
 static inline int att_slice_log2(int lpr_log2, int lists) {
   const int batch_log2 = 2 + (6 - lpr_log2) + 3;     // 4 waves x 64 / LPR rows x ATT_BATCH steps
   if (batch_log2 >= SLICE_LOG2) return batch_log2;

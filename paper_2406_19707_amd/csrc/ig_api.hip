@@ -764,8 +764,8 @@ int ig_decode_step_overlapped(ig_ctx *ctx, const ig_desc *d, int n_layers, const
   // stream (n_sets >= 2, so the attention of layer l - n_sets is enqueued before the rehearsal of layer l),
   // the rows by a prefetch that waits for that rehearsal.  An event of its own for the attention would
   // say the same again, and a record and a wait cost about 14 us of host time, more than the four
-  // kernels of a layer: with it a small step was bound by the host (3 layers, 64 heads, 2048 tokens, back to back:
-  // 211 -> 200 us).
+  // kernels of a layer: with it a small step was bound by the host (3 layers, 64 heads, 2048 tokens, issued
+  // back to back: 211 -> 200 us).
   for (int l = 0; l <= n_layers; ++l) {
     if (l < n_layers) {
       const ig_layer_io &io = layers[l];
