@@ -1293,17 +1293,26 @@ static bool run_time_split_pays(const ig_desc *d, int nValid, int BH, int t, int
   // beyond 32768 tokens the other form is the three kernels: 0.5..1.0
   if (nValid * ig_tile_tokens(d->dtype) > 32768) return true;
   // The other form is one workgroup per pair, its scores parked in LDS, one to a compute unit.  It leaves the
-  // chip idle with few pairs (64 pairs 0.55..0.95, 72 up to 1.08; 104 pairs of 48 tiles and more 0.70..1.03)
-  // and takes a second round for the 257th (320 pairs, r <= 16: 0.63..0.98).
-  // Just over 16 tiles its 16 waves go round twice for the one (18 tiles, r = 16 and 19, 80 and 96 pairs
-  // 0.80..0.87).
-  if (BH <= 72 || (BH <= 104 && nValid >= 48) || (BH > 256 && d->r <= 16)) return true;
-  if (BH <= 96 && nValid <= 20 && d->r <= 24) return true;
-  // In between it fills the chip, and what counts is the work a workgroup has besides its loads: little for few
-  // channels (r = 6, half precision, 128 pairs 0.68, 256 pairs 0.90; float32, 128 pairs 0.92, 160 pairs 1.00;
-  // r = 12, 96 pairs 0.91, 160 pairs 1.07; r = 19, 160 pairs 1.06, 192 pairs 1.09).
-  if (d->r <= 9) return d->dtype == IG_F16 || BH <= 128;
-  return d->r <= 12 ? BH <= 96 : (d->r <= 16 && BH <= 80);
+  // chip idle with few pairs (64 pairs 0.55..0.95, 72 up to 1.08), and takes a second round for the 257th (320
+  // pairs, r <= 16: 0.63..0.98).
+  if (BH <= 72 || (BH > 256 && d->r <= 16)) return true;
+  if (d->dtype == IG_F16) {
+    // In between it is even with the split where every pair keeps a few per cent of its tokens, and behind where
+    // lists are uneven, as they are: the longest one sets its time, a split pair's is written by all its
+    // workgroups.  (r = 12 and 19, uneven / even lists: 18000 tokens and more, 120 pairs 0.70..0.83 / 0.93..1.0,
+    // 200 pairs 0.80..0.97 / 0.98..1.06; 12000 tokens, 120 pairs 0.75, 0.91 / 1.1, 200 pairs 0.98, 1.0 / 1.16;
+    // r = 32: 23000 tokens, 160 pairs 0.90 / 1.0, 12000 tokens, 96 pairs 1.09 / 1.1; r = 6: 0.47..0.97.)
+    if (d->r <= 9) return true;
+    if (BH >= 256 && d->r > 16) return false;
+    if (nValid >= (d->r <= 24 ? 36 : 44)) return true;
+    return BH <= (d->r <= 16 ? 128 : (d->r <= 24 ? 104 : 72));
+  }
+  // float32 (half the tokens a tile, and no difference between even and uneven lists): just over 16 tiles the other
+  // form's 16 waves go round twice for the one (18 tiles, r = 19, 80 and 96 pairs 0.88); 104 pairs of 48 tiles and
+  // more 0.85..1.0; then what counts is the work a workgroup has besides its loads, little for few channels
+  // (r = 6, 128 pairs 0.92, 160 pairs 1.10; r = 12, 96 pairs 0.91..1.1, 160 pairs 1.04..1.18).
+  if ((BH <= 104 && nValid >= 48) || (BH <= 96 && nValid <= 20 && d->r <= 24)) return true;
+  return BH <= (d->r <= 9 ? 128 : (d->r <= 12 ? 96 : (d->r <= 16 ? 80 : 72)));
 }
 
 bool ig_scan_stream_form(const ig_desc *d, int *tpw, int *S) {
