@@ -4,8 +4,8 @@
 // Two kernels, both with a fixed summation order (no floating-point atomics, so a run repeats
 // bit for bit):
 //   column_abs_sums   a lane takes VEC consecutive columns (8-byte loads in half precision, 16-byte in
-//                     float32) and one of ROW_CHUNKS row ranges, walks it down and writes one partial
-//                     sum per column
+//                     float32) and a wave a quarter of one of ROW_CHUNKS row ranges; one partial
+//                     sum per column and range is written
 //   top_columns       one workgroup per head: adds the ROW_CHUNKS partial sums of each column in
 //                     order, ranks the d columns (column j beats c when its sum is larger, or
 //                     equal with j < c), keeps ranks < r and writes them in ascending order
@@ -16,20 +16,23 @@ namespace {
 constexpr int ROW_CHUNKS = 32;
 
 // HBM-bound (the rows are read once).  What it takes is bytes in flight: the grid is small (D columns
-// x 32 ranges), so a lane issues the loads of 16 rows of both matrices before it adds the first, in the
-// row order of the plain loop.  2048 rows of 4096 half columns, queries and keys (33.5 MB): 55 us with
-// 2-byte loads one row at a time, 13 us so.  Arrays whose rows or addresses do not allow the wide
-// loads go one column a lane.
-template <typename T, int VEC>
-__global__ __launch_bounds__(64) void column_abs_sums(const T *__restrict__ Qs, const T *__restrict__ Ks,
-                                                      float *__restrict__ part, int n, int D) {
+// x 32 ranges), so the four waves of a workgroup take a quarter of the range each, and a lane issues the loads
+// of U rows of both matrices before it adds the first; the waves' sums are added in wave order.  2048 rows of 4096
+// half columns, queries and keys (33.5 MB): 55 us with 2-byte loads one row at a time, with top_columns 14.6 us
+// with one wave a range (512 waves, 64 rows each in four turns), 10.1 us so (one turn of 16 rows).  U is the
+// smallest of 4, 8 and 16 that takes a wave's rows in one turn: loads past the last row read it again (56
+// heads of 128, 700 rows, 6 a wave: two turns of 4 are 0.8 us behind the one wave a range, one of 8 ahead of it).
+// Arrays whose rows or addresses do not allow the wide loads go one column a lane.
+template <typename T, int VEC, int U>
+__global__ __launch_bounds__(256) void column_abs_sums(const T *__restrict__ Qs, const T *__restrict__ Ks,
+                                                       float *__restrict__ part, int n, int D) {
   typedef T vec __attribute__((ext_vector_type(VEC)));
-  constexpr int U = 16;
-  const int c = (blockIdx.x * 64 + threadIdx.x) * VEC;
+  __shared__ float wave_sums[4][VEC][64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = (blockIdx.x * 64 + lane) * VEC, cc = min(c, D - VEC);      // (lanes past the last column repeat it)
   const int chunk = blockIdx.y;
-  const int rows_per = (n + ROW_CHUNKS - 1) / ROW_CHUNKS;
-  const int i0 = chunk * rows_per, i1 = min(n, i0 + rows_per);
-  if (c >= D) return;
+  const int rows_per = (n + ROW_CHUNKS - 1) / ROW_CHUNKS, per = (rows_per + 3) / 4;
+  const int i0 = chunk * rows_per + w * per, i1 = min(min(n, (chunk + 1) * rows_per), i0 + per);
   const T *Kp = Ks ? Ks : Qs;                // (without keys: read and not added)
   float acc[VEC];
 #pragma unroll
@@ -38,7 +41,7 @@ __global__ __launch_bounds__(64) void column_abs_sums(const T *__restrict__ Qs, 
     vec q[U], k[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const long at = (long)min(i + u, i1 - 1) * D + c;      // past the end: the last row again, not added
+      const long at = (long)min(i + u, i1 - 1) * D + cc;     // past the end: the last row again, not added
       q[u] = *reinterpret_cast<const vec *>(Qs + at);
       k[u] = *reinterpret_cast<const vec *>(Kp + at);
     }
@@ -55,7 +58,14 @@ __global__ __launch_bounds__(64) void column_abs_sums(const T *__restrict__ Qs, 
     }
   }
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) part[(long)chunk * D + c + e] = acc[e];
+  for (int e = 0; e < VEC; ++e) wave_sums[w][e][lane] = acc[e];
+  __syncthreads();
+  if (w == 0 && c < D) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+      part[(long)chunk * D + c + e] =
+          ((wave_sums[0][e][lane] + wave_sums[1][e][lane]) + wave_sums[2][e][lane]) + wave_sums[3][e][lane];
+  }
 }
 
 // One workgroup per head and a chain of dependent steps: the ROW_CHUNKS partial sums of a column in flight
@@ -118,10 +128,12 @@ int ig_launch_partial_index(ig_ctx *ctx, int dtype, int H, int d, int n, const v
                             int r, float *part, int32_t *idx, hipStream_t s) {
   const int D = H * d;
   const size_t align = (size_t)D * ig_elem_bytes(dtype) | (uintptr_t)Qs | (uintptr_t)Ks;
+  const int per = ((n + ROW_CHUNKS - 1) / ROW_CHUNKS + 3) / 4;       // rows a wave
 #define SUMS(T, VEC)                                                                               \
   {                                                                                                \
-    auto k = column_abs_sums<T, VEC>;                                                              \
-    IG_LAUNCH(ctx, IG_K_BUILD, k, dim3((D + 64 * VEC - 1) / (64 * VEC), ROW_CHUNKS), dim3(64), s,  \
+    auto k = per <= 4 ? column_abs_sums<T, VEC, 4>                                                 \
+                      : (per <= 8 ? column_abs_sums<T, VEC, 8> : column_abs_sums<T, VEC, 16>);     \
+    IG_LAUNCH(ctx, IG_K_BUILD, k, dim3((D + 64 * VEC - 1) / (64 * VEC), ROW_CHUNKS), dim3(256), s, \
               (const T *)Qs, (const T *)Ks, part, n, D);                                           \
   }
   if (dtype == IG_F16) {

@@ -127,3 +127,28 @@ def test_rows_with_nan_or_infinity_keep_r_columns(ctx, H, d):
     for h in range(H):
         want = np.sort(np.argsort(-sums[h], kind="stable")[:r])
         assert np.array_equal(got[h * r:(h + 1) * r], want), h
+
+
+@pytest.mark.parametrize("n", [1, 32, 33, 129, 512, 513, 1025, 2049, 2600])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_row_counts_at_the_edges_of_a_waves_share(ctx, dtype, n):
+    """A wave sums a quarter of one of 32 row ranges, 4, 8 or 16 rows at a time: counts at which waves or ranges
+    are left without rows, a turn is just full or one row over, and a second turn starts.  float32 sums of n
+    positive terms are within n * 2^-24 of the exact ones, whatever the order."""
+    import paper_2406_19707_amd as ig
+    H, d, r = 3, 64, 19
+    rng = np.random.default_rng(n)
+    npdt = np.float16 if dtype == "f16" else np.float32
+    Q, K = (rng.standard_normal((n, H * d)).astype(npdt) for _ in range(2))
+    idx = torch.full((H, r), -1, dtype=torch.int32, device="cuda")
+    ctx.ig_partial_index_device(ig.IG_F16 if dtype == "f16" else ig.IG_F32, H, d, n, torch.from_numpy(Q).cuda(),
+                                torch.from_numpy(K).cuda(), 0.3, idx)
+    got = idx.cpu().numpy()
+    sums = np.abs(Q.astype(np.float64)).sum(0) + np.abs(K.astype(np.float64)).sum(0)
+    tol = 4 * n * 2.0 ** -24
+    for h in range(H):
+        c = sums[h * d:(h + 1) * d]
+        cut = np.sort(c)[::-1][r - 1]
+        assert np.all(np.diff(got[h]) > 0)
+        assert np.all(c[got[h]] >= cut * (1 - tol))
+        assert np.all(np.delete(c, got[h]) <= cut * (1 + tol))
