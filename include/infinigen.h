@@ -69,9 +69,10 @@ enum { IG_POLICY_COUNTER = 0, IG_POLICY_FIFO = 1, IG_POLICY_LRU = 2 };
 
 /* Kernel identifiers for ig_profile_read. */
 enum {
-  IG_K_PROJECT = 0,  /* partial query projection (split-K partial sums) */
+  IG_K_PROJECT = 0,  /* partial query projection (split-K partial sums), where it is a launch of its own */
   IG_K_FINALIZE = 1, /* partial-sum reduction, bias, rotary embedding, partial skew */
-  IG_K_SCAN = 2,     /* partial key cache scan (+ max, threshold, compaction when fused) */
+  IG_K_SCAN = 2,     /* partial key cache scan (+ max, threshold, compaction when fused; + the projection, see
+                      * ig_set_wait_limit) */
   IG_K_SELECT = 3,   /* threshold + compaction from a score buffer (long sequences) */
   IG_K_GATHER = 4,
   IG_K_ATTENTION = 5,
@@ -428,10 +429,11 @@ int ig_decode_step_overlapped(ig_ctx *ctx, const ig_desc *desc, int n_layers, co
 
 /* Long sequences, and sequences of more than 4 tiles (2048 half or 1024 float32 tokens) when there are
  * few (sequence, head) pairs, are scanned by several workgroups per pair, which meet through device
- * memory; each waits for its partners at most `ticks` periods of the GPU's 100 MHz clock (10 ns)
- * and then finishes the pair on its own (slower, same result bit for bit).  0 restores the
- * default (20 ms); a negative value makes every such workgroup take the self-sufficient route
- * without waiting at all -- the hook the tests use to exercise that route. */
+ * memory; and where the projection runs in the scan's launch (half precision, up to 32 sequences), the
+ * scanning workgroups wait for their query.  Each waits at most `ticks` periods of the GPU's 100 MHz
+ * clock (10 ns) and then works the missing part out on its own (slower, same result bit for bit).  0
+ * restores the default (20 ms); a negative value makes every such workgroup take the self-sufficient
+ * route without waiting at all -- the hook the tests use to exercise that route. */
 int ig_set_wait_limit(ig_ctx *ctx, int64_t ticks);
 
 /* Between ig_profile_begin and ig_profile_end every kernel the context launches carries a pair of

@@ -135,6 +135,15 @@ int resolve_pool(ig_ctx *ctx, const void *p, int space, const void **out) {
   return IG_OK;
 }
 
+// Query words of the projection inside the scan's launch: words from one quarter of K to the next (whole
+// 128-byte lines), quarters, bytes in all; 0 bytes for shapes that never take it.
+int words_ld(const ig_desc *d) { return ((d->rope ? d->d : d->r) + 15) / 16 * 16; }
+int words_quarters(const ProjGeom &g) { return (g.KS + 3) / 4; }
+size_t words_bytes(const ig_desc *d, const ProjGeom &g) {
+  if (!g.mfma || g.NBtot > 2 || d->r > 64) return 0;
+  return (size_t)d->B * d->H * words_quarters(g) * words_ld(d) * sizeof(unsigned long long);
+}
+
 int reserve_for(ig_ctx *ctx, const ig_desc *d, bool scores) {
   ProjGeom g = ig_proj_geom(d);
   int k_per = 0;
@@ -150,6 +159,9 @@ int reserve_for(ig_ctx *ctx, const ig_desc *d, bool scores) {
   if (rc) return rc;
   rc = ig_ensure(ctx, (void **)&ctx->eq_cnt, &ctx->eq_cnt_bytes, (size_t)d->B * d->H * sizeof(int32_t));
   if (rc) return rc;
+  // (missing under a capture they are done without: the projection is then a kernel of its own)
+  const size_t wb = words_bytes(d, g);
+  if (wb > ctx->words_bytes && !ig_capturing(ctx) && (rc = ig_ensure_zeroed(ctx, &ctx->words, &ctx->words_bytes, wb))) return rc;
   if (scores) {
     const int tile = ig_tile_tokens(d->dtype);
     const int nTiles = (d->N_cap + tile - 1) / tile;
@@ -235,6 +247,7 @@ int ig_destroy(ig_ctx *ctx) {
   if (ctx->pair_sync) (void)hipFree(ctx->pair_sync);
   if (ctx->seq_sync) (void)hipFree(ctx->seq_sync);
   if (ctx->eq_cnt) (void)hipFree(ctx->eq_cnt);
+  if (ctx->words) (void)hipFree(ctx->words);
   if (ctx->attn_part) (void)hipFree(ctx->attn_part);
   if (ctx->attn_cnt) (void)hipFree(ctx->attn_cnt);
   if (ctx->status) (void)hipFree(ctx->status);
@@ -255,7 +268,8 @@ int ig_reserve(ig_ctx *ctx, const ig_desc *desc) {
 size_t ig_workspace_bytes(const ig_ctx *ctx) {
   if (!ctx) return 0;
   return ctx->part_bytes + ctx->qp_bytes + ctx->scores_bytes + ctx->tmax_bytes + ctx->pcount_bytes +
-         ctx->attn_part_bytes + ctx->attn_cnt_bytes + ctx->skew_ws_bytes + ctx->pair_sync_bytes + ctx->seq_sync_bytes + ctx->eq_cnt_bytes;
+         ctx->attn_part_bytes + ctx->attn_cnt_bytes + ctx->skew_ws_bytes + ctx->pair_sync_bytes + ctx->seq_sync_bytes +
+         ctx->words_bytes + ctx->eq_cnt_bytes;
 }
 
 int ig_check_status(ig_ctx *ctx) {
@@ -464,6 +478,25 @@ static int project_partials(ig_ctx *ctx, const ig_desc *d, const void *x, const 
   return ig_launch_project(ctx, d, *g, x, wq, ctx->part, s);
 }
 
+// Whether the projection goes into the scan's launch (after project_ready); *p is its argument block then.
+static bool joins_projection(const ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, const void *x, const void *wq, ProjWords *p) {
+  if (!ig_scan_joins_projection(d, g) || words_bytes(d, g) > ctx->words_bytes) return false;
+  int splits_tpw = 0, S = 0;
+  if (ig_scan_stream_form(d, &splits_tpw, &S) && S > 1 && ctx->pair_sync_bytes < (size_t)d->B * d->H * IG_PAIR_SYNC_BYTES)
+    return false;
+  const int D = d->H * d->d, KQ = words_quarters(g), width = d->rope ? d->d : d->r, ld = words_ld(d);
+  // 17..32 sequences: both blocks of 16 in one wave where a K slice takes more than one round trip anyway (7168 columns,
+  // 20 sequences 42.2 us with the scan, one block each 43.7); a workgroup for each where it is one round trip (4096 columns,
+  // 24 sequences of 300 tokens 11.4 us, both in one 12.6)
+  const bool both = g.NBtot == 2 && g.kb_per > 8;
+  const int groups = both ? 1 : g.NBtot;
+  *p = ProjWords{wq, x, static_cast<unsigned long long *>(ctx->words), d->B, D, d->H, g.nCblk, g.nKblk, g.kb_per, g.C, KQ,
+                 width, ld, (g.nCblk * KQ + 7) / 8 * 8 * groups, both, groups, ig_fast_div(KQ), ig_fast_div(width),
+                 ig_fast_div(ld), ig_fast_div(8 * groups),
+                 ctx->spin_limit};
+  return true;
+}
+
 int ig_project(ig_ctx *ctx, const ig_desc *d, const void *x, const void *wq, const float *bias,
                const float *A_p, const int32_t *pos, float *q_p, void *stream) {
   int rc = check_desc(ctx, d, stream);
@@ -547,6 +580,12 @@ int ig_speculate(ig_ctx *ctx, const ig_desc *d, const void *x, const void *wq, c
   if ((rc = project_ready(ctx, d, x, wq, A_p, pos, &g))) return rc;
   if (ig_scan_takes_projection(d, g))
     return ig_launch_project_scan(ctx, d, g, x, wq, bias, slab, sel_idx, sel_stride, sel_cnt, scores_opt, s);
+  ProjWords p;
+  if (joins_projection(ctx, d, g, x, wq, &p)) {
+    QSource q{nullptr, 1, 0, 0, bias, A_p, pos, &p};
+    if (!d->rope) q.A_p = nullptr;
+    return ig_launch_scan_select(ctx, d, q, slab, sel_idx, sel_stride, sel_cnt, scores_opt, s);
+  }
   if ((rc = ig_launch_project(ctx, d, g, x, wq, ctx->part, s))) return rc;
   if (d->rope && ig_scan_takes_rope(d)) {
     // rotary embedding and the partial skew sit between the projection and the scan: the scan's
@@ -583,7 +622,14 @@ int ig_speculate_equalized(ig_ctx *ctx, const ig_desc *d, const void *x, const v
     // one kernel after the projection: the scan's workgroups exchange their threshold counts and
     // select each head's top n from the scores they still hold in registers
     ProjGeom g;
-    if ((rc = project_partials(ctx, d, x, wq, A_p, pos, &g, s))) return rc;
+    ProjWords p;
+    if ((rc = project_ready(ctx, d, x, wq, A_p, pos, &g))) return rc;
+    if (joins_projection(ctx, d, g, x, wq, &p)) {
+      QSource q{nullptr, 1, 0, 0, bias, A_p, pos, &p};
+      if (!d->rope) q.A_p = nullptr;
+      return ig_launch_scan_equalized(ctx, d, q, slab, cap, sel_idx, sel_stride, sel_cnt, thr_cnt_opt, s);
+    }
+    if ((rc = ig_launch_project(ctx, d, g, x, wq, ctx->part, s))) return rc;
     if (d->rope) {
       QSource q{ctx->part, g.KS, (long)g.Bpad * g.Cpad, (long)g.Cpad, bias, A_p, pos};
       return ig_launch_scan_equalized(ctx, d, q, slab, cap, sel_idx, sel_stride, sel_cnt, thr_cnt_opt, s);
@@ -710,9 +756,21 @@ int ig_layer_step(ig_ctx *ctx, const ig_desc *d, const void *x, const void *wq, 
     return ig_fail(ctx, IG_EINVAL, "ig_layer_step: the next layer's lists must not alias this layer's");
   ProjGeom g;
   hipStream_t s = (hipStream_t)stream;
-  if ((rc = project_partials(ctx, d, x, wq, A_p, pos, &g, s))) return rc;
-  QSource qs{ctx->part, g.KS, (long)g.Bpad * g.Cpad, (long)g.Cpad, bias};
+  if ((rc = project_ready(ctx, d, x, wq, A_p, pos, &g))) return rc;
   const bool joint = ig_layer_step_is_joint(d);
+  ProjWords p;
+  if ((!joint || !d->rope) && joins_projection(ctx, d, g, x, wq, &p)) {
+    QSource q1{nullptr, 1, 0, 0, bias, A_p, pos, &p};
+    if (!d->rope) q1.A_p = nullptr;
+    if (joint)
+      return ig_launch_scan_attend(ctx, d, q1, slab, sel_idx_next, sel_cnt_next, q, Kpool, Vpool, sel_idx, sel_cnt, sel_stride,
+                                   k_new, v_new, out, K_sel, V_sel, s);
+    if ((rc = ig_launch_scan_select(ctx, d, q1, slab, sel_idx_next, sel_stride, sel_cnt_next, nullptr, s))) return rc;
+    return ig_launch_attention(ctx, d, q, Kpool, Vpool, sel_idx, sel_stride, sel_cnt, d->N_cap, k_new, v_new, out, K_sel,
+                               V_sel, s);
+  }
+  if ((rc = ig_launch_project(ctx, d, g, x, wq, ctx->part, s))) return rc;
+  QSource qs{ctx->part, g.KS, (long)g.Bpad * g.Cpad, (long)g.Cpad, bias};
   if (d->rope && !joint && ig_scan_takes_rope(d)) {      // (the joint launch's scan takes finished queries only)
     qs.A_p = A_p;
     qs.pos = pos;

@@ -84,6 +84,20 @@ static inline FastDiv ig_fast_div(int d) {
   return FastDiv{(unsigned)((p + d - 1) / d), 31 + s, (unsigned)d};
 }
 
+// Projection inside the scan's launch (project_device.h): its operands, and the words through which the scanning
+// workgroups get their partial query.
+struct ProjWords {
+  const void *blob, *x;        // the weight in fragment order, [B, D] half
+  unsigned long long *words;   // [B*H][KQ][ld], all zero between launches
+  int B, D, H, nCblk, nKblk, kb_per, C;
+  int KQ;                      // quarters of K: partial sums a query entry is published as
+  int width, ld;               // columns of a head (r, or d for rotary models); words from one quarter to the next
+  int blocks;                  // workgroups of the grid that project, a multiple of 8
+  int both, groups;            // whether a wave takes both blocks of 16 batch rows; else workgroups that take one each
+  FastDiv by_KQ, by_width, by_ld, by_8groups;
+  long limit;                  // bound of a scanning workgroup's wait, 100 MHz ticks
+};
+
 struct ProfRec {
   int which;
   hipEvent_t e0, e1;
@@ -102,6 +116,8 @@ struct ig_ctx {
   void *pair_sync;  size_t pair_sync_bytes;  // scan: per-(b,h) records of pairs split over workgroups, zero between calls
   void *seq_sync = nullptr;            // scan, head-equalised form: per-sequence exchange records (zero between calls)
   size_t seq_sync_bytes = 0;
+  void *words = nullptr;               // projection inside the scan's launch: query words (zero between calls)
+  size_t words_bytes = 0;
   int32_t *eq_cnt = nullptr;            // threshold counts of ig_speculate_equalized's two-kernel route
   size_t eq_cnt_bytes = 0;
   hipStream_t call_stream = nullptr;   // stream of the entry point being served (capture check in ig_ensure)
@@ -189,7 +205,11 @@ struct QSource {
   // and pos [B]
   const float *A_p = nullptr;
   const int32_t *pos = nullptr;
+  // the projection runs in the scan's own launch, shapes for which ig_scan_joins_projection(): qsrc, ks and
+  // the strides mean nothing then
+  const ProjWords *proj = nullptr;
 };
+bool ig_scan_joins_projection(const ig_desc *d, const ProjGeom &g);
 bool ig_scan_is_fused(const ig_desc *d);
 bool ig_scan_takes_rope(const ig_desc *d);
 // small folded models: projection and scan in one kernel
@@ -275,6 +295,21 @@ template <typename V> __device__ __forceinline__ void keep_loaded(V &v) {
   typedef int int4v __attribute__((ext_vector_type(4)));
   static_assert(sizeof(V) == 16, "four registers");
   asm volatile("" : "+v"(*reinterpret_cast<int4v *>(&v)));
+}
+
+// ---- split-K partial sums --------------------------------------------------------------------------
+// Everything that adds the partial sums of a query entry adds them in this order: groups of four, each in order,
+// then the groups.  (A group is what the waves of one workgroup add up where the projection runs inside the
+// scan's launch.)
+template <int KSM> __device__ __forceinline__ float add_partials(float acc, const float (&v)[KSM], int ks) {
+#pragma unroll
+  for (int g = 0; g < KSM; g += 4) {
+    float t = g < ks ? v[g] : 0.f;
+#pragma unroll
+    for (int s = g + 1; s < g + 4 && s < KSM; ++s) t += s < ks ? v[s] : 0.f;
+    acc += t;
+  }
+  return acc;
 }
 
 // ---- wave helpers -------------------------------------------------------------------------------

@@ -478,10 +478,7 @@ __global__ __launch_bounds__(64) void finalize_folded(const float *__restrict__ 
   float v[KSM];
 #pragma unroll
   for (int s = 0; s < KSM; ++s) v[s] = p[(long)min(s, KS - 1) * ks_stride];
-  float acc = bias ? bias[c] : 0.f;
-#pragma unroll
-  for (int s = 0; s < KSM; ++s) acc += s < KS ? v[s] : 0.f;
-  q_p[(long)b * C + c] = acc;
+  q_p[(long)b * C + c] = add_partials<KSM>(bias ? bias[c] : 0.f, v, KS);
 }
 template <int KSM, int PF>
 __global__ __launch_bounds__(256) void finalize_query(const float *__restrict__ part,
@@ -534,15 +531,11 @@ __global__ __launch_bounds__(256) void finalize_query(const float *__restrict__ 
   double freq = 0.0, sn = 0.0, cs = 1.0;
   if (t < half) freq = exp2((double)t * freq_step);
   {
-    float acc = bias ? bs : 0.f;
-#pragma unroll
-    for (int s = 0; s < KSM; ++s) acc += s < KS ? v[s] : 0.f;
+    const float acc = add_partials<KSM>(bias ? bs : 0.f, v, KS);
     if (t < d) q[t] = acc;
   }
   if (d > 256) {
-    float acc = bs2;
-#pragma unroll
-    for (int s = 0; s < KSM; ++s) acc += s < KS ? v2[s] : 0.f;
+    const float acc = add_partials<KSM>(bs2, v2, KS);
     if (t + 256 < d) q[t + 256] = acc;
   }
   if (t < half) rope_sincos((double)position * freq, &sn, &cs);

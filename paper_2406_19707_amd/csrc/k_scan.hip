@@ -21,6 +21,14 @@ template <typename T, int CH, int NW>
 __global__ __launch_bounds__(NW * 64) void scan_select_fused(ScanArgs a) {
   scan_select_fused_body<T, CH, NW>(a, blockIdx.x);
 }
+// the same with the projection in front, in the grid's first p.blocks workgroups
+template <typename T, int CH, int NW>
+__global__ __launch_bounds__(NW * 64, 4) void project_and_scan_fused(ScanArgs a, ProjWords p) {
+  __shared__ __attribute__((aligned(16))) float red[NW / 4 * PROJECT_LDS];
+  const int id = (int)blockIdx.x - p.blocks;
+  if (id >= 0) scan_select_fused_body<T, CH, NW, true>(a, id, &p, red);
+  else project_publish<NW / 4>(p, blockIdx.x, red);
+}
 
 // The same for small models, with the projection in the workgroup too: a head's r columns of the weight are a
 // few tens of KB there, and reading them again for every sequence costs less than the launch and the chain
@@ -69,12 +77,10 @@ __global__ __launch_bounds__(256) void project_scan_select(ScanArgs a, ProjectAr
   }
   __syncthreads();
   const int j = min(lane, a.r - 1);
-  float q = a.bias ? a.bias[h * a.r + j] : 0.f;
+  float sums[IG_KS_MAX];
 #pragma unroll
-  for (int s = 0; s < IG_KS_MAX; ++s) {
-    const float t = part[min(s, a.ks - 1) * a.r + j];
-    q += s < a.ks ? t : 0.f;
-  }
+  for (int s = 0; s < IG_KS_MAX; ++s) sums[s] = part[min(s, a.ks - 1) * a.r + j];
+  const float q = add_partials<IG_KS_MAX>(a.bias ? a.bias[h * a.r + j] : 0.f, sums, a.ks);
   const float qv[4] = {lane < a.r ? q * a.scale : 0.f, 0.f, 0.f, 0.f};
   float acc[TPL];
 #pragma unroll
@@ -687,15 +693,17 @@ struct RopeLoads {
   float apf[PF];
   int position;
 };
-template <int THREADS, int PF, int r>
+template <int THREADS, int PF, int r, bool FP>
 __device__ __forceinline__ void rope_issue(const ScanArgs &a, const RopeArgs &ra, int b, int h, RopeLoads<PF> &L) {
   // straight-line code, every load unconditional (addresses clamped, surplus values discarded
   // later): the compiler can then count exactly how many loads may still be outstanding at each
   // use, instead of waiting for all of them -- the slab window included -- after a branch
   const int t = threadIdx.x, d = ra.d;
-  const float *p = a.qsrc + (long)b * a.b_stride + (long)h * d + min(t, d - 1);
+  if constexpr (!FP) {
+    const float *p = a.qsrc + (long)b * a.b_stride + (long)h * d + min(t, d - 1);
 #pragma unroll
-  for (int s = 0; s < IG_KS_MAX; ++s) L.part[s] = p[(long)min(s, a.ks - 1) * a.ks_stride];
+    for (int s = 0; s < IG_KS_MAX; ++s) L.part[s] = p[(long)min(s, a.ks - 1) * a.ks_stride];
+  }
   L.bias = a.bias ? a.bias[h * d + min(t, d - 1)] : 0.f;
   L.position = ra.pos[b];
   constexpr int G = THREADS / r;
@@ -714,17 +722,17 @@ __device__ __forceinline__ void rope_frequency(const RopeArgs &ra, RopeLoads<PF>
 // (LEAN: one LDS read after another instead of all of them in flight, for the kernels that also build
 // equalised lists and have no registers left: with the reads in flight they spill, and 384 pairs of 2048
 // tokens take 24.7 us instead of 22.8)
+template <int PF>
+__device__ __forceinline__ void rope_sum(const ScanArgs &a, const RopeArgs &ra, const RopeLoads<PF> &L, float *q_lds) {
+  const float acc = add_partials<IG_KS_MAX>(L.bias, L.part, a.ks);
+  if ((int)threadIdx.x < ra.d) q_lds[threadIdx.x] = acc;
+  __syncthreads();
+}
+// from the head's query in q_lds (a barrier past)
 template <int THREADS, int PF, int r, bool LEAN>
 __device__ __forceinline__ void rope_finish(const ScanArgs &a, const RopeArgs &ra, const RopeLoads<PF> &L,
                                             float *q_lds, float *qr_lds, float *psum, float *qp_lds) {
   const int t = threadIdx.x, d = ra.d;
-  {
-    float acc = L.bias;
-#pragma unroll
-    for (int s = 0; s < IG_KS_MAX; ++s) acc += s < a.ks ? L.part[s] : 0.f;
-    if (t < d) q_lds[t] = acc;
-  }
-  __syncthreads();
   const int half = d / 2;
   if (t < half) {
     double sn, cs;
@@ -764,8 +772,9 @@ static inline bool rope_prologue_fits(int threads, int d, int r) {
   return (d + G - 1) / G <= rope_pf(r);
 }
 
-template <typename T, int R, int NW, int TPW, int WIN, int MINW, bool ROPE, bool EQ>
-__global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, RopeArgs ra, EqArgs eq, int S, FastDiv by_8S, int BH, PairSync *sync, long spin_limit) {
+// FP: the projection runs in the grid's first p.blocks workgroups (project_device.h).
+template <typename T, int R, int NW, int TPW, int WIN, int MINW, bool ROPE, bool EQ, bool FP>
+__global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, RopeArgs ra, EqArgs eq, ProjWords p, int S, FastDiv by_8S, int BH, PairSync *sync, long spin_limit) {
   constexpr int TPL = SlabElem<T>::TPL;
   constexpr int TILE = IG_WAVE * TPL;
   constexpr int NLOAD = TPW * R;              // 1 KiB loads of a wave with all its tiles valid (R > 0)
@@ -774,8 +783,18 @@ __global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, 
   __shared__ float lds_max[NW];
   __shared__ int lds_cnt[NW];
   __shared__ int lds_flag[2];
-  __shared__ int32_t stage[NW * TPW * TILE];
+  __shared__ __attribute__((aligned(16))) int32_t stage[NW * TPW * TILE];
   __shared__ float lds_gmax;
+  int id = blockIdx.x;
+  float *const red = reinterpret_cast<float *>(stage);
+  if constexpr (FP) {
+    static_assert(NW == 4 && sizeof(stage) >= PROJECT_LDS * sizeof(float), "the projecting workgroups' sums lie in the stage");
+    if (id < p.blocks) {
+      project_publish<1>(p, id, red);
+      return;
+    }
+    id -= p.blocks;
+  }
   // Workgroup -> (pair, split): groups of 8 pairs take 8*S consecutive ids, split-major inside the
   // group (id = group*8*S + split*8 + pair%8).  Workgroups are handed to the 8 XCDs round-robin by
   // id, so the S workgroups of a pair land on one XCD and what they all read besides the slab (the
@@ -783,7 +802,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, 
   // fetched into that XCD's L2 once instead of S times, while a pair's workgroups still start
   // within 8*S ids of each other.  (Only where bytes are fetched from changes with the hardware's
   // dispatch order, not the result.)
-  const int grp = by_8S.div(blockIdx.x), rem = blockIdx.x - grp * 8 * S;
+  const int grp = by_8S.div(id), rem = id - grp * 8 * S;
   const int s = rem >> 3, bh = grp * 8 + (rem & 7);
   if (bh >= BH) return;                                   // the grid is rounded up to whole groups
   const int b = a.by_H.div(bh), h = bh - b * a.H;
@@ -808,27 +827,61 @@ __global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, 
   QueryLoads ql;
   constexpr int PF = rope_pf(R > 0 ? R : 64);
   RopeLoads<PF> rl;
-  if constexpr (ROPE) rope_issue<NW * 64, PF, R>(a, ra, b, h, rl);
+  if constexpr (ROPE) rope_issue<NW * 64, PF, R, FP>(a, ra, b, h, rl);
+  else if constexpr (FP) ql.bias = a.bias ? a.bias[h * a.r + min(lane, a.r - 1)] : 0.f;
   else query_issue(a, b, h, lane, 0, ql);
   __builtin_amdgcn_sched_barrier(0);
   // (unconditional, like the query's loads: a branch here would make the compiler wait for the
   // whole window wherever the query is first used)
+  auto fill_window = [&]() {
 #pragma unroll
-  for (int k = 0; k < WIN; ++k) {
-    if constexpr (R > 0) {
-      if (k < NLOAD) v[k] = *reinterpret_cast<const vec *>(tbase[k / R] + (k % R) * PLANE + lane_off);
-    } else {
-      v[k] = *reinterpret_cast<const vec *>(tbase[0] + (long)min(k, nload - 1) * PLANE + lane_off);
+    for (int k = 0; k < WIN; ++k) {
+      if constexpr (R > 0) {
+        if (k < NLOAD) v[k] = *reinterpret_cast<const vec *>(tbase[k / R] + (k % R) * PLANE + lane_off);
+      } else {
+        v[k] = *reinterpret_cast<const vec *>(tbase[0] + (long)min(k, nload - 1) * PLANE + lane_off);
+      }
     }
-  }
+  };
+  fill_window();
   __builtin_amdgcn_sched_barrier(0);
   float q_lane;
-  __shared__ float q_lds[ROPE ? 256 : 1], qr_lds[ROPE ? 256 : 1], psum[ROPE ? NW * 64 : 1], qp_lds[ROPE ? 64 : 1];
+  bool seen = true;      // FP: the query's words were there in time
+  __shared__ float q_lds[ROPE ? 256 : (FP ? 64 : 1)], qr_lds[ROPE ? 256 : 1], psum[ROPE ? NW * 64 : 1], qp_lds[ROPE ? 64 : 1];
   if constexpr (ROPE) {
     rope_frequency(ra, rl);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (FP) {
+      const int t = threadIdx.x;
+      float q = rl.bias;
+      const bool ok = await_query(p, bh, min(t, ra.d - 1), t < ra.d, q);
+      if (t < ra.d) q_lds[t] = q;
+      seen = __syncthreads_and(ok) != 0;
+      if (!seen) {
+        own_query(p, a.bias, b, h, red, q_lds);
+        fill_window();
+      }
+      if (S == 1) clear_words(p, bh, t, NW * IG_WAVE, seen);
+    } else {
+      rope_sum(a, ra, rl, q_lds);
+    }
     rope_finish<NW * 64, PF, R, EQ>(a, ra, rl, q_lds, qr_lds, psum, qp_lds);
     q_lane = lane < R ? qp_lds[lane] * a.scale : 0.f;
+  } else if constexpr (FP) {
+    if (w == 0) {
+      float q = ql.bias;
+      const bool ok = await_query(p, bh, min(lane, a.r - 1), lane < a.r, q);
+      q_lds[lane] = q;
+      if (lane == 0) lds_flag[0] = ok;
+      if (S == 1) clear_words(p, bh, lane, IG_WAVE, ok);
+    }
+    __syncthreads();
+    seen = lds_flag[0] != 0;
+    if (!seen) {
+      own_query(p, a.bias, b, h, red, q_lds);
+      fill_window();
+    }
+    q_lane = lane < a.r ? q_lds[lane] * a.scale : 0.f;
   } else {
     q_lane = query_finish(a, ql);
   }
@@ -947,11 +1000,17 @@ __global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, 
         float q2;
         if constexpr (ROPE) {
           RopeLoads<PF> rl2;
-          rope_issue<NW * 64, PF, R>(a, ra, b, h2, rl2);
+          rope_issue<NW * 64, PF, R, FP>(a, ra, b, h2, rl2);
           rope_frequency(ra, rl2);
           __syncthreads();
+          if constexpr (FP) own_query(p, a.bias, b, h2, red, q_lds);      // (that head's words may be cleared already)
+          else rope_sum(a, ra, rl2, q_lds);
           rope_finish<NW * 64, PF, R, EQ>(a, ra, rl2, q_lds, qr_lds, psum, qp_lds);
           q2 = lane < R ? qp_lds[lane] * a.scale : 0.f;
+        } else if constexpr (FP) {
+          __syncthreads();
+          own_query(p, a.bias, b, h2, red, q_lds);
+          q2 = lane < a.r ? q_lds[lane] * a.scale : 0.f;
         } else {
           QueryLoads ql2;
           query_issue(a, b, h2, lane, 0, ql2);
@@ -1052,6 +1111,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void scan_select_stream(ScanArgs a, 
         __hip_atomic_store(&ps->scnt[lane], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       if (lane == 0) __hip_atomic_store(&ps->done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if constexpr (FP) clear_words(p, bh, lane, IG_WAVE, seen);
     }
   }
 }
@@ -1109,19 +1169,20 @@ int launch_fused(ig_ctx *ctx, const ScanArgs &a, int BH, int ch, hipStream_t s) 
 // streaming form: the (kept channels, tiles per wave) combinations that are built; 4 waves per
 // workgroup, 8 loads of 1 KiB in flight per wave (deeper windows measured the same), registers held
 // to 96 so that five workgroups share a compute unit (one tile or two per wave) or to 128 (four)
-template <typename T, int R, int NW, int TPW, int WIN, int MINW>
-int launch_stream_one(ig_ctx *ctx, const ScanArgs &a, const RopeArgs *ra, const EqArgs *eq, int BH, int S, hipStream_t s) {
-  dim3 grid((unsigned)((BH + 7) / 8 * 8 * S)), block(NW * 64);
+template <typename T, int R, int NW, int TPW, int WIN, int MINW, bool FP>
+int launch_stream_one(ig_ctx *ctx, const ScanArgs &a, const RopeArgs *ra, const EqArgs *eq, const ProjWords &p, int BH, int S,
+                      hipStream_t s) {
+  dim3 grid((unsigned)((BH + 7) / 8 * 8 * S) + (FP ? p.blocks : 0)), block(NW * 64);
   PairSync *sync = static_cast<PairSync *>(ctx->pair_sync);
   if (eq) {
     if constexpr (TPW <= 2 && R > 0) {      // head-equalised lists: the forms with one workgroup per pair
       if (S != 1) return ig_fail(ctx, IG_ESHAPE, "scan: head-equalised lists need one workgroup per pair");
       if (ra) {
-        auto k = scan_select_stream<T, R, NW, TPW, WIN, 3, true, true>;    // (few workgroups per compute unit here)
-        IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, *ra, *eq, S, ig_fast_div(8 * S), BH, sync, ctx->spin_limit);
+        auto k = scan_select_stream<T, R, NW, TPW, WIN, 3, true, true, FP>;    // (few workgroups per compute unit here)
+        IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, *ra, *eq, p, S, ig_fast_div(8 * S), BH, sync, ctx->spin_limit);
       } else {
-        auto k = scan_select_stream<T, R, NW, TPW, WIN, 4, false, true>;
-        IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, RopeArgs{}, *eq, S, ig_fast_div(8 * S), BH, sync, ctx->spin_limit);
+        auto k = scan_select_stream<T, R, NW, TPW, WIN, 4, false, true, FP>;
+        IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, RopeArgs{}, *eq, p, S, ig_fast_div(8 * S), BH, sync, ctx->spin_limit);
       }
       return IG_OK;
     }
@@ -1129,40 +1190,47 @@ int launch_stream_one(ig_ctx *ctx, const ScanArgs &a, const RopeArgs *ra, const 
   }
   if (ra) {
     if constexpr (R > 0) {
-      auto k = scan_select_stream<T, R, NW, TPW, WIN, MINW, true, false>;
-      IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, *ra, EqArgs{}, S, ig_fast_div(8 * S), BH, sync, ctx->spin_limit);
+      auto k = scan_select_stream<T, R, NW, TPW, WIN, MINW, true, false, FP>;
+      IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, *ra, EqArgs{}, p, S, ig_fast_div(8 * S), BH, sync, ctx->spin_limit);
     } else {
       return ig_fail(ctx, IG_ESHAPE, "scan: no rotary prologue for r = %d", a.r);
     }
   } else {
-    auto k = scan_select_stream<T, R, NW, TPW, WIN, MINW, false, false>;
-    IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, RopeArgs{}, EqArgs{}, S, ig_fast_div(8 * S), BH, sync, ctx->spin_limit);
+    auto k = scan_select_stream<T, R, NW, TPW, WIN, MINW, false, false, FP>;
+    IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, RopeArgs{}, EqArgs{}, p, S, ig_fast_div(8 * S), BH, sync, ctx->spin_limit);
   }
   return IG_OK;
 }
 
-template <typename T, int R>
-int launch_stream_r(ig_ctx *ctx, const ScanArgs &a, const RopeArgs *ra, const EqArgs *eq, int BH, int TPW, int S, hipStream_t s) {
-  if (TPW == 1) return launch_stream_one<T, R, 4, 1, 8, 5>(ctx, a, ra, eq, BH, S, s);
-  if (TPW == 2) return launch_stream_one<T, R, 4, 2, 8, 5>(ctx, a, ra, eq, BH, S, s);
+template <typename T, int R, bool FP>
+int launch_stream_r(ig_ctx *ctx, const ScanArgs &a, const RopeArgs *ra, const EqArgs *eq, const ProjWords &p, int BH, int TPW,
+                    int S, hipStream_t s) {
+  if (TPW == 1) return launch_stream_one<T, R, 4, 1, 8, 5, FP>(ctx, a, ra, eq, p, BH, S, s);
+  if (TPW == 2) return launch_stream_one<T, R, 4, 2, 8, 5, FP>(ctx, a, ra, eq, p, BH, S, s);
   if constexpr (R <= 32) {   // (with more channels the unrolled stream of 4 tiles no longer stays in registers; R == 0 is a loop)
-    if (TPW == 4) return launch_stream_one<T, R, 4, 4, 8, 4>(ctx, a, ra, eq, BH, S, s);
+    if (TPW == 4) return launch_stream_one<T, R, 4, 4, 8, 4, FP>(ctx, a, ra, eq, p, BH, S, s);
   }
   return ig_fail(ctx, IG_ESHAPE, "scan: streaming form with %d tiles per wave is not built", TPW);
 }
 
 template <typename T>
-int launch_stream(ig_ctx *ctx, const ScanArgs &a, const RopeArgs *ra, const EqArgs *eq, int BH, int TPW, int S, hipStream_t s) {
+int launch_stream(ig_ctx *ctx, const ScanArgs &a, const RopeArgs *ra, const EqArgs *eq, const ProjWords *p, int BH, int TPW, int S,
+                  hipStream_t s) {
   if (S < 1 || S > IG_SPLIT_MAX) return ig_fail(ctx, IG_ESHAPE, "scan: %d splits per pair", S);
   if (S > 1) {
     int rc = ig_ensure_zeroed(ctx, &ctx->pair_sync, &ctx->pair_sync_bytes, (size_t)BH * IG_PAIR_SYNC_BYTES);
     if (rc) return rc;
   }
   if constexpr (sizeof(T) == 2) {
-    if (a.r == 38) return launch_stream_r<T, 38>(ctx, a, ra, eq, BH, TPW, S, s);
-    if (a.r == 25) return launch_stream_r<T, 25>(ctx, a, ra, eq, BH, TPW, S, s);
+    if (p) {
+      if (a.r == 38) return launch_stream_r<T, 38, true>(ctx, a, ra, eq, *p, BH, TPW, S, s);
+      if (a.r == 25) return launch_stream_r<T, 25, true>(ctx, a, ra, eq, *p, BH, TPW, S, s);
+      return launch_stream_r<T, 0, true>(ctx, a, ra, eq, *p, BH, TPW, S, s);
+    }
+    if (a.r == 38) return launch_stream_r<T, 38, false>(ctx, a, ra, eq, ProjWords{}, BH, TPW, S, s);
+    if (a.r == 25) return launch_stream_r<T, 25, false>(ctx, a, ra, eq, ProjWords{}, BH, TPW, S, s);
   }
-  if (a.r <= 64) return launch_stream_r<T, 0>(ctx, a, ra, eq, BH, TPW, S, s);
+  if (a.r <= 64) return launch_stream_r<T, 0, false>(ctx, a, ra, eq, ProjWords{}, BH, TPW, S, s);
   return ig_fail(ctx, IG_ESHAPE, "scan: streaming form is not built for r = %d", a.r);
 }
 
@@ -1223,8 +1291,23 @@ int launch_project_scan(ig_ctx *ctx, const ig_desc *d, const ScanArgs &a, const 
 #undef CASE
 }
 
+// Loads in flight per wave: a rolling window, which need not divide r.  As many as leave four workgroups a compute unit, 20,
+// so that the projecting ones and the scan's fit the chip together (256 pairs: 12, 16, 20, 24, 40 loads the same to
+// 0.5 us, 40 a little behind), and 12, six workgroups, where there are more pairs than that (1120 pairs: 12 loads
+// 42.2 us, 20 42.8, 40 43.6).  One sequence's 32 pairs lose 1.8 us with 12.
+template <int NW>
+int launch_project_and_scan_fused(ig_ctx *ctx, const ScanArgs &a, ProjWords p, int BH, hipStream_t s) {
+  p.blocks = (p.nCblk * p.KQ + NW / 4 * 8 - 1) / (NW / 4 * 8) * 8 * p.groups;
+  dim3 grid(BH + p.blocks), block(NW * 64);
+  auto k = a.r <= 4 ? project_and_scan_fused<half_t, 4, NW>
+                    : (a.r <= 8 ? project_and_scan_fused<half_t, 8, NW>
+                                : (a.r <= 12 || BH > 512 ? project_and_scan_fused<half_t, 12, NW> : project_and_scan_fused<half_t, 20, NW>));
+  IG_LAUNCH(ctx, IG_K_SCAN, k, grid, block, s, a, p);
+  return IG_OK;
+}
+
 template <typename T>
-int launch_scan(ig_ctx *ctx, const ig_desc *d, ScanArgs &a, const QSource *rope, const EqArgs *eq, hipStream_t s) {
+int launch_scan(ig_ctx *ctx, const ig_desc *d, ScanArgs &a, const QSource *rope, const EqArgs *eq, const ProjWords *p, hipStream_t s) {
   const int BH = d->B * d->H;
   const int nTiles = a.nValid;     // the work, not the capacity, picks the kernel
   // One workgroup per (b,h) when it fits and there are enough (b,h) pairs to fill the chip;
@@ -1234,15 +1317,22 @@ int launch_scan(ig_ctx *ctx, const ig_desc *d, ScanArgs &a, const QSource *rope,
   // A split needs the pairs' records.  Where they would have to be allocated under a capture, which is
   // refused, the forms below serve the call with the same lists: one workgroup per pair without any
   // workspace (64 pairs and more, up to 32768 tokens), or the three kernels if theirs are there.
-  if (stream && S > 1 && !rope && !eq && ctx->pair_sync_bytes < (size_t)BH * IG_PAIR_SYNC_BYTES && ig_capturing(ctx))
+  if constexpr (sizeof(T) == 2) {
+    if (p && !rope && !eq) {
+      if (nTiles <= 4) return launch_project_and_scan_fused<4>(ctx, a, *p, BH, s);
+      if (!stream && BH >= 128 && nTiles <= 8) return launch_project_and_scan_fused<8>(ctx, a, *p, BH, s);
+    }
+  }
+  if (stream && S > 1 && !rope && !eq && !p && ctx->pair_sync_bytes < (size_t)BH * IG_PAIR_SYNC_BYTES && ig_capturing(ctx))
     stream = false;
   if (stream) {
-    if (!rope) return launch_stream<T>(ctx, a, nullptr, eq, BH, tpw, S, s);
+    if (!rope) return launch_stream<T>(ctx, a, nullptr, eq, p, BH, tpw, S, s);
     RopeArgs ra{rope->A_p, rope->pos, d->d, -2.0 / (double)d->d * log2((double)d->rope_theta)};
-    return launch_stream<T>(ctx, a, &ra, eq, BH, tpw, S, s);
+    return launch_stream<T>(ctx, a, &ra, eq, p, BH, tpw, S, s);
   }
   if (rope) return ig_fail(ctx, IG_EINVAL, "scan: a rotary query source needs the streaming form");
   if (eq) return ig_fail(ctx, IG_EINVAL, "scan: head-equalised lists need the streaming form");
+  if (p) return ig_fail(ctx, IG_EINVAL, "scan: this shape's launch does not hold the projection");
   const bool fused = ig_scan_is_fused(d);
   if (fused) {
     // When all workgroups fit on the chip at once (one round) a wave should have all its channels
@@ -1373,6 +1463,15 @@ bool ig_scan_takes_rope(const ig_desc *d) {
   return d->rope && built_in(d) && ig_scan_stream_form(d, &tpw, &S) && rope_prologue_fits(256, d->d, d->r);
 }
 
+// Shapes whose scan's launch holds the projection too.
+bool ig_scan_joins_projection(const ig_desc *d, const ProjGeom &g) {
+  if (!g.mfma || g.NBtot > 2 || d->r > 64) return false;
+  if (d->rope) return ig_scan_takes_rope(d);
+  int tpw = 0, S = 0;
+  const int nValid = (d->N + ig_tile_tokens(d->dtype) - 1) / ig_tile_tokens(d->dtype);
+  return nValid <= 4 || ig_scan_stream_form(d, &tpw, &S) || (nValid <= 8 && d->B * d->H >= 128);
+}
+
 // One workgroup per (b,h) and a single kernel when a pair fits 16 waves (scores stay in registers)
 // or 32768 tokens (scores parked in LDS) and there are enough pairs to fill the chip; otherwise
 // one wave per tile and the threshold pass in two further kernels.
@@ -1446,8 +1545,9 @@ int ig_launch_scan_select(ig_ctx *ctx, const ig_desc *d, const QSource &q, const
   if (rc) return rc;
   const QSource *rope = q.A_p ? &q : nullptr;
   if (rope && !ig_scan_takes_rope(d)) return ig_fail(ctx, IG_EINVAL, "scan: this shape takes no rotary query source");
-  return d->dtype == IG_F16 ? launch_scan<half_t>(ctx, d, a, rope, nullptr, s)
-                            : launch_scan<float>(ctx, d, a, rope, nullptr, s);
+  if (q.proj && d->dtype != IG_F16) return ig_fail(ctx, IG_EINVAL, "scan: the projection joins half precision only");
+  return d->dtype == IG_F16 ? launch_scan<half_t>(ctx, d, a, rope, nullptr, q.proj, s)
+                            : launch_scan<float>(ctx, d, a, rope, nullptr, nullptr, s);
 }
 
 // Shapes whose scan builds the head-equalised lists itself: the streaming form with one
@@ -1469,5 +1569,5 @@ int ig_launch_scan_equalized(ig_ctx *ctx, const ig_desc *d, const QSource &q, co
   if (rc) return rc;
   EqArgs eq{static_cast<unsigned long long *>(ctx->seq_sync), thr_cnt_opt, cap};
   const QSource *rope = q.A_p ? &q : nullptr;
-  return launch_scan<half_t>(ctx, d, a, rope, &eq, s);
+  return launch_scan<half_t>(ctx, d, a, rope, &eq, q.proj, s);
 }

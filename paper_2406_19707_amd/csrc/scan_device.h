@@ -4,7 +4,7 @@
 // layer's attention in one launch.
 #ifndef IG_SCAN_DEVICE_H
 #define IG_SCAN_DEVICE_H
-#include "ig_internal.h"
+#include "project_device.h"
 
 struct ScanArgs {
   const void *slab;
@@ -52,9 +52,7 @@ __device__ __forceinline__ void query_issue(const ScanArgs &a, int b, int h, int
   ql.live = lane + 64 * k < a.r;
 }
 __device__ __forceinline__ float query_finish(const ScanArgs &a, const QueryLoads &ql) {
-  float acc = ql.bias;
-#pragma unroll
-  for (int s = 0; s < IG_KS_MAX; ++s) acc += s < a.ks ? ql.part[s] : 0.f;
+  const float acc = add_partials<IG_KS_MAX>(ql.bias, ql.part, a.ks);
   return ql.live ? acc * a.scale : 0.f;
 }
 // lane l (< CH) gets q[j0 + l] out of the four per-lane registers
@@ -141,6 +139,36 @@ __device__ __forceinline__ void scan_tile_given_q(const ScanArgs &a, const T *ti
   for (int j0 = CH; j0 < a.r; j0 += CH) {
     load_block<T, CH>(tile, a.r, j0, lane, v);
     fma_block<T, CH>(v, query_block(qv, j0, lane), acc);
+  }
+}
+
+// The same for at most 64 channels (lane l holds channel l's entry) as a rolling window of CH loads: a register is
+// refilled as soon as it is used, so that CH loads stay in flight up to the last block.
+template <typename T, int CH>
+__device__ __forceinline__ void scan_tile_rolling(const ScanArgs &a, const T *tile, int lane, typename SlabElem<T>::vec (&v)[CH],
+                                                  float q_lane, float (&acc)[SlabElem<T>::TPL]) {
+  constexpr int TPL = SlabElem<T>::TPL;
+  constexpr int PLANE = IG_WAVE * TPL * (int)sizeof(T);
+  const char *base = reinterpret_cast<const char *>(tile) + lane * (int)(TPL * sizeof(T));
+  const int qbits = __float_as_int(q_lane);
+  int j0 = 0;
+  for (; j0 + CH < a.r; j0 += CH) {
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      const float qj = __int_as_float(__builtin_amdgcn_readlane(qbits, j0 + j));
+#pragma unroll
+      for (int e = 0; e < TPL; ++e) acc[e] = fmaf((float)v[j][e], qj, acc[e]);
+      v[j] = *reinterpret_cast<const typename SlabElem<T>::vec *>(base + (long)min(j0 + CH + j, a.r - 1) * PLANE);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < CH; ++j) {
+    if (j0 + j < a.r) {
+      const float qj = __int_as_float(__builtin_amdgcn_readlane(qbits, j0 + j));
+#pragma unroll
+      for (int e = 0; e < TPL; ++e) acc[e] = fmaf((float)v[j][e], qj, acc[e]);
+    }
   }
 }
 
@@ -237,8 +265,11 @@ __device__ __forceinline__ void select_held(const ScanArgs &a, const int bh, flo
 }
 
 // One workgroup per (b,h); wave w scans tile w (nValid <= NW) and keeps its scores in registers.
-template <typename T, int CH, int NW>
-__device__ __forceinline__ void scan_select_fused_body(const ScanArgs &a, const int bh) {
+// FP: the query comes from the projecting workgroups of the same launch.  It is waited for behind the first
+// block of slab loads, by wave 0; LDS and a barrier hand it to the others.
+template <typename T, int CH, int NW, bool FP = false>
+__device__ __forceinline__ void scan_select_fused_body(const ScanArgs &a, const int bh, const ProjWords *p = nullptr,
+                                                       float *red = nullptr) {
   constexpr int TPL = SlabElem<T>::TPL;
   constexpr int TILE = IG_WAVE * TPL;
   const int b = a.by_H.div(bh), h = bh - b * a.H;
@@ -249,7 +280,30 @@ __device__ __forceinline__ void scan_select_fused_body(const ScanArgs &a, const 
   float acc[TPL];
 #pragma unroll
   for (int e = 0; e < TPL; ++e) acc[e] = 0.f;
-  if (active) scan_tile<T, CH>(a, tile, b, h, lane, acc);
+  if constexpr (FP) {
+    __shared__ float q_lds[IG_WAVE];
+    __shared__ int q_seen;
+    float q = a.bias ? a.bias[h * a.r + min(lane, a.r - 1)] : 0.f;
+    typename SlabElem<T>::vec v[CH];
+    load_block<T, CH>(tile, a.r, 0, lane, v);
+    __builtin_amdgcn_sched_barrier(0);
+    if (w == 0) {
+      const bool seen = await_query(*p, bh, min(lane, a.r - 1), lane < a.r, q);
+      q_lds[lane] = q;
+      if (lane == 0) q_seen = seen;
+      clear_words(*p, bh, lane, IG_WAVE, seen);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < CH; ++i) keep_loaded(v[i]);
+    if (!q_seen) {
+      own_query(*p, a.bias, b, h, red, q_lds);
+      load_block<T, CH>(tile, a.r, 0, lane, v);
+    }
+    if (active) scan_tile_rolling<T, CH>(a, tile, lane, v, lane < a.r ? q_lds[lane] * a.scale : 0.f, acc);
+  } else {
+    if (active) scan_tile<T, CH>(a, tile, b, h, lane, acc);
+  }
   select_held<T, NW>(a, bh, acc, active, w, lane);
 }
 
