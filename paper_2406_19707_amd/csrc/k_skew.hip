@@ -74,25 +74,31 @@ __global__ __launch_bounds__(256) void gram_heads(const float *__restrict__ Qcal
 // registers, so that a pair's inner product is RP = DP/4 multiply-adds and two cross-lane steps and every
 // lane works out its own pair's rotation.  All m with the same highest bit that differ only in m's low
 // (up to 4) bits run without leaving the registers: between two of them the B columns change lanes, by
-// one DPP move (xor 1, 2, 7 or 15 inside 16 lanes reaches every pairing).  Then the columns go back to
-// LDS, the only point where the waves meet (11 times a sweep of 127 rounds at DP = 128).
+// one DPP move (xor 1, 2, 7 or 15 inside 16 lanes reaches every pairing).  The 31 rounds inside the wave's own 32
+// columns (m < 32) trade columns between the A and B registers instead of going through LDS (four instructions
+// a register, against 3.3 us for a trip of both columns); then blocks of 16 meet, all m with the same highest
+// bit with the A columns kept and only the B columns stored and loaded (6 such trips a sweep of 127 rounds at
+// DP = 128, the points where the waves meet).
 // Rotations are square-root free on the columns (two multiply-adds an element pair; the cosines
 // are collected in a factor per column and multiplied in when it goes back to LDS).  Angles come from
 // float32 (a rotation by a slightly wrong angle is still a rotation; its cosine is worked out in double),
 // which leaves 1e-7 of a pair's inner product for the next sweep.
-// The sweeps end with one that met no pair further from orthogonal than a cosine of 1e-13, where rounding
-// leaves 1e-15.  Nothing coarser will do: columns whose norms differ by less than their cosine are still
-// turned by large angles, which carries what a later pair has left into a pair that was done already, and
-// nearly equal singular values make their columns of V as much worse as they are close.  (With an end at a
-// cosine of 1e-5, which is one sweep less, 128 singular values within 1e-3 of each other left A^T A 2.8e-7
-// from the identity and moved entries of V by 1e-3.)
+// When a sweep has met no cosine over 1e-6, S^T S is formed on the matrix cores (10 us) and every pair is looked at:
+// cosines of at most 1e-13, where rounding leaves 1e-15, end the sweeps if each is also small against the distance
+// of its pair's squared norms (1e-10 of it); if not, after one more sweep.  Nothing coarser will do: columns whose
+// norms differ by less than their cosine are still turned by large angles, which carries what a later pair has
+// left into a pair that was done already, and nearly equal singular values make their columns of V as much worse
+// as they are close.  (With an end at a cosine of 1e-5, 128 singular values within 1e-3 of each other left A^T A
+// 2.8e-7 from the identity and moved entries of V by 1e-3; with 1e-13 whatever the distance, 64 within 1e-4 of
+// each other moved them by 1e-5.)
 // Bound by the double-precision issue rate of the head's compute unit, one wave per SIMD: a round is
 // 3 multiply-adds and 2 moves for each of RP rows and a chain of about 40 dependent operations.
-// The pivoted factor matters: L's columns come out graded, which takes 9 sweeps where the columns of G
+// The pivoted factor matters: L's columns come out graded, which takes 8 sweeps where the columns of G
 // itself take more than 20, and a head without full rank is found by a pivot at rounding level: those
 // columns are left out of the rotations and V is completed to an orthonormal basis.
-// Measured on 32 heads of 128 columns: 0.89 ms (factor 0.12, nine sweeps 0.72, check and output 0.04), against
-// 34.8 ms for two-sided rotations of G and V through the L2 (jacobi_heads).
+// Measured on 32 heads of 128 columns, with the Gram matrices: 0.72 to 0.76 ms; 0.92 with both columns through LDS at
+// every highest bit and a ninth sweep that only looked, of which the kept A columns are worth 0.05, the trades
+// 0.02 and the sweep 0.08.  Two-sided rotations of G and V through the L2 (jacobi_heads): 34.8 ms.
 __device__ __forceinline__ double join_d(unsigned lo, unsigned hi) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
@@ -120,11 +126,12 @@ template <int RP> __device__ __forceinline__ double column_dot(const double (&a)
   for (int k = 0; k < RP; ++k) s[k & 3] = fma(a[k], b[k], s[k & 3]);
   return sum_parts((s[0] + s[1]) + (s[2] + s[3]));
 }
+constexpr double FAR2 = 1e-12;             // a cosine of 1e-6, squared
 // Tangent, cosine and 1 / cosine of the rotation that makes columns with squared norms al, be and inner
-// product ga orthogonal (0, 1, 1 where they are to rounding); `big` is set when they were not nearly so.
-__device__ __forceinline__ void rotation(double al, double be, double ga, double &t, double &c, double &ic, bool &big) {
+// product ga orthogonal (0, 1, 1 where they are to rounding); `far` is set when they were not nearly so.
+__device__ __forceinline__ void rotation(double al, double be, double ga, double &t, double &c, double &ic, bool &far) {
   const double g2 = ga * ga, ab = al * be;
-  big = big || g2 > 1e-26 * ab;
+  far = far || g2 > FAR2 * ab;
   const float z = (float)(be - al) * __builtin_amdgcn_rcpf((float)(2.0 * ga)), az = fabsf(z);
   // (z^2 leaves float32's range where one column is far shorter than the other)
   float tf = __builtin_amdgcn_rcpf(az + (az < 1e9f ? __builtin_amdgcn_sqrtf(fmaf(z, z, 1.f)) : az));
@@ -145,10 +152,10 @@ template <int RP> struct Pair {
 // Rounds X, X + 1, .. of `rounds` (1, 2, 4, 8 or 16): rotate every pair, move the B columns on.  Spelled out
 // by recursion: a loop around the four kinds of move copies the columns at every turn.
 template <int X, int RP>
-__device__ __forceinline__ void rotate_rounds(Pair<RP> &P, int rounds, bool &big) {
+__device__ __forceinline__ void rotate_rounds(Pair<RP> &P, int rounds, bool &far) {
   const double ga = column_dot<RP>(P.a, P.b) * (P.Da * P.Db);
   double t, c, ic;
-  rotation(P.na, P.nb, ga, t, c, ic, big);
+  rotation(P.na, P.nb, ga, t, c, ic, far);
   const double ta = -t * (P.Db * P.Ia), tb = t * (P.Da * P.Ib);
 #pragma unroll
   for (int k = 0; k < RP; ++k) {
@@ -174,8 +181,48 @@ __device__ __forceinline__ void rotate_rounds(Pair<RP> &P, int rounds, bool &big
     P.nb = dpp_d<CTRL>(P.nb);
     P.Db = dpp_d<CTRL>(P.Db);
     P.Ib = dpp_d<CTRL>(P.Ib);
-    rotate_rounds<X + 1, RP>(P, rounds, big);
+    rotate_rounds<X + 1, RP>(P, rounds, far);
   }
+}
+// From pairs that differ in bit X of their column number to pairs that differ in bit X + 1: column A of the lanes
+// with bit X of their number set and column B of those without change places, between lanes l and l ^ (1 << X).
+template <int X> __device__ __forceinline__ int lane_xor(int v) {
+  static_assert(X >= 0 && X < 4, "inside 16 lanes");
+  if constexpr (X == 0) return __builtin_amdgcn_mov_dpp(v, DPP_QUAD_1032, 0xF, 0xF, true);
+  if constexpr (X == 1) return __builtin_amdgcn_mov_dpp(v, DPP_QUAD_2301, 0xF, 0xF, true);
+  if constexpr (X == 2) return __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(v, DPP_ROW_HALF_MIRROR, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+  return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);       // row_ror:8
+}
+template <int X> __device__ __forceinline__ void trade(int &a, int &b, bool set) {
+  const int got = lane_xor<X>(set ? a : b);
+  a = set ? got : a;
+  b = set ? b : got;
+}
+template <int X> __device__ __forceinline__ void trade(double &a, double &b, bool set) {
+  const unsigned long long ua = (unsigned long long)__double_as_longlong(a), ub = (unsigned long long)__double_as_longlong(b);
+  int al = (int)ua, ah = (int)(ua >> 32), bl = (int)ub, bh = (int)(ub >> 32);
+  trade<X>(al, bl, set);
+  trade<X>(ah, bh, set);
+  a = join_d((unsigned)al, (unsigned)ah);
+  b = join_d((unsigned)bl, (unsigned)bh);
+}
+// 1 / D anew.  The product that rotate_rounds keeps drifts from it by a few roundings a round, always the same way, and
+// a rotation whose two columns are scaled by factors that do not cancel is not orthogonal: with 32 to 64 rounds
+// between, singular values within 1e-3 of each other had their vectors off by 7e-7.
+__device__ __forceinline__ double inverse_of(double D) {
+  double y = __builtin_amdgcn_rcp(D);
+  y = fma(fma(-D, y, 1.0), y, y);
+  return fma(fma(-D, y, 1.0), y, y);
+}
+template <int X, int RP> __device__ __forceinline__ void regroup(Pair<RP> &P, int &ia, int &ib, int lane) {
+  const bool set = (lane >> X) & 1;
+#pragma unroll
+  for (int k = 0; k < RP; ++k) trade<X>(P.a[k], P.b[k], set);
+  trade<X>(P.na, P.nb, set);
+  trade<X>(P.Da, P.Db, set);
+  P.Ia = inverse_of(P.Da);
+  P.Ib = inverse_of(P.Db);
+  trade<X>(ia, ib, set);
 }
 __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
   v = max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, DPP_QUAD_1032, 0xF, 0xF, false));
@@ -185,6 +232,23 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
   const unsigned r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
   const unsigned r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
   return max(max(r0, r1), max(r2, r3));
+}
+
+// S^T S by the four waves, in tiles of 16 x 16 (the diagonal ones or those above): f(row, column, value) for
+// each entry of a tile, rows and columns as in gram_heads (entries past the head's columns are zeros).
+template <int DP, int LD, typename F>
+__device__ __forceinline__ void gram_tiles(const double *S, int w, int g, int part, bool diagonal, F &&f) {
+  constexpr int NBLK = DP / 16, RP = DP / 4;
+  for (int t = w; t < (diagonal ? NBLK : NBLK * (NBLK - 1) / 2); t += 4) {
+    int ta = diagonal ? t : 0, rest = diagonal ? 0 : t + 1;
+    while (!diagonal && rest >= NBLK - ta) { rest -= NBLK - ta - 1; ++ta; }
+    const double *va = S + (ta * 16 + g) * LD + part, *vb = S + ((ta + rest) * 16 + g) * LD + part;
+    double4v acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+    for (int k = 0; k < RP; ++k) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(va[4 * k], vb[4 * k], acc, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) f(ta * 16 + v * 4 + part, (ta + rest) * 16 + g, acc[v]);
+  }
 }
 
 template <int DP>
@@ -257,10 +321,9 @@ __global__ __launch_bounds__(256, 1) void onesided_heads(const double *__restric
   __syncthreads();
   const double least = 2.3e-16 * top;      // a pivot no larger than G's rounding ends the factorisation
   int rank = 0;
+  unsigned k0 = key[lane], k1 = DP > 64 ? key[64 % DP + lane] : 0u;
   for (int j = 0; j < d; ++j) {
-    unsigned k = key[lane];
-    if constexpr (DP > 64) k = max(k, key[64 + lane]);
-    k = wave_max_u32(k);                   // the same in every wave
+    const unsigned k = wave_max_u32(max(k0, k1));      // the same in every wave
     if (k == 0u) break;
     const int p = 127 - (int)(k & 127u);
     const double best = diag[p];
@@ -292,13 +355,17 @@ __global__ __launch_bounds__(256, 1) void onesided_heads(const double *__restric
       rr[i] = S[j * LD + rb + 16 * i];
       cc[i] = S[j * LD + cb + 16 * i] * -inv;
     }
+    __syncthreads();
+    // (the next pivot's keys come in under the update)
+    k0 = key[lane];
+    k1 = DP > 64 ? key[64 % DP + lane] : 0u;
 #pragma unroll
     for (int jj = 0; jj < TR; ++jj)
 #pragma unroll
       for (int i = 0; i < TR; ++i) T[i][jj] = fma(rr[i], cc[jj], T[i][jj]);
-    __syncthreads();
     rank = j + 1;
   }
+  __syncthreads();
   for (int e = tid; e < DP * DP; e += NT) {
     const int c = e / DP;
     S[c * LD + e % DP] = c < rank ? S[c * LD + e % DP] * (1.0 / sqrt(lvec[c])) : 0.0;
@@ -306,64 +373,100 @@ __global__ __launch_bounds__(256, 1) void onesided_heads(const double *__restric
   __syncthreads();
   // ---- one-sided Jacobi sweeps ----
   const int g = lane & 15, part = lane >> 4;
-  bool big = true;
-  for (int sweep = 0; sweep < MAX_SWEEPS && big; ++sweep) {
-    big = false;
-    for (int pass = 0; pass < 4 + NBLK - 1; ++pass) {
-      // passes 0..3: m's highest bit is `pass`, pairs inside the wave's own 32 columns; passes 4..: block
-      // b against block b ^ M, M = pass - 3
-      int ca, cbx, rounds;
-      if (pass < 4) {
-        const int lowbits = (1 << pass) - 1;
-        ca = 32 * w + (((g & ~lowbits) << 1) | (g & lowbits));
-        cbx = ca ^ (1 << pass);
-        rounds = 1 << pass;
-      } else {
-        const int M = pass - 3, hb = 31 - __clz(M);
-        const int b0 = ((w >> hb) << (hb + 1)) | (w & ((1 << hb) - 1));
-        ca = b0 * 16 + g;
-        cbx = (b0 ^ M) * 16 + g;
-        rounds = 16;
-      }
-      if (w < NBLK / 2) {
-        double *pa = S + ca * LD + part;
-        const double *pb = S + cbx * LD + part;
-        Pair<RP> P;
+  bool straight = false, square = false, seen_small = false;
+  for (int sweep = 0; sweep < MAX_SWEEPS && !straight; ++sweep) {
+    bool far = false;
+    Pair<RP> P;
+    double *pa = S, *pb = S;               // where the lane's columns A and B lie
+    auto load_a = [&]() {
 #pragma unroll
-        for (int k = 0; k < RP; ++k) {
-          P.a[k] = pa[4 * k];
-          P.b[k] = pb[4 * k];
-        }
-        P.na = column_dot<RP>(P.a, P.a);
-        P.nb = column_dot<RP>(P.b, P.b);
-        P.Da = P.Ia = P.Db = P.Ib = 1.0;
-        rotate_rounds<0, RP>(P, rounds, big);
-        // where the moves (xor 1, 2, 1, 7, 1, 2, 1, 15, ...) have taken the B columns: lane g holds lane
-        // g ^ moved's (in passes 0..3 only bits below `pass` flip, which the lane's column shares with g)
-        const int moved = rounds == 4 ? 2 : rounds - 1;
-        double *qb = S + (cbx ^ moved) * LD + part;
+      for (int k = 0; k < RP; ++k) P.a[k] = pa[4 * k];
+      P.na = column_dot<RP>(P.a, P.a);
+      P.Da = P.Ia = 1.0;
+    };
+    auto load_b = [&]() {
 #pragma unroll
-        for (int k = 0; k < RP; ++k) {
-          pa[4 * k] = P.a[k] * P.Da;
-          qb[4 * k] = P.b[k] * P.Db;
+      for (int k = 0; k < RP; ++k) P.b[k] = pb[4 * k];
+      P.nb = column_dot<RP>(P.b, P.b);
+      P.Db = P.Ib = 1.0;
+    };
+    auto store_a = [&]() {
+#pragma unroll
+      for (int k = 0; k < RP; ++k) pa[4 * k] = P.a[k] * P.Da;
+    };
+    auto store_b = [&]() {
+#pragma unroll
+      for (int k = 0; k < RP; ++k) pb[4 * k] = P.b[k] * P.Db;
+    };
+    // pairs inside the wave's own 32 columns, by the highest bit in which their numbers differ; ia, ib: which
+    // columns the lane holds.  The rounds' moves (xor 1, 2, 1, 7, 1, 2, 1, 15, ...) have taken the B columns to where
+    // lane g holds lane g ^ 0, 1, 2, 7 and 15's (bits below the pair's own: any order in there meets every pair).
+    if (w < NBLK / 2) {
+      int ia = 32 * w + 2 * g, ib = ia + 1;
+      pa = S + ia * LD + part;
+      pb = S + ib * LD + part;
+      load_a();
+      load_b();
+      rotate_rounds<0, RP>(P, 1, far);
+      regroup<0, RP>(P, ia, ib, lane);
+      rotate_rounds<0, RP>(P, 2, far);
+      ib = __shfl_xor(ib, 1, 64);
+      regroup<1, RP>(P, ia, ib, lane);
+      rotate_rounds<0, RP>(P, 4, far);
+      ib = __shfl_xor(ib, 2, 64);
+      regroup<2, RP>(P, ia, ib, lane);
+      rotate_rounds<0, RP>(P, 8, far);
+      ib = __shfl_xor(ib, 7, 64);
+      regroup<3, RP>(P, ia, ib, lane);
+      rotate_rounds<0, RP>(P, 16, far);
+      ib = __shfl_xor(ib, 15, 64);
+      pa = S + ia * LD + part;
+      pb = S + ib * LD + part;
+      store_a();
+      store_b();
+    }
+    __syncthreads();
+    // block b0 against block b0 ^ M.  All M with the same highest bit hb pair the blocks without that bit with
+    // those that have it, so a wave keeps its block A through them.
+    for (int hb = 1; (1 << hb) < NBLK; ++hb) {
+      const int b0 = ((w >> hb) << (hb + 1)) | (w & ((1 << hb) - 1));
+      pa = S + (b0 * 16 + g) * LD + part;
+      if (w < NBLK / 2) load_a();
+      for (int M = 1 << hb; M < 2 << hb; ++M) {
+        if (w < NBLK / 2) {
+          pb = S + ((b0 ^ M) * 16 + g) * LD + part;
+          load_b();
+          P.Ia = inverse_of(P.Da);
+          rotate_rounds<0, RP>(P, 16, far);
+          pb = S + ((b0 ^ M) * 16 + (g ^ 15)) * LD + part;
+          store_b();
+          if (M == (2 << hb) - 1) store_a();
         }
+        __syncthreads();
       }
-      __syncthreads();
     }
-    big = __syncthreads_or(big) != 0;
+    if (__syncthreads_or(far) && sweep + 1 < MAX_SWEEPS) continue;
+    // S^T S on the matrix cores: the diagonal tiles give the squared norms, the others are held against them
+    bool off13 = false, off9 = false, close = false;
+    gram_tiles<DP, LD>(S, w, g, part, true, [&](int r, int c, double v) {
+      if (r == c) diag[r] = v;
+    });
+    __syncthreads();
+    gram_tiles<DP, LD>(S, w, g, part, false, [&](int r, int c, double v) {
+      const double nn = diag[r] * diag[c];
+      off13 = off13 || (r != c && !(v * v <= 1e-26 * nn));
+      off9 = off9 || (r != c && !(v * v <= 1e-18 * nn));
+      // (how far the pair is from the vectors it stands for: its cosine over the distance of its squared norms)
+      const double most = fmax(diag[r], diag[c]), apart = diag[r] - diag[c];
+      close = close || (r != c && !(v * v * most * most <= 1e-20 * apart * apart * nn));
+    });
+    const bool small = __syncthreads_or(off13) == 0;
+    square = __syncthreads_or(off9) == 0;
+    straight = small && (__syncthreads_or(close) == 0 || seen_small);
+    seen_small = small;
   }
-  // ---- norms, normalised columns (diag and lvec now belong to columns) ----
-  if (tid < DP) {
-    const int c = tid;
-    double n2 = 0.0;
-#pragma unroll 8
-    for (int i = 0; i < DP; ++i) {
-      const double v = S[c * LD + (i + c) % DP];      // (a different row per lane: no bank twice)
-      n2 = fma(v, v, n2);
-    }
-    diag[c] = n2;
-    lvec[c] = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
-  }
+  // ---- normalised columns (diag, the squared norms, and lvec now belong to columns) ----
+  if (tid < DP) lvec[tid] = diag[tid] > 0.0 ? 1.0 / sqrt(diag[tid]) : 0.0;
   __syncthreads();
   for (int e = tid; e < DP * DP; e += NT) S[(e / DP) * LD + e % DP] *= lvec[e / DP];
   __syncthreads();
@@ -402,20 +505,12 @@ __global__ __launch_bounds__(256, 1) void onesided_heads(const double *__restric
     if (tid < d) S[c * LD + tid] *= 1.0 / sqrt(n2);
     __syncthreads();
   }
-  // ---- what the result rests on, measured on the result: V^T V against the identity (18 us on 32 heads) ----
-  bool off = false;
-  for (int t = w; t < NBLK * (NBLK + 1) / 2; t += 4) {
-    int ta = 0, rest = t;
-    while (rest >= NBLK - ta) { rest -= NBLK - ta; ++ta; }
-    const double *va = S + (ta * 16 + g) * LD + part, *vb = S + ((ta + rest) * 16 + g) * LD + part;
-    double4v acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 8
-    for (int k = 0; k < RP; ++k) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(va[4 * k], vb[4 * k], acc, 0, 0, 0);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {            // (rows and columns as in gram_heads; those past d are zeros)
-      const int r = v * 4 + part;
-      off = off || !(fabs(acc[v] - (rest == 0 && r == g && ta * 16 + r < d ? 1.0 : 0.0)) <= 1e-9);
-    }
+  // ---- what the result rests on: the cosines measured last, and for a completed V what V^T V is ----
+  bool off = !square;
+  if (rank < d) {
+    const auto check = [&](int r, int c, double v) { off = off || !(fabs(v - (r == c && r < d ? 1.0 : 0.0)) <= 1e-9); };
+    gram_tiles<DP, LD>(S, w, g, part, true, check);
+    gram_tiles<DP, LD>(S, w, g, part, false, check);
   }
   if (__ballot(off) && lane == 0) atomicOr(status, IG_STATUS_NOCONV);
   // ---- rank the singular values (descending, the earlier column first on ties), fix signs, write ----

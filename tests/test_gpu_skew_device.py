@@ -185,3 +185,26 @@ def test_queries_that_are_not_finite_are_reported(ctx, d, bad):
     assert np.array_equal(A[[0, 2]], A0[[0, 2]]) and np.array_equal(sigma[[0, 2]], sigma0[[0, 2]])
     if d <= 128:
         assert np.isnan(A[1]).all() and np.isnan(sigma[1]).all()
+
+
+@pytest.mark.parametrize("d", [34, 64, 96, 128])
+@pytest.mark.parametrize("spread", [1e-3, 1e-4, 1e-5])
+def test_many_heads_of_close_singular_values(ctx, d, spread):
+    """Sixteen heads a case, so that some end their sweeps at the first look at all pairs and some at the second: every
+    column settled as far as rounding and the distance of its eigenvalue allow (the bound of the test above)."""
+    n, H = 4 * d, 16
+    rng = np.random.default_rng(int(1e6 * spread) + d)
+    heads = []
+    for _ in range(H):
+        U, W = np.linalg.qr(rng.standard_normal((n, d)))[0], np.linalg.qr(rng.standard_normal((d, d)))[0]
+        heads.append((U * (1.0 + spread * np.linspace(1.0, 0.0, d))) @ W.T)
+    Q32 = np.ascontiguousarray(np.concatenate(heads, 1), dtype=np.float32)
+    A, sigma, status = skew_on_gpu(ctx, Q32, H)
+    assert status == 0
+    for h in range(H):
+        _, s, Vt = np.linalg.svd(Q32[:, h * d:(h + 1) * d].astype(np.float64), full_matrices=False)
+        assert np.abs(A[h].T @ A[h] - np.eye(d)).max() <= ROUNDED
+        gap = np.minimum(np.abs(np.diff(s, prepend=np.inf)), np.abs(np.diff(s, append=-np.inf))) / s[0]
+        V = Vt.T * np.sign(Vt.T[np.abs(A[h]).argmax(0), np.arange(d)])
+        settled = 2.0 ** -24 + 2 * d * 2.0 ** -52 / (2 * gap)
+        assert np.all(np.abs(A[h] - V).max(0) <= settled), (h, (np.abs(A[h] - V).max(0) / settled).max())
