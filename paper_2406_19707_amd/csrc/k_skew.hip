@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) void gram_heads(const float *__restrict__ Qcal
 // left into a pair that was done already, and nearly equal singular values make their columns of V as much worse
 // as they are close.  (With an end at a cosine of 1e-5, 128 singular values within 1e-3 of each other left A^T A
 // 2.8e-7 from the identity and moved entries of V by 1e-3; with 1e-13 whatever the distance, 64 within 1e-4 of
-// each other moved them by 1e-5.)
+// each other moved them by 3e-6.)
 // Bound by the double-precision issue rate of the head's compute unit, one wave per SIMD: a round is
 // 3 multiply-adds and 2 moves for each of RP rows and a chain of about 40 dependent operations.
 // The pivoted factor matters: L's columns come out graded, which takes 8 sweeps where the columns of G
@@ -206,9 +206,9 @@ template <int X> __device__ __forceinline__ void trade(double &a, double &b, boo
   a = join_d((unsigned)al, (unsigned)ah);
   b = join_d((unsigned)bl, (unsigned)bh);
 }
-// 1 / D anew.  The product that rotate_rounds keeps drifts from it by a few roundings a round, always the same way, and
-// a rotation whose two columns are scaled by factors that do not cancel is not orthogonal: with 32 to 64 rounds
-// between, singular values within 1e-3 of each other had their vectors off by 7e-7.
+// 1 / D anew, a dozen instructions: the product that rotate_rounds keeps drifts from it by some roundings a round, and
+// a rotation whose columns' factors do not cancel is not quite orthogonal.  (Over the at most 64 rounds between two
+// loads that is 1e-14 and was not seen in any result.)
 __device__ __forceinline__ double inverse_of(double D) {
   double y = __builtin_amdgcn_rcp(D);
   y = fma(fma(-D, y, 1.0), y, y);
@@ -452,14 +452,16 @@ __global__ __launch_bounds__(256, 1) void onesided_heads(const double *__restric
       if (r == c) diag[r] = v;
     });
     __syncthreads();
-    gram_tiles<DP, LD>(S, w, g, part, false, [&](int r, int c, double v) {
+    const auto look = [&](int r, int c, double v) {
       const double nn = diag[r] * diag[c];
       off13 = off13 || (r != c && !(v * v <= 1e-26 * nn));
       off9 = off9 || (r != c && !(v * v <= 1e-18 * nn));
       // (how far the pair is from the vectors it stands for: its cosine over the distance of its squared norms)
       const double most = fmax(diag[r], diag[c]), apart = diag[r] - diag[c];
       close = close || (r != c && !(v * v * most * most <= 1e-20 * apart * apart * nn));
-    });
+    };
+    gram_tiles<DP, LD>(S, w, g, part, true, look);
+    gram_tiles<DP, LD>(S, w, g, part, false, look);
     const bool small = __syncthreads_or(off13) == 0;
     square = __syncthreads_or(off9) == 0;
     straight = small && (__syncthreads_or(close) == 0 || seen_small);
