@@ -8,7 +8,9 @@ if the shared library is missing the import of any entry point raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
+import sys
 
 import numpy as np
 
@@ -188,6 +190,38 @@ def _current_stream():
     return handle
 
 
+def _through_ctypes(name, *args):
+    """An entry point with its arguments marshalled here: the context's address, the descriptor where there is one,
+    tensors / numpy arrays / addresses / None, numbers."""
+    has_desc = name not in ("ig_skew_device", "ig_partial_index_device")
+    at = [ctypes.byref(a) if has_desc and i == 1 else a if isinstance(a, (int, float, np.number)) else _ptr(a)
+          for i, a in enumerate(args)]
+    return getattr(lib(), name)(*at)
+
+
+class _Entries:
+    """The device entry points as functions of (context address, descriptor, tensors, numbers): those of the native
+    module where it has been built and torch is there, the others through ctypes.  Looked up at the first call."""
+
+    def __getattr__(self, name):
+        native = None
+        if "torch" in sys.modules and not os.environ.get("IG_LIBRARY"):
+            lib()
+            try:
+                from . import _ig_call
+                _ig_call.setup(IgDesc, _through_ctypes)
+                native = getattr(_ig_call, name, None)
+            except ImportError:
+                pass
+        fn = native or functools.partial(_through_ctypes, name)
+        if native or "torch" in sys.modules:
+            setattr(self, name, fn)
+        return fn
+
+
+_entries = _Entries()
+
+
 def _host_f32(a):
     return None if a is None else np.ascontiguousarray(a, dtype=np.float32)
 
@@ -284,11 +318,12 @@ class Context:
         if rc != IG_OK:
             raise IgError(rc, "ig_create failed (no usable GPU?)")
         self._h = h
+        self._address = h.value
 
     def close(self):
         if getattr(self, "_h", None):
             lib().ig_destroy(self._h)
-            self._h = None
+            self._h = self._address = None
 
     def __del__(self):
         try:
@@ -317,135 +352,111 @@ class Context:
         return lib().ig_check_status(self._h)
 
     def ig_wq_build(self, desc, Wq, idx_dev, wq, stream=None):
-        self._ck(lib().ig_wq_build(self._h, ctypes.byref(desc), _ptr(Wq), _ptr(idx_dev), _ptr(wq),
-                                   _stream(stream)))
+        self._ck(_entries.ig_wq_build(self._address, desc, Wq, idx_dev, wq, _stream(stream)))
 
     def ig_slab_build(self, desc, Kpool, pool_space, idx_dev, slab, stream=None):
-        self._ck(lib().ig_slab_build(self._h, ctypes.byref(desc), _ptr(Kpool), pool_space,
-                                     _ptr(idx_dev), _ptr(slab), _stream(stream)))
+        self._ck(_entries.ig_slab_build(self._address, desc, Kpool, pool_space, idx_dev, slab, _stream(stream)))
 
     def ig_skew_device(self, D, H, n_cal, Qcal, A, sigma=None, stream=None):
-        self._ck(lib().ig_skew_device(self._h, D, H, n_cal, _ptr(Qcal), _ptr(A), _ptr(sigma),
-                                      _stream(stream)))
+        self._ck(_entries.ig_skew_device(self._address, D, H, n_cal, Qcal, A, sigma, _stream(stream)))
 
     def ig_partial_index_device(self, dtype, H, d, n, Qs, Ks, ratio, idx_dev, stream=None):
-        self._ck(lib().ig_partial_index_device(self._h, dtype, H, d, n, _ptr(Qs), _ptr(Ks),
-                                               float(ratio), _ptr(idx_dev), _stream(stream)))
+        self._ck(_entries.ig_partial_index_device(self._address, dtype, H, d, n, Qs, Ks, float(ratio), idx_dev,
+                                                  _stream(stream)))
 
     def ig_append_token(self, desc, k_new, v_new, idx_dev, slab, Kpool, Vpool, pool_space, stream=None):
-        self._ck(lib().ig_append_token(self._h, ctypes.byref(desc), _ptr(k_new), _ptr(v_new),
-                                       _ptr(idx_dev), _ptr(slab), _ptr(Kpool), _ptr(Vpool),
-                                       pool_space, _stream(stream)))
+        self._ck(_entries.ig_append_token(self._address, desc, k_new, v_new, idx_dev, slab, Kpool, Vpool, pool_space,
+                                          _stream(stream)))
 
     def ig_pool_touch(self, desc, sel_idx, sel_stride, sel_cnt, counters, counter_max=255, stream=None):
-        self._ck(lib().ig_pool_touch(self._h, ctypes.byref(desc), _ptr(sel_idx), sel_stride,
-                                     _ptr(sel_cnt), _ptr(counters), counter_max, _stream(stream)))
+        self._ck(_entries.ig_pool_touch(self._address, desc, sel_idx, sel_stride, sel_cnt, counters, counter_max,
+                                        _stream(stream)))
 
     def ig_pool_victim(self, desc, counters, victim, stream=None):
-        self._ck(lib().ig_pool_victim(self._h, ctypes.byref(desc), _ptr(counters), _ptr(victim),
-                                      _stream(stream)))
+        self._ck(_entries.ig_pool_victim(self._address, desc, counters, victim, _stream(stream)))
 
     def ig_pool_replace(self, desc, victim, k_new, v_new, idx_dev, slab, Kpool, Vpool, pool_space,
                         counters=None, stream=None):
-        self._ck(lib().ig_pool_replace(self._h, ctypes.byref(desc), _ptr(victim), _ptr(k_new),
-                                       _ptr(v_new), _ptr(idx_dev), _ptr(slab), _ptr(Kpool),
-                                       _ptr(Vpool), pool_space, _ptr(counters), _stream(stream)))
+        self._ck(_entries.ig_pool_replace(self._address, desc, victim, k_new, v_new, idx_dev, slab, Kpool, Vpool,
+                                          pool_space, counters, _stream(stream)))
 
     def ig_pool_touch_policy(self, desc, policy, sel_idx, sel_stride, sel_cnt, state, param, stream=None):
-        self._ck(lib().ig_pool_touch_policy(self._h, ctypes.byref(desc), policy, _ptr(sel_idx), sel_stride,
-                                            _ptr(sel_cnt), _ptr(state), param, _stream(stream)))
+        self._ck(_entries.ig_pool_touch_policy(self._address, desc, policy, sel_idx, sel_stride, sel_cnt, state,
+                                               param, _stream(stream)))
 
     def ig_pool_replace_policy(self, desc, policy, victim, k_new, v_new, idx_dev, slab, Kpool, Vpool,
                                pool_space, state, now, stream=None):
-        self._ck(lib().ig_pool_replace_policy(self._h, ctypes.byref(desc), policy, _ptr(victim), _ptr(k_new),
-                                              _ptr(v_new), _ptr(idx_dev), _ptr(slab), _ptr(Kpool),
-                                              _ptr(Vpool), pool_space, _ptr(state), now, _stream(stream)))
+        self._ck(_entries.ig_pool_replace_policy(self._address, desc, policy, victim, k_new, v_new, idx_dev, slab,
+                                                 Kpool, Vpool, pool_space, state, now, _stream(stream)))
 
     def ig_speculate(self, desc, x, wq, bias, A_p, pos, slab, sel_idx, sel_stride, sel_cnt,
                      scores_opt=None, stream=None):
-        self._ck(lib().ig_speculate(self._h, ctypes.byref(desc), _ptr(x), _ptr(wq), _ptr(bias),
-                                    _ptr(A_p), _ptr(pos), _ptr(slab), _ptr(sel_idx), sel_stride,
-                                    _ptr(sel_cnt), _ptr(scores_opt), _stream(stream)))
+        self._ck(_entries.ig_speculate(self._address, desc, x, wq, bias, A_p, pos, slab, sel_idx, sel_stride, sel_cnt,
+                                       scores_opt, _stream(stream)))
 
     def ig_project(self, desc, x, wq, bias, A_p, pos, q_p, stream=None):
-        self._ck(lib().ig_project(self._h, ctypes.byref(desc), _ptr(x), _ptr(wq), _ptr(bias),
-                                  _ptr(A_p), _ptr(pos), _ptr(q_p), _stream(stream)))
+        self._ck(_entries.ig_project(self._address, desc, x, wq, bias, A_p, pos, q_p, _stream(stream)))
 
     def ig_scan_select(self, desc, q_p, slab, sel_idx, sel_stride, sel_cnt, scores_opt=None,
                        stream=None):
-        self._ck(lib().ig_scan_select(self._h, ctypes.byref(desc), _ptr(q_p), _ptr(slab),
-                                      _ptr(sel_idx), sel_stride, _ptr(sel_cnt), _ptr(scores_opt),
-                                      _stream(stream)))
+        self._ck(_entries.ig_scan_select(self._address, desc, q_p, slab, sel_idx, sel_stride, sel_cnt, scores_opt,
+                                         _stream(stream)))
 
     def ig_project_indexed(self, desc, x, Wq, idx_dev, bias, q_p, stream=None):
-        self._ck(lib().ig_project_indexed(self._h, ctypes.byref(desc), _ptr(x), _ptr(Wq), _ptr(idx_dev),
-                                          _ptr(bias), _ptr(q_p), _stream(stream)))
+        self._ck(_entries.ig_project_indexed(self._address, desc, x, Wq, idx_dev, bias, q_p, _stream(stream)))
 
     def ig_speculate_indexed(self, desc, x, Wq, idx_dev, bias, slab, sel_idx, sel_stride, sel_cnt,
                              scores_opt=None, stream=None):
-        self._ck(lib().ig_speculate_indexed(self._h, ctypes.byref(desc), _ptr(x), _ptr(Wq),
-                                            _ptr(idx_dev), _ptr(bias), _ptr(slab), _ptr(sel_idx),
-                                            sel_stride, _ptr(sel_cnt), _ptr(scores_opt),
-                                            _stream(stream)))
+        self._ck(_entries.ig_speculate_indexed(self._address, desc, x, Wq, idx_dev, bias, slab, sel_idx, sel_stride,
+                                               sel_cnt, scores_opt, _stream(stream)))
 
     def ig_layer_step(self, desc, x, wq, bias, A_p, pos, slab, sel_idx_next, sel_cnt_next, q, Kpool,
                       Vpool, sel_idx, sel_cnt, sel_stride, K_sel, V_sel, k_new, v_new, out, stream=None):
-        self._ck(lib().ig_layer_step(self._h, ctypes.byref(desc), _ptr(x), _ptr(wq), _ptr(bias),
-                                     _ptr(A_p), _ptr(pos), _ptr(slab), _ptr(sel_idx_next),
-                                     _ptr(sel_cnt_next), _ptr(q), _ptr(Kpool), _ptr(Vpool),
-                                     _ptr(sel_idx), _ptr(sel_cnt), sel_stride, _ptr(K_sel), _ptr(V_sel),
-                                     _ptr(k_new), _ptr(v_new), _ptr(out), _stream(stream)))
+        self._ck(_entries.ig_layer_step(self._address, desc, x, wq, bias, A_p, pos, slab, sel_idx_next, sel_cnt_next,
+                                        q, Kpool, Vpool, sel_idx, sel_cnt, sel_stride, K_sel, V_sel, k_new, v_new,
+                                        out, _stream(stream)))
 
     def ig_gather_kv(self, desc, Kpool, Vpool, pool_space, sel_idx, sel_stride, sel_cnt, K_sel,
                      V_sel, stream=None):
-        self._ck(lib().ig_gather_kv(self._h, ctypes.byref(desc), _ptr(Kpool), _ptr(Vpool),
-                                    pool_space, _ptr(sel_idx), sel_stride, _ptr(sel_cnt),
-                                    _ptr(K_sel), _ptr(V_sel), _stream(stream)))
+        self._ck(_entries.ig_gather_kv(self._address, desc, Kpool, Vpool, pool_space, sel_idx, sel_stride, sel_cnt,
+                                       K_sel, V_sel, _stream(stream)))
 
     def ig_sparse_attention(self, desc, q, K_sel, V_sel, sel_cnt, sel_stride, k_new, v_new, out,
                             stream=None):
-        self._ck(lib().ig_sparse_attention(self._h, ctypes.byref(desc), _ptr(q), _ptr(K_sel),
-                                           _ptr(V_sel), _ptr(sel_cnt), sel_stride, _ptr(k_new),
-                                           _ptr(v_new), _ptr(out), _stream(stream)))
+        self._ck(_entries.ig_sparse_attention(self._address, desc, q, K_sel, V_sel, sel_cnt, sel_stride, k_new, v_new,
+                                              out, _stream(stream)))
 
     def ig_sparse_attention_static(self, desc, q, K_sel, V_sel, sel_cnt, sel_stride, k_new, v_new, out,
                                    stream=None):
-        self._ck(lib().ig_sparse_attention_static(self._h, ctypes.byref(desc), _ptr(q), _ptr(K_sel),
-                                                  _ptr(V_sel), _ptr(sel_cnt), sel_stride, _ptr(k_new),
-                                                  _ptr(v_new), _ptr(out), _stream(stream)))
+        self._ck(_entries.ig_sparse_attention_static(self._address, desc, q, K_sel, V_sel, sel_cnt, sel_stride, k_new,
+                                                     v_new, out, _stream(stream)))
 
     def ig_sparse_attention_indexed(self, desc, q, Kpool, Vpool, sel_idx, sel_stride, sel_cnt,
                                     k_new, v_new, out, stream=None):
-        self._ck(lib().ig_sparse_attention_indexed(self._h, ctypes.byref(desc), _ptr(q),
-                                                   _ptr(Kpool), _ptr(Vpool), _ptr(sel_idx),
-                                                   sel_stride, _ptr(sel_cnt), _ptr(k_new),
-                                                   _ptr(v_new), _ptr(out), _stream(stream)))
+        self._ck(_entries.ig_sparse_attention_indexed(self._address, desc, q, Kpool, Vpool, sel_idx, sel_stride,
+                                                      sel_cnt, k_new, v_new, out, _stream(stream)))
 
     def ig_speculate_equalized(self, desc, x, wq, bias, A_p, pos, slab, max_frac, sel_idx, sel_stride, sel_cnt,
                                thr_cnt_opt=None, stream=None):
-        self._ck(self.call("ig_speculate_equalized", ctypes.byref(desc), _ptr(x), _ptr(wq), _ptr(bias), _ptr(A_p),
-                           _ptr(pos), _ptr(slab), float(max_frac), _ptr(sel_idx), sel_stride, _ptr(sel_cnt),
-                           _ptr(thr_cnt_opt), _stream(stream)))
+        self._ck(_entries.ig_speculate_equalized(self._address, desc, x, wq, bias, A_p, pos, slab, float(max_frac),
+                                                 sel_idx, sel_stride, sel_cnt, thr_cnt_opt, _stream(stream)))
 
     def ig_equalize_heads(self, desc, scores, thr_cnt, max_frac, sel_idx, sel_stride, sel_cnt,
                           stream=None):
-        self._ck(lib().ig_equalize_heads(self._h, ctypes.byref(desc), _ptr(scores), _ptr(thr_cnt),
-                                         float(max_frac), _ptr(sel_idx), sel_stride, _ptr(sel_cnt),
-                                         _stream(stream)))
+        self._ck(_entries.ig_equalize_heads(self._address, desc, scores, thr_cnt, float(max_frac), sel_idx,
+                                            sel_stride, sel_cnt, _stream(stream)))
 
     def ig_gather_attention(self, desc, q, Kpool, Vpool, sel_idx, sel_stride, sel_cnt, K_sel, V_sel,
                             k_new, v_new, out, stream=None):
-        self._ck(lib().ig_gather_attention(self._h, ctypes.byref(desc), _ptr(q), _ptr(Kpool),
-                                           _ptr(Vpool), _ptr(sel_idx), sel_stride, _ptr(sel_cnt),
-                                           _ptr(K_sel), _ptr(V_sel), _ptr(k_new), _ptr(v_new),
-                                           _ptr(out), _stream(stream)))
+        self._ck(_entries.ig_gather_attention(self._address, desc, q, Kpool, Vpool, sel_idx, sel_stride, sel_cnt,
+                                              K_sel, V_sel, k_new, v_new, out, _stream(stream)))
 
     def ig_decode_step_overlapped(self, desc, layers, wq, bias, A_p, pos, pool_space, sets, sel_stride,
                                   main_stream, side_stream):
         """layers: ctypes array of IgLayerIO; sets: ctypes array of IgBufferSet (kept by the caller)."""
-        self._ck(self.call("ig_decode_step_overlapped", ctypes.byref(desc), len(layers), ctypes.addressof(layers),
-                           _ptr(wq), _ptr(bias), _ptr(A_p), _ptr(pos), pool_space, len(sets), ctypes.addressof(sets),
-                           sel_stride, _stream(main_stream), _stream(side_stream)))
+        self._ck(_entries.ig_decode_step_overlapped(self._address, desc, len(layers), ctypes.addressof(layers), wq,
+                                                    bias, A_p, pos, pool_space, len(sets), ctypes.addressof(sets),
+                                                    sel_stride, _stream(main_stream), _stream(side_stream)))
 
     def ig_set_wait_limit(self, ticks: int):
         self._ck(lib().ig_set_wait_limit(self._h, int(ticks)))

@@ -1,14 +1,17 @@
 """Builds libinfinigen_hip.so for gfx950 with hipcc (cross-compiles without a GPU)."""
 from __future__ import annotations
 
+import importlib.util
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libinfinigen_hip.so")
+CALL = os.path.join(HERE, "_ig_call.so")
 SOURCES = ["ig_api.hip", "k_scan.hip", "k_project.hip", "k_kv.hip", "k_layer.hip", "k_equalize.hip", "k_index.hip", "k_skew.hip", "ig_host.cpp"]
 HIPCC = "/opt/rocm/bin/hipcc"
 # packed-fp32 instruction selection is switched off for every device compile
@@ -32,9 +35,20 @@ def build(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
     subprocess.check_call([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB, *objs])
+    _build_call()
     if verbose:
         print("built", LIB)
     return LIB
+
+
+def _build_call() -> None:
+    """The marshalling module of the Python binding: host code over the library and torch's tensor class."""
+    torch_dir = list(importlib.util.find_spec("torch").submodule_search_locations)[0]
+    inc = [sysconfig.get_paths()["include"], os.path.join(torch_dir, "include"),
+           os.path.join(torch_dir, "include", "torch", "csrc", "api", "include")]
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", *[f"-I{d}" for d in inc],
+                           os.path.join(CSRC, "ig_call.cpp"), "-o", CALL, "-L" + os.path.join(torch_dir, "lib"),
+                           "-ltorch_python", "-ltorch_cpu", "-lc10", "-L" + HERE, "-linfinigen_hip", "-Wl,-rpath,$ORIGIN"])
 
 
 HOST_SANITIZED = ["ig_api.hip", "ig_host.cpp"]      # the files whose host code checks and computes

@@ -1,0 +1,77 @@
+"""The native marshalling of the binding against its ctypes form: the same outcome for every kind of argument (no GPU
+needed: a NULL context is refused by the library before anything else is looked at)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2406_19707_amd as ig
+from paper_2406_19707_amd import binding
+
+
+def outcome(f):
+    try:
+        return f()
+    except Exception as e:        # noqa: BLE001 -- its type and text are what is compared
+        return type(e), str(e)
+
+
+class Odd(torch.Tensor):
+    pass
+
+
+@pytest.fixture(scope="module")
+def native():
+    if binding.os.environ.get("IG_LIBRARY"):
+        pytest.skip("another build of the library is under test")
+    fn = binding._Entries().ig_pool_touch
+    assert type(fn).__name__ == "builtin_function_or_method", "the native module is missing: build it"
+    return fn
+
+
+@pytest.mark.parametrize("what", ["tensor", "view", "parameter", "subclass", "transposed", "numpy", "numpy strided", "address",
+                                  "none", "text", "float stride", "numpy stride", "no descriptor", "other structure",
+                                  "too few", "empty tensor"])
+def test_same_outcome_as_through_ctypes(native, what):
+    d, t = ig.IgDesc(B=1, H=1, d=64, r=8, N=8), torch.zeros(64, dtype=torch.int32)
+    args = [None, d, t, 8, t, t, 255, 0]
+    if what == "view":
+        args[2] = t[8:16]
+    elif what == "parameter":
+        args[2] = torch.nn.Parameter(torch.zeros(4))
+    elif what == "subclass":
+        args[2] = torch.zeros(4).as_subclass(Odd)
+    elif what == "transposed":
+        args[2] = torch.zeros(4, 4).t()
+    elif what == "numpy":
+        args[2] = np.zeros(4, np.int32)
+    elif what == "numpy strided":
+        args[2] = np.zeros((4, 4), np.int32)[:, 1]
+    elif what == "address":
+        args[2] = t.data_ptr()
+    elif what == "none":
+        args[2] = None
+    elif what == "text":
+        args[2] = "x"
+    elif what == "float stride":
+        args[3] = 2.5
+    elif what == "numpy stride":
+        args[3] = np.int64(8)
+    elif what == "no descriptor":
+        args[1] = None
+    elif what == "other structure":
+        args[1] = ig.IgLayerIO()
+    elif what == "too few":
+        args.pop()
+    elif what == "empty tensor":
+        args[2] = torch.zeros(0)
+    want = outcome(lambda: binding._through_ctypes("ig_pool_touch", *args))
+    assert outcome(lambda: native(*args)) == want
+    if what in ("tensor", "view", "parameter", "subclass", "numpy", "address", "none", "empty tensor"):
+        assert want == ig.IG_EINVAL
+
+
+def test_every_device_entry_point_has_a_native_form(native):
+    from paper_2406_19707_amd import _ig_call
+    assert {n for n in dir(_ig_call) if n.startswith("ig_")} <= set(ig.EXPORTS)
+    for name in ("ig_speculate", "ig_gather_attention", "ig_layer_step", "ig_append_token", "ig_pool_victim"):
+        assert hasattr(_ig_call, name)
