@@ -23,6 +23,15 @@ struct AttnArgs {
   uint4 *K_out, *V_out;        // INDEXED only: the rows read are also stored here (fused prefetch)
 };
 
+struct GatherArgs {
+  const uint4 *Kpool, *Vpool;
+  const int32_t *sel_idx, *sel_cnt;
+  uint4 *K_sel, *V_sel;
+  int32_t *cnt_copy;           // optional: the counts as they were, for a reader that runs beside their next writer
+  int N_cap, stride, U, BH;    // U: 16-byte units of a row
+  FastDiv by_U;
+};
+
 namespace {
 
 typedef uint4 u128;
@@ -373,7 +382,70 @@ __device__ __forceinline__ void sparse_attention_body(const AttnArgs &A, const i
 }
 
 
+// ---- gather, pinned-host pool --------------------------------------------------------------------
+// The rows of all lists are treated as one flat sequence and cut into equal ranges, one per
+// workgroup: every workgroup reads the B*H counts (one coalesced read), builds their prefix sum in
+// LDS, takes rows [T*g/G, T*(g+1)/G) of the T selected rows and finds the list of each row by
+// binary search in the prefix array.  The split is therefore even whatever the skew of the list
+// lengths, consecutive workgroups (which go to different XCDs) take consecutive ranges, the grid
+// is fixed, and the host never reads a count.
+// A thread copies one 16-byte unit of K and of V at a time: 40 workgroups then have 328 KB on their way, a few times
+// what the link's latency covers.  More is not better: the link's rate falls with what is asked of it at once, and
+// requests for nothing (a batch filled up with its last unit again) are worst.  128 workgroups with eight units a
+// thread, filled up, against 40 with one: 165 rows of 256 bytes 15.0 -> 5.7 us, 2835 rows (25.4 us at the rate of a
+// large copy) 36.5 -> 31.0, 4574 (40.9) 52.5 -> 46.5, 37625 rows of 128 bytes (168) 202 -> 190, 100574 of 256 (900) 935 ->
+// 908.  With one unit 32 workgroups are within 1 us of 40 below 5000 rows and 4 us behind at 100574, 64 are up to 1.5
+// and up to 40 us behind.  The compute units stay free for what runs beside this.
+constexpr int GATHER_FLAT_BLOCKS = 40;
+__device__ __forceinline__ void gather_flat_body(const GatherArgs &A, int g, int G, int *pre /* [BH + 1] */) {
+  __shared__ int wave_tot[4];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, BH = A.BH;
+  // pre[i] = rows of lists 0..i-1: each thread sums a run of consecutive clamped counts
+  const int per = (BH + 255) / 256;
+  const int i0 = tid * per;
+  int run = 0;
+  for (int i = i0; i < min(BH, i0 + per); ++i) {
+    const int cnt = A.sel_cnt[i];
+    if (A.cnt_copy && g == 0) A.cnt_copy[i] = cnt;
+    run += min(cnt, A.stride);
+    pre[i + 1] = run;                    // local to the thread's run for now
+  }
+  int incl = wave_incl_scan(run);
+  if (lane == 63) wave_tot[w] = incl;
+  __syncthreads();
+  int offset = incl - run;
+  for (int k = 0; k < w; ++k) offset += wave_tot[k];
+  for (int i = i0; i < min(BH, i0 + per); ++i) pre[i + 1] += offset;
+  if (tid == 0) pre[0] = 0;
+  __syncthreads();
+  const int T = pre[BH];
+  const int per_wg = max((T + G - 1) / G, max(1, 256 / A.U));        // (a unit a thread at least, when there are that many)
+  const int r0 = min(T, g * per_wg), total = (min(T, r0 + per_wg) - r0) * A.U;
+  int top = 1;
+  while (top * 2 < BH) top *= 2;
+  for (int u = tid; u < total; u += 256) {
+    const int q = A.by_U.div(u), row = r0 + q, c = u - q * A.U;
+    // list of this row: the last bh with pre[bh] <= row
+    int lo = 0;
+    for (int step = top; step >= 1; step >>= 1) {
+      const int cand = lo + step;
+      if (cand < BH && pre[cand] <= row) lo = cand;
+    }
+    const int j = row - pre[lo];
+    const long t = min(max(A.sel_idx[(long)lo * A.stride + j], 0), A.N_cap - 1);   // a slot outside the pool is clamped
+    const long src = ((long)lo * A.N_cap + t) * A.U + c, dst = ((long)lo * A.stride + j) * A.U + c;
+    const u128 k = A.Kpool[src], v = A.Vpool[src];
+    A.K_sel[dst] = k;                    // plain stores: with a pinned-host pool the streamed form
+    A.V_sel[dst] = v;                    // measured slower (pipelined step 1107 vs 1083 us per layer)
+  }
+}
+
 }  // namespace
+
+// fills the gather's argument block (pinned-host pool); LDS bytes of its prefix sums
+int ig_gather_args(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const void *Vpool, const int32_t *sel_idx,
+                   int32_t sel_stride, const int32_t *sel_cnt, void *K_sel, void *V_sel, GatherArgs *A);
+size_t ig_gather_lds(const ig_desc *d);
 
 // fills the attention argument block; grows the slice-state workspaces if needed
 // (ig_attn_fill: the same with the slice-state / counter memory given by the caller, no allocation)
