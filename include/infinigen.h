@@ -413,7 +413,11 @@ int ig_layer_step(ig_ctx *ctx, const ig_desc *desc, const void *x, const void *w
  * the context keeps a second context for the side stream's workspaces and the events, created on
  * the first call (so the first call allocates; calls for larger shapes may too).  Nothing is
  * synchronised: when the call returns everything is enqueued, and main_stream's last work depends
- * on side_stream's. */
+ * on side_stream's.
+ * Folded half-precision shapes of up to four tiles (2048 tokens) and 32 sequences over a pinned pool
+ * take one launch a layer on main_stream instead, outside stream capture and unless a layer's x lies
+ * in the output of the layer but one before it; earlier work of side_stream is then done before the
+ * first prefetch and later work starts behind the last one, as if the prefetches ran there. */
 typedef struct {
   const void *x, *slab, *q, *Kpool, *Vpool, *k_new, *v_new;
   void *out;

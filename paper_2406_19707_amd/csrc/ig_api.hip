@@ -178,6 +178,8 @@ int reserve_for(ig_ctx *ctx, const ig_desc *d, bool scores) {
     if (rc) return rc;
     rc = ig_ensure_zeroed(ctx, (void **)&ctx->attn_cnt, &ctx->attn_cnt_bytes,
                           (size_t)d->B * d->H * sizeof(int32_t));
+    if (rc) return rc;
+    rc = ig_ensure(ctx, (void **)&ctx->cnt_copy, &ctx->cnt_copy_bytes, (size_t)2 * d->B * d->H * sizeof(int32_t));
   }
   return rc;
 }
@@ -248,6 +250,7 @@ int ig_destroy(ig_ctx *ctx) {
   if (ctx->seq_sync) (void)hipFree(ctx->seq_sync);
   if (ctx->eq_cnt) (void)hipFree(ctx->eq_cnt);
   if (ctx->words) (void)hipFree(ctx->words);
+  if (ctx->cnt_copy) (void)hipFree(ctx->cnt_copy);
   if (ctx->attn_part) (void)hipFree(ctx->attn_part);
   if (ctx->attn_cnt) (void)hipFree(ctx->attn_cnt);
   if (ctx->status) (void)hipFree(ctx->status);
@@ -269,7 +272,7 @@ size_t ig_workspace_bytes(const ig_ctx *ctx) {
   if (!ctx) return 0;
   return ctx->part_bytes + ctx->qp_bytes + ctx->scores_bytes + ctx->tmax_bytes + ctx->pcount_bytes +
          ctx->attn_part_bytes + ctx->attn_cnt_bytes + ctx->skew_ws_bytes + ctx->pair_sync_bytes + ctx->seq_sync_bytes +
-         ctx->words_bytes + ctx->eq_cnt_bytes;
+         ctx->words_bytes + ctx->cnt_copy_bytes + ctx->eq_cnt_bytes;
 }
 
 int ig_check_status(ig_ctx *ctx) {
@@ -788,6 +791,57 @@ int ig_layer_step(ig_ctx *ctx, const ig_desc *d, const void *x, const void *wq, 
                                sel_cnt, sel_stride, k_new, v_new, out, K_sel, V_sel, s);
 }
 
+// The step over a host pool on one stream, a launch a layer (k_layer.hip): rehearsal of layer 0, then per layer its
+// prefetch beside the next rehearsal and the previous attention, then the last attention.  The side stream's part is
+// ordered as if it had run there: its earlier work before the first prefetch, its later work behind the last one
+// (two events in a step; a record and a wait cost about 12 us of host time, four kernels').
+static int host_step_joint(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, int n_layers, const ig_layer_io *layers,
+                           const void *wq, const float *bias, int n_sets, const ig_buffer_set *sets, int32_t sel_stride,
+                           hipStream_t ms, hipStream_t ss) {
+  int rc;
+  const size_t BH = (size_t)d->B * d->H;
+  if ((rc = ig_ensure(ctx, (void **)&ctx->cnt_copy, &ctx->cnt_copy_bytes, 2 * BH * sizeof(int32_t)))) return rc;
+  while (ctx->pipe_events.size() < 2) {
+    hipEvent_t e;
+    IG_HIP(ctx, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    ctx->pipe_events.push_back(e);
+  }
+  IG_HIP(ctx, hipEventRecord(ctx->pipe_events[0], ss));
+  if ((rc = ig_speculate(ctx, d, layers[0].x, wq, bias, nullptr, nullptr, layers[0].slab, sets[0].sel_idx, sel_stride,
+                         sets[0].sel_cnt, nullptr, ms)))
+    return rc;
+  IG_HIP(ctx, hipStreamWaitEvent(ms, ctx->pipe_events[0], 0));
+  for (int l = 0; l < n_layers; ++l) {
+    const ig_layer_io &io = layers[l];
+    const ig_buffer_set &st = sets[l % n_sets];
+    const void *kp = nullptr, *vp = nullptr;
+    if ((rc = resolve_pool(ctx, io.Kpool, IG_MEM_HOST_PINNED, &kp))) return rc;
+    if ((rc = resolve_pool(ctx, io.Vpool, IG_MEM_HOST_PINNED, &vp))) return rc;
+    IgHostNext next;
+    IgHostPrev prev;
+    ProjWords p;
+    const bool has_next = l + 1 < n_layers;
+    if (has_next) {
+      const ig_buffer_set &sn = sets[(l + 1) % n_sets];
+      if (!joins_projection(ctx, d, g, layers[l + 1].x, wq, &p)) return ig_fail(ctx, IG_EINVAL, "host step: the shape's projection does not join");
+      next = IgHostNext{layers[l + 1].slab, bias, sn.sel_idx, sn.sel_cnt, &p};
+    }
+    if (l >= 1) {
+      const ig_layer_io &ip = layers[l - 1];
+      const ig_buffer_set &sp = sets[(l - 1) % n_sets];
+      prev = IgHostPrev{ip.q, sp.K_sel, sp.V_sel, ctx->cnt_copy + ((l - 1) & 1) * BH, ip.k_new, ip.v_new, ip.out};
+    }
+    if ((rc = ig_launch_host_step(ctx, d, kp, vp, st.sel_idx, st.sel_cnt, sel_stride, st.K_sel, st.V_sel,
+                                  ctx->cnt_copy + (l & 1) * BH, has_next ? &next : nullptr, l >= 1 ? &prev : nullptr, ms)))
+      return rc;
+  }
+  IG_HIP(ctx, hipEventRecord(ctx->pipe_events[1], ms));
+  IG_HIP(ctx, hipStreamWaitEvent(ss, ctx->pipe_events[1], 0));
+  const ig_layer_io &io = layers[n_layers - 1];
+  const ig_buffer_set &st = sets[(n_layers - 1) % n_sets];
+  return ig_sparse_attention(ctx, d, io.q, st.K_sel, st.V_sel, st.sel_cnt, sel_stride, io.k_new, io.v_new, io.out, ms);
+}
+
 int ig_decode_step_overlapped(ig_ctx *ctx, const ig_desc *d, int n_layers, const ig_layer_io *layers,
                               const void *wq, const float *bias, const float *A_p, const int32_t *pos,
                               int pool_space, int n_sets, const ig_buffer_set *sets, int32_t sel_stride,
@@ -801,6 +855,31 @@ int ig_decode_step_overlapped(ig_ctx *ctx, const ig_desc *d, int n_layers, const
     if (!sets[i].sel_idx || !sets[i].sel_cnt || !sets[i].K_sel || !sets[i].V_sel)
       return ig_fail(ctx, IG_EINVAL, "ig_decode_step_overlapped: buffer set %d has a NULL member", i);
   if ((rc = set_device(ctx))) return rc;
+  if (pool_space == IG_MEM_HOST_PINNED && !ig_capturing(ctx)) {
+    // One stream, where the shape allows it and every argument is what the three calls would take (what they refuse
+    // is left to them), and where no rehearsal reads what the attention beside it writes.  Not under a capture: the side
+    // stream joins one only by a fork from the captured stream.
+    ProjGeom g = ig_proj_geom(d);
+    const int row = d->d * 2;
+    bool one = ig_host_step_is_joint(d, g) && wq && sel_stride >= 1 && row <= 1024 && !(row & (row - 1)) && ig_gather_fits(d) &&
+               !check_aligned(ctx, "", {wq});
+    for (int l = 0; one && l < n_layers; ++l) {
+      const ig_layer_io &io = layers[l];
+      one = io.x && io.slab && io.q && io.Kpool && io.Vpool && io.out && (!io.k_new) == (!io.v_new) &&
+            !check_aligned(ctx, "", {io.x, io.q, io.Kpool, io.Vpool, io.k_new, io.v_new});
+      const size_t bytes = (size_t)d->B * d->H * d->d * 2;
+      if (one && l >= 2) {
+        const uintptr_t a = (uintptr_t)io.x, b = (uintptr_t)layers[l - 2].out;
+        one = a + bytes <= b || b + bytes <= a;
+      }
+    }
+    for (int i = 0; one && i < n_sets; ++i) one = !check_aligned(ctx, "", {sets[i].K_sel, sets[i].V_sel});
+    ProjWords p;
+    if (one && !(rc = reserve_for(ctx, d, false)) && joins_projection(ctx, d, g, layers[0].x, wq, &p))
+      return host_step_joint(ctx, d, g, n_layers, layers, wq, bias, n_sets, sets, sel_stride, (hipStream_t)main_stream,
+                             (hipStream_t)side_stream);
+    if (rc) return rc;
+  }
   if (!ctx->side) {
     if ((rc = ig_create(ctx->device, &ctx->side))) return ig_fail(ctx, rc, "ig_decode_step_overlapped: no context for the side stream");
   }

@@ -116,6 +116,8 @@ struct ig_ctx {
   void *pair_sync;  size_t pair_sync_bytes;  // scan: per-(b,h) records of pairs split over workgroups, zero between calls
   void *seq_sync = nullptr;            // scan, head-equalised form: per-sequence exchange records (zero between calls)
   size_t seq_sync_bytes = 0;
+  int32_t *cnt_copy = nullptr;         // host-pool step: the counts of the lists being fetched and attended [2][B*H]
+  size_t cnt_copy_bytes = 0;
   void *words = nullptr;               // projection inside the scan's launch: query words (zero between calls)
   size_t words_bytes = 0;
   int32_t *eq_cnt = nullptr;            // threshold counts of ig_speculate_equalized's two-kernel route
@@ -257,6 +259,24 @@ int ig_launch_scan_attend(ig_ctx *ctx, const ig_desc *d, const QSource &qs, cons
                           const void *Kpool, const void *Vpool, const int32_t *sel_idx,
                           const int32_t *sel_cnt, int32_t sel_stride, const void *k_new,
                           const void *v_new, void *out, void *K_sel, void *V_sel, hipStream_t s);
+// one layer of a host-pool step: prefetch, the next layer's rehearsal and the previous layer's attention in one launch
+struct IgHostNext {
+  const void *slab;
+  const float *bias;
+  int32_t *sel_idx, *sel_cnt;
+  const ProjWords *proj;
+};
+struct IgHostPrev {
+  const void *q, *K_sel, *V_sel;
+  const int32_t *cnt;
+  const void *k_new, *v_new;
+  void *out;
+};
+bool ig_gather_fits(const ig_desc *d);
+bool ig_host_step_is_joint(const ig_desc *d, const ProjGeom &g);
+int ig_launch_host_step(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const void *Vpool, const int32_t *sel_idx,
+                        const int32_t *sel_cnt, int32_t sel_stride, void *K_sel, void *V_sel, int32_t *cnt_copy,
+                        const IgHostNext *next, const IgHostPrev *prev, hipStream_t s);
 // attention whose slice states and arrival counters live in the static scratch array (no allocation)
 int ig_static_scratch_bind(ig_ctx *ctx);
 int ig_launch_attention_static(ig_ctx *ctx, const ig_desc *d, const void *q, const void *K, const void *V,

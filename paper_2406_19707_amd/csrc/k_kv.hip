@@ -358,11 +358,12 @@ int ig_launch_gather(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const voi
   return IG_OK;
 }
 
+bool ig_gather_fits(const ig_desc *d) { return ig_gather_lds(d) <= 60 * 1024; }
 size_t ig_gather_lds(const ig_desc *d) { return ((size_t)d->B * d->H + 1) * sizeof(int); }
 
 int ig_gather_args(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const void *Vpool, const int32_t *sel_idx,
                    int32_t sel_stride, const int32_t *sel_cnt, void *K_sel, void *V_sel, GatherArgs *A) {
-  if (ig_gather_lds(d) > 60 * 1024) return ig_fail(ctx, IG_ESHAPE, "host gather: B*H = %d exceeds %d", d->B * d->H, 60 * 256 - 1);
+  if (!ig_gather_fits(d)) return ig_fail(ctx, IG_ESHAPE, "host gather: B*H = %d exceeds %d", d->B * d->H, 60 * 256 - 1);
   *A = GatherArgs{(const uint4 *)Kpool, (const uint4 *)Vpool, sel_idx, sel_cnt, (uint4 *)K_sel, (uint4 *)V_sel, nullptr,
                   (int)d->N_cap, (int)sel_stride, d->d * ig_elem_bytes(d->dtype) / 16, d->B * d->H,
                   ig_fast_div(d->d * ig_elem_bytes(d->dtype) / 16)};

@@ -53,6 +53,32 @@ int launch_projecting(ig_ctx *ctx, const ScanArgs &sa, const AttnArgs &aa, const
   return ig_fail(ctx, IG_ESHAPE, "layer step: unsupported channel block %d", ch);
 }
 
+// One layer of a host-pool decode step in one launch (Fig. 3(d)): the prefetch of layer l over PCIe, the rehearsal of
+// layer l + 1 and the attention of layer l - 1.  None of them depends on another: the prefetch reads the lists that the
+// launch before this one wrote, the attention the rows that one fetched, and the rehearsal writes a list set that only
+// the attention still uses, of which it has a copy of the counts.  What bounds it is the link.  On two streams the
+// list had to wait 15 us for its prefetch and the rows 11 us for their attention, each a hand-over between queues,
+// and the link with them: three layers of 64 lists, 12239 rows whose prefetches take 126 us back to back, 186 us a step,
+// 156 so (issued on an idle GPU 213 and 187, of which the host 120 and 60).
+template <int LG>
+__global__ __launch_bounds__(256, 4) void prefetch_rehearse_attend(GatherArgs ga, ScanArgs sa, AttnArgs aa, ProjWords p,
+                                                                   int gather_blocks, int scan_blocks) {
+  extern __shared__ int pre[];
+  __shared__ __attribute__((aligned(16))) float red[PROJECT_LDS];
+  int id = blockIdx.x;
+  if (id < gather_blocks) {
+    gather_flat_body(ga, id, gather_blocks, pre);
+    return;
+  }
+  id -= gather_blocks + p.blocks;
+  if (id >= scan_blocks)
+    sparse_attention_body<half_t, false, LG>(aa, id - scan_blocks);
+  else if (id >= 0)
+    scan_select_fused_body<half_t, 12, 4, true>(sa, id, &p, red);
+  else
+    project_publish<1>(p, id + p.blocks, red);
+}
+
 template <typename T, int LG>
 int launch_t(ig_ctx *ctx, const ScanArgs &sa, const AttnArgs &aa, int BH, int ch, hipStream_t s) {
   dim3 grid(BH + BH * slices_at_most((long)aa.stride + 1, aa.slice_log2)), block(256);
@@ -110,4 +136,42 @@ int ig_launch_scan_attend(ig_ctx *ctx, const ig_desc *d, const QSource &qs, cons
     return launch_t<half_t, -1>(ctx, sa, aa, BH, ch, s);
   }
   return aa.lpr_log2 == 4 ? launch_t<float, 4>(ctx, sa, aa, BH, ch, s) : launch_t<float, -1>(ctx, sa, aa, BH, ch, s);
+}
+
+// The host-pool step's launch takes the folded half-precision shapes whose scan is the 4-wave form with the
+// projection in its launch.
+bool ig_host_step_is_joint(const ig_desc *d, const ProjGeom &g) {
+  const int tile = ig_tile_tokens(d->dtype);
+  return d->dtype == IG_F16 && !d->rope && ig_scan_joins_projection(d, g) && (d->N + tile - 1) / tile <= 4;
+}
+
+// next: the rehearsal (qs.proj set) or NULL, prev: the attention or NULL
+int ig_launch_host_step(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const void *Vpool, const int32_t *sel_idx,
+                        const int32_t *sel_cnt, int32_t sel_stride, void *K_sel, void *V_sel, int32_t *cnt_copy,
+                        const IgHostNext *next, const IgHostPrev *prev, hipStream_t s) {
+  GatherArgs ga;
+  int rc = ig_gather_args(ctx, d, Kpool, Vpool, sel_idx, sel_stride, sel_cnt, K_sel, V_sel, &ga);
+  if (rc) return rc;
+  ga.cnt_copy = cnt_copy;
+  ScanArgs sa{};
+  ProjWords p{};
+  int scan_blocks = 0, attn_blocks = 0;
+  if (next) {
+    QSource qs{nullptr, 1, 0, 0, next->bias, nullptr, nullptr, next->proj};
+    if ((rc = ig_scan_args(ctx, d, qs, next->slab, next->sel_idx, sel_stride, next->sel_cnt, nullptr, &sa))) return rc;
+    p = *next->proj;
+    scan_blocks = d->B * d->H;
+  }
+  AttnArgs aa{};
+  if (prev) {
+    if ((rc = ig_attn_args(ctx, d, prev->q, prev->K_sel, prev->V_sel, nullptr, sel_stride, prev->cnt, sel_stride, prev->k_new,
+                           prev->v_new, prev->out, nullptr, nullptr, &aa)))
+      return rc;
+    attn_blocks = aa.BH * slices_at_most((long)sel_stride + 1, aa.slice_log2);
+  }
+  dim3 grid((unsigned)(GATHER_FLAT_BLOCKS + p.blocks + scan_blocks + attn_blocks)), block(256);
+  const int row16_log2 = __builtin_ctz(d->d * 2 / 16);
+  auto k = row16_log2 == 3 ? prefetch_rehearse_attend<3> : (row16_log2 == 4 ? prefetch_rehearse_attend<4> : prefetch_rehearse_attend<-1>);
+  IG_LAUNCH_LDS(ctx, IG_K_LAYER, k, grid, block, (unsigned)ig_gather_lds(d), s, ga, sa, aa, p, (int)GATHER_FLAT_BLOCKS, scan_blocks);
+  return IG_OK;
 }
