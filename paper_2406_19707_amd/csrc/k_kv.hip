@@ -103,21 +103,43 @@ __global__ __launch_bounds__(64) void append_token(const T *__restrict__ k_new, 
 // list holds a slot once, so plain stores suffice; if a counter reached the saturation value, all
 // counters of the pool are halved after the increments.  victim: the slot with the smallest count
 // among the N valid ones, the lowest slot on ties (minimum over count * 2^32 + slot).
+//
+// Bound by the chain of trips through memory, so what can be asked for early is: a thread's first TOUCH_BATCH list
+// entries while the count is on its way (entries past it are not used), all counters of a batch together.
+// 256 pools of 2048 slots, lists of 100 on average: 3.8 -> 3.3 us, of which an empty launch is 2.
+constexpr int TOUCH_BATCH = 4;
 __global__ __launch_bounds__(256) void pool_touch(const int32_t *__restrict__ sel_idx,
                                                   const int32_t *__restrict__ sel_cnt,
                                                   int32_t *__restrict__ counters, int stride, int N,
                                                   int N_cap, int counter_max) {
   const int bh = blockIdx.x;
   int32_t *c = counters + (long)bh * N_cap;
+  const int32_t *list = sel_idx + (long)bh * stride;
+  int t[TOUCH_BATCH];
+  auto load_entries = [&](int j0) {
+#pragma unroll
+    for (int i = 0; i < TOUCH_BATCH; ++i) t[i] = list[min(j0 + 256 * i, stride - 1)];
+  };
+  load_entries(threadIdx.x);
   const int n = min(sel_cnt[bh], stride);
   int sat = 0;
-  for (int j = threadIdx.x; j < n; j += 256) {
-    const int t = sel_idx[(long)bh * stride + j];
-    if (t >= 0 && t < N) {
-      const int v = min(c[t] + 1, counter_max);
-      c[t] = v;
-      sat |= v >= counter_max;
+  for (int j0 = threadIdx.x; j0 < n;) {
+    int v[TOUCH_BATCH];
+    bool ok[TOUCH_BATCH];
+#pragma unroll
+    for (int i = 0; i < TOUCH_BATCH; ++i) {
+      ok[i] = j0 + 256 * i < n && t[i] >= 0 && t[i] < N;
+      t[i] = ok[i] ? t[i] : 0;
+      v[i] = c[t[i]];
     }
+#pragma unroll
+    for (int i = 0; i < TOUCH_BATCH; ++i)
+      if (ok[i]) {
+        const int u = min(v[i] + 1, counter_max);
+        c[t[i]] = u;
+        sat |= u >= counter_max;
+      }
+    if ((j0 += 256 * TOUCH_BATCH) < n) load_entries(j0);
   }
   if (__syncthreads_or(sat))
     for (int t = threadIdx.x; t < N; t += 256) c[t] >>= 1;
@@ -137,15 +159,32 @@ __global__ __launch_bounds__(256) void pool_touch_lru(const int32_t *__restrict_
   }
 }
 
+// W: counters a load takes, 4 where every pool's counters lie on 16 bytes.  A batch of VICTIM_BATCH loads a thread is in
+// flight together (2048 slots: one trip instead of one after another for every 256).
+// 256 pools of 2048 slots 3.3 -> 2.8 us.
+constexpr int VICTIM_BATCH = 4;
+template <int W>
 __global__ __launch_bounds__(256) void pool_victim(const int32_t *__restrict__ counters,
                                                    int32_t *__restrict__ victim, int N, int N_cap) {
+  typedef int32_t vec __attribute__((ext_vector_type(W)));
   __shared__ unsigned long long best[4];
   const int bh = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int32_t *c = counters + (long)bh * N_cap;
+  const vec *c = reinterpret_cast<const vec *>(counters + (long)bh * N_cap);
+  const int units = (N + W - 1) / W;                 // (W == 4: N_cap is a multiple, the last unit lies inside it)
   unsigned long long m = ~0ull;
-  for (int t = threadIdx.x; t < N; t += 256) {
-    const unsigned long long key = ((unsigned long long)(unsigned)c[t] << 32) | (unsigned)t;
-    m = key < m ? key : m;
+  for (int u0 = threadIdx.x; u0 < units; u0 += 256 * VICTIM_BATCH) {
+    vec v[VICTIM_BATCH];
+#pragma unroll
+    for (int i = 0; i < VICTIM_BATCH; ++i) v[i] = c[min(u0 + 256 * i, units - 1)];
+#pragma unroll
+    for (int i = 0; i < VICTIM_BATCH; ++i) {
+      const int t0 = min(u0 + 256 * i, units - 1) * W;
+#pragma unroll
+      for (int e = 0; e < W; ++e) {
+        const unsigned long long key = ((unsigned long long)(unsigned)v[i][e] << 32) | (unsigned)(t0 + e);
+        m = t0 + e < N && key < m ? key : m;
+      }
+    }
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
@@ -328,7 +367,7 @@ int ig_launch_pool_touch_lru(ig_ctx *ctx, const ig_desc *d, const int32_t *sel_i
 
 int ig_launch_pool_victim(ig_ctx *ctx, const ig_desc *d, const int32_t *counters, int32_t *victim,
                           hipStream_t s) {
-  auto k = pool_victim;
+  auto k = d->N_cap % 4 == 0 && (uintptr_t)counters % 16 == 0 ? pool_victim<4> : pool_victim<1>;
   IG_LAUNCH(ctx, IG_K_BUILD, k, dim3(d->B * d->H), dim3(256), s, counters, victim, (int)d->N,
             (int)d->N_cap);
   return IG_OK;
