@@ -3,6 +3,7 @@
 // kernel that runs a layer's attention next to the next layer's scan in one launch.
 #ifndef IG_ATTN_DEVICE_H
 #define IG_ATTN_DEVICE_H
+#include <type_traits>
 #include "ig_internal.h"
 
 struct AttnArgs {
@@ -12,11 +13,12 @@ struct AttnArgs {
   int stride, kv_rows;
   int lpr_log2;               // a row is 1 << lpr_log2 pieces of 16 bytes
   int slice_log2;             // rows of a slice: see slice_range
+  int most_log2;              // slices of a list at most, 1 << most_log2
   const void *k_new, *v_new;  // optional always-attended row
   void *out;
   float scale;
   int d;
-  float *part;                // per-slice softmax states [B*H][SLICE_MAX][d+2]
+  float *part;                // per-slice softmax states [B*H][1 << most_log2][d+2]
   int32_t *counters;          // per-(b,h) arrival counters, zero between calls
   int H, BH;
   FastDiv by_H, by_BH;
@@ -48,7 +50,7 @@ __device__ __forceinline__ void store_stream(u128 *p, const u128 &v) {
 // ---- work split shared by gather and attention --------------------------------------------------
 // Selected-token lists are very uneven (a few heads keep a thousand rows, most a few dozen), and
 // one compute unit moves well under 100 GB/s, so a list is cut into slices of 1 << slice_log2 rows, or,
-// when that would be more than SLICE_MAX of them, into SLICE_MAX equal ones.  Every workgroup derives
+// when that would be more than 1 << most_log2 of them, into that many equal ones.  Every workgroup derives
 // this from the device-side count, so the host never reads the counts; surplus workgroups leave at
 // once.  They are most of a grid, so the way to the exit has no division in it: with the work item
 // decoded by run-time divisions and slices of rows*s/slices, 320 lists of 250 rows on average took 28.6 us
@@ -62,8 +64,8 @@ __device__ __forceinline__ void store_stream(u128 *p, const u128 &v) {
 // (b, h, slice) on XCD (h + b + 5*slice) % 8: the slices of one list, the sequences of one head and
 // the heads of one sequence are each spread over all XCDs.
 constexpr int SLICE_LOG2 = 7;
-constexpr int SLICE_MAX = IG_SLICE_MAX, SLICE_MAX_LOG2 = 4;
-static_assert(SLICE_MAX == 1 << SLICE_MAX_LOG2, "");
+constexpr int SLICE_MAX_LOG2 = 4, SLICE_MAX_LONG_LOG2 = 5;
+static_assert(IG_SLICE_MAX == 1 << SLICE_MAX_LOG2 && IG_SLICE_MAX_LONG == 1 << SLICE_MAX_LONG_LOG2, "");
 __device__ __forceinline__ void work_item(int id, int H, int BH, const FastDiv &by_H, const FastDiv &by_BH, int *bh, int *slice) {
   const int s = by_BH.div(id), t = id - s * BH;
   const int b = by_H.div(t);
@@ -72,28 +74,29 @@ __device__ __forceinline__ void work_item(int id, int H, int BH, const FastDiv &
   *bh = b * H + h;
   *slice = s;
 }
-__device__ __forceinline__ bool slice_range(int rows, int s, int slice_log2, int *row0, int *row1, int *slices) {
-  if (rows <= (SLICE_MAX << slice_log2)) {
+__device__ __forceinline__ bool slice_range(int rows, int s, int slice_log2, int most_log2, int *row0, int *row1, int *slices) {
+  const int most = 1 << most_log2;
+  if (rows <= (most << slice_log2)) {
     const int n = max(1, (rows + (1 << slice_log2) - 1) >> slice_log2);
     *slices = n;
     *row0 = s << slice_log2;
     *row1 = min(rows, *row0 + (1 << slice_log2));
     return s < n;
   }
-  const int per = (rows + SLICE_MAX - 1) >> SLICE_MAX_LOG2;
-  *slices = SLICE_MAX;
+  const int per = (rows + most - 1) >> most_log2;
+  *slices = most;
   *row0 = min(rows, s * per);
   *row1 = min(rows, *row0 + per);
   return true;
 }
 // workgroups per list that a list of at most `rows` rows can need
-static inline int slices_at_most(long rows, int slice_log2) {
+static inline int slices_at_most(long rows, int slice_log2, int most_log2) {
   const long n = (rows + (1l << slice_log2) - 1) >> slice_log2;
-  return n < 1 ? 1 : (n < SLICE_MAX ? (int)n : SLICE_MAX);
+  return n < 1 ? 1 : (n < (1l << most_log2) ? (int)n : 1 << most_log2);
 }
 
 // ---- attention ----------------------------------------------------------------------------------
-// grid B*H*SLICE_MAX (see work_item), 4 waves per workgroup, one slice of the (b,h) list each.  A row of d
+// grid B*H x slices_at_most() (see work_item), 4 waves per workgroup, one slice of the (b,h) list each.  A row of d
 // elements is covered by LPR = d*sizeof(T)/16 lanes, 16 bytes each, so a wave step covers 64/LPR
 // rows; waves interleave over the rows, and steps are issued in batches of ATT_BATCH so that a
 // batch's K and V loads are all in flight before the first is used.  Every lane group keeps an
@@ -121,6 +124,18 @@ static inline int att_slice_log2(int lpr_log2, int lists) {
   return batch_log2 + 1 < SLICE_LOG2 && lists < 256 ? batch_log2 + 1 : SLICE_LOG2;
 }
 static_assert(ATT_BATCH == 8, "att_slice_log2 counts on it");
+// Slices of a list at most, as a power of two: 16, or 32 where lists can be longer than 16 slices and their rows come
+// out of the pool through the list: the longest lists set the time, and a slice of more than one batch of loads is a
+// second round of trips.  Whole steps with 16 and with 32, lists of rows of 256 bytes: 512 rotary lists of 4096 tokens
+// 79.7 -> 77.4 us, 320 of 2500 50.0 -> 48.8, 256 of 8192 51.1 -> 49.4, 80 of 16384 92.4 -> 78.5, 128 of 9000 55.0 -> 50.7;
+// 384 of 6000, rows of 128 bytes, 43.0 -> 41.4.  With fewer than 256 lists only where they can be four times as long as
+// that: the larger grid costs 32 lists of 8192 tokens 0.5 us (17.3 -> 17.8), and they rarely hold one so long.
+// The joint launches keep 16, whose larger grid costs each of them 1 us, and so does the attention over rows that
+// have been fetched: it runs beside the prefetch of a host-pool step, which more workgroups hold up.
+static inline int att_most_log2(int slice_log2, int lists, long longest) {
+  const long rows = (long)IG_SLICE_MAX << slice_log2;
+  return longest > (lists >= 256 ? rows : 4 * rows) ? SLICE_MAX_LONG_LOG2 : SLICE_MAX_LOG2;
+}
 
 template <typename T> __device__ __forceinline__ void to_float(const u128 &raw, float (&f)[Elem<T>::TPL]);
 template <> __device__ __forceinline__ void to_float<half_t>(const u128 &raw, float (&f)[8]) {
@@ -150,7 +165,9 @@ __device__ __forceinline__ float coherent_load(const float *p) {
 // waited for before the rows are asked for: 1120 lists of 77 rows of 128 half columns 30.1 -> 24.3 us,
 // 512 lists of 229 rows, 120 MB read and written, 33.3 -> 31.6 us, 192 lists of 120 rows of 64 columns
 // 9.5 -> 5.3 us).
-template <typename T, bool INDEXED, int LG>
+// LONG: lists are cut into 32 slices at most instead of 16 (att_most_log2).  A form of its own: with the limit and
+// the merge's second pass decided at run time every attention of lists in several slices lost 0.3 us.
+template <typename T, bool INDEXED, int LG, bool LONG = false>
 __device__ __forceinline__ void sparse_attention_body(const AttnArgs &A, const int id) {
   const T *__restrict__ q = static_cast<const T *>(A.q);
   const u128 *__restrict__ K = A.K;
@@ -171,13 +188,13 @@ __device__ __forceinline__ void sparse_attention_body(const AttnArgs &A, const i
   __shared__ float sm[4], sz[4];
   __shared__ float sacc[4][512];
   __shared__ int s_last;
-  constexpr int max_slices = SLICE_MAX;
+  constexpr int most_log2 = LONG ? SLICE_MAX_LONG_LOG2 : SLICE_MAX_LOG2;
   int bh, slice;
   work_item(id, A.H, A.BH, A.by_H, A.by_BH, &bh, &slice);
   const int n = min(sel_cnt[bh], stride);
   const int rows = n + (k_new ? 1 : 0);
   int row0 = 0, row1 = 0, slices = 1;
-  if (!slice_range(rows, slice, A.slice_log2, &row0, &row1, &slices)) return;
+  if (!slice_range(rows, slice, A.slice_log2, most_log2, &row0, &row1, &slices)) return;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int RPW = 64 >> lpr_log2;      // rows per wave step
   const int sub = lane >> lpr_log2, li = lane & (LPR - 1);
@@ -312,7 +329,7 @@ __device__ __forceinline__ void sparse_attention_body(const AttnArgs &A, const i
     return;
   }
   // several slices: publish this slice's state; the last arrival merges all of them
-  float *mine = part + ((long)bh * max_slices + slice) * (d + 2);
+  float *mine = part + (((long)bh << most_log2) + slice) * (d + 2);
   for (int c = threadIdx.x; c < d; c += 256) {
     float a = 0.f;
 #pragma unroll
@@ -347,34 +364,50 @@ __device__ __forceinline__ void sparse_attention_body(const AttnArgs &A, const i
   if (s_last) {
     // wave 0 of the last arrival: lane c owns output channels c, c + 64, ...; all loads of a pass
     // (independent, slices past the last read it again) are issued before any is used
-    const float *all = part + (long)bh * max_slices * (d + 2);
-    static_assert(SLICE_MAX == 16, "lane k of a 16-lane row has slice k's maximum and normaliser");
+    const float *all = part + ((long)bh << most_log2) * (d + 2);
     const float *state = all + (long)min(lane, slices - 1) * (d + 2);
     constexpr int CPP = 2;               // channels per lane and pass
+    constexpr int SPP = 16;              // slices per pass: of 32, the others follow, in the same registers
     for (int c0 = lane; c0 - lane < d; c0 += 64 * CPP) {   // (all lanes stay: they hold the weights)
-      float mk = coherent_load(state), zk = coherent_load(state + 1), ak[CPP][SLICE_MAX];
+      float mk = coherent_load(state), zk = coherent_load(state + 1), a[CPP], zz = 0.f;
+      int wbits = 0;
+      auto pass = [&](auto first) {
+        constexpr int k0 = decltype(first)::value;
+        float ak[CPP][SPP];
 #pragma unroll
-      for (int q = 0; q < CPP; ++q)
+        for (int q = 0; q < CPP; ++q)
 #pragma unroll
-        for (int k = 0; k < SLICE_MAX; ++k)
-          ak[q][k] = coherent_load(all + (long)min(k, slices - 1) * (d + 2) + 2 + min(c0 + 64 * q, d - 1));
-      __builtin_amdgcn_sched_barrier(0);
-      // (One lane a slice works out its weight, and the loop below reads them one by one.  With every slice's
-      // maximum, normaliser and weight in every lane this merge set the kernel's registers, 144 instead of 117,
-      // three waves a SIMD instead of four: 1120 lists of 77 rows 26.2 -> 23.4 us.)
-      mk = lane < slices ? mk : -INFINITY;
-      zk = lane < slices ? zk : 0.f;
-      const float wk = exp_or_zero(mk, wave_max(mk));
-      const int wbits = __float_as_int(wk);
-      const float zs = row16_sum(zk * wk);     // (lanes 16 and up hold zeros)
-      const float zz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(zs), 0));
+          for (int k = 0; k < SPP; ++k)
+            ak[q][k] = coherent_load(all + (long)min(k0 + k, slices - 1) * (d + 2) + 2 + min(c0 + 64 * q, d - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (k0 == 0) {
+          // (One lane a slice works out its weight, and the loop below reads them one by one.  With every slice's
+          // maximum, normaliser and weight in every lane this merge set the kernel's registers, 144 instead of 117,
+          // three waves a SIMD instead of four: 1120 lists of 77 rows 26.2 -> 23.4 us.)
+          mk = lane < slices ? mk : -INFINITY;
+          zk = lane < slices ? zk : 0.f;
+          const float wk = exp_or_zero(mk, wave_max(mk));
+          wbits = __float_as_int(wk);
+          const int zs = __float_as_int(row16_sum(zk * wk));     // (lanes past the last slice hold zeros)
+          zz = __int_as_float(__builtin_amdgcn_readlane(zs, 0));
+          if constexpr (LONG) zz += __int_as_float(__builtin_amdgcn_readlane(zs, 16));
+        }
+#pragma unroll
+        for (int q = 0; q < CPP; ++q) {
+          float t = k0 == 0 ? 0.f : a[q];
+#pragma unroll
+          for (int k = 0; k < SPP; ++k)
+            t = fmaf(k0 + k < slices ? ak[q][k] : 0.f, __int_as_float(__builtin_amdgcn_readlane(wbits, k0 + k)), t);
+          a[q] = t;
+        }
+      };
+      pass(std::integral_constant<int, 0>{});
+      if constexpr (LONG)
+        if (slices > SPP) pass(std::integral_constant<int, SPP>{});
 #pragma unroll
       for (int q = 0; q < CPP; ++q) {
         const int c = c0 + 64 * q;
-        float a = 0.f;
-#pragma unroll
-        for (int k = 0; k < SLICE_MAX; ++k) a = fmaf(k < slices ? ak[q][k] : 0.f, __int_as_float(__builtin_amdgcn_readlane(wbits, k)), a);
-        if (c < d) out[(long)bh * d + c] = (T)(zz > 0.f ? a / zz : 0.f);
+        if (c < d) out[(long)bh * d + c] = (T)(zz > 0.f ? a[q] / zz : 0.f);
       }
     }
   }

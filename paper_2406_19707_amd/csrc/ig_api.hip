@@ -174,7 +174,7 @@ int reserve_for(ig_ctx *ctx, const ig_desc *d, bool scores) {
                    (size_t)d->B * d->H * ((d->N_cap + 4095) / 4096) * sizeof(int32_t));
     if (rc) return rc;
     rc = ig_ensure(ctx, (void **)&ctx->attn_part, &ctx->attn_part_bytes,
-                   (size_t)d->B * d->H * IG_SLICE_MAX * (d->d + 2) * sizeof(float));
+                   (size_t)d->B * d->H * IG_SLICE_MAX_LONG * (d->d + 2) * sizeof(float));
     if (rc) return rc;
     rc = ig_ensure_zeroed(ctx, (void **)&ctx->attn_cnt, &ctx->attn_cnt_bytes,
                           (size_t)d->B * d->H * sizeof(int32_t));

@@ -43,6 +43,7 @@ constexpr int IG_SPLIT_MAX = 28;         // workgroups a (b,h) pair's tiles are 
 constexpr int IG_PAIR_SYNC_BYTES = 512;
 constexpr long IG_WAIT_LIMIT_DEFAULT = 2000000;   // 20 ms of the 100 MHz clock  // per-pair record through which the splits of a pair meet
 constexpr int IG_SLICE_MAX = 16;   // slices a selected-token list is cut into at most (gather, attention)
+constexpr int IG_SLICE_MAX_LONG = 32;   // the same for long lists read out of the pool by the attention (att_most_log2)
 
 // Slab geometry: tokens are grouped in tiles of 64 lanes x TPL tokens; inside a tile the r kept
 // channels are planes of TILE contiguous tokens:  slab[(bh*nTiles + tile)*r*TILE + j*TILE + t%TILE].
@@ -111,7 +112,7 @@ struct ig_ctx {
   float *scores;    size_t scores_bytes;  // long-sequence path: s [B*H, N]
   float *tmax;      size_t tmax_bytes;    // long-sequence path: per-tile maxima [B*H, nTiles]
   int32_t *pcount;  size_t pcount_bytes;  // long-sequence path: kept tokens per 4096-token part
-  float *attn_part; size_t attn_part_bytes;  // attention: per-slice softmax states [B*H][16][d+2]
+  float *attn_part; size_t attn_part_bytes;  // attention: room for per-slice softmax states [B*H][32][d+2]
   int32_t *attn_cnt; size_t attn_cnt_bytes;  // attention: per-(b,h) arrival counters, zero between calls
   void *pair_sync;  size_t pair_sync_bytes;  // scan: per-(b,h) records of pairs split over workgroups, zero between calls
   void *seq_sync = nullptr;            // scan, head-equalised form: per-sequence exchange records (zero between calls)

@@ -213,7 +213,7 @@ __global__ __launch_bounds__(256) void gather_rows_sliced(
   work_item(blockIdx.x, H, BH, by_H, by_BH, &bh, &slice);
   const int cnt = min(sel_cnt[bh], stride);
   int row0, row1, slices;
-  if (!slice_range(cnt, slice, slice_log2, &row0, &row1, &slices) || row1 <= row0) return;
+  if (!slice_range(cnt, slice, slice_log2, SLICE_MAX_LOG2, &row0, &row1, &slices) || row1 <= row0) return;
   const int32_t *list = sel_idx + (long)bh * stride + row0;
   const long src0 = (long)bh * N_cap * U, dst0 = ((long)bh * stride + row0) * U;
   const int total = (row1 - row0) * U;
@@ -251,9 +251,9 @@ __global__ __launch_bounds__(256) void gather_rows_flat(GatherArgs A) {
 }
 
 // ---- attention (body in attn_device.h) ----------------------------------------------------------
-template <typename T, bool INDEXED, int LG>
+template <typename T, bool INDEXED, int LG, bool LONG>
 __global__ __launch_bounds__(256) void sparse_attention(AttnArgs A) {
-  sparse_attention_body<T, INDEXED, LG>(A, blockIdx.x);
+  sparse_attention_body<T, INDEXED, LG, LONG>(A, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void copy_bytes(const u128 *__restrict__ src, u128 *__restrict__ dst,
@@ -382,7 +382,7 @@ int ig_launch_gather(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const voi
     // rows of a slice: 1 << SLICE_LOG2, but no more than two batches of a workgroup's copies (see att_slice_log2)
     int slice_log2 = SLICE_LOG2;
     while (slice_log2 > 4 && ((long)U << slice_log2) > 2 * 256 * GATHER_BATCH) --slice_log2;
-    dim3 grid(BH * slices_at_most(sel_stride, slice_log2)), block(256);
+    dim3 grid(BH * slices_at_most(sel_stride, slice_log2, SLICE_MAX_LOG2)), block(256);
     auto k = gather_rows_sliced;
     IG_LAUNCH(ctx, IG_K_GATHER, k, grid, block, s, (const u128 *)Kpool, (const u128 *)Vpool, sel_idx,
               sel_cnt, (u128 *)K_sel, (u128 *)V_sel, (int)d->N_cap, (int)sel_stride, slice_log2, ig_fast_div(U),
@@ -427,6 +427,7 @@ int ig_attn_fill(ig_ctx *ctx, const ig_desc *d, const void *q, const void *K, co
   A->kv_rows = kv_rows;
   A->lpr_log2 = __builtin_ctz(LPR);
   A->slice_log2 = att_slice_log2(A->lpr_log2, d->B * d->H);
+  A->most_log2 = SLICE_MAX_LOG2;
   A->k_new = k_new;
   A->v_new = v_new;
   A->out = out;
@@ -448,7 +449,7 @@ int ig_attn_args(ig_ctx *ctx, const ig_desc *d, const void *q, const void *K, co
                  const void *k_new, const void *v_new, void *out, void *K_out, void *V_out, AttnArgs *A) {
   const int BH = d->B * d->H;
   int rc = ig_ensure(ctx, (void **)&ctx->attn_part, &ctx->attn_part_bytes,
-                     (size_t)BH * SLICE_MAX * (d->d + 2) * sizeof(float));
+                     (size_t)BH * IG_SLICE_MAX_LONG * (d->d + 2) * sizeof(float));
   if (rc) return rc;
   if ((rc = ig_ensure_zeroed(ctx, (void **)&ctx->attn_cnt, &ctx->attn_cnt_bytes, (size_t)BH * sizeof(int32_t))))
     return rc;
@@ -457,17 +458,17 @@ int ig_attn_args(ig_ctx *ctx, const ig_desc *d, const void *q, const void *K, co
 }
 
 // the attention kernel for a type and row length (see LG at sparse_attention_body)
-template <bool INDEXED>
+template <bool INDEXED, bool LONG>
 static void (*attention_kernel(int dtype, int lpr_log2))(AttnArgs) {
   if (dtype == IG_F16) {
-    if (lpr_log2 == 3) return sparse_attention<half_t, INDEXED, 3>;
-    if (lpr_log2 == 4) return sparse_attention<half_t, INDEXED, 4>;
-    if (lpr_log2 == 5) return sparse_attention<half_t, INDEXED, 5>;
-    return sparse_attention<half_t, INDEXED, -1>;
+    if (lpr_log2 == 3) return sparse_attention<half_t, INDEXED, 3, LONG>;
+    if (lpr_log2 == 4) return sparse_attention<half_t, INDEXED, 4, LONG>;
+    if (lpr_log2 == 5) return sparse_attention<half_t, INDEXED, 5, LONG>;
+    return sparse_attention<half_t, INDEXED, -1, LONG>;
   }
-  if (lpr_log2 == 4) return sparse_attention<float, INDEXED, 4>;
-  if (lpr_log2 == 5) return sparse_attention<float, INDEXED, 5>;
-  return sparse_attention<float, INDEXED, -1>;
+  if (lpr_log2 == 4) return sparse_attention<float, INDEXED, 4, LONG>;
+  if (lpr_log2 == 5) return sparse_attention<float, INDEXED, 5, LONG>;
+  return sparse_attention<float, INDEXED, -1, LONG>;
 }
 
 int ig_launch_attention(ig_ctx *ctx, const ig_desc *d, const void *q, const void *K, const void *V,
@@ -478,8 +479,11 @@ int ig_launch_attention(ig_ctx *ctx, const ig_desc *d, const void *q, const void
   int rc = ig_attn_args(ctx, d, q, K, V, sel_idx, sel_stride, sel_cnt, kv_rows_per_bh, k_new, v_new, out,
                         K_out, V_out, &A);
   if (rc) return rc;
-  dim3 grid(A.BH * slices_at_most((long)sel_stride + 1, A.slice_log2)), block(256);
-  const auto k = sel_idx ? attention_kernel<true>(d->dtype, A.lpr_log2) : attention_kernel<false>(d->dtype, A.lpr_log2);
+  if (sel_idx) A.most_log2 = att_most_log2(A.slice_log2, A.BH, sel_stride < d->N ? sel_stride : d->N);
+  dim3 grid(A.BH * slices_at_most((long)sel_stride + 1, A.slice_log2, A.most_log2)), block(256);
+  const auto k = !sel_idx ? attention_kernel<false, false>(d->dtype, A.lpr_log2)
+                          : (A.most_log2 == SLICE_MAX_LOG2 ? attention_kernel<true, false>(d->dtype, A.lpr_log2)
+                                                           : attention_kernel<true, true>(d->dtype, A.lpr_log2));
   IG_LAUNCH(ctx, IG_K_ATTENTION, k, grid, block, s, A);
   return IG_OK;
 }
@@ -491,7 +495,7 @@ int ig_launch_attention(ig_ctx *ctx, const ig_desc *d, const void *q, const void
 // own copy of the array, at its own address, until the process ends; the address is looked up
 // once per context (ig_create, with the context's device current) and host code only ever uses
 // that address, never the array's name.  Layout: counters int32 [B*H] (padded to 256 bytes), then
-// states float [B*H][SLICE_MAX][d+2].
+// states float [B*H][IG_SLICE_MAX][d+2].
 constexpr size_t STATIC_SCRATCH_BYTES = (size_t)16 << 20;
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 
@@ -521,7 +525,7 @@ int ig_launch_attention_static(ig_ctx *ctx, const ig_desc *d, const void *q, con
   if (!ctx->static_scratch) return ig_fail(ctx, IG_EHIP, "the static scratch array was not bound on this device");
   const size_t BH = (size_t)d->B * d->H;
   const size_t cnt_bytes = (BH * sizeof(int32_t) + 255) / 256 * 256;
-  const size_t need = cnt_bytes + BH * SLICE_MAX * ((size_t)d->d + 2) * sizeof(float);
+  const size_t need = cnt_bytes + BH * IG_SLICE_MAX * ((size_t)d->d + 2) * sizeof(float);
   if (need > ctx->static_scratch_bytes)
     return ig_fail(ctx, IG_ECAPACITY,
                    "ig_sparse_attention_static: B*H = %zu heads of d = %d need %zu bytes of slice states, "
@@ -536,8 +540,8 @@ int ig_launch_attention_static(ig_ctx *ctx, const ig_desc *d, const void *q, con
   // behind): the arrival counters start from zero on every call.  A fill kernel, not a memset, so
   // that the sequence can be captured into a graph.
   hipLaunchKernelGGL(zero_words, dim3((unsigned)((BH + 255) / 256)), dim3(256), 0, s, counters, (int)BH);
-  dim3 grid((unsigned)(BH * slices_at_most((long)sel_stride + 1, A.slice_log2))), block(256);
-  hipLaunchKernelGGL(attention_kernel<false>(d->dtype, A.lpr_log2), grid, block, 0, s, A);
+  dim3 grid((unsigned)(BH * slices_at_most((long)sel_stride + 1, A.slice_log2, A.most_log2))), block(256);
+  hipLaunchKernelGGL((attention_kernel<false, false>(d->dtype, A.lpr_log2)), grid, block, 0, s, A);
   hipError_t le = hipGetLastError();
   if (le != hipSuccess) return ig_hip_fail(ctx, le, "sparse_attention (static scratch)");
   return IG_OK;

@@ -38,7 +38,7 @@ __global__ __launch_bounds__(256, 4) void project_scan_next_attend_this(ScanArgs
 
 template <int LG>
 int launch_projecting(ig_ctx *ctx, const ScanArgs &sa, const AttnArgs &aa, const ProjWords &p, int BH, int ch, hipStream_t s) {
-  dim3 grid(p.blocks + BH + BH * slices_at_most((long)aa.stride + 1, aa.slice_log2)), block(256);
+  dim3 grid(p.blocks + BH + BH * slices_at_most((long)aa.stride + 1, aa.slice_log2, aa.most_log2)), block(256);
 #define CASE(CHV)                                                              \
   case CHV: {                                                                  \
     auto k = project_scan_next_attend_this<CHV, LG>;                           \
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(256, 4) void prefetch_rehearse_attend(GatherArgs ga
 
 template <typename T, int LG>
 int launch_t(ig_ctx *ctx, const ScanArgs &sa, const AttnArgs &aa, int BH, int ch, hipStream_t s) {
-  dim3 grid(BH + BH * slices_at_most((long)aa.stride + 1, aa.slice_log2)), block(256);
+  dim3 grid(BH + BH * slices_at_most((long)aa.stride + 1, aa.slice_log2, aa.most_log2)), block(256);
 #define CASE(CHV)                                                              \
   case CHV: {                                                                  \
     auto k = scan_next_attend_this<T, CHV, LG>;                                \
@@ -167,7 +167,7 @@ int ig_launch_host_step(ig_ctx *ctx, const ig_desc *d, const void *Kpool, const 
     if ((rc = ig_attn_args(ctx, d, prev->q, prev->K_sel, prev->V_sel, nullptr, sel_stride, prev->cnt, sel_stride, prev->k_new,
                            prev->v_new, prev->out, nullptr, nullptr, &aa)))
       return rc;
-    attn_blocks = aa.BH * slices_at_most((long)sel_stride + 1, aa.slice_log2);
+    attn_blocks = aa.BH * slices_at_most((long)sel_stride + 1, aa.slice_log2, aa.most_log2);
   }
   dim3 grid((unsigned)(GATHER_FLAT_BLOCKS + p.blocks + scan_blocks + attn_blocks)), block(256);
   const int row16_log2 = __builtin_ctz(d->d * 2 / 16);
