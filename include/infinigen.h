@@ -390,10 +390,11 @@ int ig_gather_attention(ig_ctx *ctx, const ig_desc *desc, const void *q, const v
  * prefetch + attention of THIS layer -- q, Kpool, Vpool, sel_idx, sel_cnt, K_sel, V_sel, k_new,
  * v_new, out as in ig_gather_attention.  Both list pairs use sel_stride; the two must not
  * alias.  Same results, bit for bit, as ig_speculate (without score dump) followed by
- * ig_gather_attention.  The projection goes out first; the next layer's scan and this layer's
- * attention are independent and, for sequences of at most 4 tiles (2048 half-precision tokens)
- * with enough (sequence, head) pairs, leave as ONE launch; other shapes get the two launches one
- * after the other. */
+ * ig_gather_attention.  The next layer's scan and this layer's attention are independent and, for
+ * sequences of at most 4 tiles (2048 half-precision tokens), leave as ONE launch; other shapes get
+ * two launches one after the other.  The projection is in the scan's launch in most half-precision
+ * shapes of up to 32 sequences (not in the joint launch of rotary models), unless x lies in what
+ * that launch stores: x may be the same memory as out.  Otherwise it goes out first, on its own. */
 int ig_layer_step(ig_ctx *ctx, const ig_desc *desc, const void *x, const void *wq, const float *bias,
                   const float *A_p, const int32_t *pos, const void *slab, int32_t *sel_idx_next,
                   int32_t *sel_cnt_next, const void *q, const void *Kpool, const void *Vpool,
@@ -416,7 +417,7 @@ int ig_layer_step(ig_ctx *ctx, const ig_desc *desc, const void *x, const void *w
  * on side_stream's.
  * Folded half-precision shapes of up to four tiles (2048 tokens) and 32 sequences over a pinned pool
  * take one launch a layer on main_stream instead, outside stream capture and unless a layer's x lies
- * in the output of the layer but one before it; earlier work of side_stream is then done before the
+ * in its own lists or in the output of the layer but one before it; earlier work of side_stream is then done before the
  * first prefetch and later work starts behind the last one, as if the prefetches ran there. */
 typedef struct {
   const void *x, *slab, *q, *Kpool, *Vpool, *k_new, *v_new;

@@ -481,9 +481,23 @@ static int project_partials(ig_ctx *ctx, const ig_desc *d, const void *x, const 
   return ig_launch_project(ctx, d, *g, x, wq, ctx->part, s);
 }
 
-// Whether the projection goes into the scan's launch (after project_ready); *p is its argument block then.
-static bool joins_projection(const ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, const void *x, const void *wq, ProjWords *p) {
+struct Span {
+  const void *at;
+  size_t bytes;
+};
+static bool apart(const Span &a, const Span &b) {
+  return !a.at || !b.at || (uintptr_t)a.at + a.bytes <= (uintptr_t)b.at || (uintptr_t)b.at + b.bytes <= (uintptr_t)a.at;
+}
+
+// Whether the projection goes into the scan's launch (after project_ready); *p is its argument block then.  `written`:
+// what that launch stores.  x may lie in it, one buffer for a layer's input and output for instance: a projection of its
+// own has read all of x before anything is stored, one in the same launch has not.
+static bool joins_projection(const ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, const void *x, const void *wq,
+                             std::initializer_list<Span> written, ProjWords *p) {
   if (!ig_scan_joins_projection(d, g) || words_bytes(d, g) > ctx->words_bytes) return false;
+  const Span input{x, (size_t)d->B * d->H * d->d * ig_elem_bytes(d->dtype)};
+  for (const Span &o : written)
+    if (!apart(input, o)) return false;
   int splits_tpw = 0, S = 0;
   if (ig_scan_stream_form(d, &splits_tpw, &S) && S > 1 && ctx->pair_sync_bytes < (size_t)d->B * d->H * IG_PAIR_SYNC_BYTES)
     return false;
@@ -584,7 +598,8 @@ int ig_speculate(ig_ctx *ctx, const ig_desc *d, const void *x, const void *wq, c
   if (ig_scan_takes_projection(d, g))
     return ig_launch_project_scan(ctx, d, g, x, wq, bias, slab, sel_idx, sel_stride, sel_cnt, scores_opt, s);
   ProjWords p;
-  if (joins_projection(ctx, d, g, x, wq, &p)) {
+  const size_t BH = (size_t)d->B * d->H;
+  if (joins_projection(ctx, d, g, x, wq, {{sel_idx, BH * sel_stride * 4}, {sel_cnt, BH * 4}, {scores_opt, BH * d->N * 4}}, &p)) {
     QSource q{nullptr, 1, 0, 0, bias, A_p, pos, &p};
     if (!d->rope) q.A_p = nullptr;
     return ig_launch_scan_select(ctx, d, q, slab, sel_idx, sel_stride, sel_cnt, scores_opt, s);
@@ -627,7 +642,8 @@ int ig_speculate_equalized(ig_ctx *ctx, const ig_desc *d, const void *x, const v
     ProjGeom g;
     ProjWords p;
     if ((rc = project_ready(ctx, d, x, wq, A_p, pos, &g))) return rc;
-    if (joins_projection(ctx, d, g, x, wq, &p)) {
+    const size_t BH = (size_t)d->B * d->H;
+    if (joins_projection(ctx, d, g, x, wq, {{sel_idx, BH * sel_stride * 4}, {sel_cnt, BH * 4}, {thr_cnt_opt, BH * 4}}, &p)) {
       QSource q{nullptr, 1, 0, 0, bias, A_p, pos, &p};
       if (!d->rope) q.A_p = nullptr;
       return ig_launch_scan_equalized(ctx, d, q, slab, cap, sel_idx, sel_stride, sel_cnt, thr_cnt_opt, s);
@@ -762,7 +778,12 @@ int ig_layer_step(ig_ctx *ctx, const ig_desc *d, const void *x, const void *wq, 
   if ((rc = project_ready(ctx, d, x, wq, A_p, pos, &g))) return rc;
   const bool joint = ig_layer_step_is_joint(d);
   ProjWords p;
-  if ((!joint || !d->rope) && joins_projection(ctx, d, g, x, wq, &p)) {
+  const size_t BH = (size_t)d->B * d->H, row = (size_t)d->d * ig_elem_bytes(d->dtype);
+  // (the joint launch stores this layer's part too; not joint, the attention is a launch behind the scan's)
+  const Span lists{sel_idx_next, BH * sel_stride * 4}, counts{sel_cnt_next, BH * 4};
+  const Span rows_k{joint ? K_sel : nullptr, BH * sel_stride * row}, rows_v{joint ? V_sel : nullptr, BH * sel_stride * row};
+  const Span result{joint ? out : nullptr, BH * row};
+  if ((!joint || !d->rope) && joins_projection(ctx, d, g, x, wq, {lists, counts, rows_k, rows_v, result}, &p)) {
     QSource q1{nullptr, 1, 0, 0, bias, A_p, pos, &p};
     if (!d->rope) q1.A_p = nullptr;
     if (joint)
@@ -823,7 +844,7 @@ static int host_step_joint(ig_ctx *ctx, const ig_desc *d, const ProjGeom &g, int
     const bool has_next = l + 1 < n_layers;
     if (has_next) {
       const ig_buffer_set &sn = sets[(l + 1) % n_sets];
-      if (!joins_projection(ctx, d, g, layers[l + 1].x, wq, &p)) return ig_fail(ctx, IG_EINVAL, "host step: the shape's projection does not join");
+      if (!joins_projection(ctx, d, g, layers[l + 1].x, wq, {}, &p)) return ig_fail(ctx, IG_EINVAL, "host step: the shape's projection does not join");
       next = IgHostNext{layers[l + 1].slab, bias, sn.sel_idx, sn.sel_cnt, &p};
     }
     if (l >= 1) {
@@ -857,8 +878,8 @@ int ig_decode_step_overlapped(ig_ctx *ctx, const ig_desc *d, int n_layers, const
   if ((rc = set_device(ctx))) return rc;
   if (pool_space == IG_MEM_HOST_PINNED && !ig_capturing(ctx)) {
     // One stream, where the shape allows it and every argument is what the three calls would take (what they refuse
-    // is left to them), and where no rehearsal reads what the attention beside it writes.  Not under a capture: the side
-    // stream joins one only by a fork from the captured stream.
+    // is left to them), and where no rehearsal's input lies in what its launch writes, its lists and the output of the
+    // attention beside it.  Not under a capture: the side stream joins one only by a fork from the captured stream.
     ProjGeom g = ig_proj_geom(d);
     const int row = d->d * 2;
     bool one = ig_host_step_is_joint(d, g) && wq && sel_stride >= 1 && row <= 1024 && !(row & (row - 1)) && ig_gather_fits(d) &&
@@ -867,15 +888,15 @@ int ig_decode_step_overlapped(ig_ctx *ctx, const ig_desc *d, int n_layers, const
       const ig_layer_io &io = layers[l];
       one = io.x && io.slab && io.q && io.Kpool && io.Vpool && io.out && (!io.k_new) == (!io.v_new) &&
             !check_aligned(ctx, "", {io.x, io.q, io.Kpool, io.Vpool, io.k_new, io.v_new});
-      const size_t bytes = (size_t)d->B * d->H * d->d * 2;
-      if (one && l >= 2) {
-        const uintptr_t a = (uintptr_t)io.x, b = (uintptr_t)layers[l - 2].out;
-        one = a + bytes <= b || b + bytes <= a;
-      }
+      const size_t BH = (size_t)d->B * d->H;
+      const Span input{io.x, BH * row};
+      const ig_buffer_set &st = sets[l % n_sets];
+      if (one && l >= 1) one = apart(input, {st.sel_idx, BH * sel_stride * 4}) && apart(input, {st.sel_cnt, BH * 4});
+      if (one && l >= 2) one = apart(input, {layers[l - 2].out, BH * row});
     }
     for (int i = 0; one && i < n_sets; ++i) one = !check_aligned(ctx, "", {sets[i].K_sel, sets[i].V_sel});
     ProjWords p;
-    if (one && !(rc = reserve_for(ctx, d, false)) && joins_projection(ctx, d, g, layers[0].x, wq, &p))
+    if (one && !(rc = reserve_for(ctx, d, false)) && joins_projection(ctx, d, g, layers[0].x, wq, {}, &p))
       return host_step_joint(ctx, d, g, n_layers, layers, wq, bias, n_sets, sets, sel_stride, (hipStream_t)main_stream,
                              (hipStream_t)side_stream);
     if (rc) return rc;

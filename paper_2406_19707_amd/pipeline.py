@@ -329,9 +329,10 @@ class Rehearsal:
 
     def step_joint(self):
         """HBM-pool decode step on one stream with ig_layer_step: after the first layer's rehearsal,
-        every call issues the next layer's projection and then ONE launch that holds the next
-        layer's scan / threshold / lists and this layer's prefetch + attention (Fig. 3(d): the next
-        layer is speculated while the current one computes).  The index lists and fetched rows are
+        every call issues ONE launch that holds the next layer's projection, scan / threshold / lists
+        and this layer's prefetch + attention (Fig. 3(d): the next layer is speculated while the
+        current one computes; the projection is a launch before it in float32, for rotary models
+        and for more than 32 sequences).  The index lists and fetched rows are
         double-buffered."""
         self._use(0)
         self.speculate(0)

@@ -120,6 +120,24 @@ def test_an_input_may_be_an_earlier_layers_output(back):
     s.ctx.close()
 
 
+def test_an_input_may_lie_in_its_own_layers_list():
+    s = Step(2, 4, 128, 900, 4, 2)
+    want, b = s.in_order()
+    lists = s.sets[3 % 2]["sel_idx"]           # the fourth layer's
+    n = s.x[3].numel()
+    # (that set is the second layer's too: the step must find the input there, so its lists may not reach that far)
+    reach = int(b[1]["sel_cnt"][-1])
+    s.x[3] = lists.view(-1)[-(n // 2):].view(torch.float16).view_as(s.x[3])
+    assert n // 2 < s.N - reach
+    s.x[3].copy_(s.up[3].x)
+    s.ctx.ig_profile_begin()
+    s.run(torch.cuda.Stream(), torch.cuda.Stream())
+    s.ctx.ig_profile_end()
+    assert s.ctx.ig_profile_read(s.ig.IG_K_LAYER)[1] == 0, "the rehearsal must not project beside the scan that writes the list"
+    check(s, want, b)
+    s.ctx.close()
+
+
 def test_the_side_streams_own_work_is_ordered_around_the_prefetches():
     s = Step(2, 8, 128, 1500, 3, 2)
     main, side = torch.cuda.Stream(), torch.cuda.Stream()

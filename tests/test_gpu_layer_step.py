@@ -93,6 +93,38 @@ def test_shapes_that_take_two_launches(ctx, cfg, B, H, d, N, gain):
     check_layer_step(ctx, w, gain=gain)
 
 
+@pytest.mark.parametrize("where", ["apart", "out", "out, second half", "K_sel", "sel_idx_next"])
+def test_input_in_what_the_launch_stores(ctx, where):
+    """One buffer for the next layer's input and this layer's output: the input is read whole before anything is stored,
+    so the projection must not be in the launch that stores."""
+    import paper_2406_19707_amd as ig
+    from ig_gpu import Uploaded
+    w = wl.shrink(wl.WORKLOADS[2], B=4, H=4, N=1100, heavy_count=20)
+    c = make_case(w, gain=6.0)
+    up = Uploaded(ctx, c)
+    d, BH, n = up.desc, w.B * w.H, w.B * w.D
+    idx0, cnt0 = torch.full((BH, c.N), -1, dtype=torch.int32, device="cuda"), torch.zeros(BH, dtype=torch.int32, device="cuda")
+    ctx.ig_speculate(d, up.x, up.wq, None, None, None, up.slab, idx0, c.N, cnt0)
+    K_ref, V_ref = (torch.zeros((BH, c.N, w.d), dtype=torch.float16, device="cuda") for _ in range(2))
+    out_ref = torch.zeros(n, dtype=torch.float16, device="cuda")
+    ctx.ig_gather_attention(d, up.q, up.K, up.V, idx0, c.N, cnt0, K_ref, V_ref, None, None, out_ref)
+    idx1, cnt1 = torch.full_like(idx0, -1), torch.zeros_like(cnt0)
+    K_sel, V_sel, store = torch.zeros_like(K_ref), torch.zeros_like(V_ref), torch.zeros(2 * n, dtype=torch.float16, device="cuda")
+    out, x = store[:n], {"apart": store[n:], "out": store[:n], "out, second half": store[n // 2:n // 2 + n],
+                         "K_sel": K_sel.view(-1)[:n], "sel_idx_next": idx1.view(torch.float16).view(-1)[:n]}[where]
+    x.copy_(up.x.view(-1))
+    ctx.ig_profile_begin()
+    ctx.ig_layer_step(d, x, up.wq, None, None, None, up.slab, idx1, cnt1, up.q, up.K, up.V, idx0, cnt0, c.N, K_sel, V_sel,
+                      None, None, out)
+    ctx.ig_profile_end()
+    assert ctx.ig_profile_read(ig.IG_K_LAYER)[1] == 1
+    assert ctx.ig_profile_read(ig.IG_K_PROJECT)[1] == (0 if where == "apart" else 1)
+    assert torch.equal(cnt1, cnt0) and torch.equal(out, out_ref)
+    for i, m in enumerate(cnt0.tolist()):
+        assert torch.equal(idx1[i, :m], idx0[i, :m]) and torch.equal(K_sel[i, :m], K_ref[i, :m])
+    assert torch.equal(V_sel, V_ref)
+
+
 def test_error_paths(ctx):
     import paper_2406_19707_amd as ig
     from ig_gpu import Uploaded
