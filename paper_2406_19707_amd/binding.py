@@ -193,10 +193,14 @@ def _current_stream():
 def _through_ctypes(name, *args):
     """An entry point with its arguments marshalled here: the context's address, the descriptor where there is one,
     tensors / numpy arrays / addresses / None, numbers."""
-    has_desc = name not in ("ig_skew_device", "ig_partial_index_device")
-    at = [ctypes.byref(a) if has_desc and i == 1 else a if isinstance(a, (int, float, np.number)) else _ptr(a)
-          for i, a in enumerate(args)]
-    return getattr(lib(), name)(*at)
+    entry = getattr(lib(), name)
+    # by the parameter's type and not the argument's: a number may come as a tensor or array of one whole number, whose value
+    # and not whose address is meant
+    marshal = {_vp: _ptr, _dp: ctypes.byref}
+    types = entry.argtypes
+    if len(args) != len(types):
+        return entry(*args)                       # (refused there)
+    return entry(*[marshal[t](a) if t in marshal else a for t, a in zip(types, args)])
 
 
 class _Entries:

@@ -1,5 +1,7 @@
 """The native marshalling of the binding against its ctypes form: the same outcome for every kind of argument (no GPU
 needed: a NULL context is refused by the library before anything else is looked at)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -68,6 +70,37 @@ def test_same_outcome_as_through_ctypes(native, what):
     assert outcome(lambda: native(*args)) == want
     if what in ("tensor", "view", "parameter", "subclass", "numpy", "address", "none", "empty tensor"):
         assert want == ig.IG_EINVAL
+
+
+@pytest.mark.parametrize("number", [np.int64(8), np.array(8), torch.tensor(8), torch.tensor([8], dtype=torch.int32)], ids=repr)
+@pytest.mark.parametrize("form", ["native", "ctypes"])
+def test_a_number_is_passed_by_value_whatever_holds_it(native, monkeypatch, number, form):
+    """Both integers of the call, next to a tensor that does go by its address."""
+    t, got = torch.zeros(8, dtype=torch.int32), []
+    real = binding.lib().ig_pool_touch
+
+    @ctypes.CFUNCTYPE(real.restype, *real.argtypes)
+    def record(ctx, desc, sel_idx, sel_stride, sel_cnt, counters, counter_max, stream):
+        got.append((sel_idx, sel_stride, counter_max))
+        return 0
+    record.argtypes = real.argtypes
+
+    class Library:
+        ig_pool_touch = record
+    monkeypatch.setattr(binding, "lib", lambda: Library)
+    args = (None, ig.IgDesc(B=1, H=1, d=64, r=8, N=8), t, number, t, t, number, 0)
+    call = native if form == "native" else lambda *a: binding._through_ctypes("ig_pool_touch", *a)
+    assert call(*args) == 0
+    assert got == [(t.data_ptr(), 8, 8)]
+
+
+@pytest.mark.parametrize("wrong", [torch.zeros(4, dtype=torch.int32), np.zeros(4, np.int32), torch.zeros(1), None, 2.5, "x"], ids=repr)
+def test_what_is_no_whole_number_is_refused(native, wrong):
+    t = torch.zeros(8, dtype=torch.int32)
+    args = (None, ig.IgDesc(B=1, H=1, d=64, r=8, N=8), t, wrong, t, t, 255, 0)
+    for call in (native, lambda *a: binding._through_ctypes("ig_pool_touch", *a)):
+        with pytest.raises((ctypes.ArgumentError, TypeError)):
+            call(*args)
 
 
 def test_every_device_entry_point_has_a_native_form(native):
