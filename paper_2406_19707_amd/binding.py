@@ -205,7 +205,8 @@ def _through_ctypes(name, *args):
 
 class _Entries:
     """The device entry points as functions of (context address, descriptor, tensors, numbers): those of the native
-    module where it has been built and torch is there, the others through ctypes.  Looked up at the first call."""
+    module where it has been built and the torch that it was built for is there, the others through ctypes.  Looked
+    up at the first call."""
 
     def __getattr__(self, name):
         native = None
@@ -213,8 +214,9 @@ class _Entries:
             lib()
             try:
                 from . import _ig_call
-                _ig_call.setup(IgDesc, _through_ctypes)
-                native = getattr(_ig_call, name, None)
+                if getattr(_ig_call, "built_for", None) == str(sys.modules["torch"].__version__):
+                    _ig_call.setup(IgDesc, _through_ctypes)
+                    native = getattr(_ig_call, name, None)
             except ImportError:
                 pass
         fn = native or functools.partial(_through_ctypes, name)

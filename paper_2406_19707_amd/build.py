@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import importlib.util
 import os
+import runpy
 import subprocess
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
@@ -11,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libinfinigen_hip.so")
-CALL = os.path.join(HERE, "_ig_call.so")
+CALL = os.path.join(HERE, "_ig_call" + sysconfig.get_config_var("EXT_SUFFIX"))    # for this Python alone
 SOURCES = ["ig_api.hip", "k_scan.hip", "k_project.hip", "k_kv.hip", "k_layer.hip", "k_equalize.hip", "k_index.hip", "k_skew.hip", "ig_host.cpp"]
 HIPCC = "/opt/rocm/bin/hipcc"
 # packed-fp32 instruction selection is switched off for every device compile
@@ -42,12 +43,24 @@ def build(verbose: bool = False) -> str:
 
 
 def _build_call() -> None:
-    """The marshalling module of the Python binding: host code over the library and torch's tensor class."""
-    torch_dir = list(importlib.util.find_spec("torch").submodule_search_locations)[0]
-    inc = [sysconfig.get_paths()["include"], os.path.join(torch_dir, "include"),
-           os.path.join(torch_dir, "include", "torch", "csrc", "api", "include")]
-    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", *[f"-I{d}" for d in inc],
-                           os.path.join(CSRC, "ig_call.cpp"), "-o", CALL, "-L" + os.path.join(torch_dir, "lib"),
+    """The marshalling module of the Python binding: host code over the library and torch's tensor class.  It only makes
+    calls cheaper, so without torch, its headers or Python's the build goes on without it (and without an old one, which
+    may be of another library): the binding marshals through ctypes then."""
+    if os.path.exists(CALL):
+        os.remove(CALL)
+    spec = importlib.util.find_spec("torch")
+    torch_dir = list(spec.submodule_search_locations)[0] if spec else None
+    python_inc = sysconfig.get_paths()["include"]
+    for what, path in (("torch", torch_dir), ("Python.h", os.path.join(python_inc, "Python.h")),
+                       ("torch's C++ headers", torch_dir and os.path.join(torch_dir, "include", "torch", "csrc", "autograd", "python_variable.h"))):
+        if not path or not os.path.exists(path):
+            print(f"no native marshalling ({what} not found): calls from Python go through ctypes")
+            return
+    inc = [python_inc, os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include")]
+    # the accessors of torch's tensor class are inlined: the binding uses the module with this torch only
+    version = runpy.run_path(os.path.join(torch_dir, "version.py"))["__version__"]
+    subprocess.check_call([HIPCC, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f'-DIG_BUILT_FOR="{version}"', *[f"-I{d}" for d in inc],
+                           "-x", "c++", os.path.join(CSRC, "ig_call.cpp"), "-o", CALL, "-L" + os.path.join(torch_dir, "lib"),
                            "-ltorch_python", "-ltorch_cpu", "-lc10", "-L" + HERE, "-linfinigen_hip", "-Wl,-rpath,$ORIGIN"])
 
 

@@ -153,4 +153,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_ig_call", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__ig_call() { return PyModule_Create(&module); }
+// built_for: the torch version whose tensor class this was compiled against, to be compared before any other use
+PyMODINIT_FUNC PyInit__ig_call() {
+  PyObject *m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "built_for", IG_BUILT_FOR) < 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

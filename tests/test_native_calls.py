@@ -103,6 +103,25 @@ def test_what_is_no_whole_number_is_refused(native, wrong):
             call(*args)
 
 
+def test_another_torch_than_the_modules_own_goes_through_ctypes(native, monkeypatch):
+    from paper_2406_19707_amd import _ig_call
+    monkeypatch.setattr(_ig_call, "built_for", "0.0")
+    assert type(binding._Entries().ig_pool_touch).__name__ == "partial"
+
+
+@pytest.mark.parametrize("missing", ["torch", "python_variable.h", "Python.h"])
+def test_the_build_goes_on_without_the_module(missing, tmp_path, monkeypatch, capsys):
+    from paper_2406_19707_amd import build
+    stale = tmp_path / "_ig_call.so"
+    stale.write_bytes(b"of another library")
+    find, exists = build.importlib.util.find_spec, build.os.path.exists
+    monkeypatch.setattr(build, "CALL", str(stale))
+    monkeypatch.setattr(build.importlib.util, "find_spec", lambda n: None if n == missing else find(n))
+    monkeypatch.setattr(build.os.path, "exists", lambda p: not str(p).endswith("/" + missing) and exists(p))
+    build._build_call()
+    assert not stale.exists() and "ctypes" in capsys.readouterr().out
+
+
 def test_every_device_entry_point_has_a_native_form(native):
     from paper_2406_19707_amd import _ig_call
     assert {n for n in dir(_ig_call) if n.startswith("ig_")} <= set(ig.EXPORTS)
