@@ -209,7 +209,7 @@ def run_workload(args) -> dict:
     # ---- HIP graphs of the whole step (HBM pools): the four calls in sequence; prefetch and
     # attention in one pass; and that with the rehearsal of the next layer on a side stream ----
     variants = {}
-    launch = "eager, two streams" if R.host_pool else "eager"
+    launch = "eager, " + pcie["overlapped_issued_by"] if R.host_pool else "eager"
     value_path = "overlapped" if R.host_pool else "step"
     ms_per_step = eager_ms
     if R.host_pool and one_stream_ms < ms_per_step:
@@ -235,7 +235,7 @@ def run_workload(args) -> dict:
                                ("speculate, gather+attention in one pass", R.step_one_pass, "one_pass"),
                                ("rehearsal of the next layer on a side stream, gather+attention in one pass",
                                 R.step_two_stream, "one_pass"),
-                               ("projection, then the next layer's scan and this layer's gather+attention in one launch",
+                               ("next layer's rehearsal beside this layer's gather+attention (ig_layer_step)",
                                 R.step_joint, "joint")):
             try:
                 g = graphed(fn)
@@ -304,7 +304,7 @@ def run_workload(args) -> dict:
         names[ig.IG_K_LAYER] = "joint"
         joint = profiled([R.step_joint], pk)
         if "joint" in joint:
-            kernels["next layer's scan + this layer's gather+attention in one launch"] = joint["joint"]
+            kernels["next layer's rehearsal + this layer's gather+attention in one launch"] = joint["joint"]
         del names[ig.IG_K_LAYER]
     # streaming-read rate of this GPU on buffers of the slab's size (the slabs themselves, rotated)
     names[ig.IG_K_READ] = "read"
@@ -577,7 +577,7 @@ def run_workload(args) -> dict:
     # algorithmic bytes per launch of every kernel (layer average) and the rate they imply
     esz = 4 if w.dtype == "f32" else 2
     row_bytes = float(np.mean(fr)) * w.N * w.B * w.H * w.d * esz * 2          # K and V rows of a layer
-    joint_name = "next layer's scan + this layer's gather+attention in one launch"
+    joint_name = "next layer's rehearsal + this layer's gather+attention in one launch"
     kbytes = {"project": ig.ig_wq_bytes(R.desc), "scan": scan_bytes, "gather": 2 * row_bytes,
               "attention": row_bytes, "gather+attention in one pass": 2 * row_bytes,
               joint_name: scan_bytes + 2 * row_bytes}

@@ -417,8 +417,9 @@ int ig_layer_step(ig_ctx *ctx, const ig_desc *desc, const void *x, const void *w
  * on side_stream's.
  * Folded half-precision shapes of up to four tiles (2048 tokens) and 32 sequences over a pinned pool
  * take one launch a layer on main_stream instead, outside stream capture and unless a layer's x lies
- * in its own lists or in the output of the layer but one before it; earlier work of side_stream is then done before the
- * first prefetch and later work starts behind the last one, as if the prefetches ran there. */
+ * in its own lists or in the output of the layer but one before it; earlier work of side_stream is
+ * then done before the first prefetch and later work starts behind the last one, as if the prefetches
+ * ran there. */
 typedef struct {
   const void *x, *slab, *q, *Kpool, *Vpool, *k_new, *v_new;
   void *out;

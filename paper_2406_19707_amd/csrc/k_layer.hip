@@ -1,12 +1,13 @@
 // One launch for two independent pieces of a decode step (Section 4.1, Fig. 3(d): the next layer
 // is speculated while the current one computes): the scan / threshold / list kernel of the NEXT
 // layer's rehearsal and the one-pass prefetch + attention of THIS layer.  The scan needs the next
-// layer's projection sums (the launch before this one) and the attention needs this layer's index
-// lists (the launch of the previous step), so neither depends on the other, and both are short,
-// latency-bound kernels: run as the two halves of one grid they share the launch and overlap fully,
-// without streams or events between them.  Workgroups [0, B*H) run the scan body (4 waves, one
-// tile each), the remaining ones run the attention body; the bodies are those of the
-// stand-alone kernels, so the results are the same bit for bit.
+// layer's partial query (sums of the launch before this one, or words of projecting workgroups in the
+// same grid) and the attention needs this layer's index lists (the launch of the previous step), so
+// neither depends on the other, and both are short, latency-bound kernels: run as the halves of one
+// grid they share the launch and overlap fully, without streams or events between them.  The first
+// workgroups project, where the projection is in the grid, B*H run the scan body (4 waves, one tile
+// each), the remaining ones the attention body; the bodies are those of the stand-alone kernels, so the
+// results are the same bit for bit.
 #include "scan_device.h"
 #include "attn_device.h"
 

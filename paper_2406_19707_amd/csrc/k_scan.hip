@@ -1314,15 +1314,15 @@ int launch_scan(ig_ctx *ctx, const ig_desc *d, ScanArgs &a, const QSource *rope,
   // otherwise one wave per tile so that long sequences spread over all compute units.
   int tpw = 0, S = 0;
   bool stream = ig_scan_stream_form(d, &tpw, &S);
-  // A split needs the pairs' records.  Where they would have to be allocated under a capture, which is
-  // refused, the forms below serve the call with the same lists: one workgroup per pair without any
-  // workspace (64 pairs and more, up to 32768 tokens), or the three kernels if theirs are there.
   if constexpr (sizeof(T) == 2) {
     if (p && !rope && !eq) {
       if (nTiles <= 4) return launch_project_and_scan_fused<4>(ctx, a, *p, BH, s);
       if (!stream && BH >= 128 && nTiles <= 8) return launch_project_and_scan_fused<8>(ctx, a, *p, BH, s);
     }
   }
+  // A split needs the pairs' records.  Where they would have to be allocated under a capture, which is
+  // refused, the forms below serve the call with the same lists: one workgroup per pair without any
+  // workspace (64 pairs and more, up to 32768 tokens), or the three kernels if theirs are there.
   if (stream && S > 1 && !rope && !eq && !p && ctx->pair_sync_bytes < (size_t)BH * IG_PAIR_SYNC_BYTES && ig_capturing(ctx))
     stream = false;
   if (stream) {
